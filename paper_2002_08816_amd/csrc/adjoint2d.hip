@@ -118,7 +118,7 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
 
   for (int q = tid; q < NQ; q += NT) {
     const int ly = 2 + q / R1, lx = 2 + q % R1;
-    double in19[19], d[19];
+    double in19[19], fold[hw2::NFOLD], d[19];
 #pragma unroll
     for (int k = 0; k < 19; ++k) d[k] = 0.0;
     int wall = 0;   // bits: low x, high x, low y, high y face on a transmissive side
@@ -135,12 +135,13 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
       if (P.bcy != BC_PERIODIC) wall |= (gyq == 0 ? 4 : 0) | (gyq == ny - 1 ? 8 : 0);
     }
     gather19<1>(s_in, 0, ly, lx, in19);
+    hw2::lin2d_fold(in19, fold);
     const double lU = S(s_lam, 0, ly, lx);
     // volume terms of eq. ode2: the x moment gains (1/dx) sum w f(u(G)), the y moment
     // (1/dy) sum w g(u(G))
     {
       double inner[9], ub[9];
-      hw2::lin2d_inner(in19, inner);
+      hw2::lin2d_inner(fold, inner);
       const double lv = S(s_lam, 1, ly, lx) * idx, lw = S(s_lam, 2, ly, lx) * idy;
 #pragma unroll
       for (int p = 0; p < 9; ++p) {
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
                    pQ = S(s_lam, fQ, ly + oy, lx + ox);
       double v[2 * NGE];
       if (hyb) hweno2d_combine<NGE>(in19, P.w, dir, om, v);
-      else lin_edges<NGE>(in19, dir, v, v + NGE);
+      else lin_faces<NGE>(fold, dir, v, v + NGE);
       double ub[2 * NGE];
 #pragma unroll
       for (int k = 0; k < NGE; ++k) {
@@ -592,9 +593,10 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
     double inner[NC][9];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      double in[19];
+      double in[19], fold[hw2::NFOLD];
       gather19<NC, W>(s_w, c, ly, lx, in);
-      hw2::lin2d_inner(in, inner[c]);
+      hw2::lin2d_fold(in, fold);
+      hw2::lin2d_inner(fold, inner[c]);
     }
     double lv[NC], lw[NC];
 #pragma unroll
@@ -627,9 +629,10 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
     if (!hyb) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        double in[19];
+        double in[19], fold[hw2::NFOLD];
         gather19<NC, W>(s_w, c, ly, lx, in);
-        lin_edges<NGE>(in, dir, v[c], v[c] + NGE);
+        hw2::lin2d_fold(in, fold);
+        lin_faces<NGE>(fold, dir, v[c], v[c] + NGE);
       }
     } else {
 #pragma unroll

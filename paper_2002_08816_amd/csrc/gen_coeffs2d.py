@@ -15,13 +15,15 @@ target cell, neighbours at integer offsets (labels 1..9 of Figure 1):
   integrals over the target cell, each multi-index counted once.
 
 Emitted code
-* lin2d_inner / lin2d_xedges_ng<NG> / lin2d_yedges_ng<NG>: the linear path (Steps 5.2
-  and 5.3) for one field: values of p0 at the 3 x 3 interior Gauss points, at the Gauss
-  points of the left and right edges, and of the bottom and top edges.  The stencil data are folded into the four reflection-parity classes of the
-  3x3 stencil (even/odd under xi -> -xi and under eta -> -eta); since p0 commutes with
-  both reflections, each parity part of a point value depends only on the inputs of the
-  same class, and the four mirror images of a point follow by a butterfly.  This cuts
-  the multiply count per field to about a quarter of the dense map.
+* lin2d_fold, lin2d_inner, lin2d_xparts_ng<NG> / lin2d_xface_ng<NG>: the linear path (Steps
+  5.2 and 5.3) for one field.  lin2d_fold folds the stencil data into the four
+  reflection-parity classes of the 3x3 stencil (even/odd under xi -> -xi and under eta ->
+  -eta); since p0 commutes with both reflections, each parity part of a point value depends
+  only on the folds of the same class, and the mirror images of a point follow by a
+  butterfly: about a quarter of the dense map's multiplies.  lin2d_inner: values of p0 at
+  the 3 x 3 interior Gauss points; lin2d_xparts: the parity parts of the left and right
+  edges' Gauss points, lin2d_xface: one of the two edges from them.  p0 also commutes with
+  the exchange of x and y: the bottom and top edges are the x edges of lin2d_transpose.
 * p0_coeffs / pq_coeffs<n>: monomial coefficients of p0 and p_n, for the HWENO path.
 * beta_p0 / beta_pq: the smoothness indicators as sparse quadratic forms.
 * edge monomial tables for evaluating the candidates at the edge Gauss points.
@@ -190,10 +192,9 @@ def folded_inputs():
     return {
         "ee": [{u(5): 1}, {u(4): 1, u(6): 1}, {u(2): 1, u(8): 1}, {u(1): 1, u(3): 1, u(7): 1, u(9): 1},
                {v(6): 1, v(4): -1}, {w(8): 1, w(2): -1}],
-        "oe": [{u(6): 1, u(4): -1}, {u(3): 1, u(9): 1, u(1): -1, u(7): -1}, {v(5): 1},
-               {v(4): 1, v(6): 1}, {v(2): 1, v(8): 1}],
-        "eo": [{u(8): 1, u(2): -1}, {u(7): 1, u(9): 1, u(1): -1, u(3): -1}, {w(5): 1},
-               {w(2): 1, w(8): 1}, {w(4): 1, w(6): 1}],
+        # (the sums v4 + v6, v2 + v8, w2 + w8, w4 + w6 enter no value of p0)
+        "oe": [{u(6): 1, u(4): -1}, {u(3): 1, u(9): 1, u(1): -1, u(7): -1}, {v(5): 1}],
+        "eo": [{u(8): 1, u(2): -1}, {u(7): 1, u(9): 1, u(1): -1, u(3): -1}, {w(5): 1}],
         "oo": [{u(1): 1, u(9): 1, u(3): -1, u(7): -1}, {v(8): 1, v(2): -1}, {w(6): 1, w(4): -1}],
     }
 
@@ -234,39 +235,111 @@ def main():
     w("namespace hw2 {")
     w("")
     w("// ---------------------------------------------------------------- linear path")
-    w("// Point values of p0 for one field: reflection-parity folding of the 19 inputs,")
-    w("// then a butterfly per orbit of mirror-image points.")
-    def emit_points(fname, pts_and_targets):
-        """One straight-line function: fold the inputs, evaluate the parity parts at the
-        representative points, and assemble the requested point values."""
+    w("// One field: reflection-parity folding of the 19 inputs, then the point values of p0 from the")
+    w("// folds, with a butterfly per orbit of mirror-image points.")
+    names = [f"{cls}{i}" for cls, fl in classes.items() for i in range(len(fl))]
+    slot = {nm: f"f[{k}]" for k, nm in enumerate(names)}
+
+    # the folding, with the four corners through their diagonal sums and differences: the
+    # same operations, up to the order of commuting operands, on the transposed stencil, so
+    # that lin2d_transpose of a fold equals the fold of the transposed stencil to the bit
+    fold = {
+        "ee0": "in[4]", "ee1": "in[3] + in[5]", "ee2": "in[1] + in[7]", "ee3": "s0 + s1",
+        "ee4": "in[12] - in[10]", "ee5": "in[18] - in[14]",
+        "oe0": "in[5] - in[3]", "oe1": "d0 + d1", "oe2": "in[11]",
+        "eo0": "in[7] - in[1]", "eo1": "d0 - d1", "eo2": "in[16]",
+        "oo0": "s0 - s1", "oo1": "in[13] - in[9]", "oo2": "in[17] - in[15]"}
+    corner = {"s0": "in[0] + in[8]", "s1": "in[2] + in[6]", "d0": "in[8] - in[0]", "d1": "in[2] - in[6]"}
+    sym = [sp.Symbol(f"i{k}") for k in range(19)]
+    def value(expr):
+        import re as _re
+        return sp.sympify(eval(_re.sub(r"in\[(\d+)\]", r"sym[\1]", expr),
+                               {"sym": sym, **{k: value(v) for k, v in corner.items() if k in expr}}))
+    for cls, fl in classes.items():
+        for i, f in enumerate(fl):
+            assert sp.expand(value(fold[f"{cls}{i}"]) - sum(sg * sym[k] for k, sg in f.items())) == 0
+    w(f"constexpr int NFOLD = {len(names)};")
+    w("__device__ __forceinline__ void lin2d_fold(const double* in, double* f) {")
+    for nm, expr in corner.items():
+        w(f"  const double {nm} = {expr};")
+    for nm in names:
+        w(f"  {slot[nm]} = {fold[nm]};")
+    w("}")
+    w("// the fold of the stencil with x and y exchanged")
+    w("__device__ __forceinline__ void lin2d_transpose(const double* f, double* g) {")
+    swap = {"ee1": "ee2", "ee4": "ee5", "oe0": "eo0", "oe1": "eo1", "oe2": "eo2", "oo1": "oo2"}
+    swap.update({v: k for k, v in swap.items()})
+    for nm in names:
+        w(f"  {slot[nm].replace('f', 'g')} = {slot[swap.get(nm, nm)]};")
+    w("}")
+    w("")
+
+    def emit_points(fname, pts_and_targets, orbits):
+        """One straight-line function of the folded inputs: the parity parts at the
+        representative points, and the requested point values by a butterfly over each
+        orbit of mirror-image points (orbits: four targets (-,-), (+,-), (-,+), (+,+) of
+        one representative each)."""
         w(f"__device__ __forceinline__ void {fname} {{")
-        for cls, fl in classes.items():
-            for i, f in enumerate(fl):
-                terms = []
-                for idx, sg in f.items():
-                    terms.append(("+" if sg > 0 else "-") + f"in[{idx}]")
-                expr = " ".join(terms).lstrip("+").strip()
-                w(f"  const double {cls}{i} = {expr};")
         reps.clear()
+        at = dict(pts_and_targets)
+        done = set()
+        for n, orb in enumerate(orbits):
+            x, y = at[orb[3]]
+            p = {cls: part(cls, x, y) for cls in cls_sign}
+            w(f"  const double p{n} = {p['ee']} + {p['oo']}, m{n} = {p['ee']} - {p['oo']};")
+            w(f"  const double q{n} = {p['oe']} + {p['eo']}, r{n} = {p['oe']} - {p['eo']};")
+            for t, e in zip(orb, (f"p{n} - q{n}", f"m{n} + r{n}", f"m{n} - r{n}", f"p{n} + q{n}")):
+                point(*at[t])   # (its self-check)
+                w(f"  {t} = {e};")
+                done.add(t)
         for target, (x, y) in pts_and_targets:
-            w(f"  {target} = {point(x, y)};")
+            if target not in done:
+                w(f"  {target} = {point(x, y)};")
         w("}")
         w("")
 
+    def emit_face(ng):
+        """The x faces' points: parity parts at (1/2, |e_k|), then one face from its side's
+        sign (side = -1 low, +1 high; its products are exact)."""
+        nodes = gauss_nodes(ng)
+        reps.clear()
+        w(f"// parity parts of the x-face points ({'ee oe eo oo at the outer pair' + (', ee oe at the middle' if ng == 3 else '')})")
+        w(f"__device__ __forceinline__ void lin2d_xparts_ng{ng}(const double* f, double* p) {{")
+        e = nodes[-1]
+        for k, cls in enumerate(cls_sign):
+            w(f"  p[{k}] = {part_expr(cls, HALF, e)};")
+        if ng == 3:
+            w(f"  p[4] = {part_expr('ee', HALF, sp.Integer(0))};")
+            w(f"  p[5] = {part_expr('oe', HALF, sp.Integer(0))};")
+        w("}")
+        w(f"__device__ __forceinline__ void lin2d_xface_ng{ng}(const double* p, double side, double* v) {{")
+        w("  v[0] = fma(side, fma(-side, p[2], p[1]), fma(-side, p[3], p[0]));")
+        if ng == 3:
+            w("  v[1] = fma(side, p[5], p[4]);")
+        w(f"  v[{ng - 1}] = fma(side, fma(side, p[2], p[1]), fma(side, p[3], p[0]));")
+        w("}")
+        w("")
+        for x in (-HALF, HALF):
+            for y in nodes:
+                point(x, y, emit=False)
+
     reps = {}
 
-    def part(cls, x, y):
-        key = (cls, x, y)
-        if key in reps:
-            return reps[key]
+    def part_expr(cls, x, y):
         row = value_row(C0, mons4, x, y)
         coefs = parity_part_rows(row, classes[cls])
+        return emit_sum([(c, slot[f"{cls}{i}"]) for i, c in enumerate(coefs)])
+
+    def part(cls, x, y, emit=True):
+        key = (cls, x, y)
+        if not emit or key in reps:
+            return reps.get(key, "")
         name = f"P{cls}_{len(reps)}"
-        w(f"  const double {name} = {emit_sum([(c, f'{cls}{i}') for i, c in enumerate(coefs)])};")
+        w(f"  const double {name} = {part_expr(cls, x, y)};")
         reps[key] = name
         return name
 
-    def point(x, y):
+    def point(x, y, emit=True):
         """expression for p0 at (x, y) from the parity parts at (|x|, |y|)."""
         ax, ay = abs(x), abs(y)
         sx = -1 if x < 0 else 1
@@ -276,7 +349,7 @@ def main():
             if (px == -1 and ax == 0) or (py == -1 and ay == 0):
                 continue   # odd part vanishes on the mirror line
             sgn = (sx if px == -1 else 1) * (sy if py == -1 else 1)
-            terms.append((sgn, part(cls, ax, ay)))
+            terms.append((sgn, part(cls, ax, ay, emit)))
         # self-check: the parity parts add up to the dense row of p0 at (x, y)
         dense = value_row(C0, mons4, x, y)
         back = [sp.Integer(0)] * 19
@@ -300,17 +373,12 @@ def main():
         return expr
 
     inner_nodes = gauss_nodes(3)
-    emit_points("lin2d_inner(const double* in, double* inner)",
+    emit_points("lin2d_inner(const double* f, double* inner)",
                 [(f"inner[{3 * l + k}]", (a, b)) for l, b in enumerate(inner_nodes)
-                 for k, a in enumerate(inner_nodes)])
+                 for k, a in enumerate(inner_nodes)],
+                [("inner[0]", "inner[2]", "inner[6]", "inner[8]")])
     for ng in (2, 3):
-        nodes = gauss_nodes(ng)
-        emit_points(f"lin2d_xedges_ng{ng}(const double* in, double* xl, double* xr)",
-                    [(f"xl[{k}]", (-HALF, e)) for k, e in enumerate(nodes)]
-                    + [(f"xr[{k}]", (HALF, e)) for k, e in enumerate(nodes)])
-        emit_points(f"lin2d_yedges_ng{ng}(const double* in, double* yb, double* yt)",
-                    [(f"yb[{k}]", (e, -HALF)) for k, e in enumerate(nodes)]
-                    + [(f"yt[{k}]", (e, HALF)) for k, e in enumerate(nodes)])
+        emit_face(ng)
 
     # ---------------------------------------------------------------- HWENO path
     w("// ---------------------------------------------------------------- HWENO path")

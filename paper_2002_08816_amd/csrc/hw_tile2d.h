@@ -31,15 +31,30 @@ struct Gauss<3> {
 // interior 3-point Gauss rule (volume integrals of eq. ode2)
 __device__ constexpr double VW[3] = {5.0 / 18.0, 4.0 / 9.0, 5.0 / 18.0};
 
+// one x face's points (side -1: low, +1: high) from the folded stencil's parity parts
 template <int NGE>
-__device__ __forceinline__ void lin_edges(const double* in, int dir, double* lo, double* hi) {
-  if constexpr (NGE == 2) {
-    if (dir == 0) hw2::lin2d_xedges_ng2(in, lo, hi);
-    else hw2::lin2d_yedges_ng2(in, lo, hi);
+__device__ __forceinline__ void lin_xparts(const double* f, double* p) {
+  if constexpr (NGE == 2) hw2::lin2d_xparts_ng2(f, p);
+  else hw2::lin2d_xparts_ng3(f, p);
+}
+template <int NGE>
+__device__ __forceinline__ void lin_xface(const double* p, double side, double* v) {
+  if constexpr (NGE == 2) hw2::lin2d_xface_ng2(p, side, v);
+  else hw2::lin2d_xface_ng3(p, side, v);
+}
+// both faces of direction dir from the folded stencil f (dir = 1: the x faces of the
+// transposed fold)
+template <int NGE>
+__device__ __forceinline__ void lin_faces(const double* f, int dir, double* lo, double* hi) {
+  double p[6], g[hw2::NFOLD];
+  if (dir == 0) {
+    lin_xparts<NGE>(f, p);
   } else {
-    if (dir == 0) hw2::lin2d_xedges_ng3(in, lo, hi);
-    else hw2::lin2d_yedges_ng3(in, lo, hi);
+    hw2::lin2d_transpose(f, g);
+    lin_xparts<NGE>(g, p);
   }
+  lin_xface<NGE>(p, -1.0, lo);
+  lin_xface<NGE>(p, 1.0, hi);
 }
 
 template <int NGE>

@@ -13,15 +13,13 @@
 //                 would otherwise each run their whole share on one compute unit.
 //  stage2d_kernel per 16 x 16 tile with two ghost layers (flags, hybrid masks and
 //                 limited moments read back): interior Gauss values of the least-squares quartic -> volume
-//                 integrals (Step 5.3); per direction, the edge values of the cell and of
-//                 its two neighbours (Step 5.2 linear, or the stored HWENO values), the
-//                 Lax-Friedrichs fluxes of its two faces and the edge quadratures of eq.
-//                 ode2; the TVD-RK3 stage combination (eq. RK) with the limited moments,
-//                 the store, and the block's share of the next stage's speeds.  Each cell
-//                 evaluates its own edge values once; a neighbour's come from a lane
-//                 shuffle, from the LDS row between two waves, or, across the tile's
-//                 sides, from the ring cells the tile evaluates once in LDS.  Each face's
-//                 flux is then formed by both of its cells from the same values.
+//                 integrals (Step 5.3); the edge values of the cell (Step 5.2 linear, or the
+//                 stored HWENO values), its shares of its four faces' Lax-Friedrichs fluxes and
+//                 the edge quadratures of eq. ode2; the TVD-RK3 stage combination (eq. RK) with the
+//                 limited moments, the store, and the block's share of the next stage's
+//                 speeds.  Each cell evaluates its own edge values and flux shares once; its
+//                 neighbours' shares, summed over the edge's Gauss points, come through LDS,
+//                 those across the tile's sides from the ring cells the tile evaluates once.
 // Without detection only stage2d_kernel runs.
 //
 // The limited first moments of the stage input replace the stored ones in the stage
@@ -541,20 +539,14 @@ __global__ __launch_bounds__(NT, BK == BK_DMR ? 2 : 1) void stage2d_hweno_kernel
 
 // ------------------------------------------------------------------ main stage kernel
 
-// Edge values of the cell at LDS position (ly, lx) on the faces of direction dir (lo:
-// left or bottom, hi: right or top; either may be null): p0 at the edge Gauss points
-// (Step 5.2), or for a hybrid cell the values the prepass stored (Step 5.1).  A ghost's
-// stored values are those of the cell it mirrors, faces and edge points reflected.
-// The 19 stencil values of component c around (ly, lx) as seen along direction dir: for
-// dir = 1 the stencil is transposed (x and y offsets swapped, x and y moments swapped),
-// so that the y-face values are the x-face map of the transposed stencil.  Every y-face
-// value in this kernel is formed this way, so the two cells of a face agree to the bit.
-// (DIR = 0 or 1: a direction known at compile time, so that the offsets are immediates;
-// DIR = -1: the direction dir of each lane)
-template <int NC, int DIR>
+// The 19 stencil values of component c around (ly, lx) as seen along the direction dir of
+// each lane: for dir = 1 the stencil is transposed (x and y offsets swapped, x and y moments
+// swapped), so that the y-face values are the x-face map of the transposed stencil.  The
+// fold of these values equals lin2d_transpose of the untransposed fold to the bit, so a
+// cell's trace is the same whether the cell itself or a neighbouring tile evaluates it.
+template <int NC>
 __device__ __forceinline__ void gather19_dir(const double* s, int c, int ly, int lx, int dir,
                                              double* in) {
-  if constexpr (DIR >= 0) dir = DIR;
   const int sa = dir == 0 ? L2 : 1, sb = dir == 0 ? 1 : L2;   // strides of dy, dx
   const double* p = s + c * NP2 + ly * L2 + lx;
 #pragma unroll
@@ -569,33 +561,13 @@ __device__ __forceinline__ void gather19_dir(const double* s, int c, int ly, int
   }
 }
 
-template <int NGE>
-__device__ __forceinline__ void lin_xfaces(const double* in, double* lo, double* hi) {
-  if constexpr (NGE == 2) hw2::lin2d_xedges_ng2(in, lo, hi);
-  else hw2::lin2d_xedges_ng3(in, lo, hi);
-}
-
-template <int EQ, int NGE, int DIR, int BK>
-__device__ __forceinline__ void cell_traces(const Stage2D& P, const double* s_u, bool hyb, int ly,
-                                            int lx, int dir, int gx0, int gy0, double (*lo)[NGE],
-                                            double (*hi)[NGE]) {
+// The HWENO edge values the prepass stored (Step 5.1) for the hybrid cell at LDS position
+// (ly, lx) on its face of direction dir and side (0 low, 1 high).  A ghost's are those of
+// the cell it mirrors, faces and edge points reflected.
+template <int EQ, int NGE, int BK>
+__device__ __forceinline__ void stored_trace(const Stage2D& P, int ly, int lx, int dir, int side,
+                                             int gx0, int gy0, double (*v)[NGE]) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
-  if constexpr (DIR >= 0) dir = DIR;
-  if (!hyb) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      double in[19], a[NGE], b[NGE];
-      gather19_dir<NC, DIR>(s_u, c, ly, lx, dir, in);
-      lin_xfaces<NGE>(in, a, b);
-#pragma unroll
-      for (int k = 0; k < NGE; ++k) {
-        if (lo) lo[c][k] = a[k];
-        if (hi) hi[c][k] = b[k];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    return;
-  }
   double sx, sy, fu = 1.0, fv = 1.0;
   int gx, gy;
   if constexpr (BK == BK_STEP) {
@@ -613,7 +585,7 @@ __device__ __forceinline__ void cell_traces(const Stage2D& P, const double* s_u,
   const bool mx = sx < 0.0, my = sy < 0.0;
   const bool swap = dir == 0 ? mx : my, flip = dir == 0 ? my : mx;
   const size_t plane = (size_t)P.nx * P.ny, gi = (size_t)gy * P.nx + gx;
-  const int slo = swap ? 1 : 0, shi = 1 - slo;
+  const int s = swap ? 1 - side : side;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     double wf;
@@ -622,46 +594,193 @@ __device__ __forceinline__ void cell_traces(const Stage2D& P, const double* s_u,
 #pragma unroll
     for (int k = 0; k < NGE; ++k) {
       const int kk = flip ? NGE - 1 - k : k;
-      if (lo) lo[c][k] = wf * P.G[((((size_t)(dir * 2 + slo) * NGE + kk) * NC + c)) * plane + gi];
-      if (hi) hi[c][k] = wf * P.G[((((size_t)(dir * 2 + shi) * NGE + kk) * NC + c)) * plane + gi];
+      v[c][k] = wf * P.G[((((size_t)(dir * 2 + s) * NGE + kk) * NC + c)) * plane + gi];
     }
   }
 }
 
-template <int EQ>
-__device__ __forceinline__ void point_flux(const double* U, int d, const Stage2D& P, double* f) {
+// One side's share f(U) + s U of twice the Lax-Friedrichs flux f(u-) + f(u+) - alpha (u+ - u-)
+// at a point: s = alpha for the low cell's trace u-, -alpha for the high cell's u+.  The flux
+// is a sum of one term per side, so each cell evaluates its own two sides once and its
+// neighbours add theirs: half the point fluxes of a form in which both cells of a face
+// evaluate all of it.  (D: direction; adv: the advection speed along it)
+template <int EQ, int D>
+__device__ __forceinline__ void flux_share(const double* U, double s, double gam, double adv, double* F) {
   if constexpr (EQ == EQ_EULER) {
-    if (d == 0) euler_flux2d_x(U, P.gam, f);
-    else euler_flux2d_y(U, P.gam, f);
+    constexpr int n = 1 + D, t = 2 - D;   // normal and tangential momentum
+    const double r = rcp_nr(U[0]);
+    const double un = U[n] * r;
+    const double p = (gam - 1.0) * (U[3] - 0.5 * (U[n] * un + U[t] * (U[t] * r)));
+    const double us = un + s;
+    F[0] = fma(s, U[0], U[n]);
+    F[n] = fma(U[n], us, p);
+    F[t] = U[t] * us;
+    F[3] = fma(U[3], us, p * un);
   } else {
-    f[0] = scalar_flux<EQ>(U[0], d == 0 ? P.adv0 : P.adv1);
+    F[0] = fma(s, U[0], scalar_flux<EQ>(U[0], adv));
   }
 }
 
-// Twice the Lax-Friedrichs flux, f(u-) + f(u+) - alpha (u+ - u-), at one face point (the
-// factor 1/2 is applied with the quadrature weight)
-template <int EQ>
-__device__ __forceinline__ void lf_flux2(const double* um, const double* up, int d, double alpha,
-                                         const Stage2D& P, double* F) {
+// Twice the flux's sums over a face's Gauss points enter the right-hand sides only through
+// S0 = sum w_k F_k and S1 = sum w_k e_k F_k (both linear in the shares, so neighbours
+// exchange two sums instead of NGE point values).  Returned up to the factors C0, C1.
+template <int NGE>
+struct FaceSums;
+template <>
+struct FaceSums<2> {
+  static constexpr double C0 = 0.5, C1 = 0.5 * 0.28867513459481288225457439025097873;
+};
+template <>
+struct FaceSums<3> {
+  static constexpr double C0 = 4.0 / 9.0, C1 = (5.0 / 18.0) * 0.38729833462074168851792653997823996;
+};
+template <int EQ, int NGE, int D>
+__device__ __forceinline__ void face_sums(const double (*tr)[NGE], double s, double gam, double adv,
+                                          double* S /* [2][NC] */) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
-  double fm[NC], fp[NC];
-  point_flux<EQ>(um, d, P, fm);
-  point_flux<EQ>(up, d, P, fp);
+  double F[NGE][NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) F[c] = fma(-alpha, up[c] - um[c], fm[c] + fp[c]);
+  for (int k = 0; k < NGE; ++k) {
+    double U[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) U[c] = tr[c][k];
+    flux_share<EQ, D>(U, s, gam, adv, F[k]);
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    if constexpr (NGE == 2) S[c] = F[0][c] + F[1][c];
+    else S[c] = fma(0.625, F[0][c] + F[2][c], F[1][c]);
+    S[NC + c] = F[NGE - 1][c] - F[0][c];
+  }
 }
 
+// Faces whose other side follows a boundary's face rule instead of a neighbour's values: the
+// forward step's inflow, outflow and walls, the double Mach reflection's top side.  Returns
+// 0 (none), 1 (the low face) or 2 (the high face) in the low two bits and above them which
+// of the direction's (at most three) such grid lines it is; that side's share sums go to
+// entry 16 * line + (position along the line) of s_spec, [sum][NC][64].  (Held in registers
+// until the exchange they would not fit beside the traces.)
+template <int EQ, int NGE, int BK, int D>
+__device__ __forceinline__ int special_face(const Stage2D& P, int gx, int gy, int along,
+                                            const double (*lo)[NGE], const double (*hi)[NGE],
+                                            double alpha, double dtv, double* s_spec) {
+  constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
+  int which = 0, line = 0;
+  double u[NC][NGE];
+  if constexpr (BK == BK_STEP) {
+    // the inflow state on the left side; at the bottom wall and the step's top face the
+    // cell's own trace with rho v reversed
+    if (D == 0 ? gx == 0 : (gy == 0 || (gy == P.sj && gx >= P.si))) {
+      which = 1;
+      line = (D == 1 && gy != 0) ? 1 : 0;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int k = 0; k < NGE; ++k) u[c][k] = D == 0 ? P.uin[c] : (c == 2 ? -lo[c][k] : lo[c][k]);
+    }
+    // the outflow takes the cell's own trace; the step's left face (rho u) and the top wall
+    // (rho v) reverse the normal momentum
+    if (D == 0 ? (gx == P.nx - 1 || (gx == P.si - 1 && gy < P.sj)) : gy == P.ny - 1) {
+      which = 2;
+      line = (D == 0 && gx != P.nx - 1) ? 1 : 2;
+      const int cn = D == 0 ? (gx == P.nx - 1 ? -1 : 1) : 2;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int k = 0; k < NGE; ++k) u[c][k] = c == cn ? -hi[c][k] : hi[c][k];
+    }
+  }
+  if constexpr (BK == BK_DMR && D == 1) {
+    // the prescribed ghost's trace is the exact state at the face's Gauss points (also where
+    // that ghost sits inside a partial last row of tiles)
+    if (gy == P.ny - 1) {
+      which = 2;
+#pragma unroll
+      for (int k = 0; k < NGE; ++k) {
+        double U[4];
+        dmr::point_state(P.x0 + (gx + 0.5 + Gauss<NGE>::node[k]) * P.dx, P.y0 + P.ny * P.dy,
+                         stage_time_of<BK>(P, dtv), P.gam, U);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) u[c][k] = U[c];
+      }
+    }
+  }
+  if (which) {
+    double S[2 * NC];
+    face_sums<EQ, NGE, D>(u, which == 1 ? alpha : -alpha, P.gam, 0.0, S);
+#pragma unroll
+    for (int v = 0; v < 2 * NC; ++v) s_spec[v * 64 + line * 16 + along] = S[v];
+  }
+  return which | (line << 2);
+}
+
+// (1/dx) sum w f(u(G)) and (1/dy) sum w g(u(G)) without the factors 1/dx, 1/dy: the volume
+// quadrature over the 3 x 3 interior Gauss points.  The rule is exact for the quartic, so
+// the parts of f and g that are linear in u are the cell averages ub themselves.
+template <int EQ>
+__device__ __forceinline__ void volume_sums(const double (*inner)[9], const double* ub, const Stage2D& P,
+                                            double* sf, double* sg) {
+  if constexpr (EQ == EQ_EULER) {
+    double muu = 0.0, muv = 0.0, mvv = 0.0, mp = 0.0, hu = 0.0, hv = 0.0;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+      const double w = VW[q % 3] * VW[q / 3];
+      const double m = inner[1][q], n = inner[2][q], E = inner[3][q];
+      const double r = rcp_nr(inner[0][q]);
+      const double u = m * r, v = n * r;
+      const double a = m * u, b = n * v;
+      const double p = (P.gam - 1.0) * (E - 0.5 * (a + b));
+      const double H = E + p;
+      muu = fma(w, a, muu);
+      muv = fma(w, n * u, muv);
+      mvv = fma(w, b, mvv);
+      mp = fma(w, p, mp);
+      hu = fma(w, u * H, hu);
+      hv = fma(w, v * H, hv);
+    }
+    sf[0] = ub[1];
+    sf[1] = muu + mp;
+    sf[2] = muv;
+    sf[3] = hu;
+    sg[0] = ub[2];
+    sg[1] = muv;
+    sg[2] = mvv + mp;
+    sg[3] = hv;
+  } else if constexpr (EQ == EQ_BURGERS) {
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) s = fma(0.5 * VW[q % 3] * VW[q / 3], inner[0][q] * inner[0][q], s);
+    sf[0] = sg[0] = s;
+  } else {
+    sf[0] = P.adv0 * ub[0];
+    sg[0] = P.adv1 * ub[0];
+  }
+}
+
+// Bound by VALU issue, then by LDS and HBM (1024^2 Euler, NG = 2: 308 MB of HBM traffic a
+// launch, about 50 us; the instructions about 45 us; the phases overlap only in part), so the
+// arithmetic per cell is what counts: one fold of a stencil serves all its point values of a
+// gather, a flux is evaluated once per trace instead of once per cell of the face, and only
+// sums over the edge's points are exchanged.  Measured against a form that gathered three
+// times, evaluated each face's flux in both of its cells and exchanged point values by lane
+// shuffles: 121 -> 96 us at 1024^2 NG = 2; 248 -> 155 us at 1501 x 997 NG = 3, where the smaller
+// exchange also lets three workgroups run per CU instead of two; 162 -> 101 us on the double
+// Mach reflection at 1920 x 480; 63 -> 40 us on the forward step at 960 x 320.  168 VGPRs and
+// 43-52 KB of LDS: three workgroups per CU.
 template <int EQ, int NGE, int BK>
-__global__ __launch_bounds__(NT, NGE == 2 ? 3 : 2) void stage2d_kernel(Stage2D P) {
+__global__ __launch_bounds__(NT, 3) void stage2d_kernel(Stage2D P) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
   constexpr int NF = 3 * NC;
-  __shared__ double s_u[NF * NP2];   // stage input, limited, on tile+2
-  __shared__ double s_ring[2 * 2 * TX * NC * NGE];          // ring cells' face values
-  __shared__ double s_bnd[(NT / 64) * 2 * TX * NC * NGE];   // y faces between waves
+  constexpr int NV = 4 * NC;         // exchanged per direction: [side: high, low][sum][NC]
+  __shared__ double s_u[NF * NP2];   // stage input, limited, on tile+2; then the exchange
+  __shared__ double s_ring[2 * NC * 64];   // ring cells' share sums [sum][NC][ring cell]
   __shared__ uint8_t s_T[NP2];
   __shared__ uint8_t s_H[NP2];
+  constexpr int NSPEC = BK == BK_RECT ? 0 : 2 * NC * 64;
+  __shared__ double s_spec[2 * NSPEC + 1];   // boundary face rules' share sums, per direction
   __shared__ double s_red[8];
   __shared__ double s_alpha[2];
+  static_assert((NT / 64) * NV * 64 <= NF * NP2, "the exchange fits the staged input's space");
 
   const int mode = P.mode;
   // the time step (zero once the run has reached its final time: nothing to do) is
@@ -681,56 +800,118 @@ __global__ __launch_bounds__(NT, NGE == 2 ? 3 : 2) void stage2d_kernel(Stage2D P
   // each thread's (at most NR) positions: flags and stored values are loaded first, the
   // limited moments of the (few) flagged cells replace the moments afterwards
   constexpr int NR = (NP2 + NT - 1) / NT;
-  size_t gsr[NR];
-  double sxr[NR], syr[NR];
-  uint8_t tr[NR], hr[NR];
-  uint8_t fwr[NR];   // forward step: bit 0 rho u, bit 1 rho v reversed
-  double v[NR][NF];
+  // a tile whose staged positions are all mesh cells needs no boundary mapping: offsets from
+  // the tile's corner, below 2^32 bytes for rows of at most 2^24 cells
+  bool inside = gx0 >= 0 && gy0 >= 0 && gx0 + L2 <= nx && gy0 + L2 <= ny && nx <= (1 << 24);
+  if constexpr (BK == BK_STEP) inside = inside && (gx0 + L2 <= P.si || gy0 >= P.sj);
+  if (inside) {
+    const size_t corner = (size_t)gy0 * nx + gx0;
+    double v[NR][NF];
+    uint32_t off[NR];
+    uint8_t tr[NR], hr[NR];
 #pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const int q = tid + r * NT;
-    tr[r] = 0;
-    hr[r] = 0;
-    fwr[r] = 0;
-    if (q < NP2) {
-      const int ly = q / L2, lx = q - ly * L2;
-      int gx, gy;
-      if constexpr (BK == BK_STEP) {
-        const step::Src sr = step::resolve(gx0 + lx, gy0 + ly, nx, ny, P.si, P.sj);
-        gx = sr.x;
-        gy = sr.y;
-        sxr[r] = sr.sx;
-        syr[r] = sr.sy;
-        fwr[r] = (sr.fu < 0.0 ? 1 : 0) | (sr.fv < 0.0 ? 2 : 0);
-        if (sr.pres) {
-          // inflow: the prescribed state, zero first moments, never troubled
-          gsr[r] = 0;
+    for (int r = 0; r < NR; ++r) {
+      const int q = tid + r * NT;
+      tr[r] = hr[r] = 0;
+      if (q < NP2) {
+        const int ly = q / L2, lx = q - ly * L2;
+        off[r] = (uint32_t)(ly * nx + lx);
+        if (tc) {
+          tr[r] = (P.Tcur + corner)[off[r]];
+          hr[r] = (P.Hcur + corner)[off[r]];
+        }
 #pragma unroll
-          for (int f = 0; f < NF; ++f) v[r][f] = f < NC ? P.uin[f] : 0.0;
+        for (int f = 0; f < NF; ++f)
+          v[r][f] = *(const double*)((const char*)(P.in + (f * plane + corner)) + off[r] * 8u);
+      }
+    }
+    if (mode != MODE_L && dt == 0.0) return;   // uniform over the grid
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int q = tid + r * NT;
+      if (q < NP2) {
+        if (tr[r]) {
+#pragma unroll
+          for (int f = NC; f < NF; ++f) v[r][f] = (P.limcur + ((f - NC) * plane + corner))[off[r]];
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) s_u[f * NP2 + q] = v[r][f];
+        s_T[q] = tr[r];
+        s_H[q] = hr[r];
+      }
+    }
+  } else {
+    size_t gsr[NR];
+    double sxr[NR], syr[NR];
+    uint8_t tr[NR], hr[NR];
+    uint8_t fwr[NR];   // forward step: bit 0 rho u, bit 1 rho v reversed
+    double v[NR][NF];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int q = tid + r * NT;
+      tr[r] = 0;
+      hr[r] = 0;
+      fwr[r] = 0;
+      if (q < NP2) {
+        const int ly = q / L2, lx = q - ly * L2;
+        int gx, gy;
+        if constexpr (BK == BK_STEP) {
+          const step::Src sr = step::resolve(gx0 + lx, gy0 + ly, nx, ny, P.si, P.sj);
+          gx = sr.x;
+          gy = sr.y;
+          sxr[r] = sr.sx;
+          syr[r] = sr.sy;
+          fwr[r] = (sr.fu < 0.0 ? 1 : 0) | (sr.fv < 0.0 ? 2 : 0);
+          if (sr.pres) {
+            // inflow: the prescribed state, zero first moments, never troubled
+            gsr[r] = 0;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[r][f] = f < NC ? P.uin[f] : 0.0;
+            continue;
+          }
+        } else {
+          gx = map_index(gx0 + lx, nx, P.bcx, sxr[r]);
+          gy = map_index(gy0 + ly, ny, P.bcy, syr[r]);
+        }
+        gsr[r] = (size_t)gy * nx + gx;
+        if (dmr_prescribed<BK>(P, gx0 + lx, gy0 + ly)) {
+          // prescribed ghost: the exact solution, never troubled, no mirror signs
+          const double ts = stage_time_of<BK>(P, dtv);
+#pragma unroll
+          for (int f = 0; f < NF; ++f) v[r][f] = dmr_value(P, f, gx0 + lx, gy0 + ly, ts);
+          sxr[r] = syr[r] = 1.0;
           continue;
         }
-      } else {
-        gx = map_index(gx0 + lx, nx, P.bcx, sxr[r]);
-        gy = map_index(gy0 + ly, ny, P.bcy, syr[r]);
-      }
-      gsr[r] = (size_t)gy * nx + gx;
-      if (dmr_prescribed<BK>(P, gx0 + lx, gy0 + ly)) {
-        // prescribed ghost: the exact solution, never troubled, no mirror signs
-        const double ts = stage_time_of<BK>(P, dtv);
+        if (tc) {
+          tr[r] = P.Tcur[gsr[r]];
+          hr[r] = P.Hcur[gsr[r]];   // a ghost's mask is that of the cell it mirrors
+        }
 #pragma unroll
-        for (int f = 0; f < NF; ++f) v[r][f] = dmr_value(P, f, gx0 + lx, gy0 + ly, ts);
-        sxr[r] = syr[r] = 1.0;
-        continue;
+        for (int f = 0; f < NF; ++f) v[r][f] = P.in[f * plane + gsr[r]];
       }
-      if (tc) {
-        tr[r] = P.Tcur[gsr[r]];
-        hr[r] = P.Hcur[gsr[r]];   // a ghost's mask is that of the cell it mirrors
-      }
+    }
+    if (mode != MODE_L && dt == 0.0) return;   // uniform over the grid
 #pragma unroll
-      for (int f = 0; f < NF; ++f) v[r][f] = P.in[f * plane + gsr[r]];
+    for (int r = 0; r < NR; ++r) {
+      const int q = tid + r * NT;
+      if (q < NP2) {
+        if (tr[r]) {
+#pragma unroll
+          for (int f = NC; f < NF; ++f) v[r][f] = P.limcur[(f - NC) * plane + gsr[r]];
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          const int m = f / NC, c = f % NC;
+          double wf;
+          if constexpr (BK == BK_STEP) wf = ((c == 1 && (fwr[r] & 1)) || (c == 2 && (fwr[r] & 2))) ? -1.0 : 1.0;
+          else wf = wall_factor<EQ>(c, sxr[r] < 0.0, syr[r] < 0.0, P.bcx, P.bcy);
+          s_u[f * NP2 + q] = wf * (m == 1 ? sxr[r] * v[r][f] : (m == 2 ? syr[r] * v[r][f] : v[r][f]));
+        }
+        s_T[q] = tr[r];
+        s_H[q] = hr[r];
+      }
     }
   }
-  if (mode != MODE_L && dt == 0.0) return;   // uniform over the grid
   // this stage's prepasses are done: record the list lengths, empty the lists for the next
   // stage
   if (tc && blockIdx.x == 0 && tid == 0) {
@@ -741,26 +922,6 @@ __global__ __launch_bounds__(NT, NGE == 2 ? 3 : 2) void stage2d_kernel(Stage2D P
     P.counts[1] = 0;
   }
   reduce_speeds(P.alpha_in, s_alpha);   // visible after the staging barrier
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const int q = tid + r * NT;
-    if (q < NP2) {
-      if (tr[r]) {
-#pragma unroll
-        for (int f = NC; f < NF; ++f) v[r][f] = P.limcur[(f - NC) * plane + gsr[r]];
-      }
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const int m = f / NC, c = f % NC;
-        double wf;
-        if constexpr (BK == BK_STEP) wf = ((c == 1 && (fwr[r] & 1)) || (c == 2 && (fwr[r] & 2))) ? -1.0 : 1.0;
-        else wf = wall_factor<EQ>(c, sxr[r] < 0.0, syr[r] < 0.0, P.bcx, P.bcy);
-        s_u[f * NP2 + q] = wf * (m == 1 ? sxr[r] * v[r][f] : (m == 2 ? syr[r] * v[r][f] : v[r][f]));
-      }
-      s_T[q] = tr[r];
-      s_H[q] = hr[r];
-    }
-  }
   __syncthreads();
 
   // ---------------------------------------------------------------- tile cell
@@ -771,21 +932,52 @@ __global__ __launch_bounds__(NT, NGE == 2 ? 3 : 2) void stage2d_kernel(Stage2D P
   // the solid cells of the forward step are never updated
   bool active = inmesh;
   if constexpr (BK == BK_STEP) active = inmesh && !step::solid(gx, gy, P.si, P.sj);
-
+  const size_t gi = active ? (size_t)gy * nx + gx : 0;
   const int lane = tid & 63, wv = tid >> 6;
-  // stages 2 and 3: whether u^n of this cell was limited (read now, so that the epilogue
-  // issues the loads of u^n and of its limited moments together)
-  const bool rk23 = mode == MODE_RK2 || mode == MODE_RK3;
-  const uint8_t tn = (rk23 && active) ? P.Tn[(size_t)gy * nx + gx] : 0;
+
+  // out = a W(u^n) + b (W(u^(s)) + dt L) with (a, b) of the stage (eq. RK): acc starts with
+  // the first two terms, and every part of L is added with the factor b dt.  The operator
+  // alone: a = b = 0 and the factor 1.
+  double ca, cb;
+  rk_coeffs(mode, ca, cb);
+  const double cdt = mode == MODE_L ? 1.0 : cb * dt;
+  if (mode == MODE_L) cb = 0.0;
+  // stages 2 and 3: W(u^n), loaded now and used after the volume quadrature
+  double Wn[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) Wn[f] = 0.0;
+  if ((mode == MODE_RK2 || mode == MODE_RK3) && active) {
+    const bool tn = tc && P.Tn[gi] != 0;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) Wn[f] = P.base[(size_t)f * plane + gi];
+    if (tn) {
+#pragma unroll
+      for (int f = NC; f < NF; ++f) Wn[f] = P.limn[(size_t)(f - NC) * plane + gi];
+    }
+  }
+
   // ring cells (the tile's neighbours across its four sides), all 64 by wave 0: lanes
-  // 32 d .. 32 d + 31 those of direction d, the low side's high-face values and the high
-  // side's low-face values
+  // 32 d .. 32 d + 31 those of direction d, the low side's high faces and the high side's
+  // low faces
   if (wv == 0) {
     const int rd = lane / (2 * TX), rs = (lane / TX) & 1, rp = lane % TX;
     const int rly = rd == 0 ? H2 + rp : (rs == 0 ? H2 - 1 : H2 + TY);
     const int rlx = rd == 0 ? (rs == 0 ? H2 - 1 : H2 + TX) : H2 + rp;
-    double a[NC][NGE], b[NC][NGE];
-    cell_traces<EQ, NGE, -1, BK>(P, s_u, s_H[rly * L2 + rlx] != 0, rly, rlx, rd, gx0, gy0, a, b);
+    double a[NC][NGE];
+    if (s_H[rly * L2 + rlx] == 0) {
+      const double side = rs == 0 ? 1.0 : -1.0;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        double in[19], f[hw2::NFOLD], p[6];
+        gather19_dir<NC>(s_u, c, rly, rlx, rd, in);
+        hw2::lin2d_fold(in, f);
+        lin_xparts<NGE>(f, p);
+        lin_xface<NGE>(p, side, a[c]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      stored_trace<EQ, NGE, BK>(P, rly, rlx, rd, rs == 0 ? 1 : 0, gx0, gy0, a);
+    }
     if constexpr (BK == BK_DMR) {
       if (dmr_prescribed<BK>(P, gx0 + rlx, gy0 + rly)) {
         // the face shared with the tile: the ring cell's high face (rs = 0) or low face
@@ -804,240 +996,219 @@ __global__ __launch_bounds__(NT, NGE == 2 ? 3 : 2) void stage2d_kernel(Stage2D P
           }
           dmr::point_state(x, y, ts, P.gam, U);
 #pragma unroll
-          for (int c = 0; c < NC; ++c) a[c][k] = b[c][k] = U[c];
+          for (int c = 0; c < NC; ++c) a[c][k] = U[c];
         }
       }
     }
+    // both directions as x fluxes: the momenta exchanged for y
+    if constexpr (EQ == EQ_EULER) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+      for (int k = 0; k < NGE; ++k) {
+        const double m = a[1][k], n = a[2][k];
+        a[1][k] = rd == 0 ? m : n;
+        a[2][k] = rd == 0 ? n : m;
+      }
+    }
+    double S[2 * NC];
+    const double al = s_alpha[rd];
+    face_sums<EQ, NGE, 0>(a, rs == 0 ? al : -al, P.gam, rd == 0 ? P.adv0 : P.adv1, S);
 #pragma unroll
-      for (int k = 0; k < NGE; ++k)
-        s_ring[(((rd * 2 + rs) * NC + c) * NGE + k) * TX + rp] = rs == 0 ? b[c][k] : a[c][k];
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int cc = (c == 0 || c == 3) ? c : (rd == 0 ? c : 3 - c);
+        s_ring[(j * NC + cc) * 64 + lane] = S[j * NC + c];
+      }
   }
-  double RU[NC], RV[NC], RW[NC];
-  // volume quadrature: (1/dx) sum w_k w_l f(u(G_kl)) and (1/dy) sum w_k w_l g(u(G_kl))
+
+  double acc[NF];
   {
-    double inner[NC][9];
+    double inner[NC][9], ub[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      double in[19];
+      double in[19], f[hw2::NFOLD];
       gather19<NC, L2>(s_u, c, ly, lx, in);
-      hw2::lin2d_inner(in, inner[c]);
+      ub[c] = in[4];
+      acc[c] = cb * in[4];
+      acc[NC + c] = cb * in[11];
+      acc[2 * NC + c] = cb * in[16];
+      hw2::lin2d_fold(in, f);
+      hw2::lin2d_inner(f, inner[c]);
       __builtin_amdgcn_sched_barrier(0);
     }
     double sf[NC], sg[NC];
+    volume_sums<EQ>(inner, ub, P, sf, sg);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) sf[c] = sg[c] = 0.0;
+    for (int c = 0; c < NC; ++c) {
+      acc[c] = fma(ca, Wn[c], acc[c]);
+      acc[NC + c] = fma(cdt * P.idx, sf[c], fma(ca, Wn[NC + c], acc[NC + c]));
+      acc[2 * NC + c] = fma(cdt * P.idy, sg[c], fma(ca, Wn[2 * NC + c], acc[2 * NC + c]));
+    }
+    // formed here: left to itself the compiler sinks this phase to the stores, holding the
+    // interior values in scratch until then
 #pragma unroll
-    for (int p = 0; p < 9; ++p) {
-      const double wq = VW[p % 3] * VW[p / 3];
-      double U[NC], f[NC], g[NC];
+    for (int f = 0; f < NF; ++f) asm volatile("" : "+v"(acc[f]));
+  }
+  if (mode == MODE_L && P.wout && active) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) U[c] = inner[c][p];
-      if constexpr (EQ == EQ_EULER) {
-        euler_flux2d_xy(U, P.gam, f, g);
-      } else {
-        f[0] = scalar_flux<EQ>(U[0], P.adv0);
-        g[0] = scalar_flux<EQ>(U[0], P.adv1);
-      }
+    for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gi] = S<L2>(s_u, f, ly, lx);
+  }
+
+  // ---------------------------------------------------------------- traces and share sums
+  // the cell's traces on its four faces (p0, or the stored HWENO values of a hybrid cell)
+  // and, per direction, the sums of its shares: E[dir][0] its high face's (u- there),
+  // E[dir][1] its low face's (u+ there)
+  // the stencils are gathered again (kept from the volume phase they would take 120 VGPRs):
+  // the row is made opaque so that the compiler does not keep them
+  int ly2 = ly;
+  asm volatile("" : "+v"(ly2));
+  const bool hyb = s_H[ly * L2 + lx] != 0;
+  const double al0 = s_alpha[0], al1 = s_alpha[1];
+  double E[2][2][2 * NC];
+  int sp[2] = {0, 0};
+  if constexpr (NGE == 2) {
+    // both directions from one gather
+    double xl[NC][NGE], xh[NC][NGE], yl[NC][NGE], yh[NC][NGE];
+    if (!hyb) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        sf[c] = fma(wq, f[c], sf[c]);
-        sg[c] = fma(wq, g[c], sg[c]);
+        double in[19], f[hw2::NFOLD];
+        gather19<NC, L2>(s_u, c, ly2, lx, in);
+        hw2::lin2d_fold(in, f);
+        lin_faces<NGE>(f, 0, xl[c], xh[c]);
+        lin_faces<NGE>(f, 1, yl[c], yh[c]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+    } else {
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 0, 0, gx0, gy0, xl);
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 0, 1, gx0, gy0, xh);
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 1, 0, gx0, gy0, yl);
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 1, 1, gx0, gy0, yh);
+    }
+    if constexpr (BK != BK_RECT) {
+      sp[0] = special_face<EQ, NGE, BK, 0>(P, gx, gy, ty, xl, xh, al0, dtv, s_spec);
+      sp[1] = special_face<EQ, NGE, BK, 1>(P, gx, gy, tx, yl, yh, al1, dtv, s_spec + NSPEC);
+    }
+    face_sums<EQ, NGE, 0>(xh, al0, P.gam, P.adv0, E[0][0]);
+    face_sums<EQ, NGE, 0>(xl, -al0, P.gam, P.adv0, E[0][1]);
+    face_sums<EQ, NGE, 1>(yh, al1, P.gam, P.adv1, E[1][0]);
+    face_sums<EQ, NGE, 1>(yl, -al1, P.gam, P.adv1, E[1][1]);
+  } else {
+    // three points per edge: one direction at a time (96 VGPRs of traces otherwise)
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+      double tl[NC][NGE], th[NC][NGE];
+      asm volatile("" : "+v"(ly2));
+      if (!hyb) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          double in[19], f[hw2::NFOLD];
+          gather19<NC, L2>(s_u, c, ly2, lx, in);
+          hw2::lin2d_fold(in, f);
+          lin_faces<NGE>(f, dir, tl[c], th[c]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 0, gx0, gy0, tl);
+        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 1, gx0, gy0, th);
+      }
+      if (dir == 0) {
+        if constexpr (BK != BK_RECT) sp[0] = special_face<EQ, NGE, BK, 0>(P, gx, gy, ty, tl, th, al0, dtv, s_spec);
+        face_sums<EQ, NGE, 0>(th, al0, P.gam, P.adv0, E[0][0]);
+        face_sums<EQ, NGE, 0>(tl, -al0, P.gam, P.adv0, E[0][1]);
+      } else {
+        if constexpr (BK != BK_RECT) sp[1] = special_face<EQ, NGE, BK, 1>(P, gx, gy, tx, tl, th, al1, dtv, s_spec + NSPEC);
+        face_sums<EQ, NGE, 1>(th, al1, P.gam, P.adv1, E[1][0]);
+        face_sums<EQ, NGE, 1>(tl, -al1, P.gam, P.adv1, E[1][1]);
+      }
+#pragma unroll
+      for (int v = 0; v < 2 * NC; ++v) asm volatile("" : "+v"(E[dir][0][v]), "+v"(E[dir][1][v]));
+    }
+  }
+  __syncthreads();   // the staged input is done with: its space holds the exchange
+
+  // ---------------------------------------------------------------- exchange and faces
+  // a cell's two faces of each direction: its own share sums plus the neighbour's, read from
+  // the wave's own block (x; y inside the wave's four rows), the neighbouring wave's block,
+  // or the ring.  Both cells of a face add the same two values.
+  double* const own_blk = s_u + wv * NV * 64 + lane;
+#pragma unroll
+  for (int dir = 0; dir < 2; ++dir) {
+#pragma unroll
+    for (int v = 0; v < 2 * NC; ++v) {
+      own_blk[v * 64] = E[dir][0][v];
+      own_blk[(2 * NC + v) * 64] = E[dir][1][v];
+    }
+    const double *lo, *hi;   // the low neighbour's high-face sums, the high neighbour's low-face sums
+    if (dir == 0) {
+      // x neighbours share the wave: its LDS operations stay in order, no barrier
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      lo = tx == 0 ? s_ring + ty : own_blk - 1;
+      hi = tx == TX - 1 ? s_ring + TX + ty : own_blk + 2 * NC * 64 + 1;
+    } else {
+      __syncthreads();
+      lo = (ty & 3) != 0 ? own_blk - TX : (wv == 0 ? s_ring + 2 * TX + tx : own_blk - NV * 64 + 48);
+      hi = (ty & 3) != 3 ? own_blk + 2 * NC * 64 + TX
+                         : (wv == NT / 64 - 1 ? s_ring + 3 * TX + tx : own_blk + (NV + 2 * NC) * 64 - 48);
+    }
+    const double k = cdt * (dir == 0 ? P.idx : P.idy);
+    const double kU = -0.5 * FaceSums<NGE>::C0 * k, kP = 0.5 * kU, kQ = -0.5 * FaceSums<NGE>::C1 * k;
+    const int fP = dir == 0 ? NC : 2 * NC, fQ = dir == 0 ? 2 * NC : NC;
+    if constexpr (BK != BK_RECT) {
+      const double* spec = s_spec + dir * NSPEC + (sp[dir] >> 2) * 16 + (dir == 0 ? ty : tx);
+      if ((sp[dir] & 3) == 1) lo = spec;
+      if ((sp[dir] & 3) == 2) hi = spec;
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      RU[c] = 0.0;
-      RV[c] = sf[c] * P.idx;
-      RW[c] = sg[c] * P.idy;
+      const double L0 = lo[c * 64] + E[dir][1][c], R0 = E[dir][0][c] + hi[c * 64];
+      const double L1 = lo[(NC + c) * 64] + E[dir][1][NC + c], R1 = E[dir][0][NC + c] + hi[(NC + c) * 64];
+      acc[c] = fma(kU, R0 - L0, acc[c]);
+      acc[fP + c] = fma(kP, L0 + R0, acc[fP + c]);
+      acc[fQ + c] = fma(kQ, R1 - L1, acc[fQ + c]);
     }
-  }
-
-  const double* node = Gauss<NGE>::node;
-  const double* wt = Gauss<NGE>::wt;
-#pragma unroll 1
-  for (int dir = 0; dir < 2; ++dir) {
-    // edge values: this cell's two sides; the low neighbour's high side and the high
-    // neighbour's low side come from the lanes that own those cells (x: the next lane of
-    // the 16-lane row; y: 16 lanes away, or the neighbouring wave's row through LDS), and
-    // across the tile's sides from the ring values
-    double ol[NC][NGE], oh[NC][NGE];
-    const bool hyb = s_H[ly * L2 + lx] != 0;
-    if (dir == 0) cell_traces<EQ, NGE, 0, BK>(P, s_u, hyb, ly, lx, 0, gx0, gy0, ol, oh);
-    else cell_traces<EQ, NGE, 1, BK>(P, s_u, hyb, ly, lx, 1, gx0, gy0, ol, oh);
-    const bool edge_lo = dir == 0 ? tx == 0 : (ty & 3) == 0;
-    const bool edge_hi = dir == 0 ? tx == TX - 1 : (ty & 3) == 3;
-    if (dir == 1) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int k = 0; k < NGE; ++k) {
-          if (edge_lo) s_bnd[(((wv * 2 + 0) * NC + c) * NGE + k) * TX + tx] = ol[c][k];
-          if (edge_hi) s_bnd[(((wv * 2 + 1) * NC + c) * NGE + k) * TX + tx] = oh[c][k];
-        }
-    }
-    __syncthreads();
-    // where the neighbour's value is read from LDS (ring or neighbouring wave)
-    const double* lo_src = nullptr;
-    const double* hi_src = nullptr;
     if (dir == 0) {
-      lo_src = s_ring + (0 * 2 + 0) * NC * NGE * TX + ty;
-      hi_src = s_ring + (0 * 2 + 1) * NC * NGE * TX + ty;
-    } else {
-      lo_src = wv == 0 ? s_ring + (1 * 2 + 0) * NC * NGE * TX + tx
-                       : s_bnd + ((wv - 1) * 2 + 1) * NC * NGE * TX + tx;
-      hi_src = wv == NT / 64 - 1 ? s_ring + (1 * 2 + 1) * NC * NGE * TX + tx
-                                 : s_bnd + ((wv + 1) * 2 + 0) * NC * NGE * TX + tx;
-    }
-    const int step = dir == 0 ? 1 : TX;
-    const int from_lo = (lane - step) & 63, from_hi = (lane + step) & 63;
-    const double alpha = s_alpha[dir];
-    const double inv = dir == 0 ? P.idx : P.idy;
-    // face fluxes point by point, accumulated straight into the right-hand sides:
-    // x faces feed the x moment with (F_L + F_R)/2 and the y moment with the node-weighted
-    // difference, y faces the other way round
-#pragma unroll
-    for (int k = 0; k < NGE; ++k) {
-      double um[NC], up[NC], FL[NC], FR[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double l = __shfl(oh[c][k], from_lo, 64);
-        um[c] = edge_lo ? lo_src[(c * NGE + k) * TX] : l;
-        up[c] = ol[c][k];
-      }
-      if constexpr (BK == BK_STEP) {
-        // face rule: the inflow state on the left side; at the bottom wall and the step's
-        // top face the cell's own trace with rho v reversed
-        if (dir == 0 ? gx == 0 : (gy == 0 || (gy == P.sj && gx >= P.si))) {
-#pragma unroll
-          for (int c = 0; c < NC; ++c) um[c] = dir == 0 ? P.uin[c] : (c == 2 ? -ol[c][k] : ol[c][k]);
-        }
-      }
-      lf_flux2<EQ>(um, up, dir, alpha, P, FL);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double r = __shfl(ol[c][k], from_hi, 64);
-        um[c] = oh[c][k];
-        up[c] = edge_hi ? hi_src[(c * NGE + k) * TX] : r;
-      }
-      if constexpr (BK == BK_STEP) {
-        // face rule: the outflow takes the cell's own trace; the step's left face (rho u)
-        // and the top wall (rho v) reverse the normal momentum
-        if (dir == 0 ? (gx == nx - 1 || (gx == P.si - 1 && gy < P.sj)) : gy == ny - 1) {
-          const int cn = dir == 0 ? (gx == nx - 1 ? -1 : 1) : 2;
-#pragma unroll
-          for (int c = 0; c < NC; ++c) up[c] = c == cn ? -oh[c][k] : oh[c][k];
-        }
-      }
-      if constexpr (BK == BK_DMR) {
-        // the top boundary: the prescribed ghost's trace is the exact state at the face's
-        // Gauss points (the ring pass stores the same values; this also covers a ghost
-        // that sits inside a partial last row of tiles)
-        if (dir == 1 && gy == ny - 1) {
-          double U[4];
-          dmr::point_state(P.x0 + (gx + 0.5 + node[k]) * P.dx, P.y0 + ny * P.dy,
-                           stage_time_of<BK>(P, dtv), P.gam, U);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) up[c] = U[c];
-        }
-      }
-      lf_flux2<EQ>(um, up, dir, alpha, P, FR);
-      // FL, FR hold twice the fluxes
-      const double wd = 0.5 * wt[k] * inv, wm = 0.5 * wt[k] * node[k] * inv;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        RU[c] = fma(-wd, FR[c] - FL[c], RU[c]);
-        if (dir == 0) {
-          RV[c] = fma(-0.5 * wd, FL[c] + FR[c], RV[c]);
-          RW[c] = fma(-wm, FR[c] - FL[c], RW[c]);
-        } else {
-          RW[c] = fma(-0.5 * wd, FL[c] + FR[c], RW[c]);
-          RV[c] = fma(-wm, FR[c] - FL[c], RV[c]);
-        }
-      }
+      // the block is written again for y once every lane of the wave has read it
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   }
 
   // ---------------------------------------------------------------- epilogue
-  const uint8_t myT = s_T[ly * L2 + lx];
   double sp0 = 0.0, sp1 = 0.0;
   if constexpr (BK == BK_STEP) {
     // solid cells: no flags; the operator alone reports zero and the stored state
     if (inmesh && !active) {
-      const size_t gi = (size_t)gy * nx + gx;
-      if (P.flagsT) P.flagsT[gi] = 0;
-      if (P.flagsH) P.flagsH[gi] = 0;
+      const size_t gs = (size_t)gy * nx + gx;
+      if (P.flagsT) P.flagsT[gs] = 0;
+      if (P.flagsH) P.flagsH[gs] = 0;
       if (mode == MODE_L) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) P.out[(size_t)f * plane + gi] = 0.0;
+        for (int f = 0; f < NF; ++f) P.out[(size_t)f * plane + gs] = 0.0;
         if (P.wout) {
 #pragma unroll
-          for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gi] = P.in[(size_t)f * plane + gi];
+          for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gs] = P.in[(size_t)f * plane + gs];
         }
       }
     }
   }
   if (active) {
-    const size_t gi = (size_t)gy * nx + gx;
-    if (P.flagsT) P.flagsT[gi] = myT;
+    if (P.flagsT) P.flagsT[gi] = s_T[ly * L2 + lx];
     if (P.flagsH) P.flagsH[gi] = s_H[ly * L2 + lx];
-    double own[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) own[f] = S<L2>(s_u, f, ly, lx);   // limited stage input
-    if (mode == MODE_L) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        P.out[(size_t)c * plane + gi] = RU[c];
-        P.out[(size_t)(NC + c) * plane + gi] = RV[c];
-        P.out[(size_t)(2 * NC + c) * plane + gi] = RW[c];
-      }
-      if (P.wout) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gi] = own[f];
-      }
-    } else {
-      double Wn[NF];
-      if (mode == MODE_RK1) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) Wn[f] = own[f];
-      } else {
-#pragma unroll
-        for (int f = 0; f < NC; ++f) Wn[f] = P.base[(size_t)f * plane + gi];
-        if (tn) {
-#pragma unroll
-          for (int f = NC; f < NF; ++f) Wn[f] = P.limn[(size_t)(f - NC) * plane + gi];
-        } else {
-#pragma unroll
-          for (int f = NC; f < NF; ++f) Wn[f] = P.base[(size_t)f * plane + gi];
-        }
-      }
-      // out = a W(u^n) + b (W(u^(s)) + dt L), with (a, b) of the stage (eq. RK)
-      double ca, cb;
-      rk_coeffs(mode, ca, cb);
-      const double cdt = cb * dt;
-      double res[NF];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double L3[3] = {RU[c], RV[c], RW[c]};
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          const int f = m * NC + c;
-          res[f] = fma(cdt, L3[m], fma(ca, Wn[f], cb * own[f]));
-        }
-      }
+    for (int f = 0; f < NF; ++f) P.out[(size_t)f * plane + gi] = acc[f];
+    if (mode != MODE_L) {
       int bad = 0;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        P.out[(size_t)f * plane + gi] = res[f];
-        if (!isfinite(res[f])) bad |= 1;
-      }
+      for (int f = 0; f < NF; ++f)
+        if (!isfinite(acc[f])) bad |= 1;
       if constexpr (EQ == EQ_EULER) {
         double p;
-        euler_speeds2d(res, P.gam, sp0, sp1, p);
-        if (!(res[0] > 0.0) || !(p > 0.0)) bad |= 2;
+        euler_speeds2d(acc, P.gam, sp0, sp1, p);
+        if (!(acc[0] > 0.0) || !(p > 0.0)) bad |= 2;
       } else if constexpr (EQ == EQ_BURGERS) {
-        sp0 = sp1 = fabs(res[0]);
+        sp0 = sp1 = fabs(acc[0]);
       } else {
         sp0 = fabs(P.adv0);
         sp1 = fabs(P.adv1);
