@@ -42,6 +42,7 @@ struct Stage2D {
   int* flist;             // flagged cells (global index)
   int* hlist;             // hybrid cells (global index)
   long long* stats;       // per stage of the last step: flagged [3], hybrid [3] cell counts
+                          // (the one-launch stage adds to its entries, zeroed before the step)
   const unsigned long long* alpha_in;   // Lax-Friedrichs speeds of the stage input [2][ASPREAD]
   unsigned long long* alpha_out;        // max accumulator of the output's speeds [2][ASPREAD]
   const double* dt;       // device time step
@@ -49,6 +50,7 @@ struct Stage2D {
   uint8_t* flagsH;        // optional export of this stage's hybrid mask H
   double* wout;           // optional export of the limited stage input
   int* status;            // bit 0: non-finite output, bit 1: rho <= 0 or p <= 0
+  int keep_lists;         // one-launch stage: store the work lists too (a recorded stage)
   int nx, ny, bcx, bcy, tc_mode, mode;
   double dx, dy, h, gam, adv0, adv1;
   double idx, idy;        // 1/dx, 1/dy

@@ -33,10 +33,11 @@ thread_local std::string g_last_error;
 // Start of a step: the speeds of u^n (slot 3 of the previous step, or of a freshly set
 // state) move to slot 0, the time step follows (fixed, or CFL), slots 1-3 are cleared.
 // 1D: one thread per instance, one entry per direction.  2D (one instance): one 64-lane
-// wave, lane j handling partial-maximum entry j of each direction.
+// wave, lane j handling partial-maximum entry j of each direction; stats (may be null) are the
+// step's list lengths.
 __global__ void dt_kernel(int ninst, int ndir, int spread, unsigned long long* alpha, double* dt,
                           double* t, long long* steps, double fixed_dt, double T_end, double cfl,
-                          const double* dxs, double dy) {
+                          const double* dxs, double dy, long long* stats) {
   double a[2] = {0.0, 0.0};
   int b, lane = 0, W;
   if (spread == 1) {
@@ -77,6 +78,8 @@ __global__ void dt_kernel(int ninst, int ndir, int spread, unsigned long long* a
         else alpha[s * W + d * spread + lane] = 0ull;
       }
   }
+  // list lengths of the step (2D; the one-launch stages add to them)
+  if (stats && lane < 6 && h != 0.0) stats[lane] = 0;
   if (lane == 0) {
     dt[b] = h;
     if (h > 0.0) {
@@ -86,9 +89,11 @@ __global__ void dt_kernel(int ninst, int ndir, int spread, unsigned long long* a
   }
 }
 
-__global__ void zero_u64(unsigned long long* p, int n) {
+// zeroes p[0..n) and, when q is not null, q[0], q[stride] .. q[(m - 1) stride]
+__global__ void zero_u64(unsigned long long* p, int n, unsigned long long* q, int m, int stride) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0ull;
+  if (q && i < m) q[i * stride] = 0ull;
 }
 
 }  // namespace
@@ -495,9 +500,13 @@ extern "C" hw_status hw_get_sizes(const hw_solver* h, long* cells, int* ncomp, i
 
 // ------------------------------------------------------------------------------ launches
 
-static hw_status launch_alpha(hw_solver* h, const double* U, unsigned long long* out) {
+// the speeds of U into out; stats (may be null): the list lengths a following operator adds to
+// (its entries of the first stage, [0] and [3])
+static hw_status launch_alpha(hw_solver* h, const double* U, unsigned long long* out,
+                              long long* stats = nullptr) {
   const int W = h->aw;
-  hipLaunchKernelGGL(zero_u64, dim3((W + 255) / 256), dim3(256), 0, h->stream, out, W);
+  hipLaunchKernelGGL(zero_u64, dim3((W + 255) / 256), dim3(256), 0, h->stream, out, W,
+                     (unsigned long long*)stats, 2, 3);
   HWCHK(hipGetLastError());
   if (h->dim == 2) {
     int si, sj;
@@ -572,6 +581,7 @@ static hw_status launch_stage(hw_solver* h, int mode, const double* in, const do
       P.flist = rec->wl + 2;
       P.hlist = rec->wl + 2 + h->ncell;
       P.stats = rec->stats;
+      P.keep_lists = 1;
     }
     P.alpha_in = ain; P.alpha_out = aout; P.dt = dtp ? dtp : h->dt;
     P.flagsT = fT; P.flagsH = fH; P.wout = wout; P.status = h->status;
@@ -611,10 +621,11 @@ static void launch_dt(hw_solver* h, double fixed_dt, double T_end) {
   const double dy = h->dim == 2 ? (h->cfg.y1 - h->cfg.y0) / h->cfg.ny : 1.0;
   if (h->dim == 2)
     hipLaunchKernelGGL(dt_kernel, dim3(1), dim3(64), 0, h->stream, 1, 2, hw::ASPREAD, h->alpha, h->dt,
-                       h->t, h->steps, fixed_dt, T_end, h->cfg.cfl, h->dxs, dy);
+                       h->t, h->steps, fixed_dt, T_end, h->cfg.cfl, h->dxs, dy, h->stats);
   else
     hipLaunchKernelGGL(dt_kernel, dim3((h->ninst + 63) / 64), dim3(64), 0, h->stream, h->ninst, h->ndir, 1,
-                       h->alpha, h->dt, h->t, h->steps, fixed_dt, T_end, h->cfg.cfl, h->dxs, dy);
+                       h->alpha, h->dt, h->t, h->steps, fixed_dt, T_end, h->cfg.cfl, h->dxs, dy,
+                       (long long*)nullptr);
 }
 
 static hw_status enqueue_step(hw_solver* h, double fixed_dt, double T_end, int persistent) {
@@ -878,7 +889,7 @@ extern "C" hw_status hw_run(hw_solver* h, double T, long max_steps, long* steps_
 extern "C" hw_status hw_apply_operator(hw_solver* h, const double* d_in, double* d_L, double* d_lim) {
   if (!h) return fail(nullptr, HW_EINVAL, "null handle");
   if (!d_in || !d_L) return fail(h, HW_EINVAL, "null device array");
-  hw_status s = launch_alpha(h, d_in, h->alpha_op);
+  hw_status s = launch_alpha(h, d_in, h->alpha_op, h->stats);
   if (s != HW_OK) return s;
   return launch_stage(h, hw::MODE_L, d_in, d_in, d_L, h->alpha_op, nullptr, 0, d_lim, 0);
 }
@@ -1160,10 +1171,12 @@ extern "C" hw_status hw_adjoint(hw_solver* h, const double* d_lambda_T, double* 
     HWCHK(hipMemcpyAsync(h->hist, h->ckpt + (size_t)seg * st, st * sizeof(double),
                          hipMemcpyDeviceToDevice, h->stream));
     const int na = (3 * m + 1) * h->aw;
-    hipLaunchKernelGGL(zero_u64, dim3((na + 255) / 256), dim3(256), 0, h->stream, h->ahist, na);
+    const bool rec = h->recT != nullptr;
+    // the segment's speeds and its recorded stages' list lengths start at zero
+    hipLaunchKernelGGL(zero_u64, dim3((na + 255) / 256), dim3(256), 0, h->stream, h->ahist, na,
+                       (unsigned long long*)h->recStats, rec ? 6 * m : 0, 1);
     HWCHK(hipGetLastError());
     if ((s = launch_alpha(h, h->hist, h->ahist)) != HW_OK) return s;
-    const bool rec = h->recT != nullptr;
     for (int i = 0; i < m; ++i) {
       double* S = h->hist + 3 * (size_t)i * st;
       const int aw = h->aw;

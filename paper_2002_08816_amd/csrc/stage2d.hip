@@ -20,7 +20,8 @@
 //                 speeds.  Each cell evaluates its own edge values and flux shares once; its
 //                 neighbours' shares, summed over the edge's Gauss points, come through LDS,
 //                 those across the tile's sides from the ring cells the tile evaluates once.
-// Without detection only stage2d_kernel runs.
+// Without detection only stage2d_kernel runs.  Small rectangular meshes with detection take
+// one launch per stage, stage2d_fused_kernel.
 //
 // The limited first moments of the stage input replace the stored ones in the stage
 // combination; the flags and limited moments of u^n (stage 1) are kept for stages 2, 3.
@@ -544,15 +545,15 @@ __global__ __launch_bounds__(NT, BK == BK_DMR ? 2 : 1) void stage2d_hweno_kernel
 // swapped), so that the y-face values are the x-face map of the transposed stencil.  The
 // fold of these values equals lin2d_transpose of the untransposed fold to the bit, so a
 // cell's trace is the same whether the cell itself or a neighbouring tile evaluates it.
-template <int NC>
+template <int NC, int W>
 __device__ __forceinline__ void gather19_dir(const double* s, int c, int ly, int lx, int dir,
                                              double* in) {
-  const int sa = dir == 0 ? L2 : 1, sb = dir == 0 ? 1 : L2;   // strides of dy, dx
-  const double* p = s + c * NP2 + ly * L2 + lx;
+  const int sa = dir == 0 ? W : 1, sb = dir == 0 ? 1 : W;   // strides of dy, dx
+  const double* p = s + c * W * W + ly * W + lx;
 #pragma unroll
   for (int k = 0; k < 9; ++k) in[k] = p[(k / 3 - 1) * sa + (k % 3 - 1) * sb];
-  const double* pv = p + (dir == 0 ? NC : 2 * NC) * NP2;   // moment along dir
-  const double* pw = p + (dir == 0 ? 2 * NC : NC) * NP2;   // the other moment
+  const double* pv = p + (dir == 0 ? NC : 2 * NC) * W * W;   // moment along dir
+  const double* pw = p + (dir == 0 ? 2 * NC : NC) * W * W;   // the other moment
   const int cy[5] = {-1, 0, 0, 0, 1}, cx[5] = {0, -1, 0, 1, 0};
 #pragma unroll
   for (int j = 0; j < 5; ++j) {
@@ -655,7 +656,7 @@ __device__ __forceinline__ void face_sums(const double (*tr)[NGE], double s, dou
 }
 
 // Faces whose other side follows a boundary's face rule instead of a neighbour's values: the
-// forward step's inflow, outflow and walls, the double Mach reflection's top side.  Returns
+// forward step's inflow, outflow and walls.  Returns
 // 0 (none), 1 (the low face) or 2 (the high face) in the low two bits and above them which
 // of the direction's (at most three) such grid lines it is; that side's share sums go to
 // entry 16 * line + (position along the line) of s_spec, [sum][NC][64].  (Held in registers
@@ -663,7 +664,7 @@ __device__ __forceinline__ void face_sums(const double (*tr)[NGE], double s, dou
 template <int EQ, int NGE, int BK, int D>
 __device__ __forceinline__ int special_face(const Stage2D& P, int gx, int gy, int along,
                                             const double (*lo)[NGE], const double (*hi)[NGE],
-                                            double alpha, double dtv, double* s_spec) {
+                                            double alpha, double* s_spec) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
   int which = 0, line = 0;
   double u[NC][NGE];
@@ -688,21 +689,6 @@ __device__ __forceinline__ int special_face(const Stage2D& P, int gx, int gy, in
       for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int k = 0; k < NGE; ++k) u[c][k] = c == cn ? -hi[c][k] : hi[c][k];
-    }
-  }
-  if constexpr (BK == BK_DMR && D == 1) {
-    // the prescribed ghost's trace is the exact state at the face's Gauss points (also where
-    // that ghost sits inside a partial last row of tiles)
-    if (gy == P.ny - 1) {
-      which = 2;
-#pragma unroll
-      for (int k = 0; k < NGE; ++k) {
-        double U[4];
-        dmr::point_state(P.x0 + (gx + 0.5 + Gauss<NGE>::node[k]) * P.dx, P.y0 + P.ny * P.dy,
-                         stage_time_of<BK>(P, dtv), P.gam, U);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) u[c][k] = U[c];
-      }
     }
   }
   if (which) {
@@ -757,6 +743,366 @@ __device__ __forceinline__ void volume_sums(const double (*inner)[9], const doub
   }
 }
 
+// whether the position (gx, gy) lies beyond a transmissive or reflective side
+__device__ __forceinline__ bool mirrored(const Stage2D& P, int gx, int gy) {
+  return (P.bcx != BC_PERIODIC && (gx < 0 || gx >= P.nx)) || (P.bcy != BC_PERIODIC && (gy < 0 || gy >= P.ny));
+}
+
+// LDS of a stage tile beside the staged input
+template <int EQ, int NGE, int BK>
+struct TileShared {
+  static constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
+  static constexpr int NV = 4 * NC;   // exchanged per direction: [side: high, low][sum][NC]
+  static constexpr int NSPEC = BK == BK_STEP ? 2 * NC * 64 : 0;
+  double ring[2 * NC * 64];           // ring cells' share sums [sum][NC][ring cell]
+  double spec[2 * NSPEC + 1];         // boundary face rules' share sums, per direction
+  double red[8];
+  double alpha[2];
+};
+
+// The stage of one tile from its staged (limited) input s_u, rows of W = TX + 2 HB positions
+// with HB ghost layers, and the flags and hybrid masks s_T, s_H of the same positions; the
+// space of s_u is reused.  s_rtr: when not null, the HWENO values of hybrid ring cells that are
+// no mirror images, [NC][NGE][ring cell]; the tile's own hybrid cells' (and the mirror
+// images') are then those this workgroup stored in P.G before the call.
+template <int EQ, int NGE, int BK, int HB>
+__device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE, BK>& sh, double* s_u,
+                                           const uint8_t* s_T, const uint8_t* s_H,
+                                           const double* s_rtr, int bx, int by, double dtv) {
+  constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
+  constexpr int NF = 3 * NC, W = TX + 2 * HB;
+  constexpr int NV = TileShared<EQ, NGE, BK>::NV;
+  constexpr int NSPEC = TileShared<EQ, NGE, BK>::NSPEC;
+  static_assert((NT / 64) * NV * 64 <= NF * W * W, "the exchange fits the staged input's space");
+  double* const s_ring = sh.ring;
+  double* const s_spec = sh.spec;
+  double* const s_red = sh.red;
+  const double* const s_alpha = sh.alpha;
+  const int mode = P.mode, tid = threadIdx.x, nx = P.nx, ny = P.ny;
+  const double dt = mode != MODE_L ? dtv : 0.0;
+  const int gx0 = bx * TX - HB, gy0 = by * TY - HB;
+  const size_t plane = (size_t)nx * ny;
+  const bool tc = P.tc_mode != TC_NONE;
+  // the tile's mesh cells (fewer in the last column and row of tiles)
+  const int tw = min(TX, nx - bx * TX), th = min(TY, ny - by * TY);
+
+  const int tx = tid % TX, ty = tid / TX;
+  const int lx = tx + HB, ly = ty + HB;
+  const int gx = gx0 + lx, gy = gy0 + ly;
+  const bool inmesh = gx < nx && gy < ny;
+  // the solid cells of the forward step are never updated
+  bool active = inmesh;
+  if constexpr (BK == BK_STEP) active = inmesh && !step::solid(gx, gy, P.si, P.sj);
+  const size_t gi = active ? (size_t)gy * nx + gx : 0;
+  const int lane = tid & 63, wv = tid >> 6;
+
+  // out = a W(u^n) + b (W(u^(s)) + dt L) with (a, b) of the stage (eq. RK): acc starts with
+  // the first two terms, and every part of L is added with the factor b dt.  The operator
+  // alone: a = b = 0 and the factor 1.
+  double ca, cb;
+  rk_coeffs(mode, ca, cb);
+  const double cdt = mode == MODE_L ? 1.0 : cb * dt;
+  if (mode == MODE_L) cb = 0.0;
+  // stages 2 and 3: W(u^n), loaded now and used after the volume quadrature
+  double Wn[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) Wn[f] = 0.0;
+  if ((mode == MODE_RK2 || mode == MODE_RK3) && active) {
+    const bool tn = tc && P.Tn[gi] != 0;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) Wn[f] = P.base[(size_t)f * plane + gi];
+    if (tn) {
+#pragma unroll
+      for (int f = NC; f < NF; ++f) Wn[f] = P.limn[(size_t)(f - NC) * plane + gi];
+    }
+  }
+
+  double acc[NF];
+  {
+    double inner[NC][9], ub[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      double in[19], f[hw2::NFOLD];
+      gather19<NC, W>(s_u, c, ly, lx, in);
+      ub[c] = in[4];
+      acc[c] = cb * in[4];
+      acc[NC + c] = cb * in[11];
+      acc[2 * NC + c] = cb * in[16];
+      hw2::lin2d_fold(in, f);
+      hw2::lin2d_inner(f, inner[c]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    double sf[NC], sg[NC];
+    volume_sums<EQ>(inner, ub, P, sf, sg);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      acc[c] = fma(ca, Wn[c], acc[c]);
+      acc[NC + c] = fma(cdt * P.idx, sf[c], fma(ca, Wn[NC + c], acc[NC + c]));
+      acc[2 * NC + c] = fma(cdt * P.idy, sg[c], fma(ca, Wn[2 * NC + c], acc[2 * NC + c]));
+    }
+    // formed here: left to itself the compiler sinks this phase to the stores, holding the
+    // interior values in scratch until then
+#pragma unroll
+    for (int f = 0; f < NF; ++f) asm volatile("" : "+v"(acc[f]));
+  }
+  if (mode == MODE_L && P.wout && active) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gi] = S<W>(s_u, f, ly, lx);
+  }
+
+  if (s_rtr) __syncthreads();   // the workgroup's HWENO values are in place
+  // ring cells (the tile's neighbours across the four sides of its mesh cells), all 64 by
+  // wave 0: lanes
+  // 32 d .. 32 d + 31 those of direction d, the low side's high faces and the high side's
+  // low faces
+  if (wv == 0) {
+    const int rd = lane / (2 * TX), rs = (lane / TX) & 1, rp = lane % TX;
+    const int rly = rd == 0 ? HB + rp : (rs == 0 ? HB - 1 : HB + th);
+    const int rlx = rd == 0 ? (rs == 0 ? HB - 1 : HB + tw) : HB + rp;
+    double a[NC][NGE];
+    if (s_H[rly * W + rlx] == 0) {
+      const double side = rs == 0 ? 1.0 : -1.0;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        double in[19], f[hw2::NFOLD], p[6];
+        gather19_dir<NC, W>(s_u, c, rly, rlx, rd, in);
+        hw2::lin2d_fold(in, f);
+        lin_xparts<NGE>(f, p);
+        lin_xface<NGE>(p, side, a[c]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if (s_rtr && !mirrored(P, gx0 + rlx, gy0 + rly)) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int k = 0; k < NGE; ++k) a[c][k] = s_rtr[(c * NGE + k) * 64 + lane];
+    } else {
+      stored_trace<EQ, NGE, BK>(P, rly, rlx, rd, rs == 0 ? 1 : 0, gx0, gy0, a);
+    }
+    if constexpr (BK == BK_DMR) {
+      if (dmr_prescribed<BK>(P, gx0 + rlx, gy0 + rly)) {
+        // the face shared with the tile: the ring cell's high face (rs = 0) or low face
+        const double ts = stage_time_of<BK>(P, dtv);
+        const int gxr = gx0 + rlx, gyr = gy0 + rly;
+#pragma unroll
+        for (int k = 0; k < NGE; ++k) {
+          const double e = Gauss<NGE>::node[k];
+          double x, y, U[4];
+          if (rd == 0) {
+            x = P.x0 + (gxr + (rs == 0 ? 1.0 : 0.0)) * P.dx;
+            y = P.y0 + (gyr + 0.5 + e) * P.dy;
+          } else {
+            x = P.x0 + (gxr + 0.5 + e) * P.dx;
+            y = P.y0 + (gyr + (rs == 0 ? 1.0 : 0.0)) * P.dy;
+          }
+          dmr::point_state(x, y, ts, P.gam, U);
+#pragma unroll
+          for (int c = 0; c < NC; ++c) a[c][k] = U[c];
+        }
+      }
+    }
+    // both directions as x fluxes: the momenta exchanged for y
+    if constexpr (EQ == EQ_EULER) {
+#pragma unroll
+      for (int k = 0; k < NGE; ++k) {
+        const double m = a[1][k], n = a[2][k];
+        a[1][k] = rd == 0 ? m : n;
+        a[2][k] = rd == 0 ? n : m;
+      }
+    }
+    double S[2 * NC];
+    const double al = s_alpha[rd];
+    face_sums<EQ, NGE, 0>(a, rs == 0 ? al : -al, P.gam, rd == 0 ? P.adv0 : P.adv1, S);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int cc = (c == 0 || c == 3) ? c : (rd == 0 ? c : 3 - c);
+        s_ring[(j * NC + cc) * 64 + lane] = S[j * NC + c];
+      }
+  }
+
+  // ---------------------------------------------------------------- traces and share sums
+  // the cell's traces on its four faces (p0, or the stored HWENO values of a hybrid cell)
+  // and, per direction, the sums of its shares: E[dir][0] its high face's (u- there),
+  // E[dir][1] its low face's (u+ there)
+  // the stencils are gathered again (kept from the volume phase they would take 120 VGPRs):
+  // the row is made opaque so that the compiler does not keep them
+  int ly2 = ly;
+  asm volatile("" : "+v"(ly2));
+  const bool hyb = active && s_H[ly * W + lx] != 0;
+  const double al0 = s_alpha[0], al1 = s_alpha[1];
+  double E[2][2][2 * NC];
+  int sp[2] = {0, 0};
+  if constexpr (NGE == 2) {
+    // both directions from one gather
+    double xl[NC][NGE], xh[NC][NGE], yl[NC][NGE], yh[NC][NGE];
+    if (!hyb) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        double in[19], f[hw2::NFOLD];
+        gather19<NC, W>(s_u, c, ly2, lx, in);
+        hw2::lin2d_fold(in, f);
+        lin_faces<NGE>(f, 0, xl[c], xh[c]);
+        lin_faces<NGE>(f, 1, yl[c], yh[c]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 0, 0, gx0, gy0, xl);
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 0, 1, gx0, gy0, xh);
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 1, 0, gx0, gy0, yl);
+      stored_trace<EQ, NGE, BK>(P, ly, lx, 1, 1, gx0, gy0, yh);
+    }
+    if constexpr (BK == BK_STEP) {
+      sp[0] = special_face<EQ, NGE, BK, 0>(P, gx, gy, ty, xl, xh, al0, s_spec);
+      sp[1] = special_face<EQ, NGE, BK, 1>(P, gx, gy, tx, yl, yh, al1, s_spec + NSPEC);
+    }
+    face_sums<EQ, NGE, 0>(xh, al0, P.gam, P.adv0, E[0][0]);
+    face_sums<EQ, NGE, 0>(xl, -al0, P.gam, P.adv0, E[0][1]);
+    face_sums<EQ, NGE, 1>(yh, al1, P.gam, P.adv1, E[1][0]);
+    face_sums<EQ, NGE, 1>(yl, -al1, P.gam, P.adv1, E[1][1]);
+  } else {
+    // three points per edge: one direction at a time (96 VGPRs of traces otherwise)
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+      double tl[NC][NGE], th[NC][NGE];
+      asm volatile("" : "+v"(ly2));
+      if (!hyb) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          double in[19], f[hw2::NFOLD];
+          gather19<NC, W>(s_u, c, ly2, lx, in);
+          hw2::lin2d_fold(in, f);
+          lin_faces<NGE>(f, dir, tl[c], th[c]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 0, gx0, gy0, tl);
+        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 1, gx0, gy0, th);
+      }
+      if (dir == 0) {
+        if constexpr (BK == BK_STEP) sp[0] = special_face<EQ, NGE, BK, 0>(P, gx, gy, ty, tl, th, al0, s_spec);
+        face_sums<EQ, NGE, 0>(th, al0, P.gam, P.adv0, E[0][0]);
+        face_sums<EQ, NGE, 0>(tl, -al0, P.gam, P.adv0, E[0][1]);
+      } else {
+        if constexpr (BK == BK_STEP) sp[1] = special_face<EQ, NGE, BK, 1>(P, gx, gy, tx, tl, th, al1, s_spec + NSPEC);
+        face_sums<EQ, NGE, 1>(th, al1, P.gam, P.adv1, E[1][0]);
+        face_sums<EQ, NGE, 1>(tl, -al1, P.gam, P.adv1, E[1][1]);
+      }
+#pragma unroll
+      for (int v = 0; v < 2 * NC; ++v) asm volatile("" : "+v"(E[dir][0][v]), "+v"(E[dir][1][v]));
+    }
+  }
+  __syncthreads();   // the staged input is done with: its space holds the exchange
+
+  // ---------------------------------------------------------------- exchange and faces
+  // a cell's two faces of each direction: its own share sums plus the neighbour's, read from
+  // the wave's own block (x; y inside the wave's four rows), the neighbouring wave's block,
+  // or the ring.  Both cells of a face add the same two values.
+  double* const own_blk = s_u + wv * NV * 64 + lane;
+#pragma unroll
+  for (int dir = 0; dir < 2; ++dir) {
+#pragma unroll
+    for (int v = 0; v < 2 * NC; ++v) {
+      own_blk[v * 64] = E[dir][0][v];
+      own_blk[(2 * NC + v) * 64] = E[dir][1][v];
+    }
+    const double *lo, *hi;   // the low neighbour's high-face sums, the high neighbour's low-face sums
+    if (dir == 0) {
+      // x neighbours share the wave: its LDS operations stay in order, no barrier
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      lo = tx == 0 ? s_ring + ty : own_blk - 1;
+      hi = tx == tw - 1 ? s_ring + TX + ty : own_blk + 2 * NC * 64 + 1;
+    } else {
+      __syncthreads();
+      lo = (ty & 3) != 0 ? own_blk - TX : (wv == 0 ? s_ring + 2 * TX + tx : own_blk - NV * 64 + 48);
+      hi = ty == th - 1 ? s_ring + 3 * TX + tx
+                        : ((ty & 3) != 3 ? own_blk + 2 * NC * 64 + TX : own_blk + (NV + 2 * NC) * 64 - 48);
+    }
+    if (!inmesh) lo = hi = s_ring;   // (nothing is stored for this lane)
+    const double k = cdt * (dir == 0 ? P.idx : P.idy);
+    const double kU = -0.5 * FaceSums<NGE>::C0 * k, kP = 0.5 * kU, kQ = -0.5 * FaceSums<NGE>::C1 * k;
+    const int fP = dir == 0 ? NC : 2 * NC, fQ = dir == 0 ? 2 * NC : NC;
+    if constexpr (BK == BK_STEP) {
+      const double* spec = s_spec + dir * NSPEC + (sp[dir] >> 2) * 16 + (dir == 0 ? ty : tx);
+      if ((sp[dir] & 3) == 1) lo = spec;
+      if ((sp[dir] & 3) == 2) hi = spec;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const double L0 = lo[c * 64] + E[dir][1][c], R0 = E[dir][0][c] + hi[c * 64];
+      const double L1 = lo[(NC + c) * 64] + E[dir][1][NC + c], R1 = E[dir][0][NC + c] + hi[(NC + c) * 64];
+      acc[c] = fma(kU, R0 - L0, acc[c]);
+      acc[fP + c] = fma(kP, L0 + R0, acc[fP + c]);
+      acc[fQ + c] = fma(kQ, R1 - L1, acc[fQ + c]);
+    }
+    if (dir == 0) {
+      // the block is written again for y once every lane of the wave has read it
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+
+  // ---------------------------------------------------------------- epilogue
+  double sp0 = 0.0, sp1 = 0.0;
+  if constexpr (BK == BK_STEP) {
+    // solid cells: no flags; the operator alone reports zero and the stored state
+    if (inmesh && !active) {
+      const size_t gs = (size_t)gy * nx + gx;
+      if (P.flagsT) P.flagsT[gs] = 0;
+      if (P.flagsH) P.flagsH[gs] = 0;
+      if (mode == MODE_L) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) P.out[(size_t)f * plane + gs] = 0.0;
+        if (P.wout) {
+#pragma unroll
+          for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gs] = P.in[(size_t)f * plane + gs];
+        }
+      }
+    }
+  }
+  if (active) {
+    if (P.flagsT) P.flagsT[gi] = s_T[ly * W + lx];
+    if (P.flagsH) P.flagsH[gi] = s_H[ly * W + lx];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) P.out[(size_t)f * plane + gi] = acc[f];
+    if (mode != MODE_L) {
+      int bad = 0;
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        if (!isfinite(acc[f])) bad |= 1;
+      if constexpr (EQ == EQ_EULER) {
+        double p;
+        euler_speeds2d(acc, P.gam, sp0, sp1, p);
+        if (!(acc[0] > 0.0) || !(p > 0.0)) bad |= 2;
+      } else if constexpr (EQ == EQ_BURGERS) {
+        sp0 = sp1 = fabs(acc[0]);
+      } else {
+        sp0 = fabs(P.adv0);
+        sp1 = fabs(P.adv1);
+      }
+      if (bad) atomicOr(P.status, bad);
+    }
+  }
+  if (mode != MODE_L) {
+    // block maxima of both directions with one barrier
+    const double w0 = wave_max(sp0), w1 = wave_max(sp1);
+    if (lane == 0) {
+      s_red[wv] = w0;
+      s_red[4 + wv] = w1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      const double m0 = fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]));
+      const double m1 = fmax(fmax(s_red[4], s_red[5]), fmax(s_red[6], s_red[7]));
+      const int e = blockIdx.x % ASPREAD;
+      atomic_max_pos(&P.alpha_out[e], m0);
+      atomic_max_pos(&P.alpha_out[ASPREAD + e], m1);
+    }
+  }
+}
+
 // Bound by VALU issue, then by LDS and HBM (1024^2 Euler, NG = 2: 308 MB of HBM traffic a
 // launch, about 50 us; the instructions about 45 us; the phases overlap only in part), so the
 // arithmetic per cell is what counts: one fold of a stencil serves all its point values of a
@@ -771,16 +1117,10 @@ template <int EQ, int NGE, int BK>
 __global__ __launch_bounds__(NT, 3) void stage2d_kernel(Stage2D P) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
   constexpr int NF = 3 * NC;
-  constexpr int NV = 4 * NC;         // exchanged per direction: [side: high, low][sum][NC]
   __shared__ double s_u[NF * NP2];   // stage input, limited, on tile+2; then the exchange
-  __shared__ double s_ring[2 * NC * 64];   // ring cells' share sums [sum][NC][ring cell]
   __shared__ uint8_t s_T[NP2];
   __shared__ uint8_t s_H[NP2];
-  constexpr int NSPEC = BK == BK_RECT ? 0 : 2 * NC * 64;
-  __shared__ double s_spec[2 * NSPEC + 1];   // boundary face rules' share sums, per direction
-  __shared__ double s_red[8];
-  __shared__ double s_alpha[2];
-  static_assert((NT / 64) * NV * 64 <= NF * NP2, "the exchange fits the staged input's space");
+  __shared__ TileShared<EQ, NGE, BK> sh;
 
   const int mode = P.mode;
   // the time step (zero once the run has reached its final time: nothing to do) is
@@ -921,317 +1261,300 @@ __global__ __launch_bounds__(NT, 3) void stage2d_kernel(Stage2D P) {
     P.counts[0] = 0;
     P.counts[1] = 0;
   }
-  reduce_speeds(P.alpha_in, s_alpha);   // visible after the staging barrier
+  reduce_speeds(P.alpha_in, sh.alpha);   // visible after the staging barrier
   __syncthreads();
 
-  // ---------------------------------------------------------------- tile cell
-  const int tx = tid % TX, ty = tid / TX;
-  const int lx = tx + H2, ly = ty + H2;
-  const int gx = gx0 + lx, gy = gy0 + ly;
-  const bool inmesh = gx < nx && gy < ny;
-  // the solid cells of the forward step are never updated
-  bool active = inmesh;
-  if constexpr (BK == BK_STEP) active = inmesh && !step::solid(gx, gy, P.si, P.sj);
-  const size_t gi = active ? (size_t)gy * nx + gx : 0;
-  const int lane = tid & 63, wv = tid >> 6;
+  stage_tile<EQ, NGE, BK, H2>(P, sh, s_u, s_T, s_H, nullptr, bx, by, dtv);
+}
 
-  // out = a W(u^n) + b (W(u^(s)) + dt L) with (a, b) of the stage (eq. RK): acc starts with
-  // the first two terms, and every part of L is added with the factor b dt.  The operator
-  // alone: a = b = 0 and the factor 1.
-  double ca, cb;
-  rk_coeffs(mode, ca, cb);
-  const double cdt = mode == MODE_L ? 1.0 : cb * dt;
-  if (mode == MODE_L) cb = 0.0;
-  // stages 2 and 3: W(u^n), loaded now and used after the volume quadrature
-  double Wn[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) Wn[f] = 0.0;
-  if ((mode == MODE_RK2 || mode == MODE_RK3) && active) {
-    const bool tn = tc && P.Tn[gi] != 0;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) Wn[f] = P.base[(size_t)f * plane + gi];
-    if (tn) {
-#pragma unroll
-      for (int f = NC; f < NF; ++f) Wn[f] = P.limn[(size_t)(f - NC) * plane + gi];
-    }
-  }
+// ------------------------------------------------------------------ one-launch stage
+// A whole stage of a small rectangular mesh in one launch.  Where the tiles do not fill the
+// chip, the four launches of a stage cost their latency (start-up, a round trip of the state
+// and the lists through the L2s, the gap to the next launch: 30 us a stage on an 80 x 80 scalar
+// mesh, 45 us on 256^2 Euler, whatever the launches compute), so each tile recomputes on idle
+// units what it needs of its surroundings: the flags of tile+2 from three staged ghost
+// layers, the limited moments of the flagged cells among them, the HWENO edge values of the
+// hybrid cells of the tile and its ring.  The arithmetic is that of the four kernels.  Results
+// that outlast the stage (flags, masks, limited moments and edge values of the tile's own
+// cells, the list lengths, on request the lists) are stored as there.
+// The rule (one_launch below): at most 400 tiles for Euler, 1600 for scalar laws.  Measured,
+// us per step of three stages, one launch against four: scalar NG 3 with shocks 59 / 94 at 80^2 to 208^2,
+// 68 / 97 at 320^2, 92 / 118 at 512^2, 142 / 142 at 768^2 (2304 tiles); smooth Euler NG 3 65 / 84
+// at 160^2, 84 / 107 at 320^2 (400 tiles); Euler with shocks NG 2 127 / 133 at 160^2, 135 / 143 at 320^2,
+// 166 / 158 at 362^2 (529 tiles), 221 / 196 at 512^2: there two workgroups per CU (79 KB of LDS) run
+// several rounds, and the tiles a shock crosses do all their HWENO cells themselves.
 
-  // ring cells (the tile's neighbours across its four sides), all 64 by wave 0: lanes
-  // 32 d .. 32 d + 31 those of direction d, the low side's high faces and the high side's
-  // low faces
-  if (wv == 0) {
-    const int rd = lane / (2 * TX), rs = (lane / TX) & 1, rp = lane % TX;
-    const int rly = rd == 0 ? H2 + rp : (rs == 0 ? H2 - 1 : H2 + TY);
-    const int rlx = rd == 0 ? (rs == 0 ? H2 - 1 : H2 + TX) : H2 + rp;
-    double a[NC][NGE];
-    if (s_H[rly * L2 + rlx] == 0) {
-      const double side = rs == 0 ? 1.0 : -1.0;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        double in[19], f[hw2::NFOLD], p[6];
-        gather19_dir<NC>(s_u, c, rly, rlx, rd, in);
-        hw2::lin2d_fold(in, f);
-        lin_xparts<NGE>(f, p);
-        lin_xface<NGE>(p, side, a[c]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else {
-      stored_trace<EQ, NGE, BK>(P, rly, rlx, rd, rs == 0 ? 1 : 0, gx0, gy0, a);
-    }
-    if constexpr (BK == BK_DMR) {
-      if (dmr_prescribed<BK>(P, gx0 + rlx, gy0 + rly)) {
-        // the face shared with the tile: the ring cell's high face (rs = 0) or low face
-        const double ts = stage_time_of<BK>(P, dtv);
-        const int gxr = gx0 + rlx, gyr = gy0 + rly;
-#pragma unroll
-        for (int k = 0; k < NGE; ++k) {
-          const double e = Gauss<NGE>::node[k];
-          double x, y, U[4];
-          if (rd == 0) {
-            x = P.x0 + (gxr + (rs == 0 ? 1.0 : 0.0)) * P.dx;
-            y = P.y0 + (gyr + 0.5 + e) * P.dy;
-          } else {
-            x = P.x0 + (gxr + 0.5 + e) * P.dx;
-            y = P.y0 + (gyr + (rs == 0 ? 1.0 : 0.0)) * P.dy;
-          }
-          dmr::point_state(x, y, ts, P.gam, U);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) a[c][k] = U[c];
-        }
-      }
-    }
-    // both directions as x fluxes: the momenta exchanged for y
-    if constexpr (EQ == EQ_EULER) {
-#pragma unroll
-      for (int k = 0; k < NGE; ++k) {
-        const double m = a[1][k], n = a[2][k];
-        a[1][k] = rd == 0 ? m : n;
-        a[2][k] = rd == 0 ? n : m;
-      }
-    }
-    double S[2 * NC];
-    const double al = s_alpha[rd];
-    face_sums<EQ, NGE, 0>(a, rs == 0 ? al : -al, P.gam, rd == 0 ? P.adv0 : P.adv1, S);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int cc = (c == 0 || c == 3) ? c : (rd == 0 ? c : 3 - c);
-        s_ring[(j * NC + cc) * 64 + lane] = S[j * NC + c];
-      }
+// Appends the threads marked in m to a work list (no list: counts only), the length kept in a
+// 64-bit statistics entry: one atomic per workgroup that has something to append.
+__device__ __forceinline__ void block_append_stat(bool m, int value, long long* count, int* list,
+                                                  int* s_wave /* 6 ints */) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const unsigned long long a = __ballot(m);
+  if (lane == 0) s_wave[w] = __popcll(a);
+  __syncthreads();
+  const int tot = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+  if (threadIdx.x == 0 && tot)
+    s_wave[4] = (int)atomicAdd((unsigned long long*)count, (unsigned long long)tot);
+  if (!list) return;   // uniform over the grid
+  __syncthreads();
+  if (m) {
+    int off = s_wave[4];
+    for (int i = 0; i < w; ++i) off += s_wave[i];
+    list[off + __popcll(a & ((1ull << lane) - 1ull))] = value;
   }
+}
 
-  double acc[NF];
-  {
-    double inner[NC][9], ub[NC];
+// characteristic HWENO edge values of direction DIR from component f of the limited stencil
+// (four lanes per Euler cell, one per scalar cell): component f of the values
+template <int EQ, int NGE, int DIR>
+__device__ __forceinline__ void hweno_values(const Stage2D& P, const double* in, int f, double* v) {
+  if constexpr (EQ == EQ_EULER) {
+    double U[4], Lr[4], Rr[4], x[4];
+    quad_gather(in[4], U);   // the cell's own averages
+    euler_rows2d(U, P.gam, DIR, f, Lr, Rr);
+    double w19[19];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      double in[19], f[hw2::NFOLD];
-      gather19<NC, L2>(s_u, c, ly, lx, in);
-      ub[c] = in[4];
-      acc[c] = cb * in[4];
-      acc[NC + c] = cb * in[11];
-      acc[2 * NC + c] = cb * in[16];
-      hw2::lin2d_fold(in, f);
-      hw2::lin2d_inner(f, inner[c]);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int k = 0; k < 19; ++k) {
+      quad_gather(in[k], x);
+      double a = 0.0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) a = fma(Lr[c], x[c], a);
+      w19[k] = a;
     }
-    double sf[NC], sg[NC];
-    volume_sums<EQ>(inner, ub, P, sf, sg);
+    double wv[2 * NGE];
+    hweno2d_field<NGE>(w19, P.w, DIR, wv);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      acc[c] = fma(ca, Wn[c], acc[c]);
-      acc[NC + c] = fma(cdt * P.idx, sf[c], fma(ca, Wn[NC + c], acc[NC + c]));
-      acc[2 * NC + c] = fma(cdt * P.idy, sg[c], fma(ca, Wn[2 * NC + c], acc[2 * NC + c]));
+    for (int k = 0; k < 2 * NGE; ++k) {
+      quad_gather(wv[k], x);
+      double a = 0.0;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) a = fma(Rr[g], x[g], a);
+      v[k] = a;
     }
-    // formed here: left to itself the compiler sinks this phase to the stores, holding the
-    // interior values in scratch until then
-#pragma unroll
-    for (int f = 0; f < NF; ++f) asm volatile("" : "+v"(acc[f]));
-  }
-  if (mode == MODE_L && P.wout && active) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gi] = S<L2>(s_u, f, ly, lx);
-  }
-
-  // ---------------------------------------------------------------- traces and share sums
-  // the cell's traces on its four faces (p0, or the stored HWENO values of a hybrid cell)
-  // and, per direction, the sums of its shares: E[dir][0] its high face's (u- there),
-  // E[dir][1] its low face's (u+ there)
-  // the stencils are gathered again (kept from the volume phase they would take 120 VGPRs):
-  // the row is made opaque so that the compiler does not keep them
-  int ly2 = ly;
-  asm volatile("" : "+v"(ly2));
-  const bool hyb = s_H[ly * L2 + lx] != 0;
-  const double al0 = s_alpha[0], al1 = s_alpha[1];
-  double E[2][2][2 * NC];
-  int sp[2] = {0, 0};
-  if constexpr (NGE == 2) {
-    // both directions from one gather
-    double xl[NC][NGE], xh[NC][NGE], yl[NC][NGE], yh[NC][NGE];
-    if (!hyb) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        double in[19], f[hw2::NFOLD];
-        gather19<NC, L2>(s_u, c, ly2, lx, in);
-        hw2::lin2d_fold(in, f);
-        lin_faces<NGE>(f, 0, xl[c], xh[c]);
-        lin_faces<NGE>(f, 1, yl[c], yh[c]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else {
-      stored_trace<EQ, NGE, BK>(P, ly, lx, 0, 0, gx0, gy0, xl);
-      stored_trace<EQ, NGE, BK>(P, ly, lx, 0, 1, gx0, gy0, xh);
-      stored_trace<EQ, NGE, BK>(P, ly, lx, 1, 0, gx0, gy0, yl);
-      stored_trace<EQ, NGE, BK>(P, ly, lx, 1, 1, gx0, gy0, yh);
-    }
-    if constexpr (BK != BK_RECT) {
-      sp[0] = special_face<EQ, NGE, BK, 0>(P, gx, gy, ty, xl, xh, al0, dtv, s_spec);
-      sp[1] = special_face<EQ, NGE, BK, 1>(P, gx, gy, tx, yl, yh, al1, dtv, s_spec + NSPEC);
-    }
-    face_sums<EQ, NGE, 0>(xh, al0, P.gam, P.adv0, E[0][0]);
-    face_sums<EQ, NGE, 0>(xl, -al0, P.gam, P.adv0, E[0][1]);
-    face_sums<EQ, NGE, 1>(yh, al1, P.gam, P.adv1, E[1][0]);
-    face_sums<EQ, NGE, 1>(yl, -al1, P.gam, P.adv1, E[1][1]);
   } else {
-    // three points per edge: one direction at a time (96 VGPRs of traces otherwise)
-#pragma unroll
-    for (int dir = 0; dir < 2; ++dir) {
-      double tl[NC][NGE], th[NC][NGE];
-      asm volatile("" : "+v"(ly2));
-      if (!hyb) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          double in[19], f[hw2::NFOLD];
-          gather19<NC, L2>(s_u, c, ly2, lx, in);
-          hw2::lin2d_fold(in, f);
-          lin_faces<NGE>(f, dir, tl[c], th[c]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else {
-        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 0, gx0, gy0, tl);
-        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 1, gx0, gy0, th);
-      }
-      if (dir == 0) {
-        if constexpr (BK != BK_RECT) sp[0] = special_face<EQ, NGE, BK, 0>(P, gx, gy, ty, tl, th, al0, dtv, s_spec);
-        face_sums<EQ, NGE, 0>(th, al0, P.gam, P.adv0, E[0][0]);
-        face_sums<EQ, NGE, 0>(tl, -al0, P.gam, P.adv0, E[0][1]);
-      } else {
-        if constexpr (BK != BK_RECT) sp[1] = special_face<EQ, NGE, BK, 1>(P, gx, gy, tx, tl, th, al1, dtv, s_spec + NSPEC);
-        face_sums<EQ, NGE, 1>(th, al1, P.gam, P.adv1, E[1][0]);
-        face_sums<EQ, NGE, 1>(tl, -al1, P.gam, P.adv1, E[1][1]);
-      }
-#pragma unroll
-      for (int v = 0; v < 2 * NC; ++v) asm volatile("" : "+v"(E[dir][0][v]), "+v"(E[dir][1][v]));
-    }
+    hweno2d_field<NGE>(in, P.w, DIR, v);
   }
-  __syncthreads();   // the staged input is done with: its space holds the exchange
+}
 
-  // ---------------------------------------------------------------- exchange and faces
-  // a cell's two faces of each direction: its own share sums plus the neighbour's, read from
-  // the wave's own block (x; y inside the wave's four rows), the neighbouring wave's block,
-  // or the ring.  Both cells of a face add the same two values.
-  double* const own_blk = s_u + wv * NV * 64 + lane;
+// the limited first moment of direction dir from component f of the stencil along it (lanes
+// as above): component f of the limited moment
+template <int EQ>
+__device__ __forceinline__ double limited_value(const Stage2D& P, int dir, int f, double um, double u0,
+                                                double up, double vm, double vp) {
+  if constexpr (EQ == EQ_EULER) {
+    double U[4], Lr[4], Rr[4], x[4];
+    quad_gather(u0, U);
+    euler_rows2d(U, P.gam, dir, f, Lr, Rr);
+    double cm = 0.0, c0 = 0.0, cp = 0.0, wm = 0.0, wp = 0.0;
+    quad_gather(um, x);
 #pragma unroll
-  for (int dir = 0; dir < 2; ++dir) {
+    for (int c = 0; c < 4; ++c) cm = fma(Lr[c], x[c], cm);
 #pragma unroll
-    for (int v = 0; v < 2 * NC; ++v) {
-      own_blk[v * 64] = E[dir][0][v];
-      own_blk[(2 * NC + v) * 64] = E[dir][1][v];
-    }
-    const double *lo, *hi;   // the low neighbour's high-face sums, the high neighbour's low-face sums
-    if (dir == 0) {
-      // x neighbours share the wave: its LDS operations stay in order, no barrier
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      lo = tx == 0 ? s_ring + ty : own_blk - 1;
-      hi = tx == TX - 1 ? s_ring + TX + ty : own_blk + 2 * NC * 64 + 1;
-    } else {
-      __syncthreads();
-      lo = (ty & 3) != 0 ? own_blk - TX : (wv == 0 ? s_ring + 2 * TX + tx : own_blk - NV * 64 + 48);
-      hi = (ty & 3) != 3 ? own_blk + 2 * NC * 64 + TX
-                         : (wv == NT / 64 - 1 ? s_ring + 3 * TX + tx : own_blk + (NV + 2 * NC) * 64 - 48);
-    }
-    const double k = cdt * (dir == 0 ? P.idx : P.idy);
-    const double kU = -0.5 * FaceSums<NGE>::C0 * k, kP = 0.5 * kU, kQ = -0.5 * FaceSums<NGE>::C1 * k;
-    const int fP = dir == 0 ? NC : 2 * NC, fQ = dir == 0 ? 2 * NC : NC;
-    if constexpr (BK != BK_RECT) {
-      const double* spec = s_spec + dir * NSPEC + (sp[dir] >> 2) * 16 + (dir == 0 ? ty : tx);
-      if ((sp[dir] & 3) == 1) lo = spec;
-      if ((sp[dir] & 3) == 2) hi = spec;
-    }
+    for (int c = 0; c < 4; ++c) c0 = fma(Lr[c], U[c], c0);
+    quad_gather(up, x);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const double L0 = lo[c * 64] + E[dir][1][c], R0 = E[dir][0][c] + hi[c * 64];
-      const double L1 = lo[(NC + c) * 64] + E[dir][1][NC + c], R1 = E[dir][0][NC + c] + hi[(NC + c) * 64];
-      acc[c] = fma(kU, R0 - L0, acc[c]);
-      acc[fP + c] = fma(kP, L0 + R0, acc[fP + c]);
-      acc[fQ + c] = fma(kQ, R1 - L1, acc[fQ + c]);
-    }
-    if (dir == 0) {
-      // the block is written again for y once every lane of the wave has read it
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    }
+    for (int c = 0; c < 4; ++c) cp = fma(Lr[c], x[c], cp);
+    quad_gather(vm, x);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) wm = fma(Lr[c], x[c], wm);
+    quad_gather(vp, x);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) wp = fma(Lr[c], x[c], wp);
+    const double vc = limit_moment(cm, c0, cp, wm, wp, P.w.lim, P.w.eps);
+    quad_gather(vc, x);
+    double out = 0.0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) out = fma(Rr[g], x[g], out);
+    return out;
+  } else {
+    return limit_moment(um, u0, up, vm, vp, P.w.lim, P.w.eps);
   }
+}
 
-  // ---------------------------------------------------------------- epilogue
-  double sp0 = 0.0, sp1 = 0.0;
-  if constexpr (BK == BK_STEP) {
-    // solid cells: no flags; the operator alone reports zero and the stored state
-    if (inmesh && !active) {
-      const size_t gs = (size_t)gy * nx + gx;
-      if (P.flagsT) P.flagsT[gs] = 0;
-      if (P.flagsH) P.flagsH[gs] = 0;
-      if (mode == MODE_L) {
+template <int EQ, int NGE>
+__global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
+  constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
+  constexpr int NF = 3 * NC;
+  constexpr int NLIM = R2 * R2 * 2 * NC;         // limited moments of tile+2
+  constexpr int NRTR = NC * NGE * 64;            // ring cells' HWENO values
+  __shared__ double s_u[NF * NPOS];              // stage input on tile+3, limited on tile+2
+  __shared__ double s_lim[NLIM > NRTR ? NLIM : NRTR];
+  __shared__ uint8_t s_T[NPOS], s_H[NPOS];
+  __shared__ uint16_t s_fl[R2 * R2], s_hl[NT + 64];
+  __shared__ int s_cnt[2], s_wave[12];
+  __shared__ TileShared<EQ, NGE, BK_RECT> sh;
+
+  const int mode = P.mode, tid = threadIdx.x, nx = P.nx, ny = P.ny;
+  const double dtv = *P.dt;   // (valid in every mode; zero: the run has reached its final time)
+  int bx, by;
+  tile_of_block(nx, bx, by);
+  const int gx0 = bx * TX - HL, gy0 = by * TY - HL;
+  const size_t plane = (size_t)nx * ny;
+  const int tw = min(TX, nx - bx * TX), th = min(TY, ny - by * TY);
+  const int lane = tid & 63;
+
+  // ---------------------------------------------------------------- stage input -> LDS
+  {
+    constexpr int NR = (NPOS + NT - 1) / NT;
+    double v[NR][NF], sxr[NR], syr[NR];
 #pragma unroll
-        for (int f = 0; f < NF; ++f) P.out[(size_t)f * plane + gs] = 0.0;
-        if (P.wout) {
+    for (int r = 0; r < NR; ++r) {
+      const int q = tid + r * NT;
+      if (q < NPOS) {
+        const int ly = q / LX, lx = q - ly * LX;
+        const int gx = map_index(gx0 + lx, nx, P.bcx, sxr[r]);
+        const int gy = map_index(gy0 + ly, ny, P.bcy, syr[r]);
+        const size_t gs = (size_t)gy * nx + gx;
 #pragma unroll
-          for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gs] = P.in[(size_t)f * plane + gs];
+        for (int f = 0; f < NF; ++f) v[r][f] = P.in[f * plane + gs];
+      }
+    }
+    if (mode != MODE_L && dtv == 0.0) return;   // uniform over the grid
+    if (tid < 2) s_cnt[tid] = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int q = tid + r * NT;
+      if (q < NPOS) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          const int m = f / NC, c = f % NC;
+          const double wf = wall_factor<EQ>(c, sxr[r] < 0.0, syr[r] < 0.0, P.bcx, P.bcy);
+          s_u[f * NPOS + q] = wf * (m == 1 ? sxr[r] * v[r][f] : (m == 2 ? syr[r] * v[r][f] : v[r][f]));
         }
       }
     }
   }
-  if (active) {
-    if (P.flagsT) P.flagsT[gi] = s_T[ly * L2 + lx];
-    if (P.flagsH) P.flagsH[gi] = s_H[ly * L2 + lx];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) P.out[(size_t)f * plane + gi] = acc[f];
-    if (mode != MODE_L) {
-      int bad = 0;
-#pragma unroll
-      for (int f = 0; f < NF; ++f)
-        if (!isfinite(acc[f])) bad |= 1;
-      if constexpr (EQ == EQ_EULER) {
-        double p;
-        euler_speeds2d(acc, P.gam, sp0, sp1, p);
-        if (!(acc[0] > 0.0) || !(p > 0.0)) bad |= 2;
-      } else if constexpr (EQ == EQ_BURGERS) {
-        sp0 = sp1 = fabs(acc[0]);
-      } else {
-        sp0 = fabs(P.adv0);
-        sp1 = fabs(P.adv1);
-      }
-      if (bad) atomicOr(P.status, bad);
-    }
-  }
-  if (mode != MODE_L) {
-    // block maxima of both directions with one barrier
-    const double w0 = wave_max(sp0), w1 = wave_max(sp1);
-    if (lane == 0) {
-      s_red[wv] = w0;
-      s_red[4 + wv] = w1;
+  reduce_speeds(P.alpha_in, sh.alpha);
+  __syncthreads();
+
+  // ---------------------------------------------------------------- flags, masks, lists
+  // flags of tile+2; a mirror image takes the flag of the cell it mirrors
+  flags_tile<EQ>(s_u, P.tc_mode, P.adv0, P.adv1, P.dx, P.dy, P.h, s_T);
+  __syncthreads();
+  const bool walls = P.bcx != BC_PERIODIC || P.bcy != BC_PERIODIC;
+  // the LDS position of the cell a mirror image copies (-1: outside the staged block, which
+  // only belongs to positions that no mesh cell's stencil holds)
+  auto mirror_pos = [&](int ly, int lx, double& sx, double& sy) -> int {
+    const int mx = map_index(gx0 + lx, nx, P.bcx == BC_PERIODIC ? BC_TRANSMISSIVE : P.bcx, sx) - gx0;
+    const int my = map_index(gy0 + ly, ny, P.bcy == BC_PERIODIC ? BC_TRANSMISSIVE : P.bcy, sy) - gy0;
+    // (a periodic direction wraps: the position itself holds the wrapped cell)
+    const int px = P.bcx == BC_PERIODIC ? lx : mx, py = P.bcy == BC_PERIODIC ? ly : my;
+    if (P.bcx == BC_PERIODIC) sx = 1.0;
+    if (P.bcy == BC_PERIODIC) sy = 1.0;
+    return (px < 1 || px >= LX - 1 || py < 1 || py >= LX - 1) ? -1 : py * LX + px;
+  };
+  if (walls) {
+    for (int q = tid; q < R2 * R2; q += NT) {
+      const int ly = 1 + q / R2, lx = 1 + q % R2;
+      if (!mirrored(P, gx0 + lx, gy0 + ly)) continue;
+      double sx, sy;
+      const int m = mirror_pos(ly, lx, sx, sy);
+      s_T[ly * LX + lx] = m >= 0 ? s_T[m] : 0;   // (the cell mirrored is no mirror image)
     }
     __syncthreads();
-    if (tid == 0) {
-      const double m0 = fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]));
-      const double m1 = fmax(fmax(s_red[4], s_red[5]), fmax(s_red[6], s_red[7]));
-      const int e = blockIdx.x % ASPREAD;
-      atomic_max_pos(&P.alpha_out[e], m0);
-      atomic_max_pos(&P.alpha_out[ASPREAD + e], m1);
+  }
+  for (int q = tid; q < R2 * R2; q += NT) {
+    const int ly = 1 + q / R2, lx = 1 + q % R2, p = ly * LX + lx;
+    const bool own = !(walls && mirrored(P, gx0 + lx, gy0 + ly));
+    if (own && s_T[p]) s_fl[atomicAdd(&s_cnt[0], 1)] = (uint16_t)p;
+    if (ly < 2 || ly >= LX - 2 || lx < 2 || lx >= LX - 2) continue;
+    // hybrid mask of tile+1; the tile's mesh cells and the ring's four sides go to the list
+    uint8_t hm = 0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) hm |= s_T[p + (k / 3 - 1) * LX + k % 3 - 1];
+    s_H[p] = hm;
+    const int cx = lx - HL, cy = ly - HL;
+    const bool inx = cx >= 0 && cx < tw, iny = cy >= 0 && cy < th;
+    const bool wanted = (inx && iny) || (iny && (cx == -1 || cx == tw)) || (inx && (cy == -1 || cy == th));
+    if (own && hm && wanted) s_hl[atomicAdd(&s_cnt[1], 1)] = (uint16_t)p;
+  }
+  __syncthreads();
+  const int tx = tid % TX, ty = tid / TX;
+  const bool inmesh = tx < tw && ty < th;
+  const size_t gi = inmesh ? (size_t)(by * TY + ty) * nx + bx * TX + tx : 0;
+  {
+    const int p = (ty + HL) * LX + tx + HL;
+    const uint8_t t = inmesh ? s_T[p] : 0, hm = inmesh ? s_H[p] : 0;
+    if (inmesh) {
+      P.Tcur[gi] = t;
+      P.Hcur[gi] = hm;
+    }
+    const int st = mode == MODE_L ? 0 : mode - MODE_RK1;
+    block_append_stat(t != 0, (int)gi, &P.stats[st], P.keep_lists ? P.flist : nullptr, s_wave);
+    block_append_stat(hm != 0, (int)gi, &P.stats[3 + st], P.keep_lists ? P.hlist : nullptr, s_wave + 6);
+  }
+
+  // ---------------------------------------------------------------- limiter (Jacobi)
+  // one item per (cell, direction, characteristic field), four lanes side by side for Euler,
+  // as in stage2d_limit_kernel; written back once every item has read unlimited values
+  const int nfl = s_cnt[0], nhl = s_cnt[1];
+  const int nlim = nfl * 2 * NC;
+  for (int it = tid; it < nlim; it += NT) {   // (whole groups of NC lanes)
+    const int f = it % NC, dir = (it / NC) & 1, p = s_fl[it / (2 * NC)];
+    const int o = dir == 0 ? 1 : LX, mf = (1 + dir) * NC + f;
+    s_lim[it] = limited_value<EQ>(P, dir, f, s_u[f * NPOS + p - o], s_u[f * NPOS + p], s_u[f * NPOS + p + o],
+                                  s_u[mf * NPOS + p - o], s_u[mf * NPOS + p + o]);
+  }
+  __syncthreads();
+  if (nfl) {
+    for (int it = tid; it < nlim; it += NT) {
+      const int f = it % NC, dir = (it / NC) & 1, p = s_fl[it / (2 * NC)];
+      const double v = s_lim[it];
+      s_u[((1 + dir) * NC + f) * NPOS + p] = v;
+      const int cy = p / LX - HL, cx = p % LX - HL;
+      if (cx >= 0 && cx < tw && cy >= 0 && cy < th)
+        P.limcur[(size_t)(dir * NC + f) * plane + (size_t)(by * TY + cy) * nx + bx * TX + cx] = v;
+    }
+    __syncthreads();
+    if (walls) {
+      for (int q = tid; q < R2 * R2; q += NT) {
+        const int ly = 1 + q / R2, lx = 1 + q % R2, p = ly * LX + lx;
+        if (!s_T[p] || !mirrored(P, gx0 + lx, gy0 + ly)) continue;
+        double sx, sy;
+        const int m = mirror_pos(ly, lx, sx, sy);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const double wf = wall_factor<EQ>(c, sx < 0.0, sy < 0.0, P.bcx, P.bcy);
+          s_u[(NC + c) * NPOS + p] = wf * (sx * s_u[(NC + c) * NPOS + m]);
+          s_u[(2 * NC + c) * NPOS + p] = wf * (sy * s_u[(2 * NC + c) * NPOS + m]);
+        }
+      }
+      __syncthreads();
     }
   }
+
+  // ---------------------------------------------------------------- HWENO edge values
+  // groups of 64 / NC cells, the two directions of a group on two waves; the tile's own values
+  // go to P.G, the ring cells' towards the tile to LDS
+  double* const s_rtr = s_lim;
+  constexpr int CPW = 64 / NC;
+  for (int w = tid >> 6; w < 2 * ((nhl + CPW - 1) / CPW); w += NT / 64) {
+    const int cell = (w >> 1) * CPW + lane / NC, f = lane % NC, dir = w & 1;
+    if (cell >= nhl) continue;   // whole groups of NC lanes
+    const int p = s_hl[cell], cy = p / LX - HL, cx = p % LX - HL;
+    const bool in_tile = cx >= 0 && cx < tw && cy >= 0 && cy < th;
+    if (!in_tile && dir != ((cx >= 0 && cx < tw) ? 1 : 0)) continue;   // the ring's other direction
+    double in[19], v[2 * NGE];
+    gather19<NC>(s_u, f, p / LX, p % LX, in);
+    if (dir == 0) hweno_values<EQ, NGE, 0>(P, in, f, v);
+    else hweno_values<EQ, NGE, 1>(P, in, f, v);
+    if (in_tile) {
+      const size_t g = (size_t)(by * TY + cy) * nx + bx * TX + cx;
+#pragma unroll
+      for (int k = 0; k < NGE; ++k) {
+        P.G[((((size_t)(dir * 2 + 0) * NGE + k) * NC + f)) * plane + g] = v[k];
+        P.G[((((size_t)(dir * 2 + 1) * NGE + k) * NC + f)) * plane + g] = v[NGE + k];
+      }
+    } else {
+      // low side of the tile: the ring cell's high face, and the other way round
+      const bool low = dir == 0 ? cx < 0 : cy < 0;
+      const int rl = dir * 2 * TX + (low ? 0 : TX) + (dir == 0 ? cy : cx);
+#pragma unroll
+      for (int k = 0; k < NGE; ++k) s_rtr[(f * NGE + k) * 64 + rl] = low ? v[NGE + k] : v[k];
+    }
+  }
+  // (stage_tile waits for these values after its volume phase)
+  stage_tile<EQ, NGE, BK_RECT, HL>(P, sh, s_u, s_T, s_H, s_rtr, bx, by, dtv);
 }
 
 // Lax-Friedrichs speeds of a state (used before the first stage and by the operator-only
@@ -1292,6 +1615,13 @@ __global__ __launch_bounds__(NT) void dmr_table_kernel(Stage2D P) {
   }
 }
 
+// the rule of stage2d_fused_kernel (with troubled-cell detection; both sides measured there)
+constexpr int FUSED_TILES_EULER = 400, FUSED_TILES_SCALAR = 1600;
+static bool one_launch(int eq, const Stage2D* P) {
+  const long long tiles = (long long)((P->nx + TX - 1) / TX) * ((P->ny + TY - 1) / TY);
+  return P->bcx != BC_DMR && P->bcx != BC_STEP && tiles <= (eq == EQ_EULER ? FUSED_TILES_EULER : FUSED_TILES_SCALAR);
+}
+
 }  // namespace hw
 
 // ------------------------------------------------------------------ launch wrappers
@@ -1304,6 +1634,21 @@ extern "C" hipError_t hw_launch_stage2d(int eq, int ng, const hw::Stage2D* P, hi
   const int wgrid = 2048;
 #define HW_MARK(i) \
   if (ev && hipEventRecord(ev[i], s) != hipSuccess) return hipErrorLaunchFailure
+  if (pre && hw::one_launch(eq, P)) {
+    HW_MARK(0);
+    HW_MARK(1);
+    HW_MARK(2);
+#define HW_LF(E, G) hipLaunchKernelGGL((hw::stage2d_fused_kernel<E, G>), grid, block, 0, s, *P)
+    if (eq == hw::EQ_EULER && ng == 2) HW_LF(hw::EQ_EULER, 2);
+    else if (eq == hw::EQ_EULER && ng == 3) HW_LF(hw::EQ_EULER, 3);
+    else if (eq == hw::EQ_BURGERS && ng == 2) HW_LF(hw::EQ_BURGERS, 2);
+    else if (eq == hw::EQ_BURGERS && ng == 3) HW_LF(hw::EQ_BURGERS, 3);
+    else if (eq == hw::EQ_ADV && ng == 2) HW_LF(hw::EQ_ADV, 2);
+    else if (eq == hw::EQ_ADV && ng == 3) HW_LF(hw::EQ_ADV, 3);
+    else return hipErrorInvalidValue;
+#undef HW_LF
+    return hipGetLastError();
+  }
 #define HW_L2(E, G, D)                                                                  \
   do {                                                                                  \
     if (pre) hipLaunchKernelGGL((hw::stage2d_flags_kernel<E, D>), grid, block, 0, s, *P); \

@@ -42,3 +42,62 @@ def test_operator_at_the_edges_of_the_unmapped_tiles(hw, nx, ny, eq, bc, ng):
     assert array_err(L, Lo) < TOL
     assert array_err(W, info["limited"]) < TOL
     s.close()
+
+
+@pytest.mark.parametrize("tc", ["kxrcf", "all"])
+@pytest.mark.parametrize("ng", [2, 3])
+@pytest.mark.parametrize("eq,n,copies", [("euler", 120, 3), ("burgers", 135, 5), ("advection", 140, 5)])
+def test_one_launch_stage_equals_the_list_passes(hw, eq, n, copies, ng, tc):
+    """A periodic mesh small enough for the one-launch stage, and its data repeated on a mesh
+    that runs the flags, limiter, HWENO and stage launches: the same operator in every copy,
+    with the same flags, after one operator and after two steps (rounding differs only where
+    the compiler contracts differently: the operator's bound)."""
+    U = hi.euler_wall_state(n, n, 4)
+    U[1:] *= 0.02
+    if eq != "euler":
+        U = np.ascontiguousarray(U[:, :1])
+    out = []
+    for k in (1, copies):
+        s = hw.Solver(2, k * n, k * n, domain=(0.0, float(k), 0.0, float(k)), eq=eq, adv=(0.7, -0.45),
+                      bc="periodic", ng_edge=ng, tc_mode=tc)
+        s.flag_export(True)
+        V = np.ascontiguousarray(np.tile(U, (1, 1, k, k)))
+        L, W = s.apply_operator(V)
+        F = s.flags(0)
+        st0 = s.stats()[1:]
+        s.set_state(V)
+        s.steps(2, dt=2e-4)
+        out.append((L, W, F, s.get_state()[0], s.stats()[1:], st0))
+        s.close()
+    (L, W, F, S, c, c0), (Lk, Wk, Fk, Sk, ck, ck0) = out
+    for j, i in ((0, 0), (copies - 1, copies // 2)):
+        sl = np.s_[..., j * n:(j + 1) * n, i * n:(i + 1) * n]
+        assert np.array_equal(F[0], Fk[0][sl]) and np.array_equal(F[1], Fk[1][sl])
+        assert array_err(Lk[sl], L) < TOL and array_err(Wk[sl], W) < TOL
+        assert array_err(Sk[sl], S) < TOL
+    assert [m * copies ** 2 for m in c[0] + c[1]] == list(ck[0] + ck[1])
+    assert c0[0][0] * copies ** 2 == ck0[0][0] > 0 and c0[1][0] * copies ** 2 == ck0[1][0]
+
+
+@pytest.mark.parametrize("eq,bc,nx,ny", [("euler", ("reflective", "transmissive"), 329, 321),
+                                         ("euler", ("transmissive", "periodic"), 321, 337),
+                                         ("burgers", ("transmissive", "transmissive"), 650, 641)])
+def test_list_passes_on_a_mesh_with_walls(hw, eq, bc, nx, ny):
+    """The launches of the larger meshes with mirrored sides and ragged tiles, against the
+    oracle."""
+    h = 1.0 / ny
+    U = hi.euler_wall_state(nx, ny, 6)
+    U[1:] *= 0.02
+    if eq != "euler":
+        U = np.ascontiguousarray(U[:, :1])
+    kw = dict(bc=bc, ng_edge=3, tc_mode="kxrcf")
+    s = hw.Solver(2, nx, ny, domain=(0.0, nx * h, 0.0, 1.0), eq=eq, **kw)
+    s.flag_export(True)
+    L, W = s.apply_operator(U)
+    T, H = s.flags(0)
+    o = Scheme2D(Equation(eq, 2), nx, ny, 0.0, nx * h, 0.0, 1.0, **kw)
+    Lo, info = o.operator(U)
+    assert np.array_equal(T, info["T"]) and np.array_equal(H, info["H"])
+    assert array_err(L, Lo) < TOL
+    assert array_err(W, info["limited"]) < TOL
+    s.close()
