@@ -118,9 +118,11 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
 
   for (int q = tid; q < NQ; q += NT) {
     const int ly = 2 + q / R1, lx = 2 + q % R1;
-    double in19[19], fold[hw2::NFOLD], d[19];
+    double in19[19], fold[hw2::NFOLD], d[19], fb[hw2::NFOLD];
 #pragma unroll
     for (int k = 0; k < 19; ++k) d[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < hw2::NFOLD; ++k) fb[k] = 0.0;
     int wall = 0;   // bits: low x, high x, low y, high y face on a transmissive side
     if (walls) {
       int my, mx;
@@ -148,11 +150,11 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
         const double wq = VW[p % 3] * VW[p / 3];
         ub[p] = wq * (lv * dflux<EQ>(inner[p], P.adv0) + lw * dflux<EQ>(inner[p], P.adv1));
       }
-      hw2::lin2d_inner_T(ub, d);
+      hw2::lin2d_inner_T(ub, fb);
     }
     const bool hyb = s_H[ly * LX + lx] != 0;
     double beta[5], om[5];
-    if (hyb) hweno2d_weights<NGE>(in19, P.w, beta, om);
+    if (hyb) hweno2d_weights<NGE>(in19, fold, P.w, beta, om);
 #pragma unroll 1
     for (int dir = 0; dir < 2; ++dir) {
       const int oy = dir, ox = 1 - dir;
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
       const double pU = S(s_lam, 0, ly + oy, lx + ox), pP = S(s_lam, fP, ly + oy, lx + ox),
                    pQ = S(s_lam, fQ, ly + oy, lx + ox);
       double v[2 * NGE];
-      if (hyb) hweno2d_combine<NGE>(in19, P.w, dir, om, v);
+      if (hyb) hweno2d_combine<NGE>(in19, fold, P.w, dir, om, v);
       else lin_faces<NGE>(fold, dir, v, v + NGE);
       double ub[2 * NGE];
 #pragma unroll
@@ -186,9 +188,10 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
         if ((wall >> (2 * dir)) & 1) ub[k] += Flo * 0.5 * (dflux<EQ>(v[k], adv) + a);
         if ((wall >> (2 * dir + 1)) & 1) ub[NGE + k] += Fhi * 0.5 * (dflux<EQ>(v[NGE + k], adv) - a);
       }
-      if (hyb) hweno2d_field_adj<NGE>(in19, P.w, dir, beta, om, ub, d);
-      else lin_edges_T<NGE>(dir, ub, d);
+      if (hyb) hweno2d_field_adj<NGE>(in19, fold, P.w, dir, beta, om, ub, d);
+      else lin_faces_T<NGE>(dir, ub, ub + NGE, fb);
     }
+    hw2::lin2d_fold_T(fb, d);
 #pragma unroll
     for (int k = 0; k < 19; ++k) s_d[k * NQ + q] = d[k];
   }
@@ -728,14 +731,17 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
   // pull back to the stencil values, component by component
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    double d[19];
+    double d[19], fb[hw2::NFOLD];
 #pragma unroll
     for (int k = 0; k < 19; ++k) d[k] = 0.0;
-    hw2::lin2d_inner_T(ubi[c], d);
+#pragma unroll
+    for (int k = 0; k < hw2::NFOLD; ++k) fb[k] = 0.0;
+    hw2::lin2d_inner_T(ubi[c], fb);
     if (!hyb) {
-      lin_edges_T<NGE>(0, ube[0][c], d);
-      lin_edges_T<NGE>(1, ube[1][c], d);
+      lin_faces_T<NGE>(0, ube[0][c], ube[0][c] + NGE, fb);
+      lin_faces_T<NGE>(1, ube[1][c], ube[1][c] + NGE, fb);
     }
+    hw2::lin2d_fold_T(fb, d);
 #pragma unroll
     for (int k = 0; k < 19; ++k) P.D[(size_t)(c * 19 + k) * plane + gi] = d[k];
   }
@@ -754,9 +760,12 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
 // Remark 4), four lanes per cell as in the forward pass: lane f projects onto field f with
 // row f of L, reverses field f's reconstruction, and returns in ib the stencil cotangents
 // of physical component f; the eigenvectors' dependence on the cell average enters through
-// the average's cotangent.
+// the average's cotangent.  s_x: 19 x 64 doubles of this wave's own, through which the four
+// lanes of a cell read each other's stencil components and field cotangents (each value is
+// written once and read where it is used; passed round by lane exchanges the components
+// stayed in registers, 490 of them, at one wave per SIMD).
 template <int NGE, int DIR, int BND>
-__device__ __forceinline__ void adjEhw2d_cell(const Adj2D& P, int gi, int f, double* ib) {
+__device__ __forceinline__ void adjEhw2d_cell(const Adj2D& P, int gi, int f, double* s_x, double* ib) {
   constexpr int NC = 4, dir = DIR;
   constexpr bool WALLS = BND == ADJ_WALLS;
   const size_t plane = (size_t)P.nx * P.ny;
@@ -817,27 +826,38 @@ __device__ __forceinline__ void adjEhw2d_cell(const Adj2D& P, int gi, int f, dou
                    (t ? P.lim[(NC + f) * plane + g] : P.in[(2 * NC + f) * plane + g]);
     }
   }
+  const int lane = threadIdx.x & 63, q0 = lane & ~3;   // the cell's first lane
+  auto in_order = [] {   // the wave's LDS operations before this point come before those after
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+#pragma unroll
+  for (int k = 0; k < 19; ++k) s_x[k * 64 + lane] = in[k];
+  in_order();
   double U[4];
-  quad_gather_p(in[4], U);   // the cell average
+#pragma unroll
+  for (int c = 0; c < 4; ++c) U[c] = s_x[4 * 64 + q0 + c];   // the cell average
   double Lr[4], Rc[4], x[4];
   euler_eig2d_field(U, P.gam, dir, f, Lr, Rc);   // row f of L, column f of R
   double w19[19];
 #pragma unroll
   for (int k = 0; k < 19; ++k) {
-    quad_gather_p(in[k], x);
     double s = 0.0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) s = fma(Lr[c], x[c], s);
+    for (int c = 0; c < 4; ++c) s = fma(Lr[c], s_x[k * 64 + q0 + c], s);
     w19[k] = s;
   }
   double beta[5], om[5], wv[2 * NGE];
-  hweno2d_weights<NGE>(w19, P.w, beta, om);
-  hweno2d_combine<NGE>(w19, P.w, dir, om, wv);
+  double fold[hw2::NFOLD];
+  hw2::lin2d_fold(w19, fold);
+  hweno2d_weights<NGE>(w19, fold, P.w, beta, om);
+  hweno2d_combine<NGE>(w19, fold, P.w, dir, om, wv);
   // v_c = sum_f R[c][f] wv_f: the field's cotangent and column f of R-bar
   double wvb[2 * NGE], Rb[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int k = 0; k < 2 * NGE; ++k) {
-    quad_gather_p(P.E[((size_t)(dir * 2 * NGE + k) * NC + f) * plane + gi], x);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = P.E[((size_t)(dir * 2 * NGE + k) * NC + c) * plane + gi];
     double s = 0.0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -849,58 +869,60 @@ __device__ __forceinline__ void adjEhw2d_cell(const Adj2D& P, int gi, int f, dou
   double w19b[19];
 #pragma unroll
   for (int k = 0; k < 19; ++k) w19b[k] = 0.0;
-  hweno2d_field_adj<NGE>(w19, P.w, dir, beta, om, wvb, w19b);
+  hweno2d_field_adj<NGE>(w19, fold, P.w, dir, beta, om, wvb, w19b);
   // w_f = sum_c L[f][c] in_c: row f of L-bar, and component f's cotangent through
   // column f of L (lane g holds row g)
   double Lb[4] = {0.0, 0.0, 0.0, 0.0}, Lc[4];
+  int q1 = q0;   // opaque: the stencil is read again, not kept
+  asm volatile("" : "+v"(q1));
 #pragma unroll
   for (int k = 0; k < 19; ++k) {
-    quad_gather_p(in[k], x);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) Lb[c] = fma(w19b[k], x[c], Lb[c]);
+    for (int c = 0; c < 4; ++c) Lb[c] = fma(w19b[k], s_x[k * 64 + q1 + c], Lb[c]);
   }
-  {
-    double q0[4], q1[4], q2[4], q3[4];
-    quad_gather_p(Lr[0], q0);
-    quad_gather_p(Lr[1], q1);
-    quad_gather_p(Lr[2], q2);
-    quad_gather_p(Lr[3], q3);
+  in_order();   // every lane has read the stencil: the space takes L's rows, then w19b
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const double col[4] = {q0[g], q1[g], q2[g], q3[g]};
-      Lc[g] = sel4(col, f);
-    }
-  }
+  for (int c = 0; c < 4; ++c) s_x[c * 64 + lane] = Lr[c];
+  in_order();
+#pragma unroll
+  for (int g = 0; g < 4; ++g) Lc[g] = s_x[f * 64 + q0 + g];
+  in_order();
+#pragma unroll
+  for (int k = 0; k < 19; ++k) s_x[k * 64 + lane] = w19b[k];
+  in_order();
 #pragma unroll
   for (int k = 0; k < 19; ++k) {
-    quad_gather_p(w19b[k], x);
     double s = 0.0;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) s = fma(Lc[g], x[g], s);
+    for (int g = 0; g < 4; ++g) s = fma(Lc[g], s_x[k * 64 + q0 + g], s);
     ib[k] = s;
   }
   // the eigenvectors' dependence on the average: summed over the four fields, lane f
   // keeps the derivative along component f
   double ev[4] = {0.0, 0.0, 0.0, 0.0};
   euler_eig2d_field_vjp(U, P.gam, dir, f, Lb, Rb, ev);
-  double e0[4], e1[4], e2[4], e3[4];
-  quad_gather_p(ev[0], e0);
-  quad_gather_p(ev[1], e1);
-  quad_gather_p(ev[2], e2);
-  quad_gather_p(ev[3], e3);
-  const double es[4] = {e0[0] + e0[1] + e0[2] + e0[3], e1[0] + e1[1] + e1[2] + e1[3],
-                        e2[0] + e2[1] + e2[2] + e2[3], e3[0] + e3[1] + e3[2] + e3[3]};
-  ib[4] += sel4(es, f);
+  in_order();
+#pragma unroll
+  for (int c = 0; c < 4; ++c) s_x[c * 64 + lane] = ev[c];
+  in_order();
+  double es = 0.0;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) es += s_x[f * 64 + q0 + g];
+  ib[4] += es;
+  in_order();
 }
 
 // The hybrid list's reversed HWENO reconstruction: the waves of a workgroup form pairs, the
 // two waves of a pair take the same 16 cells, one the x direction, the other the y
 // direction, and the y wave hands its shares to the x wave through LDS, which adds both to
 // the stencil cotangents.  The two directions thus run side by side.
+// At most 256 VGPRs (two waves per SIMD), so that no value is kept in accumulation registers:
+// forms of this kernel that used them (up to 506 registers) returned stencil cotangents off by
+// 1e-9 on some inputs, and exact ones with the registers limited and nothing else changed.
 template <int NGE, int BND>
-__global__ __launch_bounds__(NT) void adjEhw2d_kernel(Adj2D P) {
+__global__ __launch_bounds__(NT, 2) void adjEhw2d_kernel(Adj2D P) {
   constexpr int NC = 4, CPW = 64 / NC, NPAIR = NT / 128;
-  __shared__ double s_ib[NPAIR][19][64];
+  __shared__ double s_x[NT / 64][19 * 64];
   const int ncell = P.lens ? (int)P.lens[3] : P.counts[1];
   if (ncell == 0) return;
   const size_t plane = (size_t)P.nx * P.ny;
@@ -916,17 +938,17 @@ __global__ __launch_bounds__(NT) void adjEhw2d_kernel(Adj2D P) {
     if (on) {
       gi = P.hlist[cell];
       if (dir == 0) {
-        adjEhw2d_cell<NGE, 0, BND>(P, gi, f, ib);
+        adjEhw2d_cell<NGE, 0, BND>(P, gi, f, s_x[wv], ib);
       } else {
-        adjEhw2d_cell<NGE, 1, BND>(P, gi, f, ib);
+        adjEhw2d_cell<NGE, 1, BND>(P, gi, f, s_x[wv], ib);
 #pragma unroll
-        for (int k = 0; k < 19; ++k) s_ib[pr][k][lane] = ib[k];
+        for (int k = 0; k < 19; ++k) s_x[wv][k * 64 + lane] = ib[k];
       }
     }
     __syncthreads();
     if (on && dir == 0) {
 #pragma unroll
-      for (int k = 0; k < 19; ++k) P.D[(size_t)(f * 19 + k) * plane + gi] += ib[k] + s_ib[pr][k][lane];
+      for (int k = 0; k < 19; ++k) P.D[(size_t)(f * 19 + k) * plane + gi] += ib[k] + s_x[wv + 1][k * 64 + lane];
     }
     __syncthreads();
   }

@@ -24,7 +24,8 @@ Emitted code
   the 3 x 3 interior Gauss points; lin2d_xparts: the parity parts of the left and right
   edges' Gauss points, lin2d_xface: one of the two edges from them.  p0 also commutes with
   the exchange of x and y: the bottom and top edges are the x edges of lin2d_transpose.
-* p0_coeffs / pq_coeffs<n>: monomial coefficients of p0 and p_n, for the HWENO path.
+* p0_coeffs (from the folds) / pq_coeffs<n>: monomial coefficients of p0 and p_n, for the
+  HWENO path (p0's edge values there are those of the linear path).
 * beta_p0 / beta_pq: the smoothness indicators as sparse quadratic forms.
 * edge monomial tables for evaluating the candidates at the edge Gauss points.
 
@@ -240,15 +241,17 @@ def main():
     names = [f"{cls}{i}" for cls, fl in classes.items() for i in range(len(fl))]
     slot = {nm: f"f[{k}]" for k, nm in enumerate(names)}
 
-    # the folding, with the four corners through their diagonal sums and differences: the
-    # same operations, up to the order of commuting operands, on the transposed stencil, so
-    # that lin2d_transpose of a fold equals the fold of the transposed stencil to the bit
+    # the folding, with the four corners through their diagonal sums and differences (the
+    # mixed part oo0 from differences along the edges, which are exact between close values).
+    # On the transposed stencil every operation is the same up to commuting operands, except
+    # oo0's: a reader of the transposed stencil takes lin2d_fold_oo0_T for it, and then its
+    # folds equal lin2d_transpose of the untransposed folds to the bit
     fold = {
         "ee0": "in[4]", "ee1": "in[3] + in[5]", "ee2": "in[1] + in[7]", "ee3": "s0 + s1",
         "ee4": "in[12] - in[10]", "ee5": "in[18] - in[14]",
         "oe0": "in[5] - in[3]", "oe1": "d0 + d1", "oe2": "in[11]",
         "eo0": "in[7] - in[1]", "eo1": "d0 - d1", "eo2": "in[16]",
-        "oo0": "s0 - s1", "oo1": "in[13] - in[9]", "oo2": "in[17] - in[15]"}
+        "oo0": "(in[8] - in[2]) - (in[6] - in[0])", "oo1": "in[13] - in[9]", "oo2": "in[17] - in[15]"}
     corner = {"s0": "in[0] + in[8]", "s1": "in[2] + in[6]", "d0": "in[8] - in[0]", "d1": "in[2] - in[6]"}
     sym = [sp.Symbol(f"i{k}") for k in range(19)]
     def value(expr):
@@ -265,6 +268,7 @@ def main():
     for nm in names:
         w(f"  {slot[nm]} = {fold[nm]};")
     w("}")
+    w("__device__ __forceinline__ double lin2d_fold_oo0_T(const double* in) { return (in[8] - in[6]) - (in[2] - in[0]); }")
     w("// the fold of the stencil with x and y exchanged")
     w("__device__ __forceinline__ void lin2d_transpose(const double* f, double* g) {")
     swap = {"ee1": "ee2", "ee4": "ee5", "oe0": "eo0", "oe1": "eo1", "oe2": "eo2", "oo1": "oo2"}
@@ -383,9 +387,23 @@ def main():
     # ---------------------------------------------------------------- HWENO path
     w("// ---------------------------------------------------------------- HWENO path")
     w("// Monomial order (p, q) for xi^p eta^q: by total degree, then descending p.")
-    w("__device__ __forceinline__ void p0_coeffs(const double* in, double* c) {")
+    # a monomial coefficient of p0 depends on the folds of its own parity only
+    order = {"ee": (0, 0), "oe": (1, 0), "eo": (0, 1), "oo": (1, 1)}
+    fold_rows = []
+    for s, (p, q) in enumerate(mons4):
+        cls = next(k for k, v in order.items() if v == (p % 2, q % 2))
+        row = [C0[s, k] for k in range(19)]
+        coefs = parity_part_rows(row, classes[cls])
+        back = [sp.Integer(0)] * 19
+        for f, c in zip(classes[cls], coefs):
+            for idx, sg in f.items():
+                back[idx] += c * sg
+        assert all(sp.simplify(a - b) == 0 for a, b in zip(row, back)), s
+        fold_rows.append([(c, slot[f"{cls}{i}"]) for i, c in enumerate(coefs) if c != 0])
+    w("// (p0 from the folded inputs)")
+    w("__device__ __forceinline__ void p0_coeffs(const double* f, double* c) {")
     for s in range(15):
-        w(f"  c[{s}] = {emit_sum([(C0[s, k], f'in[{k}]') for k in range(19)])};")
+        w(f"  c[{s}] = {emit_sum(fold_rows[s])};")
     w("}")
     for n in (1, 2, 3, 4):
         mons, C = pq[n]
@@ -415,14 +433,7 @@ def main():
         nodes = gauss_nodes(ng)
         pts = ([(-HALF, e) for e in nodes] + [(HALF, e) for e in nodes]
                + [(e, -HALF) for e in nodes] + [(e, HALF) for e in nodes])
-        w(f"// value of a quartic (15 coefficients) or quadratic (first 6) at edge point i")
-        w(f"__device__ __forceinline__ double edge_quartic_ng{ng}(const double* c, int i) {{")
-        w("  switch (i) {")
-        for i, (x, y) in enumerate(pts):
-            w(f"  case {i}: return {emit_sum([(x ** p * y ** q, f'c[{s}]') for s, (p, q) in enumerate(mons4)])};")
-        w("  }")
-        w("  return 0.0;")
-        w("}")
+        w(f"// value of a quadratic (6 coefficients) at edge point i")
         w(f"__device__ __forceinline__ double edge_quad_ng{ng}(const double* c, int i) {{")
         w("  switch (i) {")
         for i, (x, y) in enumerate(pts):
@@ -432,33 +443,79 @@ def main():
         w("}")
     # ---------------------------------------------------------------- adjoint pieces
     w("// ---------------------------------------------------------------- adjoint path")
-    w("// Transposes (accumulating into db[19]) of the linear point maps, of the candidate")
+    w("// Transposes (accumulating into fold cotangents fb, or db[19]) of the linear point maps, of the candidate")
     w("// coefficient maps and of the edge evaluations; gradients of the indicators.")
 
-    def emit_transpose(fname, points):
-        """db[j] += sum_k R[k][j] * ub[k] for the dense rows R of p0 at the points."""
-        rows = [value_row(C0, mons4, x, y) for (x, y) in points]
-        w(f"__device__ __forceinline__ void {fname} {{")
-        for j in range(19):
-            terms = [(rows[k][j], f"ub[{k}]") for k in range(len(points))]
-            terms = [(c, e) for c, e in terms if c != 0]
-            if not terms:
-                continue
-            acc = f"db[{j}]"
-            for c, e in terms:
+    def acc_T(pairs, indent="  "):
+        """fold cotangents fb[j] += sum coef * expr, for (expr, [(coef, 'f[j]'), ...])."""
+        by = {}
+        for expr, row in pairs:
+            for c, tgt in row:
+                if c != 0:
+                    by.setdefault(tgt, []).append((c, expr))
+        for tgt in sorted(by, key=lambda t: int(t[2:-1])):
+            acc = "fb" + tgt[1:]
+            tgt_b = acc
+            for c, e in by[tgt]:
                 acc = f"fma({cnum(c)}, {e}, {acc})"
-            w(f"  db[{j}] = {acc};")
+            w(f"{indent}{tgt_b} = {acc};")
+
+    def part_row(cls, x, y):
+        row = value_row(C0, mons4, x, y)
+        return [(c, slot[f"{cls}{i}"]) for i, c in enumerate(parity_part_rows(row, classes[cls]))]
+
+    w("// db[19] += the transpose of lin2d_fold applied to fb")
+    w("__device__ __forceinline__ void lin2d_fold_T(const double* fb, double* db) {")
+    corner_T = {0: "s0 - d0", 8: "s0 + d0", 2: "s1 + d1", 6: "s1 - d1"}
+    fi = {nm: slot[nm].replace("f[", "fb[") for nm in names}
+    w(f"  const double s0 = {fi['ee3']} + {fi['oo0']}, s1 = {fi['ee3']} - {fi['oo0']};")
+    w(f"  const double d0 = {fi['oe1']} + {fi['eo1']}, d1 = {fi['oe1']} - {fi['eo1']};")
+    for k, e in corner_T.items():
+        w(f"  db[{k}] += {e};")
+    plain = {}
+    for cls, fl in classes.items():
+        for i, f in enumerate(fl):
+            nm = f"{cls}{i}"
+            if nm in ("ee3", "oo0", "oe1", "eo1"):
+                continue
+            for idx, sg in f.items():
+                plain.setdefault(idx, []).append((sg, fi[nm]))
+    for idx in sorted(plain):
+        expr = " ".join(("+ " if sg > 0 else "- ") + e for sg, e in plain[idx])
+        expr = expr[2:] if expr.startswith("+ ") else "-" + expr[2:]
+        w(f"  db[{idx}] += {expr};")
+    w("}")
+    # self-check: the folds' transpose, corner by corner
+    for k, want in ((0, (1, 1, -1, -1)), (8, (1, 1, 1, 1)), (2, (1, -1, 1, -1)), (6, (1, -1, -1, 1))):
+        got = tuple(classes[c][i].get(k, 0) for c, i in (("ee", 3), ("oo", 0), ("oe", 1), ("eo", 1)))
+        assert got == want, (k, got)
+    w("")
+    w("// fb += the transpose of lin2d_inner applied to ub[9]")
+    w("__device__ __forceinline__ void lin2d_inner_T(const double* ub, double* fb) {")
+    w("  const double pb = ub[0] + ub[8], qb = ub[8] - ub[0], mb = ub[2] + ub[6], rb = ub[2] - ub[6];")
+    w("  const double ee0 = pb + mb, oo0 = pb - mb, oe0 = qb + rb, eo0 = qb - rb;")
+    w("  const double ee1 = ub[1] + ub[7], eo1 = ub[7] - ub[1], ee2 = ub[3] + ub[5], oe2 = ub[5] - ub[3];")
+    g, z = inner_nodes[-1], sp.Integer(0)
+    acc_T([("ee0", part_row("ee", g, g)), ("oe0", part_row("oe", g, g)), ("eo0", part_row("eo", g, g)),
+           ("oo0", part_row("oo", g, g)), ("ee1", part_row("ee", z, g)), ("eo1", part_row("eo", z, g)),
+           ("ee2", part_row("ee", g, z)), ("oe2", part_row("oe", g, z)), ("ub[4]", part_row("ee", z, z))])
+    w("}")
+    w("")
+    for ng in (2, 3):
+        e = gauss_nodes(ng)[-1]
+        w("// fb += the transpose of the x faces' values (low face lo, high face hi)")
+        w(f"__device__ __forceinline__ void lin2d_xfaces_ng{ng}_T(const double* lo, const double* hi, double* fb) {{")
+        L = ng - 1
+        w(f"  const double a = lo[0] + hi[{L}], b = hi[{L}] - lo[0], c = lo[{L}] + hi[0], d = hi[0] - lo[{L}];")
+        w("  const double p0 = a + c, p1 = b + d, p2 = b - d, p3 = a - c;")
+        rows = [("p0", part_row("ee", HALF, e)), ("p1", part_row("oe", HALF, e)),
+                ("p2", part_row("eo", HALF, e)), ("p3", part_row("oo", HALF, e))]
+        if ng == 3:
+            w("  const double p4 = lo[1] + hi[1], p5 = hi[1] - lo[1];")
+            rows += [("p4", part_row("ee", HALF, z)), ("p5", part_row("oe", HALF, z))]
+        acc_T(rows)
         w("}")
         w("")
-
-    emit_transpose("lin2d_inner_T(const double* ub, double* db)",
-                   [(a, b) for b in inner_nodes for a in inner_nodes])
-    for ng in (2, 3):
-        nodes = gauss_nodes(ng)
-        emit_transpose(f"lin2d_xedges_ng{ng}_T(const double* ub, double* db)",
-                       [(-HALF, e) for e in nodes] + [(HALF, e) for e in nodes])
-        emit_transpose(f"lin2d_yedges_ng{ng}_T(const double* ub, double* db)",
-                       [(e, -HALF) for e in nodes] + [(e, HALF) for e in nodes])
 
     def emit_coef_T(fname, C, n):
         w(f"__device__ __forceinline__ void {fname}(const double* cb, double* db) {{")
@@ -472,7 +529,10 @@ def main():
             w(f"  db[{j}] = {acc};")
         w("}")
 
-    emit_coef_T("p0_coeffs_T", C0, 15)
+    w("// fb += the transpose of p0_coeffs applied to cb[15]")
+    w("__device__ __forceinline__ void p0_coeffs_T(const double* cb, double* fb) {")
+    acc_T([(f"cb[{t}]", fold_rows[t]) for t in range(15)])
+    w("}")
     for n in (1, 2, 3, 4):
         emit_coef_T(f"p{n}_coeffs_T", pq[n][1], 6)
 
@@ -490,15 +550,7 @@ def main():
         nodes = gauss_nodes(ng)
         pts = ([(-HALF, e) for e in nodes] + [(HALF, e) for e in nodes]
                + [(e, -HALF) for e in nodes] + [(e, HALF) for e in nodes])
-        w(f"// transposes of edge_quartic / edge_quad: cb[s] += mono_s(point i) * qb")
-        w(f"__device__ __forceinline__ void edge_quartic_ng{ng}_T(double qb, int i, double* cb) {{")
-        w("  switch (i) {")
-        for i, (x, y) in enumerate(pts):
-            body = " ".join(f"cb[{t}] = fma({cnum(x ** p * y ** q)}, qb, cb[{t}]);"
-                            for t, (p, q) in enumerate(mons4) if x ** p * y ** q != 0)
-            w(f"  case {i}: {body} break;")
-        w("  }")
-        w("}")
+        w(f"// transpose of edge_quad: cb[s] += mono_s(point i) * qb")
         w(f"__device__ __forceinline__ void edge_quad_ng{ng}_T(double qb, int i, double* cb) {{")
         w("  switch (i) {")
         for i, (x, y) in enumerate(pts):

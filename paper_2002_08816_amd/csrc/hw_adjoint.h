@@ -138,20 +138,19 @@ __device__ __forceinline__ void limit_moment_adj(double um, double u0, double up
 }
 
 // ------------------------------------------------------------------ linear maps, transposed
+// fold cotangents fb += those of the values on both faces of direction dir (lin_faces)
 template <int NGE>
-__device__ __forceinline__ void lin_edges_T(int dir, const double* ub, double* db) {
-  if constexpr (NGE == 2) {
-    if (dir == 0) hw2::lin2d_xedges_ng2_T(ub, db);
-    else hw2::lin2d_yedges_ng2_T(ub, db);
+__device__ __forceinline__ void lin_faces_T(int dir, const double* lo, const double* hi, double* fb) {
+  if (dir == 0) {
+    if constexpr (NGE == 2) hw2::lin2d_xfaces_ng2_T(lo, hi, fb);
+    else hw2::lin2d_xfaces_ng3_T(lo, hi, fb);
   } else {
-    if (dir == 0) hw2::lin2d_xedges_ng3_T(ub, db);
-    else hw2::lin2d_yedges_ng3_T(ub, db);
+    double g[hw2::NFOLD];
+    hw2::lin2d_transpose(fb, g);
+    if constexpr (NGE == 2) hw2::lin2d_xfaces_ng2_T(lo, hi, g);
+    else hw2::lin2d_xfaces_ng3_T(lo, hi, g);
+    hw2::lin2d_transpose(g, fb);
   }
-}
-template <int NGE>
-__device__ __forceinline__ void edge_quartic_T(double qb, int i, double* cb) {
-  if constexpr (NGE == 2) hw2::edge_quartic_ng2_T(qb, i, cb);
-  else hw2::edge_quartic_ng3_T(qb, i, cb);
 }
 template <int NGE>
 __device__ __forceinline__ void edge_quad_T(double qb, int i, double* cb) {
@@ -193,10 +192,10 @@ __device__ __forceinline__ void hweno_pq_back(const double* w19, int dir, double
 
 // Accumulates into db[19] the cotangent of the stencil w19 for the cotangents vb[2*NGE]
 // of the edge values of direction dir (hweno2d_combine order); beta and om are the
-// forward indicators and weights of this stencil (hweno2d_weights).
+// forward indicators and weights of this stencil (hweno2d_weights), fold its lin2d_fold.
 template <int NGE>
-__device__ __forceinline__ void hweno2d_field_adj(const double* w19, const Weights& W, int dir,
-                                                  const double* beta, const double* om,
+__device__ __forceinline__ void hweno2d_field_adj(const double* w19, const double* fold, const Weights& W,
+                                                  int dir, const double* beta, const double* om,
                                                   const double* vb, double* db) {
   const double g0 = W.rec[0];
   double an[5];
@@ -206,11 +205,10 @@ __device__ __forceinline__ void hweno2d_field_adj(const double* w19, const Weigh
   // cotangents of the combination coefficients a_n
   double ab[5];
   {
-    double c[15];
-    hw2::p0_coeffs(w19, c);
-    double s = 0.0;
+    double v[2 * NGE], s = 0.0;
+    lin_faces<NGE>(fold, dir, v, v + NGE);
 #pragma unroll
-    for (int k = 0; k < 2 * NGE; ++k) s = fma(vb[k], edge_quartic<NGE>(c, dir * 2 * NGE + k), s);
+    for (int k = 0; k < 2 * NGE; ++k) s = fma(vb[k], v[k], s);
     ab[0] = s;
   }
   ab[1] = hweno_pq_dot<NGE, 1>(w19, dir, vb);
@@ -229,16 +227,18 @@ __device__ __forceinline__ void hweno2d_field_adj(const double* w19, const Weigh
   nonlinear_weights_adj<4>(beta, W.rec, W.eps, omb, bb);
   // candidates: through their edge values and their smoothness indicators
   {
-    double c[15], cb[15], gr[15];
-    hw2::p0_coeffs(w19, c);
-#pragma unroll
-    for (int t = 0; t < 15; ++t) cb[t] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 2 * NGE; ++k) edge_quartic_T<NGE>(an[0] * vb[k], dir * 2 * NGE + k, cb);
+    double c[15], gr[15], fb[hw2::NFOLD], v[2 * NGE];
+    hw2::p0_coeffs(fold, c);
     hw2::beta_p0_grad(c, gr);
 #pragma unroll
-    for (int t = 0; t < 15; ++t) cb[t] = fma(bb[0], gr[t], cb[t]);
-    hw2::p0_coeffs_T(cb, db);
+    for (int t = 0; t < 15; ++t) gr[t] *= bb[0];
+#pragma unroll
+    for (int t = 0; t < hw2::NFOLD; ++t) fb[t] = 0.0;
+    hw2::p0_coeffs_T(gr, fb);
+#pragma unroll
+    for (int k = 0; k < 2 * NGE; ++k) v[k] = an[0] * vb[k];
+    lin_faces_T<NGE>(dir, v, v + NGE, fb);
+    hw2::lin2d_fold_T(fb, db);
   }
   hweno_pq_back<NGE, 1>(w19, dir, an[1], bb[1], vb, db);
   hweno_pq_back<NGE, 2>(w19, dir, an[2], bb[2], vb, db);
@@ -282,63 +282,60 @@ __device__ __forceinline__ void euler_flux2d_vjp(const double* U, double gam, co
   ub[3] += Eb;
 }
 
-// Forward-mode number (value, derivative along one seed direction).
-struct Dual {
-  double v, d;
-};
-__device__ __forceinline__ Dual operator+(Dual a, Dual b) { return {a.v + b.v, a.d + b.d}; }
-__device__ __forceinline__ Dual operator-(Dual a, Dual b) { return {a.v - b.v, a.d - b.d}; }
-__device__ __forceinline__ Dual operator*(Dual a, Dual b) { return {a.v * b.v, a.d * b.v + a.v * b.d}; }
-__device__ __forceinline__ Dual operator*(double s, Dual a) { return {s * a.v, s * a.d}; }
-__device__ __forceinline__ Dual operator+(double s, Dual a) { return {s + a.v, a.d}; }
-__device__ __forceinline__ Dual operator-(Dual a) { return {-a.v, -a.d}; }
-__device__ __forceinline__ Dual operator/(Dual a, Dual b) {
-  const double q = a.v / b.v;
-  return {q, (a.d - q * b.d) / b.v};
-}
-__device__ __forceinline__ Dual dsqrt(Dual a) {
-  const double s = sqrt(a.v);
-  return {s, 0.5 * a.d / s};
-}
-
 // Derivatives of row f of L and column f of R (the characteristic matrices of
 // euler_eig2d_field in direction d, Remark 4) with respect to the cell average U,
 // contracted with cotangents: out[j] += sum_c Lb[c] dL[f][c]/dU_j + Rb[c] dR[c][f]/dU_j.
+// Reverse mode over the formulas of euler_eig2d_field; the field is a lane's own (selects,
+// no branches: the four lanes of a cell hold the four fields).  About 110 FP64 instructions; a
+// forward-mode form, four passes of dual numbers with their divisions, took 1400 and half of
+// the reversed HWENO pass.
 __device__ __forceinline__ void euler_eig2d_field_vjp(const double* U, double gam, int d, int f,
                                                       const double* Lb, const double* Rb,
                                                       double* out) {
-  const Dual one{1.0, 0.0}, zero{0.0, 0.0};
-#pragma unroll 1
-  for (int j = 0; j < 4; ++j) {
-    const Dual rho{U[0], j == 0 ? 1.0 : 0.0}, M{U[1], j == 1 ? 1.0 : 0.0},
-        N{U[2], j == 2 ? 1.0 : 0.0}, E{U[3], j == 3 ? 1.0 : 0.0};
-    const Dual u = M / rho, v = N / rho;
-    const Dual q2 = u * u + v * v;
-    const Dual p = (gam - 1.0) * (E - 0.5 * (rho * q2));
-    const Dual c = dsqrt((gam * p) / rho);
-    const Dual H = (E + p) / rho;
-    const Dual b1 = (gam - 1.0) * (one / (c * c)), b2 = 0.5 * (b1 * q2), ic = one / c;
-    const Dual un = d == 0 ? u : v, ut = d == 0 ? v : u;
-    Dual l[4], r[4];
-    if (f == 0) {
-      l[0] = 0.5 * (b2 + un * ic); l[1] = -0.5 * (b1 * un + ic); l[2] = -0.5 * (b1 * ut); l[3] = 0.5 * b1;
-      r[0] = one; r[1] = un - c; r[2] = ut; r[3] = H - un * c;
-    } else if (f == 1) {
-      l[0] = one - b2; l[1] = b1 * un; l[2] = b1 * ut; l[3] = -b1;
-      r[0] = one; r[1] = un; r[2] = ut; r[3] = 0.5 * q2;
-    } else if (f == 2) {
-      l[0] = -ut; l[1] = zero; l[2] = one; l[3] = zero;
-      r[0] = zero; r[1] = zero; r[2] = one; r[3] = ut;
-    } else {
-      l[0] = 0.5 * (b2 - un * ic); l[1] = -0.5 * (b1 * un - ic); l[2] = -0.5 * (b1 * ut); l[3] = 0.5 * b1;
-      r[0] = one; r[1] = un + c; r[2] = ut; r[3] = H + un * c;
-    }
-    // (normal, tangential) momentum ordering -> (x, y)
-    const int in_ = 1 + d, it_ = 2 - d;
-    double s = Lb[0] * l[0].d + Lb[3] * l[3].d + Rb[0] * r[0].d + Rb[3] * r[3].d;
-    s += Lb[in_] * l[1].d + Lb[it_] * l[2].d + Rb[in_] * r[1].d + Rb[it_] * r[2].d;
-    out[j] += s;
-  }
+  const double g1 = gam - 1.0;
+  const double r = 1.0 / U[0];
+  const double u = U[1] * r, v = U[2] * r, E = U[3];
+  const double q2 = u * u + v * v;
+  const double p = g1 * (E - 0.5 * (U[0] * q2));
+  const double c = sqrt(gam * p * r);
+  const double ic = 1.0 / c;
+  const double b1 = g1 * (ic * ic);
+  const double un = d == 0 ? u : v, ut = d == 0 ? v : u;
+  // fields 0 and 3 are acoustic (sign s of c: +1, -1), 1 the entropy, 2 the shear field
+  const double s = f == 0 ? 1.0 : (f == 3 ? -1.0 : 0.0);
+  const double k = f == 1 ? -1.0 : (f == 2 ? 0.0 : 0.5);
+  const double w = f == 2 ? 0.0 : 1.0;
+  const int in_ = 1 + d, it_ = 2 - d;   // (normal, tangential) momentum components
+  const double lb1 = Lb[in_], lb2 = Lb[it_], rb1 = Rb[in_], rb2 = Rb[it_];
+  // rows: l = k (b2, -b1 un, -b1 ut, b1) + s/2 (un ic, -ic, 0, 0) (+ 1, or -ut and 1 for shear);
+  // columns: r = (1, un - s c, ut, H - s un c), (1, un, ut, q2 / 2) or (0, 0, 1, ut)
+  const double L0 = k * Lb[0], L1 = -(k * lb1), L2 = -(k * lb2), L3 = k * Lb[3];
+  const double sc = s * Rb[3];
+  double b1b = L1 * un + L2 * ut + L3;
+  double unb = L1 * b1 + s * (ic * (0.5 * Lb[0])) + w * rb1 - sc * c;
+  double utb = L2 * b1 + w * rb2 + (f == 2 ? Rb[3] - Lb[0] : 0.0);
+  double icb = 0.5 * s * (Lb[0] * un - lb1);
+  double cb = -(s * rb1) - sc * un;
+  const double Hb = s != 0.0 ? Rb[3] : 0.0;
+  double q2b = f == 1 ? 0.5 * Rb[3] : 0.0;
+  // b2 = b1 q2 / 2, b1 = (gamma - 1) ic^2, ic = 1 / c, c^2 = gamma p / rho
+  b1b += 0.5 * q2 * L0;
+  q2b += 0.5 * b1 * L0;
+  icb += 2.0 * g1 * ic * b1b;
+  cb -= ic * ic * icb;
+  const double c2b = 0.5 * ic * cb;
+  double Eb = Hb * r, pb = Hb * r + c2b * (gam * r);
+  double rb = Hb * (E + p) + c2b * (gam * p);        // cotangent of 1 / rho
+  Eb += g1 * pb;
+  double rhob = -0.5 * g1 * q2 * pb;
+  q2b -= 0.5 * g1 * U[0] * pb;
+  const double ub = (d == 0 ? unb : utb) + 2.0 * u * q2b, vb = (d == 0 ? utb : unb) + 2.0 * v * q2b;
+  rb += ub * U[1] + vb * U[2];
+  rhob -= rb * r * r;
+  out[0] += rhob;
+  out[1] += ub * r;
+  out[2] += vb * r;
+  out[3] += Eb;
 }
 
 // x[i] for a lane-dependent index i in 0..3

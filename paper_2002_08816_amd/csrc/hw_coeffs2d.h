@@ -26,10 +26,11 @@ __device__ __forceinline__ void lin2d_fold(const double* in, double* f) {
   f[9] = in[7] - in[1];
   f[10] = d0 - d1;
   f[11] = in[16];
-  f[12] = s0 - s1;
+  f[12] = (in[8] - in[2]) - (in[6] - in[0]);
   f[13] = in[13] - in[9];
   f[14] = in[17] - in[15];
 }
+__device__ __forceinline__ double lin2d_fold_oo0_T(const double* in) { return (in[8] - in[6]) - (in[2] - in[0]); }
 // the fold of the stencil with x and y exchanged
 __device__ __forceinline__ void lin2d_transpose(const double* f, double* g) {
   g[0] = f[0];
@@ -101,22 +102,23 @@ __device__ __forceinline__ void lin2d_xface_ng3(const double* p, double side, do
 
 // ---------------------------------------------------------------- HWENO path
 // Monomial order (p, q) for xi^p eta^q: by total degree, then descending p.
-__device__ __forceinline__ void p0_coeffs(const double* in, double* c) {
-  c[0] = fma(0.421875, in[18], fma(-0.421875, in[14], fma(0.421875, in[12], fma(-0.421875, in[10], fma(0.001736111111111111, in[8], fma(-0.1154513888888889, in[7], fma(0.001736111111111111, in[6], fma(-0.1154513888888889, in[5], fma(1.4548611111111112, in[4], fma(-0.1154513888888889, in[3], fma(0.001736111111111111, in[2], fma(-0.1154513888888889, in[1], 0.001736111111111111 * in[0]))))))))))));
-  c[1] = fma(13.636363636363637, in[11], fma(-0.020833333333333332, in[8], fma(0.020833333333333332, in[6], fma(-0.026515151515151516, in[5], fma(0.026515151515151516, in[3], fma(-0.020833333333333332, in[2], 0.020833333333333332 * in[0]))))));
-  c[2] = fma(13.636363636363637, in[16], fma(-0.020833333333333332, in[8], fma(-0.026515151515151516, in[7], fma(-0.020833333333333332, in[6], fma(0.020833333333333332, in[2], fma(0.026515151515151516, in[1], 0.020833333333333332 * in[0]))))));
-  c[3] = fma(-5.625, in[12], fma(5.625, in[10], fma(-0.020833333333333332, in[8], fma(0.041666666666666664, in[7], fma(-0.020833333333333332, in[6], fma(1.4791666666666667, in[5], fma(-2.9583333333333335, in[4], fma(1.4791666666666667, in[3], fma(-0.020833333333333332, in[2], fma(0.041666666666666664, in[1], -0.020833333333333332 * in[0]))))))))));
-  c[4] = fma(6.818181818181818, in[17], fma(-6.818181818181818, in[15], fma(6.818181818181818, in[13], fma(-6.818181818181818, in[9], fma(-0.3181818181818182, in[8], fma(0.3181818181818182, in[6], fma(0.3181818181818182, in[2], -0.3181818181818182 * in[0])))))));
-  c[5] = fma(-5.625, in[18], fma(5.625, in[14], fma(-0.020833333333333332, in[8], fma(1.4791666666666667, in[7], fma(-0.020833333333333332, in[6], fma(0.041666666666666664, in[5], fma(-2.9583333333333335, in[4], fma(0.041666666666666664, in[3], fma(-0.020833333333333332, in[2], fma(1.4791666666666667, in[1], -0.020833333333333332 * in[0]))))))))));
-  c[6] = fma(-10.909090909090908, in[11], fma(0.45454545454545453, in[5], -0.45454545454545453 * in[3]));
-  c[7] = fma(0.25, in[8], fma(-0.5, in[7], fma(0.25, in[6], fma(-0.25, in[2], fma(0.5, in[1], -0.25 * in[0])))));
-  c[8] = fma(0.25, in[8], fma(-0.25, in[6], fma(-0.5, in[5], fma(0.5, in[3], fma(0.25, in[2], -0.25 * in[0])))));
-  c[9] = fma(-10.909090909090908, in[16], fma(0.45454545454545453, in[7], -0.45454545454545453 * in[1]));
-  c[10] = fma(3.75, in[12], fma(-3.75, in[10], fma(-0.625, in[5], fma(1.25, in[4], -0.625 * in[3]))));
-  c[11] = fma(-5.454545454545454, in[13], fma(5.454545454545454, in[9], fma(0.22727272727272727, in[8], fma(-0.22727272727272727, in[6], fma(-0.22727272727272727, in[2], 0.22727272727272727 * in[0])))));
-  c[12] = fma(0.25, in[8], fma(-0.5, in[7], fma(0.25, in[6], fma(-0.5, in[5], fma(1.0, in[4], fma(-0.5, in[3], fma(0.25, in[2], fma(-0.5, in[1], 0.25 * in[0]))))))));
-  c[13] = fma(-5.454545454545454, in[17], fma(5.454545454545454, in[15], fma(0.22727272727272727, in[8], fma(-0.22727272727272727, in[6], fma(-0.22727272727272727, in[2], 0.22727272727272727 * in[0])))));
-  c[14] = fma(3.75, in[18], fma(-3.75, in[14], fma(-0.625, in[7], fma(1.25, in[4], -0.625 * in[1]))));
+// (p0 from the folded inputs)
+__device__ __forceinline__ void p0_coeffs(const double* f, double* c) {
+  c[0] = fma(0.421875, f[5], fma(0.421875, f[4], fma(0.001736111111111111, f[3], fma(-0.1154513888888889, f[2], fma(-0.1154513888888889, f[1], 1.4548611111111112 * f[0])))));
+  c[1] = fma(13.636363636363637, f[8], fma(-0.020833333333333332, f[7], -0.026515151515151516 * f[6]));
+  c[2] = fma(13.636363636363637, f[11], fma(-0.020833333333333332, f[10], -0.026515151515151516 * f[9]));
+  c[3] = fma(-5.625, f[4], fma(-0.020833333333333332, f[3], fma(0.041666666666666664, f[2], fma(1.4791666666666667, f[1], -2.9583333333333335 * f[0]))));
+  c[4] = fma(6.818181818181818, f[14], fma(6.818181818181818, f[13], -0.3181818181818182 * f[12]));
+  c[5] = fma(-5.625, f[5], fma(-0.020833333333333332, f[3], fma(1.4791666666666667, f[2], fma(0.041666666666666664, f[1], -2.9583333333333335 * f[0]))));
+  c[6] = fma(-10.909090909090908, f[8], 0.45454545454545453 * f[6]);
+  c[7] = fma(0.25, f[10], -0.5 * f[9]);
+  c[8] = fma(0.25, f[7], -0.5 * f[6]);
+  c[9] = fma(-10.909090909090908, f[11], 0.45454545454545453 * f[9]);
+  c[10] = fma(3.75, f[4], fma(-0.625, f[1], 1.25 * f[0]));
+  c[11] = fma(-5.454545454545454, f[13], 0.22727272727272727 * f[12]);
+  c[12] = fma(0.25, f[3], fma(-0.5, f[2], fma(-0.5, f[1], f[0])));
+  c[13] = fma(-5.454545454545454, f[14], 0.22727272727272727 * f[12]);
+  c[14] = fma(3.75, f[5], fma(-0.625, f[2], 1.25 * f[0]));
 }
 __device__ __forceinline__ void p1_coeffs(const double* in, double* c) {
   c[0] = fma(-1.0, in[16], fma(-1.0, in[11], fma(1.1666666666666667, in[4], fma(-0.08333333333333333, in[3], -0.08333333333333333 * in[1]))));
@@ -177,20 +179,7 @@ __device__ __forceinline__ double beta_pq(const double* c) {
   b = fma(c[5], 4.333333333333333 * c[5], b);
   return b;
 }
-// value of a quartic (15 coefficients) or quadratic (first 6) at edge point i
-__device__ __forceinline__ double edge_quartic_ng2(const double* c, int i) {
-  switch (i) {
-  case 0: return fma(0.006944444444444444, c[14], fma(0.012028130608117204, c[13], fma(0.020833333333333332, c[12], fma(0.03608439182435161, c[11], fma(0.0625, c[10], fma(-0.024056261216234408, c[9], fma(-0.041666666666666664, c[8], fma(-0.07216878364870322, c[7], fma(-0.125, c[6], fma(0.08333333333333333, c[5], fma(0.14433756729740643, c[4], fma(0.25, c[3], fma(-0.28867513459481287, c[2], fma(-0.5, c[1], c[0]))))))))))))));
-  case 1: return fma(0.006944444444444444, c[14], fma(-0.012028130608117204, c[13], fma(0.020833333333333332, c[12], fma(-0.03608439182435161, c[11], fma(0.0625, c[10], fma(0.024056261216234408, c[9], fma(-0.041666666666666664, c[8], fma(0.07216878364870322, c[7], fma(-0.125, c[6], fma(0.08333333333333333, c[5], fma(-0.14433756729740643, c[4], fma(0.25, c[3], fma(0.28867513459481287, c[2], fma(-0.5, c[1], c[0]))))))))))))));
-  case 2: return fma(0.006944444444444444, c[14], fma(-0.012028130608117204, c[13], fma(0.020833333333333332, c[12], fma(-0.03608439182435161, c[11], fma(0.0625, c[10], fma(-0.024056261216234408, c[9], fma(0.041666666666666664, c[8], fma(-0.07216878364870322, c[7], fma(0.125, c[6], fma(0.08333333333333333, c[5], fma(-0.14433756729740643, c[4], fma(0.25, c[3], fma(-0.28867513459481287, c[2], fma(0.5, c[1], c[0]))))))))))))));
-  case 3: return fma(0.006944444444444444, c[14], fma(0.012028130608117204, c[13], fma(0.020833333333333332, c[12], fma(0.03608439182435161, c[11], fma(0.0625, c[10], fma(0.024056261216234408, c[9], fma(0.041666666666666664, c[8], fma(0.07216878364870322, c[7], fma(0.125, c[6], fma(0.08333333333333333, c[5], fma(0.14433756729740643, c[4], fma(0.25, c[3], fma(0.28867513459481287, c[2], fma(0.5, c[1], c[0]))))))))))))));
-  case 4: return fma(0.0625, c[14], fma(0.03608439182435161, c[13], fma(0.020833333333333332, c[12], fma(0.012028130608117204, c[11], fma(0.006944444444444444, c[10], fma(-0.125, c[9], fma(-0.07216878364870322, c[8], fma(-0.041666666666666664, c[7], fma(-0.024056261216234408, c[6], fma(0.25, c[5], fma(0.14433756729740643, c[4], fma(0.08333333333333333, c[3], fma(-0.5, c[2], fma(-0.28867513459481287, c[1], c[0]))))))))))))));
-  case 5: return fma(0.0625, c[14], fma(-0.03608439182435161, c[13], fma(0.020833333333333332, c[12], fma(-0.012028130608117204, c[11], fma(0.006944444444444444, c[10], fma(-0.125, c[9], fma(0.07216878364870322, c[8], fma(-0.041666666666666664, c[7], fma(0.024056261216234408, c[6], fma(0.25, c[5], fma(-0.14433756729740643, c[4], fma(0.08333333333333333, c[3], fma(-0.5, c[2], fma(0.28867513459481287, c[1], c[0]))))))))))))));
-  case 6: return fma(0.0625, c[14], fma(-0.03608439182435161, c[13], fma(0.020833333333333332, c[12], fma(-0.012028130608117204, c[11], fma(0.006944444444444444, c[10], fma(0.125, c[9], fma(-0.07216878364870322, c[8], fma(0.041666666666666664, c[7], fma(-0.024056261216234408, c[6], fma(0.25, c[5], fma(-0.14433756729740643, c[4], fma(0.08333333333333333, c[3], fma(0.5, c[2], fma(-0.28867513459481287, c[1], c[0]))))))))))))));
-  case 7: return fma(0.0625, c[14], fma(0.03608439182435161, c[13], fma(0.020833333333333332, c[12], fma(0.012028130608117204, c[11], fma(0.006944444444444444, c[10], fma(0.125, c[9], fma(0.07216878364870322, c[8], fma(0.041666666666666664, c[7], fma(0.024056261216234408, c[6], fma(0.25, c[5], fma(0.14433756729740643, c[4], fma(0.08333333333333333, c[3], fma(0.5, c[2], fma(0.28867513459481287, c[1], c[0]))))))))))))));
-  }
-  return 0.0;
-}
+// value of a quadratic (6 coefficients) at edge point i
 __device__ __forceinline__ double edge_quad_ng2(const double* c, int i) {
   switch (i) {
   case 0: return fma(0.08333333333333333, c[5], fma(0.14433756729740643, c[4], fma(0.25, c[3], fma(-0.28867513459481287, c[2], fma(-0.5, c[1], c[0])))));
@@ -204,24 +193,7 @@ __device__ __forceinline__ double edge_quad_ng2(const double* c, int i) {
   }
   return 0.0;
 }
-// value of a quartic (15 coefficients) or quadratic (first 6) at edge point i
-__device__ __forceinline__ double edge_quartic_ng3(const double* c, int i) {
-  switch (i) {
-  case 0: return fma(0.0225, c[14], fma(0.02904737509655563, c[13], fma(0.0375, c[12], fma(0.04841229182759271, c[11], fma(0.0625, c[10], fma(-0.05809475019311126, c[9], fma(-0.075, c[8], fma(-0.09682458365518543, c[7], fma(-0.125, c[6], fma(0.15, c[5], fma(0.19364916731037085, c[4], fma(0.25, c[3], fma(-0.3872983346207417, c[2], fma(-0.5, c[1], c[0]))))))))))))));
-  case 1: return fma(0.0625, c[10], fma(-0.125, c[6], fma(0.25, c[3], fma(-0.5, c[1], c[0]))));
-  case 2: return fma(0.0225, c[14], fma(-0.02904737509655563, c[13], fma(0.0375, c[12], fma(-0.04841229182759271, c[11], fma(0.0625, c[10], fma(0.05809475019311126, c[9], fma(-0.075, c[8], fma(0.09682458365518543, c[7], fma(-0.125, c[6], fma(0.15, c[5], fma(-0.19364916731037085, c[4], fma(0.25, c[3], fma(0.3872983346207417, c[2], fma(-0.5, c[1], c[0]))))))))))))));
-  case 3: return fma(0.0225, c[14], fma(-0.02904737509655563, c[13], fma(0.0375, c[12], fma(-0.04841229182759271, c[11], fma(0.0625, c[10], fma(-0.05809475019311126, c[9], fma(0.075, c[8], fma(-0.09682458365518543, c[7], fma(0.125, c[6], fma(0.15, c[5], fma(-0.19364916731037085, c[4], fma(0.25, c[3], fma(-0.3872983346207417, c[2], fma(0.5, c[1], c[0]))))))))))))));
-  case 4: return fma(0.0625, c[10], fma(0.125, c[6], fma(0.25, c[3], fma(0.5, c[1], c[0]))));
-  case 5: return fma(0.0225, c[14], fma(0.02904737509655563, c[13], fma(0.0375, c[12], fma(0.04841229182759271, c[11], fma(0.0625, c[10], fma(0.05809475019311126, c[9], fma(0.075, c[8], fma(0.09682458365518543, c[7], fma(0.125, c[6], fma(0.15, c[5], fma(0.19364916731037085, c[4], fma(0.25, c[3], fma(0.3872983346207417, c[2], fma(0.5, c[1], c[0]))))))))))))));
-  case 6: return fma(0.0625, c[14], fma(0.04841229182759271, c[13], fma(0.0375, c[12], fma(0.02904737509655563, c[11], fma(0.0225, c[10], fma(-0.125, c[9], fma(-0.09682458365518543, c[8], fma(-0.075, c[7], fma(-0.05809475019311126, c[6], fma(0.25, c[5], fma(0.19364916731037085, c[4], fma(0.15, c[3], fma(-0.5, c[2], fma(-0.3872983346207417, c[1], c[0]))))))))))))));
-  case 7: return fma(0.0625, c[14], fma(-0.125, c[9], fma(0.25, c[5], fma(-0.5, c[2], c[0]))));
-  case 8: return fma(0.0625, c[14], fma(-0.04841229182759271, c[13], fma(0.0375, c[12], fma(-0.02904737509655563, c[11], fma(0.0225, c[10], fma(-0.125, c[9], fma(0.09682458365518543, c[8], fma(-0.075, c[7], fma(0.05809475019311126, c[6], fma(0.25, c[5], fma(-0.19364916731037085, c[4], fma(0.15, c[3], fma(-0.5, c[2], fma(0.3872983346207417, c[1], c[0]))))))))))))));
-  case 9: return fma(0.0625, c[14], fma(-0.04841229182759271, c[13], fma(0.0375, c[12], fma(-0.02904737509655563, c[11], fma(0.0225, c[10], fma(0.125, c[9], fma(-0.09682458365518543, c[8], fma(0.075, c[7], fma(-0.05809475019311126, c[6], fma(0.25, c[5], fma(-0.19364916731037085, c[4], fma(0.15, c[3], fma(0.5, c[2], fma(-0.3872983346207417, c[1], c[0]))))))))))))));
-  case 10: return fma(0.0625, c[14], fma(0.125, c[9], fma(0.25, c[5], fma(0.5, c[2], c[0]))));
-  case 11: return fma(0.0625, c[14], fma(0.04841229182759271, c[13], fma(0.0375, c[12], fma(0.02904737509655563, c[11], fma(0.0225, c[10], fma(0.125, c[9], fma(0.09682458365518543, c[8], fma(0.075, c[7], fma(0.05809475019311126, c[6], fma(0.25, c[5], fma(0.19364916731037085, c[4], fma(0.15, c[3], fma(0.5, c[2], fma(0.3872983346207417, c[1], c[0]))))))))))))));
-  }
-  return 0.0;
-}
+// value of a quadratic (6 coefficients) at edge point i
 __device__ __forceinline__ double edge_quad_ng3(const double* c, int i) {
   switch (i) {
   case 0: return fma(0.15, c[5], fma(0.19364916731037085, c[4], fma(0.25, c[3], fma(-0.3872983346207417, c[2], fma(-0.5, c[1], c[0])))));
@@ -240,138 +212,113 @@ __device__ __forceinline__ double edge_quad_ng3(const double* c, int i) {
   return 0.0;
 }
 // ---------------------------------------------------------------- adjoint path
-// Transposes (accumulating into db[19]) of the linear point maps, of the candidate
+// Transposes (accumulating into fold cotangents fb, or db[19]) of the linear point maps, of the candidate
 // coefficient maps and of the edge evaluations; gradients of the indicators.
-__device__ __forceinline__ void lin2d_inner_T(const double* ub, double* db) {
-  db[0] = fma(-0.049298833376246944, ub[8], fma(0.006679826415709896, ub[7], fma(0.03861111111111111, ub[6], fma(0.006679826415709896, ub[5], fma(0.001736111111111111, ub[4], fma(-0.009457604193487673, ub[3], fma(0.03861111111111111, ub[2], fma(-0.009457604193487673, ub[1], fma(-0.02347894440153083, ub[0], db[0])))))))));
-  db[1] = fma(0.10027105559846916, ub[8], fma(0.07622368050191354, ub[7], fma(0.10027105559846916, ub[6], fma(-0.10920138888888889, ub[5], fma(-0.1154513888888889, ub[4], fma(-0.10920138888888889, ub[3], fma(0.07445116662375305, ub[2], fma(0.10849854172030868, ub[1], fma(0.07445116662375305, ub[0], db[1])))))))));
-  db[2] = fma(0.03861111111111111, ub[8], fma(0.006679826415709896, ub[7], fma(-0.049298833376246944, ub[6], fma(-0.009457604193487673, ub[5], fma(0.001736111111111111, ub[4], fma(0.006679826415709896, ub[3], fma(-0.02347894440153083, ub[2], fma(-0.009457604193487673, ub[1], fma(0.03861111111111111, ub[0], db[2])))))))));
-  db[3] = fma(0.10027105559846916, ub[8], fma(-0.10920138888888889, ub[7], fma(0.07445116662375305, ub[6], fma(0.07622368050191354, ub[5], fma(-0.1154513888888889, ub[4], fma(0.10849854172030868, ub[3], fma(0.10027105559846916, ub[2], fma(-0.10920138888888889, ub[1], fma(0.07445116662375305, ub[0], db[3])))))))));
-  db[4] = fma(0.6461111111111111, ub[8], fma(1.039236111111111, ub[7], fma(0.6461111111111111, ub[6], fma(1.039236111111111, ub[5], fma(1.4548611111111112, ub[4], fma(1.039236111111111, ub[3], fma(0.6461111111111111, ub[2], fma(1.039236111111111, ub[1], fma(0.6461111111111111, ub[0], db[4])))))))));
-  db[5] = fma(0.07445116662375305, ub[8], fma(-0.10920138888888889, ub[7], fma(0.10027105559846916, ub[6], fma(0.10849854172030868, ub[5], fma(-0.1154513888888889, ub[4], fma(0.07622368050191354, ub[3], fma(0.07445116662375305, ub[2], fma(-0.10920138888888889, ub[1], fma(0.10027105559846916, ub[0], db[5])))))))));
-  db[6] = fma(0.03861111111111111, ub[8], fma(-0.009457604193487673, ub[7], fma(-0.02347894440153083, ub[6], fma(0.006679826415709896, ub[5], fma(0.001736111111111111, ub[4], fma(-0.009457604193487673, ub[3], fma(-0.049298833376246944, ub[2], fma(0.006679826415709896, ub[1], fma(0.03861111111111111, ub[0], db[6])))))))));
-  db[7] = fma(0.07445116662375305, ub[8], fma(0.10849854172030868, ub[7], fma(0.07445116662375305, ub[6], fma(-0.10920138888888889, ub[5], fma(-0.1154513888888889, ub[4], fma(-0.10920138888888889, ub[3], fma(0.10027105559846916, ub[2], fma(0.07622368050191354, ub[1], fma(0.10027105559846916, ub[0], db[7])))))))));
-  db[8] = fma(-0.02347894440153083, ub[8], fma(-0.009457604193487673, ub[7], fma(0.03861111111111111, ub[6], fma(-0.009457604193487673, ub[5], fma(0.001736111111111111, ub[4], fma(0.006679826415709896, ub[3], fma(0.03861111111111111, ub[2], fma(0.006679826415709896, ub[1], fma(-0.049298833376246944, ub[0], db[8])))))))));
-  db[9] = fma(-0.9, ub[8], fma(0.9, ub[6], fma(0.9, ub[2], fma(-0.9, ub[0], db[9]))));
-  db[10] = fma(0.3375, ub[8], fma(-0.421875, ub[7], fma(0.3375, ub[6], fma(0.3375, ub[5], fma(-0.421875, ub[4], fma(0.3375, ub[3], fma(0.3375, ub[2], fma(-0.421875, ub[1], fma(0.3375, ub[0], db[10])))))))));
-  db[11] = fma(4.6475800154489, ub[8], fma(-4.6475800154489, ub[6], fma(4.6475800154489, ub[5], fma(-4.6475800154489, ub[3], fma(4.6475800154489, ub[2], fma(-4.6475800154489, ub[0], db[11]))))));
-  db[12] = fma(-0.3375, ub[8], fma(0.421875, ub[7], fma(-0.3375, ub[6], fma(-0.3375, ub[5], fma(0.421875, ub[4], fma(-0.3375, ub[3], fma(-0.3375, ub[2], fma(0.421875, ub[1], fma(-0.3375, ub[0], db[12])))))))));
-  db[13] = fma(0.9, ub[8], fma(-0.9, ub[6], fma(-0.9, ub[2], fma(0.9, ub[0], db[13]))));
-  db[14] = fma(0.3375, ub[8], fma(0.3375, ub[7], fma(0.3375, ub[6], fma(-0.421875, ub[5], fma(-0.421875, ub[4], fma(-0.421875, ub[3], fma(0.3375, ub[2], fma(0.3375, ub[1], fma(0.3375, ub[0], db[14])))))))));
-  db[15] = fma(-0.9, ub[8], fma(0.9, ub[6], fma(0.9, ub[2], fma(-0.9, ub[0], db[15]))));
-  db[16] = fma(4.6475800154489, ub[8], fma(4.6475800154489, ub[7], fma(4.6475800154489, ub[6], fma(-4.6475800154489, ub[2], fma(-4.6475800154489, ub[1], fma(-4.6475800154489, ub[0], db[16]))))));
-  db[17] = fma(0.9, ub[8], fma(-0.9, ub[6], fma(-0.9, ub[2], fma(0.9, ub[0], db[17]))));
-  db[18] = fma(-0.3375, ub[8], fma(-0.3375, ub[7], fma(-0.3375, ub[6], fma(0.421875, ub[5], fma(0.421875, ub[4], fma(0.421875, ub[3], fma(-0.3375, ub[2], fma(-0.3375, ub[1], fma(-0.3375, ub[0], db[18])))))))));
+// db[19] += the transpose of lin2d_fold applied to fb
+__device__ __forceinline__ void lin2d_fold_T(const double* fb, double* db) {
+  const double s0 = fb[3] + fb[12], s1 = fb[3] - fb[12];
+  const double d0 = fb[7] + fb[10], d1 = fb[7] - fb[10];
+  db[0] += s0 - d0;
+  db[8] += s0 + d0;
+  db[2] += s1 + d1;
+  db[6] += s1 - d1;
+  db[1] += fb[2] - fb[9];
+  db[3] += fb[1] - fb[6];
+  db[4] += fb[0];
+  db[5] += fb[1] + fb[6];
+  db[7] += fb[2] + fb[9];
+  db[9] += -fb[13];
+  db[10] += -fb[4];
+  db[11] += fb[8];
+  db[12] += fb[4];
+  db[13] += fb[13];
+  db[14] += -fb[5];
+  db[15] += -fb[14];
+  db[16] += fb[11];
+  db[17] += fb[14];
+  db[18] += fb[5];
 }
 
-__device__ __forceinline__ void lin2d_xedges_ng2_T(const double* ub, double* db) {
-  db[0] = fma(-0.04701905601354907, ub[3], fma(0.04701905601354907, ub[2], fma(0.02296279479731466, ub[1], fma(-0.02296279479731466, ub[0], db[0]))));
-  db[1] = fma(0.0362762147898146, ub[3], fma(-0.02933177034537015, ub[2], fma(0.0362762147898146, ub[1], fma(-0.02933177034537015, ub[0], db[1]))));
-  db[2] = fma(0.02296279479731466, ub[3], fma(-0.02296279479731466, ub[2], fma(-0.04701905601354907, ub[1], fma(0.04701905601354907, ub[0], db[2]))));
-  db[3] = fma(0.1856060606060606, ub[3], fma(0.1856060606060606, ub[2], fma(0.23106060606060605, ub[1], fma(0.23106060606060605, ub[0], db[3]))));
-  db[4] = fma(0.5763888888888888, ub[3], fma(0.5763888888888888, ub[2], fma(0.5763888888888888, ub[1], fma(0.5763888888888888, ub[0], db[4]))));
-  db[5] = fma(0.23106060606060605, ub[3], fma(0.23106060606060605, ub[2], fma(0.1856060606060606, ub[1], fma(0.1856060606060606, ub[0], db[5]))));
-  db[6] = fma(0.04701905601354907, ub[3], fma(-0.04701905601354907, ub[2], fma(-0.02296279479731466, ub[1], fma(0.02296279479731466, ub[0], db[6]))));
-  db[7] = fma(-0.02933177034537015, ub[3], fma(0.0362762147898146, ub[2], fma(-0.02933177034537015, ub[1], fma(0.0362762147898146, ub[0], db[7]))));
-  db[8] = fma(-0.02296279479731466, ub[3], fma(0.02296279479731466, ub[2], fma(0.04701905601354907, ub[1], fma(-0.04701905601354907, ub[0], db[8]))));
-  db[9] = fma(-0.787295821622217, ub[3], fma(0.787295821622217, ub[2], fma(0.787295821622217, ub[1], fma(-0.787295821622217, ub[0], db[9]))));
-  db[10] = fma(0.75, ub[3], fma(0.75, ub[2], fma(0.75, ub[1], fma(0.75, ub[0], db[10]))));
-  db[11] = fma(5.454545454545454, ub[3], fma(5.454545454545454, ub[2], fma(-5.454545454545454, ub[1], fma(-5.454545454545454, ub[0], db[11]))));
-  db[12] = fma(-0.75, ub[3], fma(-0.75, ub[2], fma(-0.75, ub[1], fma(-0.75, ub[0], db[12]))));
-  db[13] = fma(0.787295821622217, ub[3], fma(-0.787295821622217, ub[2], fma(-0.787295821622217, ub[1], fma(0.787295821622217, ub[0], db[13]))));
-  db[14] = fma(0.020833333333333332, ub[3], fma(0.020833333333333332, ub[2], fma(0.020833333333333332, ub[1], fma(0.020833333333333332, ub[0], db[14]))));
-  db[15] = fma(-0.9185117918925865, ub[3], fma(0.9185117918925865, ub[2], fma(0.9185117918925865, ub[1], fma(-0.9185117918925865, ub[0], db[15]))));
-  db[16] = fma(3.674047167570346, ub[3], fma(-3.674047167570346, ub[2], fma(3.674047167570346, ub[1], fma(-3.674047167570346, ub[0], db[16]))));
-  db[17] = fma(0.9185117918925865, ub[3], fma(-0.9185117918925865, ub[2], fma(-0.9185117918925865, ub[1], fma(0.9185117918925865, ub[0], db[17]))));
-  db[18] = fma(-0.020833333333333332, ub[3], fma(-0.020833333333333332, ub[2], fma(-0.020833333333333332, ub[1], fma(-0.020833333333333332, ub[0], db[18]))));
+// fb += the transpose of lin2d_inner applied to ub[9]
+__device__ __forceinline__ void lin2d_inner_T(const double* ub, double* fb) {
+  const double pb = ub[0] + ub[8], qb = ub[8] - ub[0], mb = ub[2] + ub[6], rb = ub[2] - ub[6];
+  const double ee0 = pb + mb, oo0 = pb - mb, oe0 = qb + rb, eo0 = qb - rb;
+  const double ee1 = ub[1] + ub[7], eo1 = ub[7] - ub[1], ee2 = ub[3] + ub[5], oe2 = ub[5] - ub[3];
+  fb[0] = fma(1.4548611111111112, ub[4], fma(1.039236111111111, ee2, fma(1.039236111111111, ee1, fma(0.6461111111111111, ee0, fb[0]))));
+  fb[1] = fma(-0.1154513888888889, ub[4], fma(0.09236111111111112, ee2, fma(-0.10920138888888889, ee1, fma(0.08736111111111111, ee0, fb[1]))));
+  fb[2] = fma(-0.1154513888888889, ub[4], fma(-0.10920138888888889, ee2, fma(0.09236111111111112, ee1, fma(0.08736111111111111, ee0, fb[2]))));
+  fb[3] = fma(0.001736111111111111, ub[4], fma(-0.001388888888888889, ee2, fma(-0.001388888888888889, ee1, fma(0.0011111111111111111, ee0, fb[3]))));
+  fb[4] = fma(0.421875, ub[4], fma(-0.3375, ee2, fma(0.421875, ee1, fma(-0.3375, ee0, fb[4]))));
+  fb[5] = fma(0.421875, ub[4], fma(0.421875, ee2, fma(-0.3375, ee1, fma(-0.3375, ee0, fb[5]))));
+  fb[6] = fma(0.016137430609197572, oe2, fma(-0.012909944487358056, oe0, fb[6]));
+  fb[7] = fma(-0.008068715304598786, oe2, fma(0.006454972243679028, oe0, fb[7]));
+  fb[8] = fma(4.6475800154489, oe2, fma(4.6475800154489, oe0, fb[8]));
+  fb[9] = fma(0.016137430609197572, eo1, fma(-0.012909944487358056, eo0, fb[9]));
+  fb[10] = fma(-0.008068715304598786, eo1, fma(0.006454972243679028, eo0, fb[10]));
+  fb[11] = fma(4.6475800154489, eo1, fma(4.6475800154489, eo0, fb[11]));
+  fb[12] = fma(-0.0375, oo0, fb[12]);
+  fb[13] = fma(0.9, oo0, fb[13]);
+  fb[14] = fma(0.9, oo0, fb[14]);
 }
 
-__device__ __forceinline__ void lin2d_yedges_ng2_T(const double* ub, double* db) {
-  db[0] = fma(-0.04701905601354907, ub[3], fma(0.04701905601354907, ub[2], fma(0.02296279479731466, ub[1], fma(-0.02296279479731466, ub[0], db[0]))));
-  db[1] = fma(0.1856060606060606, ub[3], fma(0.1856060606060606, ub[2], fma(0.23106060606060605, ub[1], fma(0.23106060606060605, ub[0], db[1]))));
-  db[2] = fma(0.04701905601354907, ub[3], fma(-0.04701905601354907, ub[2], fma(-0.02296279479731466, ub[1], fma(0.02296279479731466, ub[0], db[2]))));
-  db[3] = fma(0.0362762147898146, ub[3], fma(-0.02933177034537015, ub[2], fma(0.0362762147898146, ub[1], fma(-0.02933177034537015, ub[0], db[3]))));
-  db[4] = fma(0.5763888888888888, ub[3], fma(0.5763888888888888, ub[2], fma(0.5763888888888888, ub[1], fma(0.5763888888888888, ub[0], db[4]))));
-  db[5] = fma(-0.02933177034537015, ub[3], fma(0.0362762147898146, ub[2], fma(-0.02933177034537015, ub[1], fma(0.0362762147898146, ub[0], db[5]))));
-  db[6] = fma(0.02296279479731466, ub[3], fma(-0.02296279479731466, ub[2], fma(-0.04701905601354907, ub[1], fma(0.04701905601354907, ub[0], db[6]))));
-  db[7] = fma(0.23106060606060605, ub[3], fma(0.23106060606060605, ub[2], fma(0.1856060606060606, ub[1], fma(0.1856060606060606, ub[0], db[7]))));
-  db[8] = fma(-0.02296279479731466, ub[3], fma(0.02296279479731466, ub[2], fma(0.04701905601354907, ub[1], fma(-0.04701905601354907, ub[0], db[8]))));
-  db[9] = fma(-0.9185117918925865, ub[3], fma(0.9185117918925865, ub[2], fma(0.9185117918925865, ub[1], fma(-0.9185117918925865, ub[0], db[9]))));
-  db[10] = fma(0.020833333333333332, ub[3], fma(0.020833333333333332, ub[2], fma(0.020833333333333332, ub[1], fma(0.020833333333333332, ub[0], db[10]))));
-  db[11] = fma(3.674047167570346, ub[3], fma(-3.674047167570346, ub[2], fma(3.674047167570346, ub[1], fma(-3.674047167570346, ub[0], db[11]))));
-  db[12] = fma(-0.020833333333333332, ub[3], fma(-0.020833333333333332, ub[2], fma(-0.020833333333333332, ub[1], fma(-0.020833333333333332, ub[0], db[12]))));
-  db[13] = fma(0.9185117918925865, ub[3], fma(-0.9185117918925865, ub[2], fma(-0.9185117918925865, ub[1], fma(0.9185117918925865, ub[0], db[13]))));
-  db[14] = fma(0.75, ub[3], fma(0.75, ub[2], fma(0.75, ub[1], fma(0.75, ub[0], db[14]))));
-  db[15] = fma(-0.787295821622217, ub[3], fma(0.787295821622217, ub[2], fma(0.787295821622217, ub[1], fma(-0.787295821622217, ub[0], db[15]))));
-  db[16] = fma(5.454545454545454, ub[3], fma(5.454545454545454, ub[2], fma(-5.454545454545454, ub[1], fma(-5.454545454545454, ub[0], db[16]))));
-  db[17] = fma(0.787295821622217, ub[3], fma(-0.787295821622217, ub[2], fma(-0.787295821622217, ub[1], fma(0.787295821622217, ub[0], db[17]))));
-  db[18] = fma(-0.75, ub[3], fma(-0.75, ub[2], fma(-0.75, ub[1], fma(-0.75, ub[0], db[18]))));
+// fb += the transpose of the x faces' values (low face lo, high face hi)
+__device__ __forceinline__ void lin2d_xfaces_ng2_T(const double* lo, const double* hi, double* fb) {
+  const double a = lo[0] + hi[1], b = hi[1] - lo[0], c = lo[1] + hi[0], d = hi[0] - lo[1];
+  const double p0 = a + c, p1 = b + d, p2 = b - d, p3 = a - c;
+  fb[0] = fma(0.5763888888888888, p0, fb[0]);
+  fb[1] = fma(0.20833333333333334, p0, fb[1]);
+  fb[2] = fma(0.003472222222222222, p0, fb[2]);
+  fb[4] = fma(-0.75, p0, fb[4]);
+  fb[5] = fma(-0.020833333333333332, p0, fb[5]);
+  fb[6] = fma(0.022727272727272728, p1, fb[6]);
+  fb[8] = fma(5.454545454545454, p1, fb[8]);
+  fb[9] = fma(-0.03280399256759237, p2, fb[9]);
+  fb[10] = fma(0.012028130608117204, p2, fb[10]);
+  fb[11] = fma(3.674047167570346, p2, fb[11]);
+  fb[12] = fma(-0.03499092540543187, p3, fb[12]);
+  fb[13] = fma(0.787295821622217, p3, fb[13]);
+  fb[14] = fma(0.9185117918925865, p3, fb[14]);
 }
 
-__device__ __forceinline__ void lin2d_xedges_ng3_T(const double* ub, double* db) {
-  db[0] = fma(-0.06570416055347378, ub[5], fma(0.006944444444444444, ub[4], fma(0.05459304944236266, ub[3], fma(0.038984854890634184, ub[2], fma(-0.013888888888888888, ub[1], fma(-0.016762632668411964, ub[0], db[0]))))));
-  db[1] = fma(0.11630263899617292, ub[5], fma(-0.10503472222222222, ub[4], fma(0.05175291655938264, ub[3], fma(0.11630263899617292, ub[2], fma(-0.10503472222222222, ub[1], fma(0.05175291655938264, ub[0], db[1]))))));
-  db[2] = fma(0.038984854890634184, ub[5], fma(-0.013888888888888888, ub[4], fma(-0.016762632668411964, ub[3], fma(-0.06570416055347378, ub[2], fma(0.006944444444444444, ub[1], fma(0.05459304944236266, ub[0], db[2]))))));
-  db[3] = fma(0.1967171717171717, ub[5], fma(0.1717171717171717, ub[4], fma(0.1967171717171717, ub[3], fma(0.20883838383838385, ub[2], fma(0.2588383838383838, ub[1], fma(0.20883838383838385, ub[0], db[3]))))));
-  db[4] = fma(0.4152777777777778, ub[5], fma(0.7934027777777778, ub[4], fma(0.4152777777777778, ub[3], fma(0.4152777777777778, ub[2], fma(0.7934027777777778, ub[1], fma(0.4152777777777778, ub[0], db[4]))))));
-  db[5] = fma(0.20883838383838385, ub[5], fma(0.2588383838383838, ub[4], fma(0.20883838383838385, ub[3], fma(0.1967171717171717, ub[2], fma(0.1717171717171717, ub[1], fma(0.1967171717171717, ub[0], db[5]))))));
-  db[6] = fma(0.05459304944236266, ub[5], fma(0.006944444444444444, ub[4], fma(-0.06570416055347378, ub[3], fma(-0.016762632668411964, ub[2], fma(-0.013888888888888888, ub[1], fma(0.038984854890634184, ub[0], db[6]))))));
-  db[7] = fma(0.05175291655938264, ub[5], fma(-0.10503472222222222, ub[4], fma(0.11630263899617292, ub[3], fma(0.05175291655938264, ub[2], fma(-0.10503472222222222, ub[1], fma(0.11630263899617292, ub[0], db[7]))))));
-  db[8] = fma(-0.016762632668411964, ub[5], fma(-0.013888888888888888, ub[4], fma(0.038984854890634184, ub[3], fma(0.05459304944236266, ub[2], fma(0.006944444444444444, ub[1], fma(-0.06570416055347378, ub[0], db[8]))))));
-  db[9] = fma(-1.0562681853292955, ub[5], fma(1.0562681853292955, ub[3], fma(1.0562681853292955, ub[2], fma(-1.0562681853292955, ub[0], db[9]))));
-  db[10] = fma(0.75, ub[5], fma(0.75, ub[4], fma(0.75, ub[3], fma(0.75, ub[2], fma(0.75, ub[1], fma(0.75, ub[0], db[10]))))));
-  db[11] = fma(5.454545454545454, ub[5], fma(5.454545454545454, ub[4], fma(5.454545454545454, ub[3], fma(-5.454545454545454, ub[2], fma(-5.454545454545454, ub[1], fma(-5.454545454545454, ub[0], db[11]))))));
-  db[12] = fma(-0.75, ub[5], fma(-0.75, ub[4], fma(-0.75, ub[3], fma(-0.75, ub[2], fma(-0.75, ub[1], fma(-0.75, ub[0], db[12]))))));
-  db[13] = fma(1.0562681853292955, ub[5], fma(-1.0562681853292955, ub[3], fma(-1.0562681853292955, ub[2], fma(1.0562681853292955, ub[0], db[13]))));
-  db[14] = fma(0.3375, ub[5], fma(-0.421875, ub[4], fma(0.3375, ub[3], fma(0.3375, ub[2], fma(-0.421875, ub[1], fma(0.3375, ub[0], db[14]))))));
-  db[15] = fma(-1.161895003862225, ub[5], fma(1.161895003862225, ub[3], fma(1.161895003862225, ub[2], fma(-1.161895003862225, ub[0], db[15]))));
-  db[16] = fma(4.6475800154489, ub[5], fma(-4.6475800154489, ub[3], fma(4.6475800154489, ub[2], fma(-4.6475800154489, ub[0], db[16]))));
-  db[17] = fma(1.161895003862225, ub[5], fma(-1.161895003862225, ub[3], fma(-1.161895003862225, ub[2], fma(1.161895003862225, ub[0], db[17]))));
-  db[18] = fma(-0.3375, ub[5], fma(0.421875, ub[4], fma(-0.3375, ub[3], fma(-0.3375, ub[2], fma(0.421875, ub[1], fma(-0.3375, ub[0], db[18]))))));
+// fb += the transpose of the x faces' values (low face lo, high face hi)
+__device__ __forceinline__ void lin2d_xfaces_ng3_T(const double* lo, const double* hi, double* fb) {
+  const double a = lo[0] + hi[2], b = hi[2] - lo[0], c = lo[2] + hi[0], d = hi[0] - lo[2];
+  const double p0 = a + c, p1 = b + d, p2 = b - d, p3 = a - c;
+  const double p4 = lo[1] + hi[1], p5 = hi[1] - lo[1];
+  fb[0] = fma(0.7934027777777778, p4, fma(0.4152777777777778, p0, fb[0]));
+  fb[1] = fma(0.2152777777777778, p4, fma(0.20277777777777778, p0, fb[1]));
+  fb[2] = fma(-0.10503472222222222, p4, fma(0.08402777777777778, p0, fb[2]));
+  fb[3] = fma(-0.003472222222222222, p4, fma(0.002777777777777778, p0, fb[3]));
+  fb[4] = fma(-0.75, p4, fma(-0.75, p0, fb[4]));
+  fb[5] = fma(0.421875, p4, fma(-0.3375, p0, fb[5]));
+  fb[6] = fma(0.043560606060606064, p5, fma(0.006060606060606061, p1, fb[6]));
+  fb[7] = fma(-0.010416666666666666, p5, fma(0.008333333333333333, p1, fb[7]));
+  fb[8] = fma(5.454545454545454, p5, fma(5.454545454545454, p1, fb[8]));
+  fb[9] = fma(-0.032274861218395144, p2, fb[9]);
+  fb[10] = fma(0.016137430609197572, p2, fb[10]);
+  fb[11] = fma(4.6475800154489, p2, fb[11]);
+  fb[12] = fma(-0.044011174388720646, p3, fb[12]);
+  fb[13] = fma(1.0562681853292955, p3, fb[13]);
+  fb[14] = fma(1.161895003862225, p3, fb[14]);
 }
 
-__device__ __forceinline__ void lin2d_yedges_ng3_T(const double* ub, double* db) {
-  db[0] = fma(-0.06570416055347378, ub[5], fma(0.006944444444444444, ub[4], fma(0.05459304944236266, ub[3], fma(0.038984854890634184, ub[2], fma(-0.013888888888888888, ub[1], fma(-0.016762632668411964, ub[0], db[0]))))));
-  db[1] = fma(0.1967171717171717, ub[5], fma(0.1717171717171717, ub[4], fma(0.1967171717171717, ub[3], fma(0.20883838383838385, ub[2], fma(0.2588383838383838, ub[1], fma(0.20883838383838385, ub[0], db[1]))))));
-  db[2] = fma(0.05459304944236266, ub[5], fma(0.006944444444444444, ub[4], fma(-0.06570416055347378, ub[3], fma(-0.016762632668411964, ub[2], fma(-0.013888888888888888, ub[1], fma(0.038984854890634184, ub[0], db[2]))))));
-  db[3] = fma(0.11630263899617292, ub[5], fma(-0.10503472222222222, ub[4], fma(0.05175291655938264, ub[3], fma(0.11630263899617292, ub[2], fma(-0.10503472222222222, ub[1], fma(0.05175291655938264, ub[0], db[3]))))));
-  db[4] = fma(0.4152777777777778, ub[5], fma(0.7934027777777778, ub[4], fma(0.4152777777777778, ub[3], fma(0.4152777777777778, ub[2], fma(0.7934027777777778, ub[1], fma(0.4152777777777778, ub[0], db[4]))))));
-  db[5] = fma(0.05175291655938264, ub[5], fma(-0.10503472222222222, ub[4], fma(0.11630263899617292, ub[3], fma(0.05175291655938264, ub[2], fma(-0.10503472222222222, ub[1], fma(0.11630263899617292, ub[0], db[5]))))));
-  db[6] = fma(0.038984854890634184, ub[5], fma(-0.013888888888888888, ub[4], fma(-0.016762632668411964, ub[3], fma(-0.06570416055347378, ub[2], fma(0.006944444444444444, ub[1], fma(0.05459304944236266, ub[0], db[6]))))));
-  db[7] = fma(0.20883838383838385, ub[5], fma(0.2588383838383838, ub[4], fma(0.20883838383838385, ub[3], fma(0.1967171717171717, ub[2], fma(0.1717171717171717, ub[1], fma(0.1967171717171717, ub[0], db[7]))))));
-  db[8] = fma(-0.016762632668411964, ub[5], fma(-0.013888888888888888, ub[4], fma(0.038984854890634184, ub[3], fma(0.05459304944236266, ub[2], fma(0.006944444444444444, ub[1], fma(-0.06570416055347378, ub[0], db[8]))))));
-  db[9] = fma(-1.161895003862225, ub[5], fma(1.161895003862225, ub[3], fma(1.161895003862225, ub[2], fma(-1.161895003862225, ub[0], db[9]))));
-  db[10] = fma(0.3375, ub[5], fma(-0.421875, ub[4], fma(0.3375, ub[3], fma(0.3375, ub[2], fma(-0.421875, ub[1], fma(0.3375, ub[0], db[10]))))));
-  db[11] = fma(4.6475800154489, ub[5], fma(-4.6475800154489, ub[3], fma(4.6475800154489, ub[2], fma(-4.6475800154489, ub[0], db[11]))));
-  db[12] = fma(-0.3375, ub[5], fma(0.421875, ub[4], fma(-0.3375, ub[3], fma(-0.3375, ub[2], fma(0.421875, ub[1], fma(-0.3375, ub[0], db[12]))))));
-  db[13] = fma(1.161895003862225, ub[5], fma(-1.161895003862225, ub[3], fma(-1.161895003862225, ub[2], fma(1.161895003862225, ub[0], db[13]))));
-  db[14] = fma(0.75, ub[5], fma(0.75, ub[4], fma(0.75, ub[3], fma(0.75, ub[2], fma(0.75, ub[1], fma(0.75, ub[0], db[14]))))));
-  db[15] = fma(-1.0562681853292955, ub[5], fma(1.0562681853292955, ub[3], fma(1.0562681853292955, ub[2], fma(-1.0562681853292955, ub[0], db[15]))));
-  db[16] = fma(5.454545454545454, ub[5], fma(5.454545454545454, ub[4], fma(5.454545454545454, ub[3], fma(-5.454545454545454, ub[2], fma(-5.454545454545454, ub[1], fma(-5.454545454545454, ub[0], db[16]))))));
-  db[17] = fma(1.0562681853292955, ub[5], fma(-1.0562681853292955, ub[3], fma(-1.0562681853292955, ub[2], fma(1.0562681853292955, ub[0], db[17]))));
-  db[18] = fma(-0.75, ub[5], fma(-0.75, ub[4], fma(-0.75, ub[3], fma(-0.75, ub[2], fma(-0.75, ub[1], fma(-0.75, ub[0], db[18]))))));
-}
-
-__device__ __forceinline__ void p0_coeffs_T(const double* cb, double* db) {
-  db[0] = fma(0.22727272727272727, cb[13], fma(0.25, cb[12], fma(0.22727272727272727, cb[11], fma(-0.25, cb[8], fma(-0.25, cb[7], fma(-0.020833333333333332, cb[5], fma(-0.3181818181818182, cb[4], fma(-0.020833333333333332, cb[3], fma(0.020833333333333332, cb[2], fma(0.020833333333333332, cb[1], fma(0.001736111111111111, cb[0], db[0])))))))))));
-  db[1] = fma(-0.625, cb[14], fma(-0.5, cb[12], fma(-0.45454545454545453, cb[9], fma(0.5, cb[7], fma(1.4791666666666667, cb[5], fma(0.041666666666666664, cb[3], fma(0.026515151515151516, cb[2], fma(-0.1154513888888889, cb[0], db[1]))))))));
-  db[2] = fma(-0.22727272727272727, cb[13], fma(0.25, cb[12], fma(-0.22727272727272727, cb[11], fma(0.25, cb[8], fma(-0.25, cb[7], fma(-0.020833333333333332, cb[5], fma(0.3181818181818182, cb[4], fma(-0.020833333333333332, cb[3], fma(0.020833333333333332, cb[2], fma(-0.020833333333333332, cb[1], fma(0.001736111111111111, cb[0], db[2])))))))))));
-  db[3] = fma(-0.5, cb[12], fma(-0.625, cb[10], fma(0.5, cb[8], fma(-0.45454545454545453, cb[6], fma(0.041666666666666664, cb[5], fma(1.4791666666666667, cb[3], fma(0.026515151515151516, cb[1], fma(-0.1154513888888889, cb[0], db[3]))))))));
-  db[4] = fma(1.25, cb[14], fma(1.0, cb[12], fma(1.25, cb[10], fma(-2.9583333333333335, cb[5], fma(-2.9583333333333335, cb[3], fma(1.4548611111111112, cb[0], db[4]))))));
-  db[5] = fma(-0.5, cb[12], fma(-0.625, cb[10], fma(-0.5, cb[8], fma(0.45454545454545453, cb[6], fma(0.041666666666666664, cb[5], fma(1.4791666666666667, cb[3], fma(-0.026515151515151516, cb[1], fma(-0.1154513888888889, cb[0], db[5]))))))));
-  db[6] = fma(-0.22727272727272727, cb[13], fma(0.25, cb[12], fma(-0.22727272727272727, cb[11], fma(-0.25, cb[8], fma(0.25, cb[7], fma(-0.020833333333333332, cb[5], fma(0.3181818181818182, cb[4], fma(-0.020833333333333332, cb[3], fma(-0.020833333333333332, cb[2], fma(0.020833333333333332, cb[1], fma(0.001736111111111111, cb[0], db[6])))))))))));
-  db[7] = fma(-0.625, cb[14], fma(-0.5, cb[12], fma(0.45454545454545453, cb[9], fma(-0.5, cb[7], fma(1.4791666666666667, cb[5], fma(0.041666666666666664, cb[3], fma(-0.026515151515151516, cb[2], fma(-0.1154513888888889, cb[0], db[7]))))))));
-  db[8] = fma(0.22727272727272727, cb[13], fma(0.25, cb[12], fma(0.22727272727272727, cb[11], fma(0.25, cb[8], fma(0.25, cb[7], fma(-0.020833333333333332, cb[5], fma(-0.3181818181818182, cb[4], fma(-0.020833333333333332, cb[3], fma(-0.020833333333333332, cb[2], fma(-0.020833333333333332, cb[1], fma(0.001736111111111111, cb[0], db[8])))))))))));
-  db[9] = fma(5.454545454545454, cb[11], fma(-6.818181818181818, cb[4], db[9]));
-  db[10] = fma(-3.75, cb[10], fma(5.625, cb[3], fma(-0.421875, cb[0], db[10])));
-  db[11] = fma(-10.909090909090908, cb[6], fma(13.636363636363637, cb[1], db[11]));
-  db[12] = fma(3.75, cb[10], fma(-5.625, cb[3], fma(0.421875, cb[0], db[12])));
-  db[13] = fma(-5.454545454545454, cb[11], fma(6.818181818181818, cb[4], db[13]));
-  db[14] = fma(-3.75, cb[14], fma(5.625, cb[5], fma(-0.421875, cb[0], db[14])));
-  db[15] = fma(5.454545454545454, cb[13], fma(-6.818181818181818, cb[4], db[15]));
-  db[16] = fma(-10.909090909090908, cb[9], fma(13.636363636363637, cb[2], db[16]));
-  db[17] = fma(-5.454545454545454, cb[13], fma(6.818181818181818, cb[4], db[17]));
-  db[18] = fma(3.75, cb[14], fma(-5.625, cb[5], fma(0.421875, cb[0], db[18])));
+// fb += the transpose of p0_coeffs applied to cb[15]
+__device__ __forceinline__ void p0_coeffs_T(const double* cb, double* fb) {
+  fb[0] = fma(1.25, cb[14], fma(1.0, cb[12], fma(1.25, cb[10], fma(-2.9583333333333335, cb[5], fma(-2.9583333333333335, cb[3], fma(1.4548611111111112, cb[0], fb[0]))))));
+  fb[1] = fma(-0.5, cb[12], fma(-0.625, cb[10], fma(0.041666666666666664, cb[5], fma(1.4791666666666667, cb[3], fma(-0.1154513888888889, cb[0], fb[1])))));
+  fb[2] = fma(-0.625, cb[14], fma(-0.5, cb[12], fma(1.4791666666666667, cb[5], fma(0.041666666666666664, cb[3], fma(-0.1154513888888889, cb[0], fb[2])))));
+  fb[3] = fma(0.25, cb[12], fma(-0.020833333333333332, cb[5], fma(-0.020833333333333332, cb[3], fma(0.001736111111111111, cb[0], fb[3]))));
+  fb[4] = fma(3.75, cb[10], fma(-5.625, cb[3], fma(0.421875, cb[0], fb[4])));
+  fb[5] = fma(3.75, cb[14], fma(-5.625, cb[5], fma(0.421875, cb[0], fb[5])));
+  fb[6] = fma(-0.5, cb[8], fma(0.45454545454545453, cb[6], fma(-0.026515151515151516, cb[1], fb[6])));
+  fb[7] = fma(0.25, cb[8], fma(-0.020833333333333332, cb[1], fb[7]));
+  fb[8] = fma(-10.909090909090908, cb[6], fma(13.636363636363637, cb[1], fb[8]));
+  fb[9] = fma(0.45454545454545453, cb[9], fma(-0.5, cb[7], fma(-0.026515151515151516, cb[2], fb[9])));
+  fb[10] = fma(0.25, cb[7], fma(-0.020833333333333332, cb[2], fb[10]));
+  fb[11] = fma(-10.909090909090908, cb[9], fma(13.636363636363637, cb[2], fb[11]));
+  fb[12] = fma(0.22727272727272727, cb[13], fma(0.22727272727272727, cb[11], fma(-0.3181818181818182, cb[4], fb[12])));
+  fb[13] = fma(-5.454545454545454, cb[11], fma(6.818181818181818, cb[4], fb[13]));
+  fb[14] = fma(-5.454545454545454, cb[13], fma(6.818181818181818, cb[4], fb[14]));
 }
 __device__ __forceinline__ void p1_coeffs_T(const double* cb, double* db) {
   db[0] = fma(1.0, cb[4], db[0]);
@@ -432,19 +379,7 @@ __device__ __forceinline__ void beta_pq_grad(const double* c, double* g) {
   g[4] = 2.3333333333333335 * c[4];
   g[5] = 8.666666666666666 * c[5];
 }
-// transposes of edge_quartic / edge_quad: cb[s] += mono_s(point i) * qb
-__device__ __forceinline__ void edge_quartic_ng2_T(double qb, int i, double* cb) {
-  switch (i) {
-  case 0: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.5, qb, cb[1]); cb[2] = fma(-0.28867513459481287, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(0.14433756729740643, qb, cb[4]); cb[5] = fma(0.08333333333333333, qb, cb[5]); cb[6] = fma(-0.125, qb, cb[6]); cb[7] = fma(-0.07216878364870322, qb, cb[7]); cb[8] = fma(-0.041666666666666664, qb, cb[8]); cb[9] = fma(-0.024056261216234408, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(0.03608439182435161, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(0.012028130608117204, qb, cb[13]); cb[14] = fma(0.006944444444444444, qb, cb[14]); break;
-  case 1: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.5, qb, cb[1]); cb[2] = fma(0.28867513459481287, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(-0.14433756729740643, qb, cb[4]); cb[5] = fma(0.08333333333333333, qb, cb[5]); cb[6] = fma(-0.125, qb, cb[6]); cb[7] = fma(0.07216878364870322, qb, cb[7]); cb[8] = fma(-0.041666666666666664, qb, cb[8]); cb[9] = fma(0.024056261216234408, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(-0.03608439182435161, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(-0.012028130608117204, qb, cb[13]); cb[14] = fma(0.006944444444444444, qb, cb[14]); break;
-  case 2: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.5, qb, cb[1]); cb[2] = fma(-0.28867513459481287, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(-0.14433756729740643, qb, cb[4]); cb[5] = fma(0.08333333333333333, qb, cb[5]); cb[6] = fma(0.125, qb, cb[6]); cb[7] = fma(-0.07216878364870322, qb, cb[7]); cb[8] = fma(0.041666666666666664, qb, cb[8]); cb[9] = fma(-0.024056261216234408, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(-0.03608439182435161, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(-0.012028130608117204, qb, cb[13]); cb[14] = fma(0.006944444444444444, qb, cb[14]); break;
-  case 3: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.5, qb, cb[1]); cb[2] = fma(0.28867513459481287, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(0.14433756729740643, qb, cb[4]); cb[5] = fma(0.08333333333333333, qb, cb[5]); cb[6] = fma(0.125, qb, cb[6]); cb[7] = fma(0.07216878364870322, qb, cb[7]); cb[8] = fma(0.041666666666666664, qb, cb[8]); cb[9] = fma(0.024056261216234408, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(0.03608439182435161, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(0.012028130608117204, qb, cb[13]); cb[14] = fma(0.006944444444444444, qb, cb[14]); break;
-  case 4: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.28867513459481287, qb, cb[1]); cb[2] = fma(-0.5, qb, cb[2]); cb[3] = fma(0.08333333333333333, qb, cb[3]); cb[4] = fma(0.14433756729740643, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(-0.024056261216234408, qb, cb[6]); cb[7] = fma(-0.041666666666666664, qb, cb[7]); cb[8] = fma(-0.07216878364870322, qb, cb[8]); cb[9] = fma(-0.125, qb, cb[9]); cb[10] = fma(0.006944444444444444, qb, cb[10]); cb[11] = fma(0.012028130608117204, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(0.03608439182435161, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 5: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.28867513459481287, qb, cb[1]); cb[2] = fma(-0.5, qb, cb[2]); cb[3] = fma(0.08333333333333333, qb, cb[3]); cb[4] = fma(-0.14433756729740643, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(0.024056261216234408, qb, cb[6]); cb[7] = fma(-0.041666666666666664, qb, cb[7]); cb[8] = fma(0.07216878364870322, qb, cb[8]); cb[9] = fma(-0.125, qb, cb[9]); cb[10] = fma(0.006944444444444444, qb, cb[10]); cb[11] = fma(-0.012028130608117204, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(-0.03608439182435161, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 6: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.28867513459481287, qb, cb[1]); cb[2] = fma(0.5, qb, cb[2]); cb[3] = fma(0.08333333333333333, qb, cb[3]); cb[4] = fma(-0.14433756729740643, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(-0.024056261216234408, qb, cb[6]); cb[7] = fma(0.041666666666666664, qb, cb[7]); cb[8] = fma(-0.07216878364870322, qb, cb[8]); cb[9] = fma(0.125, qb, cb[9]); cb[10] = fma(0.006944444444444444, qb, cb[10]); cb[11] = fma(-0.012028130608117204, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(-0.03608439182435161, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 7: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.28867513459481287, qb, cb[1]); cb[2] = fma(0.5, qb, cb[2]); cb[3] = fma(0.08333333333333333, qb, cb[3]); cb[4] = fma(0.14433756729740643, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(0.024056261216234408, qb, cb[6]); cb[7] = fma(0.041666666666666664, qb, cb[7]); cb[8] = fma(0.07216878364870322, qb, cb[8]); cb[9] = fma(0.125, qb, cb[9]); cb[10] = fma(0.006944444444444444, qb, cb[10]); cb[11] = fma(0.012028130608117204, qb, cb[11]); cb[12] = fma(0.020833333333333332, qb, cb[12]); cb[13] = fma(0.03608439182435161, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  }
-}
+// transpose of edge_quad: cb[s] += mono_s(point i) * qb
 __device__ __forceinline__ void edge_quad_ng2_T(double qb, int i, double* cb) {
   switch (i) {
   case 0: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.5, qb, cb[1]); cb[2] = fma(-0.28867513459481287, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(0.14433756729740643, qb, cb[4]); cb[5] = fma(0.08333333333333333, qb, cb[5]); break;
@@ -457,23 +392,7 @@ __device__ __forceinline__ void edge_quad_ng2_T(double qb, int i, double* cb) {
   case 7: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.28867513459481287, qb, cb[1]); cb[2] = fma(0.5, qb, cb[2]); cb[3] = fma(0.08333333333333333, qb, cb[3]); cb[4] = fma(0.14433756729740643, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); break;
   }
 }
-// transposes of edge_quartic / edge_quad: cb[s] += mono_s(point i) * qb
-__device__ __forceinline__ void edge_quartic_ng3_T(double qb, int i, double* cb) {
-  switch (i) {
-  case 0: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.5, qb, cb[1]); cb[2] = fma(-0.3872983346207417, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(0.19364916731037085, qb, cb[4]); cb[5] = fma(0.15, qb, cb[5]); cb[6] = fma(-0.125, qb, cb[6]); cb[7] = fma(-0.09682458365518543, qb, cb[7]); cb[8] = fma(-0.075, qb, cb[8]); cb[9] = fma(-0.05809475019311126, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(0.04841229182759271, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(0.02904737509655563, qb, cb[13]); cb[14] = fma(0.0225, qb, cb[14]); break;
-  case 1: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.5, qb, cb[1]); cb[3] = fma(0.25, qb, cb[3]); cb[6] = fma(-0.125, qb, cb[6]); cb[10] = fma(0.0625, qb, cb[10]); break;
-  case 2: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.5, qb, cb[1]); cb[2] = fma(0.3872983346207417, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(-0.19364916731037085, qb, cb[4]); cb[5] = fma(0.15, qb, cb[5]); cb[6] = fma(-0.125, qb, cb[6]); cb[7] = fma(0.09682458365518543, qb, cb[7]); cb[8] = fma(-0.075, qb, cb[8]); cb[9] = fma(0.05809475019311126, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(-0.04841229182759271, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(-0.02904737509655563, qb, cb[13]); cb[14] = fma(0.0225, qb, cb[14]); break;
-  case 3: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.5, qb, cb[1]); cb[2] = fma(-0.3872983346207417, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(-0.19364916731037085, qb, cb[4]); cb[5] = fma(0.15, qb, cb[5]); cb[6] = fma(0.125, qb, cb[6]); cb[7] = fma(-0.09682458365518543, qb, cb[7]); cb[8] = fma(0.075, qb, cb[8]); cb[9] = fma(-0.05809475019311126, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(-0.04841229182759271, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(-0.02904737509655563, qb, cb[13]); cb[14] = fma(0.0225, qb, cb[14]); break;
-  case 4: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.5, qb, cb[1]); cb[3] = fma(0.25, qb, cb[3]); cb[6] = fma(0.125, qb, cb[6]); cb[10] = fma(0.0625, qb, cb[10]); break;
-  case 5: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.5, qb, cb[1]); cb[2] = fma(0.3872983346207417, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(0.19364916731037085, qb, cb[4]); cb[5] = fma(0.15, qb, cb[5]); cb[6] = fma(0.125, qb, cb[6]); cb[7] = fma(0.09682458365518543, qb, cb[7]); cb[8] = fma(0.075, qb, cb[8]); cb[9] = fma(0.05809475019311126, qb, cb[9]); cb[10] = fma(0.0625, qb, cb[10]); cb[11] = fma(0.04841229182759271, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(0.02904737509655563, qb, cb[13]); cb[14] = fma(0.0225, qb, cb[14]); break;
-  case 6: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.3872983346207417, qb, cb[1]); cb[2] = fma(-0.5, qb, cb[2]); cb[3] = fma(0.15, qb, cb[3]); cb[4] = fma(0.19364916731037085, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(-0.05809475019311126, qb, cb[6]); cb[7] = fma(-0.075, qb, cb[7]); cb[8] = fma(-0.09682458365518543, qb, cb[8]); cb[9] = fma(-0.125, qb, cb[9]); cb[10] = fma(0.0225, qb, cb[10]); cb[11] = fma(0.02904737509655563, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(0.04841229182759271, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 7: cb[0] = fma(1.0, qb, cb[0]); cb[2] = fma(-0.5, qb, cb[2]); cb[5] = fma(0.25, qb, cb[5]); cb[9] = fma(-0.125, qb, cb[9]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 8: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.3872983346207417, qb, cb[1]); cb[2] = fma(-0.5, qb, cb[2]); cb[3] = fma(0.15, qb, cb[3]); cb[4] = fma(-0.19364916731037085, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(0.05809475019311126, qb, cb[6]); cb[7] = fma(-0.075, qb, cb[7]); cb[8] = fma(0.09682458365518543, qb, cb[8]); cb[9] = fma(-0.125, qb, cb[9]); cb[10] = fma(0.0225, qb, cb[10]); cb[11] = fma(-0.02904737509655563, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(-0.04841229182759271, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 9: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.3872983346207417, qb, cb[1]); cb[2] = fma(0.5, qb, cb[2]); cb[3] = fma(0.15, qb, cb[3]); cb[4] = fma(-0.19364916731037085, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(-0.05809475019311126, qb, cb[6]); cb[7] = fma(0.075, qb, cb[7]); cb[8] = fma(-0.09682458365518543, qb, cb[8]); cb[9] = fma(0.125, qb, cb[9]); cb[10] = fma(0.0225, qb, cb[10]); cb[11] = fma(-0.02904737509655563, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(-0.04841229182759271, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 10: cb[0] = fma(1.0, qb, cb[0]); cb[2] = fma(0.5, qb, cb[2]); cb[5] = fma(0.25, qb, cb[5]); cb[9] = fma(0.125, qb, cb[9]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  case 11: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(0.3872983346207417, qb, cb[1]); cb[2] = fma(0.5, qb, cb[2]); cb[3] = fma(0.15, qb, cb[3]); cb[4] = fma(0.19364916731037085, qb, cb[4]); cb[5] = fma(0.25, qb, cb[5]); cb[6] = fma(0.05809475019311126, qb, cb[6]); cb[7] = fma(0.075, qb, cb[7]); cb[8] = fma(0.09682458365518543, qb, cb[8]); cb[9] = fma(0.125, qb, cb[9]); cb[10] = fma(0.0225, qb, cb[10]); cb[11] = fma(0.02904737509655563, qb, cb[11]); cb[12] = fma(0.0375, qb, cb[12]); cb[13] = fma(0.04841229182759271, qb, cb[13]); cb[14] = fma(0.0625, qb, cb[14]); break;
-  }
-}
+// transpose of edge_quad: cb[s] += mono_s(point i) * qb
 __device__ __forceinline__ void edge_quad_ng3_T(double qb, int i, double* cb) {
   switch (i) {
   case 0: cb[0] = fma(1.0, qb, cb[0]); cb[1] = fma(-0.5, qb, cb[1]); cb[2] = fma(-0.3872983346207417, qb, cb[2]); cb[3] = fma(0.25, qb, cb[3]); cb[4] = fma(0.19364916731037085, qb, cb[4]); cb[5] = fma(0.15, qb, cb[5]); break;

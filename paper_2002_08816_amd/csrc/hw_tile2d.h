@@ -58,11 +58,6 @@ __device__ __forceinline__ void lin_faces(const double* f, int dir, double* lo, 
 }
 
 template <int NGE>
-__device__ __forceinline__ double edge_quartic(const double* c, int i) {
-  if constexpr (NGE == 2) return hw2::edge_quartic_ng2(c, i);
-  else return hw2::edge_quartic_ng3(c, i);
-}
-template <int NGE>
 __device__ __forceinline__ double edge_quad(const double* c, int i) {
   if constexpr (NGE == 2) return hw2::edge_quad_ng2(c, i);
   else return hw2::edge_quad_ng3(c, i);
@@ -95,13 +90,14 @@ __device__ __forceinline__ void hweno_add(const double* w19, double an, int dir,
   for (int k = 0; k < 2 * NGE; ++k) vals[k] = fma(an, edge_quad<NGE>(c, dir * 2 * NGE + k), vals[k]);
 }
 
-// smoothness indicators of the five candidates and the nonlinear weights (eq. tao4)
+// smoothness indicators of the five candidates and the nonlinear weights (eq. tao4);
+// fold: lin2d_fold of w19
 template <int NGE>
-__device__ __forceinline__ void hweno2d_weights(const double* w19, const Weights& W, double* beta,
-                                                double* om) {
+__device__ __forceinline__ void hweno2d_weights(const double* w19, const double* fold, const Weights& W,
+                                                double* beta, double* om) {
   {
     double c[15];
-    hw2::p0_coeffs(w19, c);
+    hw2::p0_coeffs(fold, c);
     beta[0] = hw2::beta_p0(c);
   }
   hweno_beta<NGE, 1>(w19, beta);
@@ -113,15 +109,14 @@ __device__ __forceinline__ void hweno2d_weights(const double* w19, const Weights
 
 // the combination of Step 5.1 with given nonlinear weights
 template <int NGE>
-__device__ __forceinline__ void hweno2d_combine(const double* w19, const Weights& W, int dir,
-                                                const double* om, double* vals /* 2*NGE */) {
+__device__ __forceinline__ void hweno2d_combine(const double* w19, const double* fold, const Weights& W,
+                                                int dir, const double* om, double* vals /* 2*NGE */) {
   const double ig0 = rcp_nr(W.rec[0]);
   {
     const double a0 = om[0] * ig0;
-    double c[15];
-    hw2::p0_coeffs(w19, c);
+    lin_faces<NGE>(fold, dir, vals, vals + NGE);
 #pragma unroll
-    for (int k = 0; k < 2 * NGE; ++k) vals[k] = a0 * edge_quartic<NGE>(c, dir * 2 * NGE + k);
+    for (int k = 0; k < 2 * NGE; ++k) vals[k] *= a0;
   }
   hweno_add<NGE, 1>(w19, om[1] - om[0] * (W.rec[1] * ig0), dir, vals);
   hweno_add<NGE, 2>(w19, om[2] - om[0] * (W.rec[2] * ig0), dir, vals);
@@ -132,9 +127,10 @@ __device__ __forceinline__ void hweno2d_combine(const double* w19, const Weights
 template <int NGE>
 __device__ __forceinline__ void hweno2d_field(const double* w19, const Weights& W, int dir,
                                               double* vals /* 2*NGE */) {
-  double beta[5], om[5];
-  hweno2d_weights<NGE>(w19, W, beta, om);
-  hweno2d_combine<NGE>(w19, W, dir, om, vals);
+  double fold[hw2::NFOLD], beta[5], om[5];
+  hw2::lin2d_fold(w19, fold);
+  hweno2d_weights<NGE>(w19, fold, W, beta, om);
+  hweno2d_combine<NGE>(w19, fold, W, dir, om, vals);
 }
 
 // LDS tile of W x W positions per field (W = LX: three ghost layers)

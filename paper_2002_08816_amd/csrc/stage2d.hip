@@ -543,8 +543,9 @@ __global__ __launch_bounds__(NT, BK == BK_DMR ? 2 : 1) void stage2d_hweno_kernel
 // The 19 stencil values of component c around (ly, lx) as seen along the direction dir of
 // each lane: for dir = 1 the stencil is transposed (x and y offsets swapped, x and y moments
 // swapped), so that the y-face values are the x-face map of the transposed stencil.  The
-// fold of these values equals lin2d_transpose of the untransposed fold to the bit, so a
-// cell's trace is the same whether the cell itself or a neighbouring tile evaluates it.
+// fold of these values (with lin2d_fold_oo0_T) equals lin2d_transpose of the untransposed fold
+// to the bit, so a cell's trace is the same whether the cell itself or a neighbouring tile
+// evaluates it.
 template <int NC, int W>
 __device__ __forceinline__ void gather19_dir(const double* s, int c, int ly, int lx, int dir,
                                              double* in) {
@@ -867,6 +868,7 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
         double in[19], f[hw2::NFOLD], p[6];
         gather19_dir<NC, W>(s_u, c, rly, rlx, rd, in);
         hw2::lin2d_fold(in, f);
+        if (rd == 1) f[12] = hw2::lin2d_fold_oo0_T(in);
         lin_xparts<NGE>(f, p);
         lin_xface<NGE>(p, side, a[c]);
         __builtin_amdgcn_sched_barrier(0);
@@ -1293,9 +1295,12 @@ __device__ __forceinline__ void block_append_stat(bool m, int value, long long* 
   if (lane == 0) s_wave[w] = __popcll(a);
   __syncthreads();
   const int tot = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+  if (!list) {   // uniform over the grid; the atomic's old value is not waited for
+    if (threadIdx.x == 0 && tot) atomicAdd((unsigned long long*)count, (unsigned long long)tot);
+    return;
+  }
   if (threadIdx.x == 0 && tot)
     s_wave[4] = (int)atomicAdd((unsigned long long*)count, (unsigned long long)tot);
-  if (!list) return;   // uniform over the grid
   __syncthreads();
   if (m) {
     int off = s_wave[4];
@@ -1304,22 +1309,27 @@ __device__ __forceinline__ void block_append_stat(bool m, int value, long long* 
   }
 }
 
-// characteristic HWENO edge values of direction DIR from component f of the limited stencil
-// (four lanes per Euler cell, one per scalar cell): component f of the values
+// characteristic HWENO edge values of direction DIR of the cell at LDS position (ly, lx): the
+// Euler lane f projects the stencil onto field f with every component read from LDS (the four
+// lanes of a cell read the same address, at less cost than passing their components round),
+// reconstructs it, and returns component f of the values
 template <int EQ, int NGE, int DIR>
-__device__ __forceinline__ void hweno_values(const Stage2D& P, const double* in, int f, double* v) {
+__device__ __forceinline__ void hweno_values(const Stage2D& P, const double* s_u, int ly, int lx, int f,
+                                             double* v) {
   if constexpr (EQ == EQ_EULER) {
     double U[4], Lr[4], Rr[4], x[4];
-    quad_gather(in[4], U);   // the cell's own averages
+#pragma unroll
+    for (int c = 0; c < 4; ++c) U[c] = S(s_u, c, ly, lx);   // the cell's own averages
     euler_rows2d(U, P.gam, DIR, f, Lr, Rr);
     double w19[19];
 #pragma unroll
-    for (int k = 0; k < 19; ++k) {
-      quad_gather(in[k], x);
-      double a = 0.0;
+    for (int k = 0; k < 19; ++k) w19[k] = 0.0;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) a = fma(Lr[c], x[c], a);
-      w19[k] = a;
+    for (int c = 0; c < 4; ++c) {
+      double in[19];
+      gather19<4>(s_u, c, ly, lx, in);
+#pragma unroll
+      for (int k = 0; k < 19; ++k) w19[k] = fma(Lr[c], in[k], w19[k]);
     }
     double wv[2 * NGE];
     hweno2d_field<NGE>(w19, P.w, DIR, wv);
@@ -1332,34 +1342,34 @@ __device__ __forceinline__ void hweno_values(const Stage2D& P, const double* in,
       v[k] = a;
     }
   } else {
+    double in[19];
+    gather19<1>(s_u, 0, ly, lx, in);
     hweno2d_field<NGE>(in, P.w, DIR, v);
   }
 }
 
-// the limited first moment of direction dir from component f of the stencil along it (lanes
-// as above): component f of the limited moment
+// the limited first moment of direction dir of the cell at LDS position p (lanes as above):
+// component f of the limited moment
 template <int EQ>
-__device__ __forceinline__ double limited_value(const Stage2D& P, int dir, int f, double um, double u0,
-                                                double up, double vm, double vp) {
+__device__ __forceinline__ double limited_value(const Stage2D& P, const double* s_u, int p, int dir, int f) {
+  constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
+  const int o = dir == 0 ? 1 : LX;
+  const double* u = s_u + p;
+  const double* w = s_u + (1 + dir) * NC * NPOS + p;   // the moment along dir
   if constexpr (EQ == EQ_EULER) {
     double U[4], Lr[4], Rr[4], x[4];
-    quad_gather(u0, U);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) U[c] = u[c * NPOS];
     euler_rows2d(U, P.gam, dir, f, Lr, Rr);
     double cm = 0.0, c0 = 0.0, cp = 0.0, wm = 0.0, wp = 0.0;
-    quad_gather(um, x);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) cm = fma(Lr[c], x[c], cm);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) c0 = fma(Lr[c], U[c], c0);
-    quad_gather(up, x);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) cp = fma(Lr[c], x[c], cp);
-    quad_gather(vm, x);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) wm = fma(Lr[c], x[c], wm);
-    quad_gather(vp, x);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) wp = fma(Lr[c], x[c], wp);
+    for (int c = 0; c < 4; ++c) {
+      cm = fma(Lr[c], u[c * NPOS - o], cm);
+      c0 = fma(Lr[c], U[c], c0);
+      cp = fma(Lr[c], u[c * NPOS + o], cp);
+      wm = fma(Lr[c], w[c * NPOS - o], wm);
+      wp = fma(Lr[c], w[c * NPOS + o], wp);
+    }
     const double vc = limit_moment(cm, c0, cp, wm, wp, P.w.lim, P.w.eps);
     quad_gather(vc, x);
     double out = 0.0;
@@ -1367,7 +1377,7 @@ __device__ __forceinline__ double limited_value(const Stage2D& P, int dir, int f
     for (int g = 0; g < 4; ++g) out = fma(Rr[g], x[g], out);
     return out;
   } else {
-    return limit_moment(um, u0, up, vm, vp, P.w.lim, P.w.eps);
+    return limit_moment(u[-o], u[0], u[o], w[-o], w[o], P.w.lim, P.w.eps);
   }
 }
 
@@ -1491,9 +1501,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
   const int nlim = nfl * 2 * NC;
   for (int it = tid; it < nlim; it += NT) {   // (whole groups of NC lanes)
     const int f = it % NC, dir = (it / NC) & 1, p = s_fl[it / (2 * NC)];
-    const int o = dir == 0 ? 1 : LX, mf = (1 + dir) * NC + f;
-    s_lim[it] = limited_value<EQ>(P, dir, f, s_u[f * NPOS + p - o], s_u[f * NPOS + p], s_u[f * NPOS + p + o],
-                                  s_u[mf * NPOS + p - o], s_u[mf * NPOS + p + o]);
+    s_lim[it] = limited_value<EQ>(P, s_u, p, dir, f);
   }
   __syncthreads();
   if (nfl) {
@@ -1534,10 +1542,9 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
     const int p = s_hl[cell], cy = p / LX - HL, cx = p % LX - HL;
     const bool in_tile = cx >= 0 && cx < tw && cy >= 0 && cy < th;
     if (!in_tile && dir != ((cx >= 0 && cx < tw) ? 1 : 0)) continue;   // the ring's other direction
-    double in[19], v[2 * NGE];
-    gather19<NC>(s_u, f, p / LX, p % LX, in);
-    if (dir == 0) hweno_values<EQ, NGE, 0>(P, in, f, v);
-    else hweno_values<EQ, NGE, 1>(P, in, f, v);
+    double v[2 * NGE];
+    if (dir == 0) hweno_values<EQ, NGE, 0>(P, s_u, p / LX, p % LX, f, v);
+    else hweno_values<EQ, NGE, 1>(P, s_u, p / LX, p % LX, f, v);
     if (in_tile) {
       const size_t g = (size_t)(by * TY + cy) * nx + bx * TX + cx;
 #pragma unroll
