@@ -193,17 +193,20 @@ hw_status hw_get_stats(hw_solver* h, double* alpha, long* flagged, long* hybrid)
 
 /* Times nsteps steps (fixed dt > 0 or CFL dt) with HIP events around every stage and
  * between its launches on the handle's stream; ms_stage receives the mean duration of one
- * stage (in 2D its four launches), ms_step the mean wall time of one step, and ms_kernels
+ * stage (in 2D its one or four launches), ms_step the mean wall time of one step, and ms_kernels
  * (4 doubles, may be NULL) the mean duration of each launch of a stage: 2D flags,
- * limiter, HWENO, stage kernel (the first three 0 without troubled-cell detection); 1D:
- * 0, 0, 0, stage kernel.  Any pointer may be NULL. */
+ * limiter, HWENO, stage kernel (the first three 0 without troubled-cell detection and where
+ * a stage is one launch); 1D: 0, 0, 0, stage kernel, always in the form of one launch per
+ * stage.  Any pointer may be NULL. */
 hw_status hw_profile_steps(hw_solver* h, int nsteps, double dt, double* ms_stage, double* ms_step,
                            double* ms_kernels);
 
 /* Batched form: runs nsteps CFL steps of every instance through a captured HIP graph of
  * the step's launches; persistent = 1 runs each stage as one persistent grid over the
  * (instance, tile) work list, 0 as one workgroup per work item, -1 the form picked by
- * hw_batch_tune (one workgroup per work item until it has run). */
+ * hw_batch_tune (one workgroup per work item until it has run).  Batches on uniform meshes
+ * whose instances all have at most 1024 cells run whole steps in one workgroup per
+ * instance, whatever the form. */
 hw_status hw_batch_steps(hw_solver* h, int nsteps, int persistent);
 
 /* Autotuner of the batched stage: times one captured step (3 replays after a warm-up)

@@ -88,6 +88,16 @@ struct Stage1D {
   Weights w;
 };
 
+// Whole 1D steps in one workgroup per instance (step1d_kernel), beside a Stage1D block.
+struct Step1D {
+  double* S;               // state, [2][nc][total]
+  double *dt, *t;          // per instance
+  long long* steps;        // per instance
+  unsigned long long* alpha;   // speed slots [4][ninst]; slot 3: the current state's
+  uint8_t *flagsT[3], *flagsH[3];   // optional export, per stage
+  double fixed_dt, T_end, cfl;
+};
+
 // Reverse pass of one two-dimensional stage on periodic meshes (see adjoint2d.hip).  For
 // scalar equations the first kernel forms
 //   out = cg * lam + cl * (dL/dW)^T lam + ca * acc_in      at W = limited stage input,
@@ -143,6 +153,10 @@ hipError_t hw_launch_alpha2d(int eq, const double* U, int nx, int ny, double gam
 hipError_t hw_launch_mesh1d_setup(const double* faces, int n, int bc, double* tab, hipStream_t s);
 hipError_t hw_launch_stage1d(int eq, int persistent, int grid, int tile, const hw::Stage1D* P,
                              hipStream_t s);
+// whole steps of short 1D instances: threads per instance (0: not for this batch), nsteps steps
+int hw_step1d_threads(int maxn, int nonuniform);
+hipError_t hw_launch_step1d(int eq, int threads, int ninst, const hw::Stage1D* P, const hw::Step1D* Q,
+                            int nsteps, hipStream_t s);
 hipError_t hw_launch_alpha1d(int eq, const double* U, const int* off, int ninst, int total,
                              int maxn, double gam, double adv, unsigned long long* alpha_out,
                              hipStream_t s);

@@ -554,6 +554,16 @@ static StageRec stage_rec(hw_solver* h, int r) {
   return q;
 }
 
+static void stage1d_params(hw_solver* h, hw::Stage1D& P) {
+  P.items = h->items; P.off = h->off; P.dxs = h->dxs;
+  P.status = h->status;
+  P.nitems = h->nitems; P.total = (int)h->ncell; P.bc = h->cfg.bc_x;
+  P.tc_mode = h->cfg.tc_mode;
+  P.gam = h->cfg.gamma_gas; P.adv = h->cfg.adv[0];
+  P.w = h->w;
+  P.nu = h->nu;
+}
+
 static hw_status launch_stage(hw_solver* h, int mode, const double* in, const double* base,
                               double* out, const unsigned long long* ain, unsigned long long* aout,
                               int fslot, double* wout, int persistent,
@@ -601,15 +611,11 @@ static hw_status launch_stage(hw_solver* h, int mode, const double* in, const do
     HWCHK(hw_launch_stage2d(h->cfg.eq, h->cfg.ng_edge, &P, h->stream, ev));
   } else {
     hw::Stage1D P{};
+    stage1d_params(h, P);
     P.in = in; P.base = base; P.out = out; P.Tn = h->Tn; P.limn = h->limn;
-    P.items = h->items; P.off = h->off; P.dxs = h->dxs;
     P.alpha_in = ain; P.alpha_out = aout; P.dt = h->dt;
-    P.flagsT = fT; P.flagsH = fH; P.wout = wout; P.status = h->status;
-    P.nitems = h->nitems; P.total = (int)h->ncell; P.bc = h->cfg.bc_x;
-    P.tc_mode = h->cfg.tc_mode; P.mode = mode;
-    P.gam = h->cfg.gamma_gas; P.adv = h->cfg.adv[0];
-    P.w = h->w;
-    P.nu = h->nu;
+    P.flagsT = fT; P.flagsH = fH; P.wout = wout;
+    P.mode = mode;
     int grid = h->pgrid > 0 ? h->pgrid : 1024;
     HWCHK(hw_launch_stage1d(h->cfg.eq, persistent, grid, h->tile1d, &P, h->stream));
   }
@@ -628,7 +634,30 @@ static void launch_dt(hw_solver* h, double fixed_dt, double T_end) {
                        (long long*)nullptr);
 }
 
+// Threads per instance of the one-workgroup form of whole 1D steps (0: not for this handle)
+static int step1d_threads(const hw_solver* h) {
+  return h->dim == 1 ? hw_step1d_threads(h->maxn, h->nu != nullptr) : 0;
+}
+
+// n whole steps of every instance in one workgroup each (step1d_threads(h) != 0); a launch
+// takes at most 64 steps
+static hw_status enqueue_steps_1d(hw_solver* h, long n, double fixed_dt, double T_end) {
+  hw::Stage1D P{};
+  stage1d_params(h, P);
+  hw::Step1D Q{};
+  Q.S = h->S0; Q.dt = h->dt; Q.t = h->t; Q.steps = h->steps; Q.alpha = h->alpha;
+  for (int s = 0; s < 3; ++s) {
+    Q.flagsT[s] = h->export_flags ? h->flagsT[s] : nullptr;
+    Q.flagsH[s] = h->export_flags ? h->flagsH[s] : nullptr;
+  }
+  Q.fixed_dt = fixed_dt; Q.T_end = T_end; Q.cfl = h->cfg.cfl;
+  for (; n > 0; n -= 64)
+    HWCHK(hw_launch_step1d(h->cfg.eq, step1d_threads(h), h->ninst, &P, &Q, (int)std::min<long>(n, 64), h->stream));
+  return HW_OK;
+}
+
 static hw_status enqueue_step(hw_solver* h, double fixed_dt, double T_end, int persistent) {
+  if (step1d_threads(h)) return enqueue_steps_1d(h, 1, fixed_dt, T_end);
   const int W = h->aw;
   launch_dt(h, fixed_dt, T_end);
   HWCHK(hipGetLastError());
@@ -842,15 +871,22 @@ static hw_status launch_steps(hw_solver* h, long n) {
   return HW_OK;
 }
 
+// n steps: whole steps in one workgroup per instance where every 1D instance is short enough,
+// else from the captured graphs
+static hw_status run_steps(hw_solver* h, double fixed_dt, double T_end, int persistent, long n) {
+  if (step1d_threads(h)) return enqueue_steps_1d(h, n, fixed_dt, T_end);
+  hw_status s = capture_step(h, fixed_dt, T_end, persistent, n);
+  if (s != HW_OK) return s;
+  return launch_steps(h, n);
+}
+
 // steps are replayed from one captured graph of the step's launches (the step reads dt,
 // speeds and work-list counts from device memory, so every replay is the same launch set)
 extern "C" hw_status hw_steps(hw_solver* h, int nsteps, double dt) {
   if (!h) return fail(nullptr, HW_EINVAL, "null handle");
   if (nsteps < 0 || !std::isfinite(dt)) return fail(h, HW_EINVAL, "invalid step count or dt");
   if (nsteps == 0) return HW_OK;
-  hw_status s = capture_step(h, dt > 0.0 ? dt : 0.0, 0.0, 0, nsteps);
-  if (s != HW_OK) return s;
-  return launch_steps(h, nsteps);
+  return run_steps(h, dt > 0.0 ? dt : 0.0, 0.0, 0, nsteps);
 }
 
 extern "C" hw_status hw_run(hw_solver* h, double T, long max_steps, long* steps_out, double* t_out) {
@@ -864,11 +900,12 @@ extern "C" hw_status hw_run(hw_solver* h, double T, long max_steps, long* steps_
   HWCHK(hipStreamSynchronize(h->stream));
   long done_steps = 0;
   while (true) {
-    const long chunk = std::min<long>(16, max_steps - done_steps);
+    // (the one-workgroup form of a single instance stops by itself at T, and on a bad state
+    // after the same multiples of 16 steps)
+    const long chunk = std::min<long>(h->ninst == 1 && step1d_threads(h) ? 64 : 16, max_steps - done_steps);
     if (chunk <= 0) break;
-    hw_status s = capture_step(h, 0.0, T, 0, chunk);
+    hw_status s = run_steps(h, 0.0, T, 0, chunk);
     if (s != HW_OK) return s;
-    if ((s = launch_steps(h, chunk)) != HW_OK) return s;
     HWCHK(hipMemcpyAsync(tt.data(), h->t, h->ninst * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HWCHK(hipMemcpyAsync(ss.data(), h->steps, h->ninst * sizeof(long long), hipMemcpyDeviceToHost, h->stream));
     int st = 0;
@@ -1269,9 +1306,7 @@ extern "C" hw_status hw_batch_steps(hw_solver* h, int nsteps, int persistent) {
   if (!h) return fail(nullptr, HW_EINVAL, "null handle");
   if (h->dim != 1 || nsteps < 0) return fail(h, HW_EINVAL, "batched steps need a 1D handle and nsteps >= 0");
   const int form = persistent < 0 ? h->auto_persist : (persistent ? 1 : 0);
-  hw_status s = capture_step(h, 0.0, 0.0, form, nsteps);
-  if (s != HW_OK) return s;
-  return launch_steps(h, nsteps);
+  return run_steps(h, 0.0, 0.0, form, nsteps);
 }
 
 // ------------------------------------------------------------------------------ meshes

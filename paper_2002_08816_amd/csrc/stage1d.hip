@@ -42,13 +42,14 @@ struct Char1 {
 
 __device__ __forceinline__ Char1 char1d(double rho, double m, double E, double gam) {
   Char1 k;
-  k.u = m / rho;
+  const double ir = rcp_nr(rho);
+  k.u = m * ir;
   const double p = (gam - 1.0) * (E - 0.5 * rho * k.u * k.u);
-  k.c = sqrt(gam * p / rho);
-  k.H = (E + p) / rho;
-  k.b1 = (gam - 1.0) / (k.c * k.c);
+  k.c = sqrt(gam * p * ir);
+  k.H = (E + p) * ir;
+  k.ic = rcp_nr(k.c);
+  k.b1 = (gam - 1.0) * (k.ic * k.ic);
   k.b2 = 0.5 * k.b1 * k.u * k.u;
-  k.ic = 1.0 / k.c;
   return k;
 }
 
@@ -80,6 +81,19 @@ __device__ __forceinline__ void char1d_right(const Char1& k, int f, double* Rc) 
     Rc[1] = k.u + k.c;
     Rc[2] = k.H + k.u * k.c;
   }
+}
+
+// row f of L and row f of R (component f of every field's eigenvector), for a lane that works
+// on field f and then on component f (f = 3: an idle lane's, never used)
+__device__ __forceinline__ void char1d_rows(const Char1& k, int f, double* Lr, double* Rr) {
+  const double s = f == 0 ? 1.0 : -1.0;
+  Lr[0] = f == 1 ? 1.0 - k.b2 : 0.5 * (k.b2 + s * k.u * k.ic);
+  Lr[1] = f == 1 ? k.b1 * k.u : -0.5 * (k.b1 * k.u + s * k.ic);
+  Lr[2] = f == 1 ? -k.b1 : 0.5 * k.b1;
+  const double uc = k.u * k.c;
+  Rr[0] = f == 0 ? 1.0 : (f == 1 ? k.u - k.c : k.H - uc);
+  Rr[1] = f == 0 ? 1.0 : (f == 1 ? k.u : 0.5 * k.u * k.u);
+  Rr[2] = f == 0 ? 1.0 : (f == 1 ? k.u + k.c : k.H + uc);
 }
 
 template <int EQ>
@@ -486,6 +500,387 @@ __global__ __launch_bounds__(T1, 4) void stage1d_persistent(Stage1D P) {
   }
 }
 
+// A number of the sign of the velocity m / rho as the rounded quotient has it (zero where the
+// quotient underflows): the quotient itself only where the operands do not tell.
+__device__ __forceinline__ double velocity_sign(double m, double rho) {
+  if (rho > 0.0 && rho < 1e100 && (m == 0.0 || fabs(m) > 1e-200)) return m;
+  return m / rho;
+}
+
+// maximum over a wave of non-negative values (NaN ignored), in lane 63: register moves within
+// rows of 16 lanes, then across them
+__device__ __forceinline__ double wave_max63(double v) {
+#define HW_MAX_DPP(ctrl)                                                                         \
+  v = fmax(v, __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xF, 0xF, true), \
+                               __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xF, 0xF, true)))
+  HW_MAX_DPP(0x111);   // row_shr:1
+  HW_MAX_DPP(0x112);
+  HW_MAX_DPP(0x114);
+  HW_MAX_DPP(0x118);
+  HW_MAX_DPP(0x142);   // row_bcast:15
+  HW_MAX_DPP(0x143);   // row_bcast:31
+#undef HW_MAX_DPP
+  return v;
+}
+
+// LDS of one whole instance of at most T1 cells
+template <int EQ, int T1>
+struct WholeShared {
+  static constexpr int NC = (EQ == EQ_EULER) ? 3 : 1, NF = 2 * NC, L1 = T1 + 2 * H1;
+  double in[NF * L1];           // stage input with ghosts, then limited
+  double fm[NC * (T1 + 1)];     // u^- at the faces
+  double fp[NC * (T1 + 1)];     // u^+
+  double fx[NC * (T1 + 1)];     // limited moments of the flagged cells, then the face fluxes
+  double red[T1 / 64];
+  uint16_t fl[T1], hl[T1];      // flagged and hybrid cells
+  uint8_t T[L1];
+  int cnt[2], bad;
+};
+
+// The spatial operator on a whole instance staged in sh.in (its flags' and limiter's ghosts
+// are filled here).  Few cells of an instance are troubled, and a cell's characteristic
+// limiter or reconstruction is several times as long as the linear path, so the work lists of
+// those cells are spread over all lanes, four per Euler cell (lane f: characteristic field f,
+// then component f): the wave that holds a shock would otherwise set the stage's time.
+template <int EQ, int T1>
+__device__ __forceinline__ void whole_operator(const Stage1D& P, WholeShared<EQ, T1>& sh, int n, double h,
+                                               double idx, double alpha, double* LU, double* LV, double* own,
+                                               uint8_t& myT, uint8_t& myH) {
+  constexpr int NC = (EQ == EQ_EULER) ? 3 : 1, NF = 2 * NC, L1 = T1 + 2 * H1, F1 = T1 + 1;
+  constexpr int LPC = (EQ == EQ_EULER) ? 4 : 1;   // lanes per listed cell
+  const int tid = threadIdx.x, l = tid + H1;
+  const bool active = tid < n;
+  const bool walls = P.bc != BC_PERIODIC;
+  auto A = [&](int f, int q) -> double { return sh.in[f * L1 + q]; };
+  // the ghost next to an end that cell i is the source of (0: none)
+  auto end_ghost = [&](int i) -> int {
+    if (i == 0) return walls ? H1 - 1 : H1 + n;
+    if (i == n - 1) return walls ? H1 + n : H1 - 1;
+    return 0;
+  };
+  // ---------------------------------------------------------------- flags, work lists
+  myT = myH = 0;
+  if (active) {
+    if (P.tc_mode == TC_ALL) {
+      myT = 1;
+    } else if (P.tc_mode == TC_KXRCF) {
+      double vel;
+      if constexpr (EQ == EQ_EULER) vel = velocity_sign(A(1, l), A(0, l));
+      else if constexpr (EQ == EQ_BURGERS) vel = A(0, l);
+      else vel = P.adv;
+      constexpr int ncheck = (EQ == EQ_EULER) ? 2 : 1;
+#pragma unroll
+      for (int k = 0; k < ncheck; ++k) {
+        const int c = (k == 0) ? 0 : NC - 1;   // density, then energy
+        if (kxrcf1d(A(c, l), A(NC + c, l), A(c, l - 1), A(NC + c, l - 1), A(c, l + 1), A(NC + c, l + 1), vel, h))
+          myT = 1;
+      }
+    }
+    sh.T[l] = myT;
+    const int g = end_ghost(tid);
+    if (g) sh.T[g] = myT;
+    if (myT) sh.fl[atomicAdd(&sh.cnt[0], 1)] = (uint16_t)tid;
+  }
+  __syncthreads();
+  const int nfl = sh.cnt[0];
+  if (active) {
+    myH = sh.T[l - 1] | sh.T[l] | sh.T[l + 1];
+    if (myH) sh.hl[atomicAdd(&sh.cnt[1], 1)] = (uint16_t)tid;
+  }
+  // ---------------------------------------------------------------- limiter (Jacobi)
+  for (int it = tid; it < nfl * LPC; it += T1) {   // (whole groups of LPC lanes)
+    const int f = it % LPC, q = sh.fl[it / LPC] + H1;
+    if constexpr (EQ != EQ_EULER) {
+      sh.fx[it] = limit_moment(A(0, q - 1), A(0, q), A(0, q + 1), A(1, q - 1), A(1, q + 1), P.w.lim, P.w.eps);
+    } else {
+      const Char1 k = char1d(A(0, q), A(1, q), A(2, q), P.gam);
+      double Lr[3], Rr[3];
+      char1d_rows(k, f, Lr, Rr);
+      double um = 0.0, u0 = 0.0, up = 0.0, vm = 0.0, vp = 0.0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        um = fma(Lr[c], A(c, q - 1), um);
+        u0 = fma(Lr[c], A(c, q), u0);
+        up = fma(Lr[c], A(c, q + 1), up);
+        vm = fma(Lr[c], A(3 + c, q - 1), vm);
+        vp = fma(Lr[c], A(3 + c, q + 1), vp);
+      }
+      double x[4];
+      quad_gather(limit_moment(um, u0, up, vm, vp, P.w.lim, P.w.eps), x);
+      double out = 0.0;
+#pragma unroll
+      for (int g = 0; g < 3; ++g) out = fma(Rr[g], x[g], out);
+      if (f < 3) sh.fx[(it / LPC) * NC + f] = out;
+    }
+  }
+  __syncthreads();
+  const int nhl = sh.cnt[1];
+  for (int it = tid; it < nfl * NC; it += T1) {
+    const int c = it % NC, i = sh.fl[it / NC], g = end_ghost(i);
+    const double v = sh.fx[it];
+    sh.in[(NC + c) * L1 + i + H1] = v;
+    // a ghost at a wall holds the mirror image (the moment odd; a reflective wall also
+    // reverses the momentum)
+    if (g) sh.in[(NC + c) * L1 + g] = walls && !(EQ == EQ_EULER && P.bc == BC_REFLECTIVE && c == 1) ? -v : v;
+  }
+  __syncthreads();
+  // ---------------------------------------------------------------- reconstruction
+  auto put = [&](int i, int c, double left, double right) {
+    sh.fp[c * F1 + i] = left;
+    sh.fm[c * F1 + i + 1] = right;
+    // the faces at the ends of a periodic instance (walls: replaced below)
+    if (i == n - 1) sh.fm[c * F1] = right;
+    if (i == 0) sh.fp[c * F1 + n] = left;
+  };
+  for (int it = tid; it < nhl * LPC; it += T1) {
+    const int f = it % LPC, i = sh.hl[it / LPC], q = i + H1;
+    double left, right;
+    if constexpr (EQ != EQ_EULER) {
+      hweno1d(A(0, q - 1), A(0, q), A(0, q + 1), A(1, q - 1), A(1, q), A(1, q + 1), P.w.rec, P.w.eps, left, right);
+      put(i, 0, left, right);
+    } else {
+      const Char1 k = char1d(A(0, q), A(1, q), A(2, q), P.gam);
+      double Lr[3], Rr[3], d[6] = {0, 0, 0, 0, 0, 0};
+      char1d_rows(k, f, Lr, Rr);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        d[0] = fma(Lr[c], A(c, q - 1), d[0]);
+        d[1] = fma(Lr[c], A(c, q), d[1]);
+        d[2] = fma(Lr[c], A(c, q + 1), d[2]);
+        d[3] = fma(Lr[c], A(3 + c, q - 1), d[3]);
+        d[4] = fma(Lr[c], A(3 + c, q), d[4]);
+        d[5] = fma(Lr[c], A(3 + c, q + 1), d[5]);
+      }
+      hweno1d(d[0], d[1], d[2], d[3], d[4], d[5], P.w.rec, P.w.eps, left, right);
+      double xl[4], xr[4], ol = 0.0, orr = 0.0;
+      quad_gather(left, xl);
+      quad_gather(right, xr);
+#pragma unroll
+      for (int g = 0; g < 3; ++g) {
+        ol = fma(Rr[g], xl[g], ol);
+        orr = fma(Rr[g], xr[g], orr);
+      }
+      if (f < 3) put(i, f, ol, orr);
+    }
+  }
+  double um[NC], up[NC];
+  if (active) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      double a, b;
+      linear1d(A(c, l - 1), A(c, l), A(c, l + 1), A(NC + c, l - 1), A(NC + c, l), A(NC + c, l + 1), a, b, um[c], up[c]);
+      if (!myH) put(tid, c, a, b);
+    }
+  }
+  __syncthreads();
+  // ---------------------------------------------------------------- fluxes
+  double Fi[NC], fL[NC];   // fL: the flux at the cell's own left value, u^+ of face tid
+  for (int q = tid; q < n + 1; q += T1) {
+    double a[NC], b[NC], fa[NC], fb[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      a[c] = sh.fm[c * F1 + q];
+      b[c] = sh.fp[c * F1 + q];
+    }
+    flux1d<EQ>(b, P.gam, P.adv, fb);
+    if (q == tid) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) fL[c] = fb[c];
+    }
+    if (walls && (q == 0 || q == n)) {
+      // boundary face: the ghost's trace is the inner cell's (momentum reversed at a wall)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const double m = (EQ == EQ_EULER && P.bc == BC_REFLECTIVE && c == 1) ? -1.0 : 1.0;
+        if (q == 0) a[c] = m * b[c];
+        else b[c] = m * a[c];
+      }
+      if (q == n) flux1d<EQ>(b, P.gam, P.adv, fb);
+    }
+    flux1d<EQ>(a, P.gam, P.adv, fa);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) sh.fx[c * F1 + q] = 0.5 * (fa[c] + fb[c]) - 0.5 * alpha * (b[c] - a[c]);
+  }
+  if (active) {
+    double uR[NC], fR[NC], fm[NC], fp[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) uR[c] = sh.fm[c * F1 + tid + 1];
+    flux1d<EQ>(uR, P.gam, P.adv, fR);
+    flux1d<EQ>(um, P.gam, P.adv, fm);
+    flux1d<EQ>(up, P.gam, P.adv, fp);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) Fi[c] = (fL[c] + fR[c]) * (1.0 / 12.0) + (fm[c] + fp[c]) * (5.0 / 12.0);
+  }
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const double FL = sh.fx[c * F1 + tid], FR = sh.fx[c * F1 + tid + 1];
+      LU[c] = -(FR - FL) * idx;
+      LV[c] = (Fi[c] - 0.5 * (FL + FR)) * idx;
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) own[f] = A(f, l);   // the (limited) stage input
+  }
+}
+
+// Whole steps of short instances: one workgroup keeps an instance of at most T1 cells in LDS and
+// registers for up to nsteps TVD-RK3 steps (time step, three stages, speeds), one cell per
+// thread, and reads and writes global memory only at the two ends.  A step of separate
+// launches costs their latency, 41 us at 400 cells (time step 4.6, stages 11.5 each, gaps);
+// here a stage is six barriers among the instance's own waves, and its 5 us are a chain of
+// latencies spread evenly over them: staging and speeds 1.0, flags 0.6, limiter 0.8, write-back
+// 0.2, reconstruction 0.8, linear traces 0.8, fluxes 0.7, update 0.8.  The arithmetic per cell is
+// the tile routine's.
+//
+// Measured, us a step, Euler shock tube, separate launches -> this: 80 cells 34.9 -> 19.3; 200
+// 38.7 -> 20.3; 400 39.5 -> 21.7; 512 36.3 -> 22.1; 700 38.2 -> 26.2; 1000 38.4 -> 27.7.
+// Batches, against their best form so far: 16 instances of up to 128 cells 50.9 -> 20.5; 64 of
+// 500 to 1000 57 -> 27; 300 of them 73.6 -> 49.8; 512 of them 82.5 -> 49.2; 2000 of 50 to 120
+// 86.7 -> 43.4.
+template <int EQ, int T1>
+__global__ __launch_bounds__(T1) void step1d_kernel(Stage1D P, Step1D Q, int nsteps) {
+  constexpr int NC = (EQ == EQ_EULER) ? 3 : 1, NF = 2 * NC, L1 = T1 + 2 * H1, NW = T1 / 64;
+  __shared__ WholeShared<EQ, T1> sh;
+  double* const s_in = sh.in;
+  double* const s_red = sh.red;
+  const int inst = blockIdx.x, tid = threadIdx.x;
+  const int off = P.off[inst], n = P.off[inst + 1] - off;
+  const size_t tot = (size_t)P.total, gidx = (size_t)off + tid;
+  const bool active = tid < n;
+  const int W = gridDim.x;   // speed entries per slot
+  double u[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) u[f] = active ? Q.S[f * tot + gidx] : 0.0;
+  double t = Q.t[inst], dt = 0.0;
+  long long steps = Q.steps[inst];
+  double alpha = __longlong_as_double((long long)Q.alpha[3 * W + inst]);
+  const double dxs = P.dxs[inst], idx = 1.0 / dxs;
+  if (tid == 0) sh.bad = 0;
+  // the ghost position this cell's values also go to (each ghost has one source cell, and no
+  // cell is the source of two: n >= 7), and the factor of its first moments and momentum there
+  int ghost = -1;
+  double gs = 1.0;
+#pragma unroll
+  for (int g = 0; g < 2 * H1; ++g) {
+    const int gg = g < H1 ? g - H1 : n + g - H1;
+    double sg;
+    if (active && map_index(gg, n, P.bc, sg) == tid) {
+      ghost = gg + H1;
+      gs = sg;
+    }
+  }
+  const bool refl = EQ == EQ_EULER && P.bc == BC_REFLECTIVE && gs < 0.0;
+  int bad = 0;
+#pragma unroll 1
+  for (int k = 0; k < nsteps; ++k) {
+    // a run to a final time: stop on a non-physical state, every 16 steps (as the chunks of
+    // separate launches do)
+    if (Q.T_end > 0.0 && k > 0 && (k & 15) == 0) {
+      if (bad) sh.bad = 1;
+      __syncthreads();
+      if (sh.bad) break;
+    }
+    if (k > 0) {
+      // speed of the last stage's output (written before barriers of that stage's end)
+      __syncthreads();
+      alpha = s_red[0];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) alpha = fmax(alpha, s_red[i]);
+      if (!(alpha >= 0.0)) alpha = __longlong_as_double(0x7ff0000000000000ll);
+    }
+    dt = Q.fixed_dt > 0.0 ? Q.fixed_dt : Q.cfl * dxs / alpha;
+    if (Q.T_end > 0.0) {
+      if (t >= Q.T_end) dt = 0.0;
+      else if (t + dt > Q.T_end) dt = Q.T_end - t;
+    }
+    if (dt == 0.0) break;
+    if (dt > 0.0) {
+      t += dt;
+      steps += 1;
+    }
+    double Wn[NF];
+#pragma unroll 1
+    for (int stage = 0; stage < 3; ++stage) {
+      if (active) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          s_in[f * L1 + H1 + tid] = u[f];
+          if (ghost >= 0) {
+            const double m = (refl && f % NC == 1) ? -1.0 : 1.0;
+            s_in[f * L1 + ghost] = m * (f >= NC ? gs * u[f] : u[f]);
+          }
+        }
+      }
+      if (tid < 2) sh.cnt[tid] = 0;
+      __syncthreads();
+      if (stage > 0) {
+        alpha = s_red[0];
+#pragma unroll
+        for (int i = 1; i < NW; ++i) alpha = fmax(alpha, s_red[i]);
+        if (!(alpha >= 0.0)) alpha = __longlong_as_double(0x7ff0000000000000ll);
+      }
+      double LU[NC], LV[NC], own[NF];
+      uint8_t myT = 0, myH = 0;
+      whole_operator<EQ, T1>(P, sh, n, 0.5 * dxs, idx, alpha, LU, LV, own, myT, myH);
+      double sp = 0.0;
+      if (active) {
+        if (Q.flagsT[0]) {
+          uint8_t* fT = stage == 0 ? Q.flagsT[0] : (stage == 1 ? Q.flagsT[1] : Q.flagsT[2]);
+          uint8_t* fH = stage == 0 ? Q.flagsH[0] : (stage == 1 ? Q.flagsH[1] : Q.flagsH[2]);
+          fT[gidx] = myT;
+          fH[gidx] = myH;
+        }
+        if (stage == 0) {
+#pragma unroll
+          for (int f = 0; f < NF; ++f) Wn[f] = own[f];
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          const double Lf = f < NC ? LU[f] : LV[f - NC];
+          double v;
+          if (stage == 0) v = own[f] + dt * Lf;
+          else if (stage == 1) v = (0.75 * Wn[f] + 0.25 * own[f]) + (0.25 * dt) * Lf;
+          else v = (Wn[f] * (1.0 / 3.0) + (2.0 / 3.0) * own[f]) + ((2.0 / 3.0) * dt) * Lf;
+          u[f] = v;
+          if (!isfinite(v)) bad |= 1;
+        }
+        if constexpr (EQ == EQ_EULER) {
+          const double ir = rcp_nr(u[0]), vel = u[1] * ir;
+          const double p = (P.gam - 1.0) * (u[2] - 0.5 * u[1] * vel);
+          if (!(u[0] > 0.0) || !(p > 0.0)) bad |= 2;
+          sp = fabs(vel) + sqrt(P.gam * p * ir);
+        } else if constexpr (EQ == EQ_BURGERS) {
+          sp = fabs(u[0]);
+        } else {
+          sp = fabs(P.adv);
+        }
+      }
+      // (the last reads of s_red come before barriers of the operator above)
+      sp = wave_max63(sp);
+      if ((tid & 63) == 63) s_red[tid >> 6] = sp;
+    }
+  }
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) Q.S[f * tot + gidx] = u[f];
+  }
+  if (bad) atomicOr(P.status, bad);
+  if (tid == 0) {
+    if (steps != Q.steps[inst] || !(dt == 0.0)) {
+      // (at least one step was taken: the speed of its result)
+      double m = s_red[0];
+      for (int i = 1; i < NW; ++i) m = fmax(m, s_red[i]);
+      if (!(m >= 0.0)) m = __longlong_as_double(0x7ff0000000000000ll);
+      Q.alpha[3 * W + inst] = (unsigned long long)__double_as_longlong(m);
+    }
+    Q.dt[inst] = dt;
+    Q.t[inst] = t;
+    Q.steps[inst] = steps;
+  }
+}
+
 // Lax-Friedrichs speed per instance (before the first stage; operator-only calls)
 template <int EQ>
 __global__ __launch_bounds__(256) void alpha1d_kernel(const double* U, const int* off, int total,
@@ -755,6 +1150,37 @@ extern "C" hipError_t hw_launch_stage1d(int eq, int persistent, int grid, int ti
   if (eq == hw::EQ_EULER) return launch1d_tile<hw::EQ_EULER>(persistent, grid, tile, P, s);
   if (eq == hw::EQ_BURGERS) return launch1d_tile<hw::EQ_BURGERS>(persistent, grid, tile, P, s);
   if (eq == hw::EQ_ADV) return launch1d_tile<hw::EQ_ADV>(persistent, grid, tile, P, s);
+  return hipErrorInvalidValue;
+}
+
+// Threads per instance of the one-workgroup form: the smallest count that gives every cell a
+// thread, and 0 (separate launches) where an instance is longer than a workgroup, or where
+// there are per-cell tables: with those the kernel spills (96 us a step against 61 at 400 cells).
+extern "C" int hw_step1d_threads(int maxn, int nonuniform) {
+  if (nonuniform || maxn > 1024) return 0;
+  return maxn <= 128 ? 128 : (maxn <= 256 ? 256 : (maxn <= 512 ? 512 : 1024));
+}
+
+template <int EQ>
+static hipError_t launch_step1d(int threads, int ninst, const hw::Stage1D* P, const hw::Step1D* Q, int nsteps,
+                                hipStream_t s) {
+  const dim3 g(ninst), b(threads);
+  switch (threads) {
+    case 128: hipLaunchKernelGGL((hw::step1d_kernel<EQ, 128>), g, b, 0, s, *P, *Q, nsteps); break;
+    case 256: hipLaunchKernelGGL((hw::step1d_kernel<EQ, 256>), g, b, 0, s, *P, *Q, nsteps); break;
+    case 512: hipLaunchKernelGGL((hw::step1d_kernel<EQ, 512>), g, b, 0, s, *P, *Q, nsteps); break;
+    case 1024: hipLaunchKernelGGL((hw::step1d_kernel<EQ, 1024>), g, b, 0, s, *P, *Q, nsteps); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+extern "C" hipError_t hw_launch_step1d(int eq, int threads, int ninst, const hw::Stage1D* P,
+                                       const hw::Step1D* Q, int nsteps, hipStream_t s) {
+  if (P->nu) return hipErrorInvalidValue;
+  if (eq == hw::EQ_EULER) return launch_step1d<hw::EQ_EULER>(threads, ninst, P, Q, nsteps, s);
+  if (eq == hw::EQ_BURGERS) return launch_step1d<hw::EQ_BURGERS>(threads, ninst, P, Q, nsteps, s);
+  if (eq == hw::EQ_ADV) return launch_step1d<hw::EQ_ADV>(threads, ninst, P, Q, nsteps, s);
   return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,97 @@
+"""Whole 1D steps in one workgroup per instance (every instance of at most 1024 cells) against
+the oracle, at the edges of its thread counts (128, 256, 512, 1024) and of the rule, for every
+law, boundary and troubled-cell mode; and its instances inside a batch against a batch that an
+instance of 1025 cells sends through the tile kernels.  Tolerances: the repository's bounds
+after time stepping; between the two GPU forms, whose arithmetic per cell is the same, the
+bound of one operator evaluation per field."""
+import numpy as np
+import pytest
+
+import hweno_inputs as hi
+from oracle.physics import Equation
+from oracle.scheme1d import Scheme1D
+from parity import TOL, check_run, p1_field_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hw():
+    import paper_2002_08816_amd as pkg
+    return pkg
+
+
+def scalar_state(n, seed):
+    x = (np.arange(n) + 0.5) / n
+    U = np.zeros((2, 1, n))
+    U[0, 0] = 1.0 + 0.5 * np.sin(2 * np.pi * x) + 0.3 * (x > 0.37) - 0.2 * (x > 0.71)
+    U[1, 0] = 0.002 * np.random.default_rng(seed).normal(size=n)
+    return U
+
+
+@pytest.mark.parametrize("n", [7, 64, 128, 129, 256, 257, 512, 513, 1024, 1025])
+@pytest.mark.parametrize("eq,bc,tc", [("euler", "transmissive", "kxrcf"), ("euler", "reflective", "kxrcf"),
+                                      ("euler", "periodic", "all"), ("burgers", "periodic", "kxrcf"),
+                                      ("burgers", "transmissive", "all"), ("advection", "periodic", "none")])
+def test_steps_against_the_oracle(hw, n, eq, bc, tc):
+    U = hi.euler_riemann_1d(4, n)[0] if eq == "euler" else scalar_state(n, 5)
+    if eq == "euler" and n < 64:   # too few cells for the generator's jumps: a smooth state
+        U = hi.example_3_2(n, x1=2.0)
+    s = hw.Solver(1, n, eq=eq, adv=(0.8,), bc=bc, tc_mode=tc)
+    s.set_state(U)
+    s.flag_export(True)
+    s.steps(3)
+    got, t = s.get_state()
+    o = Scheme1D(Equation(eq, 1, adv=(0.8,)), n, 0.0, 1.0, bc=bc, tc_mode=tc)
+    Uo, to, k, _ = o.run(U, nsteps=3, cfl=0.6)
+    assert k == 3 and abs(t - to) <= 1e-13 * to
+    check_run(got, Uo, f"{eq} {bc} {tc} n={n}")
+    alpha = s.stats()[0][0]
+    assert abs(alpha - o.alpha(got)) <= 1e-12 * alpha
+    # flags of the last step's first stage: those of the state after two steps
+    s2 = hw.Solver(1, n, eq=eq, adv=(0.8,), bc=bc, tc_mode=tc)
+    s2.set_state(U)
+    s2.steps(2)
+    s2.flag_export(True)
+    s2.apply_operator(s2.get_state()[0])
+    for a, b in zip(s.flags(0), s2.flags(0)):
+        assert np.array_equal(a, b)
+    s.close()
+    s2.close()
+
+
+def test_a_run_stops_at_its_final_time_and_on_a_bad_state(hw):
+    n = 300
+    U = hi.euler_riemann_1d(2, n)[0]
+    s = hw.Solver(1, n, eq="euler", bc="transmissive", tc_mode="kxrcf")
+    s.set_state(U)
+    steps, t = s.run(0.03)
+    one = s.get_state()[0]
+    assert t == 0.03 and s.time() == (0.03, steps) and steps > 16
+    s.set_state(U)
+    k, t2 = s.run(0.03, max_steps=21)
+    assert k == 21 and 0.0 < t2 < 0.03
+    k2, t3 = s.run(0.03)
+    assert k + k2 == steps and t3 == 0.03 and np.array_equal(s.get_state()[0], one)
+    bad = U.copy()
+    bad[0, 2, 150] = -1.0   # negative pressure
+    s.set_state(bad)
+    with pytest.raises(Exception) as e:
+        s.run(0.03)
+    assert "non-" in str(e.value)
+    s.close()
+
+
+def test_batch_of_short_instances_equals_the_tile_kernels(hw):
+    sizes = [100, 1000, 37, 512, 700]
+    Us = [hi.euler_riemann_1d(b + 3, n)[0] for b, n in enumerate(sizes)]
+    out = []
+    for extra in ([], [1025]):
+        bs = hw.BatchSolver(sizes + extra, eq="euler", bc="transmissive", tc_mode="kxrcf")
+        bs.set_states(Us + [hi.euler_riemann_1d(40, n)[0] for n in extra])
+        bs.steps(6, persistent=False)
+        out.append((bs.get_states(), bs.times()[0]))
+        bs.close()
+    for b in range(len(sizes)):
+        assert p1_field_err(out[0][0][b], out[1][0][b]) < TOL
+        assert abs(out[0][1][b] - out[1][1][b]) <= 1e-14
