@@ -250,9 +250,10 @@ hw_status hw_apply_operator_adjoint(hw_solver* h, const double* d_in, const doub
 
 /* Advances the current state by nsteps TVD-RK3 steps of fixed dt > 0 (the same kernels
  * as hw_steps) and keeps a device checkpoint of the state every k steps for hw_adjoint
- * (ceil(nsteps / k) states, plus 3k + 1 states of segment workspace; Euler with
+ * (ceil(nsteps / k) states, plus 3k + 1 states of segment workspace, which the run's last
+ * segment fills; Euler with
  * troubled-cell detection also keeps, for each of the segment's 3k stages, the flags,
- * hybrid masks, limited moments, HWENO edge values and work lists of its replay: about
+ * hybrid masks, limited moments, HWENO edge values and work lists: about
  * (74 + 128 NG) bytes per cell and stage; the double Mach reflection also each stage's
  * table of prescribed ghosts and each step's time, so that the replay sees the boundary
  * data of the recorded run).  On a non-finite result returns HW_ENONFINITE
@@ -260,8 +261,9 @@ hw_status hw_apply_operator_adjoint(hw_solver* h, const double* d_in, const doub
 hw_status hw_forward_ckpt(hw_solver* h, int nsteps, double dt, int k);
 
 /* Gradient of the recorded run: d_grad_U0 = (d U(T) / d U(0))^T d_lambda_T, U(0) being
- * the state at the start of the last hw_forward_ckpt and U(T) the state after it.  Each
- * k-step segment is recomputed from its checkpoint (bit for bit the recorded run) and
+ * the state at the start of the last hw_forward_ckpt and U(T) the state after it.  The last
+ * k-step segment is in the workspace already; each other one is recomputed from its
+ * checkpoint (bit for bit the recorded run), and the segments are
  * then reversed stage by stage.  Needs a recorded run (else HW_ESTATE); leaves the state
  * unchanged and may be called again with another d_lambda_T. */
 hw_status hw_adjoint(hw_solver* h, const double* d_lambda_T, double* d_grad_U0);
