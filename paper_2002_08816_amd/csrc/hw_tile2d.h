@@ -167,14 +167,14 @@ __device__ __forceinline__ void tile_of_block(int nx, int& bx, int& by) {
 }
 
 // KXRCF flags (Step 4; Euler: density or energy fires) on the positions [lo, LX - lo)^2
-// (lo = 1: tile+2, reading tile+3)
-template <int EQ>
+// (lo = 1: tile+2, reading tile+3), by TH threads
+template <int EQ, int TH = NT>
 __device__ __forceinline__ void flags_tile(const double* s_in, int tc_mode, double adv0, double adv1,
                                            double dx, double dy, double h, uint8_t* s_T,
                                            int lo = 1) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
   const int w = LX - 2 * lo;
-  for (int q = threadIdx.x; q < w * w; q += NT) {
+  for (int q = threadIdx.x; q < w * w; q += TH) {
     const int ly = lo + q / w, lx = lo + q % w;
     uint8_t t = 0;
     if (tc_mode == TC_ALL) {

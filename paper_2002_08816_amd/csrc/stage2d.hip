@@ -766,7 +766,9 @@ struct TileShared {
 // space of s_u is reused.  s_rtr: when not null, the HWENO values of hybrid ring cells that are
 // no mirror images, [NC][NGE][ring cell]; the tile's own hybrid cells' (and the mirror
 // images') are then those this workgroup stored in P.G before the call.
-template <int EQ, int NGE, int BK, int HB>
+// TH = 2 NT threads: the waves of the second half work on the same cells as those of the first
+// and take the ring cells and the y direction's traces over from them.
+template <int EQ, int NGE, int BK, int HB, int TH = NT>
 __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE, BK>& sh, double* s_u,
                                            const uint8_t* s_T, const uint8_t* s_H,
                                            const double* s_rtr, int bx, int by, double dtv) {
@@ -779,7 +781,10 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
   double* const s_spec = sh.spec;
   double* const s_red = sh.red;
   const double* const s_alpha = sh.alpha;
-  const int mode = P.mode, tid = threadIdx.x, nx = P.nx, ny = P.ny;
+  constexpr bool HELP = TH > NT;
+  static_assert(TH == NT || (TH == 2 * NT && BK == BK_RECT), "one or two threads per cell");
+  const bool main = !HELP || threadIdx.x < NT;
+  const int mode = P.mode, tid = threadIdx.x % NT, nx = P.nx, ny = P.ny;
   const double dt = mode != MODE_L ? dtv : 0.0;
   const int gx0 = bx * TX - HB, gy0 = by * TY - HB;
   const size_t plane = (size_t)nx * ny;
@@ -808,7 +813,7 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
   double Wn[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) Wn[f] = 0.0;
-  if ((mode == MODE_RK2 || mode == MODE_RK3) && active) {
+  if ((mode == MODE_RK2 || mode == MODE_RK3) && active && main) {
     const bool tn = tc && P.Tn[gi] != 0;
 #pragma unroll
     for (int f = 0; f < NF; ++f) Wn[f] = P.base[(size_t)f * plane + gi];
@@ -819,7 +824,7 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
   }
 
   double acc[NF];
-  {
+  if (main) {
     double inner[NC][9], ub[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -846,17 +851,17 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
 #pragma unroll
     for (int f = 0; f < NF; ++f) asm volatile("" : "+v"(acc[f]));
   }
-  if (mode == MODE_L && P.wout && active) {
+  if (mode == MODE_L && P.wout && active && main) {
 #pragma unroll
     for (int f = 0; f < NF; ++f) P.wout[(size_t)f * plane + gi] = S<W>(s_u, f, ly, lx);
   }
 
   if (s_rtr) __syncthreads();   // the workgroup's HWENO values are in place
   // ring cells (the tile's neighbours across the four sides of its mesh cells), all 64 by
-  // wave 0: lanes
+  // the first wave (of the helpers): lanes
   // 32 d .. 32 d + 31 those of direction d, the low side's high faces and the high side's
   // low faces
-  if (wv == 0) {
+  if (wv == 0 && (!HELP || !main)) {
     const int rd = lane / (2 * TX), rs = (lane / TX) & 1, rp = lane % TX;
     const int rly = rd == 0 ? HB + rp : (rs == 0 ? HB - 1 : HB + th);
     const int rlx = rd == 0 ? (rs == 0 ? HB - 1 : HB + tw) : HB + rp;
@@ -936,7 +941,31 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
   const double al0 = s_alpha[0], al1 = s_alpha[1];
   double E[2][2][2 * NC];
   int sp[2] = {0, 0};
-  if constexpr (NGE == 2) {
+  if constexpr (HELP) {
+    // x by the first half, y by the second
+    auto traces = [&](auto D) {
+      constexpr int dir = decltype(D)::value;
+      double tl[NC][NGE], th[NC][NGE];
+      if (!hyb) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          double in[19], f[hw2::NFOLD];
+          gather19<NC, W>(s_u, c, ly2, lx, in);
+          hw2::lin2d_fold(in, f);
+          lin_faces<NGE>(f, dir, tl[c], th[c]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 0, gx0, gy0, tl);
+        stored_trace<EQ, NGE, BK>(P, ly, lx, dir, 1, gx0, gy0, th);
+      }
+      const double al = dir == 0 ? al0 : al1, adv = dir == 0 ? P.adv0 : P.adv1;
+      face_sums<EQ, NGE, dir>(th, al, P.gam, adv, E[dir][0]);
+      face_sums<EQ, NGE, dir>(tl, -al, P.gam, adv, E[dir][1]);
+    };
+    if (main) traces(std::integral_constant<int, 0>());
+    else traces(std::integral_constant<int, 1>());
+  } else if constexpr (NGE == 2) {
     // both directions from one gather
     double xl[NC][NGE], xh[NC][NGE], yl[NC][NGE], yh[NC][NGE];
     if (!hyb) {
@@ -1004,10 +1033,22 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
   double* const own_blk = s_u + wv * NV * 64 + lane;
 #pragma unroll
   for (int dir = 0; dir < 2; ++dir) {
+    if (HELP && dir == 1) __syncthreads();   // the x sums are read: the helpers' y sums go there
+    if (!HELP || main == (dir == 0)) {
 #pragma unroll
-    for (int v = 0; v < 2 * NC; ++v) {
-      own_blk[v * 64] = E[dir][0][v];
-      own_blk[(2 * NC + v) * 64] = E[dir][1][v];
+      for (int v = 0; v < 2 * NC; ++v) {
+        own_blk[v * 64] = E[dir][0][v];
+        own_blk[(2 * NC + v) * 64] = E[dir][1][v];
+      }
+    }
+    if (HELP && dir == 1) __syncthreads();
+    if (HELP && !main) continue;
+    if (HELP && dir == 1) {
+#pragma unroll
+      for (int v = 0; v < 2 * NC; ++v) {
+        E[1][0][v] = own_blk[v * 64];
+        E[1][1][v] = own_blk[(2 * NC + v) * 64];
+      }
     }
     const double *lo, *hi;   // the low neighbour's high-face sums, the high neighbour's low-face sums
     if (dir == 0) {
@@ -1017,7 +1058,7 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
       lo = tx == 0 ? s_ring + ty : own_blk - 1;
       hi = tx == tw - 1 ? s_ring + TX + ty : own_blk + 2 * NC * 64 + 1;
     } else {
-      __syncthreads();
+      if (!HELP) __syncthreads();
       lo = (ty & 3) != 0 ? own_blk - TX : (wv == 0 ? s_ring + 2 * TX + tx : own_blk - NV * 64 + 48);
       hi = ty == th - 1 ? s_ring + 3 * TX + tx
                         : ((ty & 3) != 3 ? own_blk + 2 * NC * 64 + TX : own_blk + (NV + 2 * NC) * 64 - 48);
@@ -1064,7 +1105,7 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
       }
     }
   }
-  if (active) {
+  if (active && main) {
     if (P.flagsT) P.flagsT[gi] = s_T[ly * W + lx];
     if (P.flagsH) P.flagsH[gi] = s_H[ly * W + lx];
 #pragma unroll
@@ -1090,12 +1131,12 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
   if (mode != MODE_L) {
     // block maxima of both directions with one barrier
     const double w0 = wave_max(sp0), w1 = wave_max(sp1);
-    if (lane == 0) {
+    if (lane == 0 && main) {
       s_red[wv] = w0;
       s_red[4 + wv] = w1;
     }
     __syncthreads();
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
       const double m0 = fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]));
       const double m1 = fmax(fmax(s_red[4], s_red[5]), fmax(s_red[6], s_red[7]));
       const int e = blockIdx.x % ASPREAD;
@@ -1279,20 +1320,31 @@ __global__ __launch_bounds__(NT, 3) void stage2d_kernel(Stage2D P) {
 // hybrid cells of the tile and its ring.  The arithmetic is that of the four kernels.  Results
 // that outlast the stage (flags, masks, limited moments and edge values of the tile's own
 // cells, the list lengths, on request the lists) are stored as there.
+// With at most one tile per compute unit (256 tiles) a tile has two threads per cell: one wave
+// per SIMD cannot hide the latency of its own chains.  The second half of the waves takes its share
+// of the staging, the flags and the lists, and the ring cells and y traces of the tile phase.
+// Measured, us a stage, one thread per cell -> two: Euler NG 2 with shocks 32.2 -> 25.8 at 256^2,
+// 27.6 -> 21.6 at 64 x 48; smooth Euler NG 3 15.7 -> 14.1 at 160^2; Burgers NG 3 13.0 -> 11.2 at 80^2.
+// With more tiles than units the larger workgroup (172 VGPRs: one at a time on a unit) loses: us a
+// step, two threads / one, 131.7 / 129.3 at 288^2 and 133.4 / 125.9 at 320^2 Euler NG 2 with shocks, 102.8 / 84.0
+// at 288^2 smooth Euler NG 3, 62.0 / 47.0 at 288^2 advection.
 // The rule (one_launch below): at most 400 tiles for Euler, 1600 for scalar laws.  Measured,
-// us per step of three stages, one launch against four: scalar NG 3 with shocks 59 / 94 at 80^2 to 208^2,
-// 68 / 97 at 320^2, 92 / 118 at 512^2, 142 / 142 at 768^2 (2304 tiles); smooth Euler NG 3 65 / 84
-// at 160^2, 84 / 107 at 320^2 (400 tiles); Euler with shocks NG 2 127 / 133 at 160^2, 135 / 143 at 320^2,
-// 166 / 158 at 362^2 (529 tiles), 221 / 196 at 512^2: there two workgroups per CU (79 KB of LDS) run
-// several rounds, and the tiles a shock crosses do all their HWENO cells themselves.
+// us per step of three stages, one launch against four: Euler with shocks NG 2 105 / 136 at 256^2,
+// 126 / 152 at 320^2 (400 tiles), 159 / 160 at 362^2 (529), 208 / 200 at 512^2, NG 3 138 / 153, 172 / 170
+// and 235 / 215 at the last three: there two workgroups per CU (79 KB of LDS) run several rounds,
+// and the tiles a shock crosses do all their HWENO cells themselves; smooth Euler NG 3 65 / 84 at
+// 256^2, 87 / 111 at 320^2, 118 / 123 at 362^2, 217 / 205 at 640^2; Burgers NG 3 with shocks 54 / 97 at
+// 256^2, 88 / 121 at 512^2, 103 / 126 at 640^2 (1600 tiles), 127 / 150 at 768^2; advection NG 2 71 / 81 at 512^2,
+// 93 / 98 at 640^2, 107 / 114 at 768^2.
 
-// Appends the threads marked in m to a work list (no list: counts only), the length kept in a
-// 64-bit statistics entry: one atomic per workgroup that has something to append.
+// Appends the threads marked in m (of the workgroup's first four waves) to a work list (no list:
+// counts only), the length kept in a 64-bit statistics entry: one atomic per workgroup that has
+// something to append.
 __device__ __forceinline__ void block_append_stat(bool m, int value, long long* count, int* list,
                                                   int* s_wave /* 6 ints */) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const unsigned long long a = __ballot(m);
-  if (lane == 0) s_wave[w] = __popcll(a);
+  if (lane == 0 && w < NT / 64) s_wave[w] = __popcll(a);
   __syncthreads();
   const int tot = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
   if (!list) {   // uniform over the grid; the atomic's old value is not waited for
@@ -1381,8 +1433,8 @@ __device__ __forceinline__ double limited_value(const Stage2D& P, const double* 
   }
 }
 
-template <int EQ, int NGE>
-__global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
+template <int EQ, int NGE, int TH>
+__global__ __launch_bounds__(TH, 2) void stage2d_fused_kernel(Stage2D P) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
   constexpr int NF = 3 * NC;
   constexpr int NLIM = R2 * R2 * 2 * NC;         // limited moments of tile+2
@@ -1405,11 +1457,11 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
 
   // ---------------------------------------------------------------- stage input -> LDS
   {
-    constexpr int NR = (NPOS + NT - 1) / NT;
+    constexpr int NR = (NPOS + TH - 1) / TH;
     double v[NR][NF], sxr[NR], syr[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const int q = tid + r * NT;
+      const int q = tid + r * TH;
       if (q < NPOS) {
         const int ly = q / LX, lx = q - ly * LX;
         const int gx = map_index(gx0 + lx, nx, P.bcx, sxr[r]);
@@ -1423,7 +1475,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
     if (tid < 2) s_cnt[tid] = 0;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const int q = tid + r * NT;
+      const int q = tid + r * TH;
       if (q < NPOS) {
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
@@ -1439,7 +1491,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
 
   // ---------------------------------------------------------------- flags, masks, lists
   // flags of tile+2; a mirror image takes the flag of the cell it mirrors
-  flags_tile<EQ>(s_u, P.tc_mode, P.adv0, P.adv1, P.dx, P.dy, P.h, s_T);
+  flags_tile<EQ, TH>(s_u, P.tc_mode, P.adv0, P.adv1, P.dx, P.dy, P.h, s_T);
   __syncthreads();
   const bool walls = P.bcx != BC_PERIODIC || P.bcy != BC_PERIODIC;
   // the LDS position of the cell a mirror image copies (-1: outside the staged block, which
@@ -1454,7 +1506,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
     return (px < 1 || px >= LX - 1 || py < 1 || py >= LX - 1) ? -1 : py * LX + px;
   };
   if (walls) {
-    for (int q = tid; q < R2 * R2; q += NT) {
+    for (int q = tid; q < R2 * R2; q += TH) {
       const int ly = 1 + q / R2, lx = 1 + q % R2;
       if (!mirrored(P, gx0 + lx, gy0 + ly)) continue;
       double sx, sy;
@@ -1463,7 +1515,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
     }
     __syncthreads();
   }
-  for (int q = tid; q < R2 * R2; q += NT) {
+  for (int q = tid; q < R2 * R2; q += TH) {
     const int ly = 1 + q / R2, lx = 1 + q % R2, p = ly * LX + lx;
     const bool own = !(walls && mirrored(P, gx0 + lx, gy0 + ly));
     if (own && s_T[p]) s_fl[atomicAdd(&s_cnt[0], 1)] = (uint16_t)p;
@@ -1480,7 +1532,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
   }
   __syncthreads();
   const int tx = tid % TX, ty = tid / TX;
-  const bool inmesh = tx < tw && ty < th;
+  const bool inmesh = tx < tw && ty < th;   // (no cell for threads from NT on)
   const size_t gi = inmesh ? (size_t)(by * TY + ty) * nx + bx * TX + tx : 0;
   {
     const int p = (ty + HL) * LX + tx + HL;
@@ -1499,13 +1551,13 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
   // as in stage2d_limit_kernel; written back once every item has read unlimited values
   const int nfl = s_cnt[0], nhl = s_cnt[1];
   const int nlim = nfl * 2 * NC;
-  for (int it = tid; it < nlim; it += NT) {   // (whole groups of NC lanes)
+  for (int it = tid; it < nlim; it += TH) {   // (whole groups of NC lanes)
     const int f = it % NC, dir = (it / NC) & 1, p = s_fl[it / (2 * NC)];
     s_lim[it] = limited_value<EQ>(P, s_u, p, dir, f);
   }
   __syncthreads();
   if (nfl) {
-    for (int it = tid; it < nlim; it += NT) {
+    for (int it = tid; it < nlim; it += TH) {
       const int f = it % NC, dir = (it / NC) & 1, p = s_fl[it / (2 * NC)];
       const double v = s_lim[it];
       s_u[((1 + dir) * NC + f) * NPOS + p] = v;
@@ -1515,7 +1567,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
     }
     __syncthreads();
     if (walls) {
-      for (int q = tid; q < R2 * R2; q += NT) {
+      for (int q = tid; q < R2 * R2; q += TH) {
         const int ly = 1 + q / R2, lx = 1 + q % R2, p = ly * LX + lx;
         if (!s_T[p] || !mirrored(P, gx0 + lx, gy0 + ly)) continue;
         double sx, sy;
@@ -1536,7 +1588,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
   // go to P.G, the ring cells' towards the tile to LDS
   double* const s_rtr = s_lim;
   constexpr int CPW = 64 / NC;
-  for (int w = tid >> 6; w < 2 * ((nhl + CPW - 1) / CPW); w += NT / 64) {
+  for (int w = tid >> 6; w < 2 * ((nhl + CPW - 1) / CPW); w += TH / 64) {
     const int cell = (w >> 1) * CPW + lane / NC, f = lane % NC, dir = w & 1;
     if (cell >= nhl) continue;   // whole groups of NC lanes
     const int p = s_hl[cell], cy = p / LX - HL, cx = p % LX - HL;
@@ -1561,7 +1613,7 @@ __global__ __launch_bounds__(NT, 2) void stage2d_fused_kernel(Stage2D P) {
     }
   }
   // (stage_tile waits for these values after its volume phase)
-  stage_tile<EQ, NGE, BK_RECT, HL>(P, sh, s_u, s_T, s_H, s_rtr, bx, by, dtv);
+  stage_tile<EQ, NGE, BK_RECT, HL, TH>(P, sh, s_u, s_T, s_H, s_rtr, bx, by, dtv);
 }
 
 // Lax-Friedrichs speeds of a state (used before the first stage and by the operator-only
@@ -1624,6 +1676,8 @@ __global__ __launch_bounds__(NT) void dmr_table_kernel(Stage2D P) {
 
 // the rule of stage2d_fused_kernel (with troubled-cell detection; both sides measured there)
 constexpr int FUSED_TILES_EULER = 400, FUSED_TILES_SCALAR = 1600;
+// two threads per cell up to one tile per compute unit (measured there)
+constexpr int HELP_TILES = 256;
 static bool one_launch(int eq, const Stage2D* P) {
   const long long tiles = (long long)((P->nx + TX - 1) / TX) * ((P->ny + TY - 1) / TY);
   return P->bcx != BC_DMR && P->bcx != BC_STEP && tiles <= (eq == EQ_EULER ? FUSED_TILES_EULER : FUSED_TILES_SCALAR);
@@ -1645,7 +1699,13 @@ extern "C" hipError_t hw_launch_stage2d(int eq, int ng, const hw::Stage2D* P, hi
     HW_MARK(0);
     HW_MARK(1);
     HW_MARK(2);
-#define HW_LF(E, G) hipLaunchKernelGGL((hw::stage2d_fused_kernel<E, G>), grid, block, 0, s, *P)
+#define HW_LF(E, G)                                                                               \
+  do {                                                                                            \
+    if (grid.x <= hw::HELP_TILES)                                                                 \
+      hipLaunchKernelGGL((hw::stage2d_fused_kernel<E, G, 2 * hw::NT>), grid, dim3(2 * hw::NT), 0, s, *P); \
+    else                                                                                          \
+      hipLaunchKernelGGL((hw::stage2d_fused_kernel<E, G, hw::NT>), grid, block, 0, s, *P);        \
+  } while (0)
     if (eq == hw::EQ_EULER && ng == 2) HW_LF(hw::EQ_EULER, 2);
     else if (eq == hw::EQ_EULER && ng == 3) HW_LF(hw::EQ_EULER, 3);
     else if (eq == hw::EQ_BURGERS && ng == 2) HW_LF(hw::EQ_BURGERS, 2);

@@ -1,0 +1,71 @@
+"""The one-launch stage with two threads per cell (up to 256 tiles) and with one (more tiles):
+the same data on a mesh of the first kind and repeated on one of the second, and both against
+the oracle at the edge between them, with walls and ragged tiles.  Tolerance: the repository's
+bound of one operator evaluation."""
+import numpy as np
+import pytest
+
+import hweno_inputs as hi
+from oracle.physics import Equation
+from oracle.scheme2d import Scheme2D
+from parity import TOL, array_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hw():
+    import paper_2002_08816_amd as pkg
+    return pkg
+
+
+def state(eq, nx, ny):
+    U = hi.euler_wall_state(nx, ny, 4)
+    U[1:] *= 0.02
+    return U if eq == "euler" else np.ascontiguousarray(U[:, :1])
+
+
+@pytest.mark.parametrize("tc", ["kxrcf", "all"])
+@pytest.mark.parametrize("ng", [2, 3])
+@pytest.mark.parametrize("eq", ["euler", "burgers", "advection"])
+def test_two_threads_per_cell_equal_one(hw, eq, ng, tc):
+    n, k = 100, 3
+    U = state(eq, n, n)
+    out = []
+    for m in (1, k):
+        s = hw.Solver(2, m * n, m * n, domain=(0.0, float(m), 0.0, float(m)), eq=eq, adv=(0.7, -0.45),
+                      bc="periodic", ng_edge=ng, tc_mode=tc)
+        s.flag_export(True)
+        V = np.ascontiguousarray(np.tile(U, (1, 1, m, m)))
+        L, W = s.apply_operator(V)
+        F = s.flags(0)
+        s.set_state(V)
+        s.steps(2, dt=2e-4)
+        out.append((L, W, F, s.get_state()[0], s.stats()))
+        s.close()
+    (L, W, F, S, st), (Lk, Wk, Fk, Sk, stk) = out
+    for j, i in ((0, 0), (k - 1, 1)):
+        sl = np.s_[..., j * n:(j + 1) * n, i * n:(i + 1) * n]
+        assert np.array_equal(F[0], Fk[0][sl]) and np.array_equal(F[1], Fk[1][sl])
+        assert array_err(Lk[sl], L) < TOL and array_err(Wk[sl], W) < TOL and array_err(Sk[sl], S) < TOL
+    assert [m * k * k for m in st[1] + st[2]] == list(stk[1] + stk[2])
+    assert np.allclose(st[0], stk[0], rtol=1e-12, atol=0.0)
+
+
+@pytest.mark.parametrize("nx,ny", [(250, 241), (255, 258), (9, 40)])
+@pytest.mark.parametrize("eq,bc,ng", [("euler", ("reflective", "transmissive"), 2), ("euler", ("periodic", "transmissive"), 3),
+                                      ("burgers", ("periodic", "transmissive"), 3)])
+def test_both_forms_against_the_oracle(hw, eq, bc, ng, nx, ny):
+    h = 1.0 / ny
+    U = state(eq, nx, ny)
+    kw = dict(bc=bc, ng_edge=ng, tc_mode="kxrcf")
+    s = hw.Solver(2, nx, ny, domain=(0.0, nx * h, 0.0, 1.0), eq=eq, **kw)
+    s.flag_export(True)
+    L, W = s.apply_operator(U)
+    T, H = s.flags(0)
+    o = Scheme2D(Equation(eq, 2), nx, ny, 0.0, nx * h, 0.0, 1.0, **kw)
+    Lo, info = o.operator(U)
+    assert np.array_equal(T, info["T"]) and np.array_equal(H, info["H"])
+    assert array_err(L, Lo) < TOL
+    assert array_err(W, info["limited"]) < TOL
+    s.close()
