@@ -37,6 +37,10 @@ __device__ __forceinline__ double dflux(double u, double a) {
   else return a;
 }
 
+// Threads of the scalar reverse kernels: their per-cell phases run over the 324 cells of tile+1,
+// one round of 384 threads instead of two of 256
+constexpr int AT = 384;
+
 __device__ __forceinline__ int tq(int ly, int lx) { return (ly - 2) * R1 + (lx - 2); }
 
 // Transmissive sides (scalar laws): the LDS position (ly, lx) of the tile with origin
@@ -57,7 +61,7 @@ __device__ __forceinline__ bool ghost_lds(const Adj2D& P, int gx0, int gy0, int 
 // masks), as in the forward stage.  A ghost's mirror is never a ghost.
 __device__ __forceinline__ void mirror_ghost_bytes(const Adj2D& P, int gx0, int gy0, uint8_t* m, int lo) {
   const int w = LX - 2 * lo;
-  for (int q = threadIdx.x; q < w * w; q += NT) {
+  for (int q = threadIdx.x; q < w * w; q += AT) {
     const int ly = lo + q / w, lx = lo + q % w;
     int my, mx;
     bool fx, fy;
@@ -65,8 +69,13 @@ __device__ __forceinline__ void mirror_ghost_bytes(const Adj2D& P, int gx0, int 
   }
 }
 
+// Bound by the latency of its chains (80 KB of LDS and the registers of a reversed
+// reconstruction leave a compute unit one or two waves per SIMD).  Burgers NG 3 at 256^2 without hybrid
+// cells: 16.0 us with 256 threads, two rounds and both kinds of cells in one loop (more than
+// 256 VGPRs, accumulation registers among them); 9.8 us now.  With the stencil of the hybrid loop kept
+// across the directions it spilled 820 B a thread.
 template <int EQ, int NGE>
-__global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
+__global__ __launch_bounds__(AT, 2) void adjL2d_kernel(Adj2D P) {
   static_assert(EQ != EQ_EULER, "scalar equations only");
   constexpr int NQ = R1 * R1;                  // cells of tile+1
   __shared__ double s_in[3 * NPOS];            // stage input, then limited
@@ -91,24 +100,24 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
   // cell it mirrors in the gather
   const bool walls = P.bcx != BC_PERIODIC || P.bcy != BC_PERIODIC;
   reduce_speeds(P.alpha, s_alpha);
-  load_tiles<3, 1>(P.in, 0, s_in, P.lam, 1, s_lam, nx, ny, P.bcx, P.bcy, gx0, gy0);
+  load_tiles<3, 1, AT>(P.in, 0, s_in, P.lam, 1, s_lam, nx, ny, P.bcx, P.bcy, gx0, gy0);
   __syncthreads();
   if (walls) {
-    for (int q = tid; q < NPOS; q += NT) {
+    for (int q = tid; q < NPOS; q += AT) {
       int my, mx;
       bool fx, fy;
       if (ghost_lds(P, gx0, gy0, q / LX, q % LX, my, mx, fx, fy))
         s_lam[q] = s_lam[NPOS + q] = s_lam[2 * NPOS + q] = 0.0;
     }
   }
-  flags_tile<EQ>(s_in, P.tc_mode, P.adv0, P.adv1, P.dx, P.dy, P.h, s_T);
+  flags_tile<EQ, AT>(s_in, P.tc_mode, P.adv0, P.adv1, P.dx, P.dy, P.h, s_T);
   __syncthreads();
   if (walls) {
     mirror_ghost_bytes(P, gx0, gy0, s_T, 1);
     __syncthreads();
   }
-  if (P.tc_mode != TC_NONE) limit_tile<EQ>(s_in, s_T, 0.0, P.w);
-  hybrid_tile(s_T, s_H);
+  if (P.tc_mode != TC_NONE) limit_tile<EQ, AT>(s_in, s_T, 0.0, P.w);
+  hybrid_tile<AT>(s_T, s_H);
   __syncthreads();
 
   const double ax = s_alpha[0], ay = s_alpha[1];
@@ -116,8 +125,12 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
   const double* node = Gauss<NGE>::node;
   const double* wt = Gauss<NGE>::wt;
 
-  for (int q = tid; q < NQ; q += NT) {
+  // the stencil cotangents of one cell of tile+1, by its kind: a hybrid cell's reconstruction
+  // takes the registers of several linear ones, so the kinds have loops of their own
+  auto stencil_cotangents = [&](int q, auto kind) {
+    constexpr bool hyb = decltype(kind)::value;
     const int ly = 2 + q / R1, lx = 2 + q % R1;
+    if ((s_H[ly * LX + lx] != 0) != hyb) return;
     double in19[19], fold[hw2::NFOLD], d[19], fb[hw2::NFOLD];
 #pragma unroll
     for (int k = 0; k < 19; ++k) d[k] = 0.0;
@@ -130,7 +143,7 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
       if (ghost_lds(P, gx0, gy0, ly, lx, my, mx, fx, fy)) {
 #pragma unroll
         for (int k = 0; k < 19; ++k) s_d[k * NQ + q] = 0.0;
-        continue;
+        return;
       }
       const int gxq = gx0 + lx, gyq = gy0 + ly;
       if (P.bcx != BC_PERIODIC) wall |= (gxq == 0 ? 1 : 0) | (gxq == nx - 1 ? 2 : 0);
@@ -152,10 +165,9 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
       }
       hw2::lin2d_inner_T(ub, fb);
     }
-    const bool hyb = s_H[ly * LX + lx] != 0;
     double beta[5], om[5];
-    if (hyb) hweno2d_weights<NGE>(in19, fold, P.w, beta, om);
-#pragma unroll 1
+    if constexpr (hyb) hweno2d_weights<NGE>(in19, fold, P.w, beta, om);
+#pragma unroll
     for (int dir = 0; dir < 2; ++dir) {
       const int oy = dir, ox = 1 - dir;
       const double inv = dir == 0 ? idx : idy;
@@ -169,7 +181,7 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
       const double pU = S(s_lam, 0, ly + oy, lx + ox), pP = S(s_lam, fP, ly + oy, lx + ox),
                    pQ = S(s_lam, fQ, ly + oy, lx + ox);
       double v[2 * NGE];
-      if (hyb) hweno2d_combine<NGE>(in19, fold, P.w, dir, om, v);
+      if constexpr (hyb) hweno2d_combine<NGE>(in19, fold, P.w, dir, om, v);
       else lin_faces<NGE>(fold, dir, v, v + NGE);
       double ub[2 * NGE];
 #pragma unroll
@@ -188,20 +200,28 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
         if ((wall >> (2 * dir)) & 1) ub[k] += Flo * 0.5 * (dflux<EQ>(v[k], adv) + a);
         if ((wall >> (2 * dir + 1)) & 1) ub[NGE + k] += Fhi * 0.5 * (dflux<EQ>(v[NGE + k], adv) - a);
       }
-      if (hyb) hweno2d_field_adj<NGE>(in19, fold, P.w, dir, beta, om, ub, d);
+      if constexpr (hyb) {
+        int l2 = ly;   // opaque: the stencil is read again, not kept
+        asm volatile("" : "+v"(l2));
+        gather19<1>(s_in, 0, l2, lx, in19);
+        hw2::lin2d_fold(in19, fold);
+        hweno2d_field_adj<NGE>(in19, fold, P.w, dir, beta, om, ub, d);
+      }
       else lin_faces_T<NGE>(dir, ub, ub + NGE, fb);
     }
     hw2::lin2d_fold_T(fb, d);
 #pragma unroll
     for (int k = 0; k < 19; ++k) s_d[k * NQ + q] = d[k];
-  }
+  };
+  for (int q = tid; q < NQ; q += AT) stencil_cotangents(q, std::false_type());
+  for (int q = tid; q < NQ; q += AT) stencil_cotangents(q, std::true_type());
   __syncthreads();
 
   // gather: slot k of cell j's stencil refers to cell j + offset_k
   const int tx = tid % TX, ty = tid / TX;
   const int lx = tx + HL, ly = ty + HL;
   const int gx = gx0 + lx, gy = gy0 + ly;
-  if (gx >= nx || gy >= ny) return;
+  if (ty >= TY || gx >= nx || gy >= ny) return;
   double Wb[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int k = 0; k < 9; ++k) Wb[0] += s_d[k * NQ + tq(ly - (k / 3 - 1), lx - (k % 3 - 1))];
@@ -256,7 +276,7 @@ __global__ __launch_bounds__(NT) void adjL2d_kernel(Adj2D P) {
 }
 
 template <int EQ>
-__global__ __launch_bounds__(NT) void adjLim2d_kernel(Adj2D P) {
+__global__ __launch_bounds__(AT, 2) void adjLim2d_kernel(Adj2D P) {
   static_assert(EQ != EQ_EULER, "scalar equations only");
   constexpr int NQ = R1 * R1;
   __shared__ double s_in[3 * NPOS];
@@ -272,16 +292,16 @@ __global__ __launch_bounds__(NT) void adjLim2d_kernel(Adj2D P) {
   const size_t plane = (size_t)nx * ny;
 
   const bool walls = P.bcx != BC_PERIODIC || P.bcy != BC_PERIODIC;
-  load_tiles<3, 1>(P.in, 0, s_in, P.lam, 2, s_g, nx, ny, P.bcx, P.bcy, gx0, gy0);
+  load_tiles<3, 1, AT>(P.in, 0, s_in, P.lam, 2, s_g, nx, ny, P.bcx, P.bcy, gx0, gy0);
   __syncthreads();
-  flags_tile<EQ>(s_in, P.tc_mode, P.adv0, P.adv1, P.dx, P.dy, P.h, s_T);
+  flags_tile<EQ, AT>(s_in, P.tc_mode, P.adv0, P.adv1, P.dx, P.dy, P.h, s_T);
   __syncthreads();
   if (walls) {
     mirror_ghost_bytes(P, gx0, gy0, s_T, 1);
     __syncthreads();
   }
   const bool lim = P.tc_mode != TC_NONE;
-  for (int q = tid; q < NQ; q += NT) {
+  for (int q = tid; q < NQ; q += AT) {
     const int ly = 2 + q / R1, lx = 2 + q % R1;
     double gxv[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, gyv[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     int my, mx;
@@ -307,7 +327,7 @@ __global__ __launch_bounds__(NT) void adjLim2d_kernel(Adj2D P) {
   const int tx = tid % TX, ty = tid / TX;
   const int lx = tx + HL, ly = ty + HL;
   const int gx = gx0 + lx, gy = gy0 + ly;
-  if (gx >= nx || gy >= ny) return;
+  if (ty >= TY || gx >= nx || gy >= ny) return;
   const int qc = tq(ly, lx), qr = tq(ly, lx + 1), ql = tq(ly, lx - 1);
   const int qt = tq(ly + 1, lx), qb = tq(ly - 1, lx);
   const bool mine = lim && s_T[ly * LX + lx];
@@ -1399,7 +1419,7 @@ __global__ __launch_bounds__(NT) void adjElim2d_kernel(Adj2D P) {
 
 extern "C" hipError_t hw_launch_adj2d(int eq, int ng, const hw::Adj2D* P, hipStream_t s) {
   dim3 grid(((P->nx + hw::TX - 1) / hw::TX) * ((P->ny + hw::TY - 1) / hw::TY));
-  dim3 block(hw::NT);
+  dim3 block(hw::AT);
 #define HW_LA(E, G) hipLaunchKernelGGL((hw::adjL2d_kernel<E, G>), grid, block, 0, s, *P)
   if (eq == hw::EQ_BURGERS && ng == 2) HW_LA(hw::EQ_BURGERS, 2);
   else if (eq == hw::EQ_BURGERS && ng == 3) HW_LA(hw::EQ_BURGERS, 3);
@@ -1412,7 +1432,7 @@ extern "C" hipError_t hw_launch_adj2d(int eq, int ng, const hw::Adj2D* P, hipStr
 
 extern "C" hipError_t hw_launch_adjlim2d(int eq, const hw::Adj2D* P, hipStream_t s) {
   dim3 grid(((P->nx + hw::TX - 1) / hw::TX) * ((P->ny + hw::TY - 1) / hw::TY));
-  dim3 block(hw::NT);
+  dim3 block(hw::AT);
   if (eq == hw::EQ_BURGERS)
     hipLaunchKernelGGL(hw::adjLim2d_kernel<hw::EQ_BURGERS>, grid, block, 0, s, *P);
   else if (eq == hw::EQ_ADV)

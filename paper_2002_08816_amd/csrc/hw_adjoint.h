@@ -14,11 +14,11 @@ namespace hw {
 // null; halo widths loa and lob), boundary conditions applied: transmissive ghosts mirror
 // the cell and negate the normal moment.  Every global load of both is issued before any
 // LDS store, so the tiles cost one memory round trip.
-template <int NF, int NC>
+template <int NF, int NC, int TH = NT>
 __device__ __forceinline__ void load_tiles(const double* a, int loa, double* sa, const double* b,
                                            int lob, double* sb, int nx, int ny, int bcx, int bcy,
                                            int gx0, int gy0) {
-  constexpr int NR = (LX * LX + NT - 1) / NT;   // positions per thread, at most
+  constexpr int NR = (LX * LX + TH - 1) / TH;   // positions per thread, at most
   const size_t plane = (size_t)nx * ny;
   double va[NR][NF], vb[NR][NF];
   int pa[NR], pb[NR];
@@ -27,7 +27,7 @@ __device__ __forceinline__ void load_tiles(const double* a, int loa, double* sa,
     const int w = LX - 2 * lo;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const int q = threadIdx.x + r * NT;
+      const int q = threadIdx.x + r * TH;
       pos[r] = -1;
       if (q < w * w) {
         const int ly = lo + q / w, lx = lo + q % w;

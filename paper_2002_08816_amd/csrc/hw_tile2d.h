@@ -215,7 +215,7 @@ __device__ __forceinline__ void flags_tile(const double* s_in, int tc_mode, doub
 // dimension by dimension, characteristic-wise for Euler; Jacobi: every value from the
 // unmodified input, written back after a barrier.  Call only when tc_mode != TC_NONE (it
 // synchronises the block).
-template <int EQ>
+template <int EQ, int TH = NT>
 __device__ __forceinline__ void limit_tile(double* s_in, const uint8_t* s_T, double gam,
                                            const Weights& w, int lo = 1) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
@@ -225,7 +225,7 @@ __device__ __forceinline__ void limit_tile(double* s_in, const uint8_t* s_T, dou
   bool limdo[2] = {false, false};
 #pragma unroll
   for (int rep = 0; rep < 2; ++rep) {
-    const int q = tid + rep * NT;
+    const int q = tid + rep * TH;
     if (q >= rw * rw) break;
     const int ly = lo + q / rw, lx = lo + q % rw;
     if (!s_T[ly * LX + lx]) continue;
@@ -267,7 +267,7 @@ __device__ __forceinline__ void limit_tile(double* s_in, const uint8_t* s_T, dou
 #pragma unroll
   for (int rep = 0; rep < 2; ++rep) {
     if (!limdo[rep]) continue;
-    const int q = tid + rep * NT;
+    const int q = tid + rep * TH;
     const int ly = lo + q / rw, lx = lo + q % rw;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -279,9 +279,10 @@ __device__ __forceinline__ void limit_tile(double* s_in, const uint8_t* s_T, dou
 
 // hybrid mask: a flag anywhere in the 3x3 block (Step 5), on [lo, LX - lo)^2 (lo = 2:
 // tile+1)
+template <int TH = NT>
 __device__ __forceinline__ void hybrid_tile(const uint8_t* s_T, uint8_t* s_H, int lo = 2) {
   const int w = LX - 2 * lo;
-  for (int q = threadIdx.x; q < w * w; q += NT) {
+  for (int q = threadIdx.x; q < w * w; q += TH) {
     const int ly = lo + q / w, lx = lo + q % w;
     uint8_t hm = 0;
     for (int dy = -1; dy <= 1; ++dy)
