@@ -359,14 +359,15 @@ __global__ __launch_bounds__(AT, 2) void adjLim2d_kernel(Adj2D P) {
 //  adjEL2d    per tile cell j: the cotangents of j's nine interior values (volume
 //             quadrature through the transposed flux Jacobians) and of its edge values
 //             (the four faces' Lax-Friedrichs fluxes), pulled back through the transposed
-//             linear maps (Step 5.2) to j's 4 x 19 stencil values.  For a hybrid cell only
-//             the interior part; its edge cotangents are stored for the next pass.
+//             linear maps (Step 5.2) to j's 4 x 19 stencil values, which the tile sums by
+//             the position they refer to.  For a hybrid cell only the interior part; its
+//             edge cotangents are stored for the next pass.
 //  adjEhw2d   over the hybrid list, four lanes per cell and direction (lane f:
 //             characteristic field f and physical component f), the x and y directions in
 //             the two waves of a pair: the reversed characteristic HWENO combination (Step
-//             5.1, Remark 4), including the eigenvectors' dependence on the cell average,
-//             added to the stencil cotangents.
-//  adjEG2d    per cell: the gather of the stencil cotangents that refer to it,
+//             5.1, Remark 4), including the eigenvectors' dependence on the cell average:
+//             the hybrid cells' own 4 x 19 stencil cotangents.
+//  adjEG2d    per cell: the gather of the sums and the hybrid cells' stencil cotangents,
 //             out = cg lam + cl (dL/dW)^T lam + ca acc, and the running cotangent of u^n;
 //  adjEC2d    over the forward's flagged list: the reversed characteristic limiter of both
 //             directions (Step 4, Remark 4);
@@ -527,12 +528,33 @@ __device__ __forceinline__ void own_trace_face(int dir, int side, int cn, double
   for (int c = 0; c < NC; ++c) uo[c] += (c == cn ? -1.0 : 1.0) * ug[c];
 }
 
+// The tile kernel's sums: position (ly, lx) of tile + 1 of tile t, moment-major field f
+constexpr int W1 = TX + 2, NP1 = W1 * W1;
+__device__ __forceinline__ size_t sum_at(int t, int f, int ly, int lx) {
+  return ((size_t)t * 12 + f) * NP1 + ly * W1 + lx;
+}
+
+// Bound by memory before: the cells' 4 x 19 stencil cotangents went through global memory to
+// the gather (80 MB a launch at 256^2 written, and read by it), and one thread per cell held more
+// than 256 registers.  Now a tile adds them up in LDS by the position they refer to, two
+// components at a time, and stores 12 sums for each of its 18 x 18 positions; two threads work
+// on a cell: the first half of the workgroup takes the interior points, the second the edges,
+// and each pulls two components back to the stencil, after an exchange of the other two.
+// Measured with the two kernels that read the sums, us a launch, before -> now: 256^2 NG 2 with
+// shocks 21.3 -> 19.3, the hybrid cells' 24.4 -> 18.3 (its results are stored, not added), the
+// gather 14.3 -> 12.4; forward step 480 x 160 NG 3 43.5 -> 39.3, 35.0 -> 27.8, 23.0 -> 26.0.  Of the 19.3 the
+// staging and start take 6, the arithmetic 9, the sums 4; 200 VGPRs: one workgroup per CU, so the
+// 300 tiles of the latter mesh take two rounds.
 template <int NGE, int BND>
-__global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
+__global__ __launch_bounds__(2 * NT, 2) void adjEL2d_kernel(Adj2D P) {
   constexpr bool WALLS = BND == ADJ_WALLS;
   constexpr int NC = 4, NF = 12, W = TX + 2, NP = W * W;   // tile + one ghost layer
-  __shared__ double s_w[NF * NP];    // limited stage input
-  __shared__ double s_l[NF * NP];    // lam
+  constexpr int NXI = 2 * 9 * NT, NXE = 2 * 4 * NGE * NT;   // exchanged: interior, edge cotangents
+  constexpr int ND = 2 * 19 * NT;                           // two components' stencil cotangents
+  constexpr int NX = 2 * NF * NP > NXI + NXE ? 2 * NF * NP : NXI + NXE;
+  __shared__ double s_buf[NX > ND ? NX : ND];
+  double* const s_w = s_buf;             // limited stage input
+  double* const s_l = s_buf + NF * NP;   // lam
   __shared__ double s_alpha[2];
 
   const int tid = threadIdx.x;
@@ -545,7 +567,7 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
   reduce_speeds(P.alpha, s_alpha);
   // ghost positions: the mirrored cell's values with their factors, and no cotangent of
   // their own (lam = 0: a ghost is not updated)
-  for (int q = tid; q < NP; q += NT) {
+  for (int q = tid; q < NP; q += 2 * NT) {
     const int ly = q / W, lx = q - ly * W;
     if constexpr (BND >= ADJ_STEP) {
       const int px = gx0 + lx, py = gy0 + ly;
@@ -595,24 +617,71 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
   }
   __syncthreads();
 
-  const int tx = tid % TX, ty = tid / TX;
+  const bool first = tid < NT;   // (whole waves)
+  const int ct = tid % NT, tx = ct % TX, ty = ct / TX;
   const int lx = tx + 1, ly = ty + 1;
   const int gx = bx * TX + tx, gy = by * TY + ty;
-  if (gx >= nx || gy >= ny) return;   // no barrier below
   // the step's solid cells: no right-hand side (their stencil cotangents are never read)
-  if constexpr (BND == ADJ_STEP) {
-    if (step::solid(gx, gy, P.si, P.sj)) return;
-  }
-  const size_t gi = (size_t)gy * nx + gx;
-  const bool hyb = P.H && P.H[gi];
+  bool active = gx < nx && gy < ny;
+  if constexpr (BND == ADJ_STEP) active = active && !step::solid(gx, gy, P.si, P.sj);
+  const size_t gi = active ? (size_t)gy * nx + gx : 0;
+  const bool hyb = active && P.H && P.H[gi];
   const double idx = 1.0 / P.dx, idy = 1.0 / P.dy;
   const double* node = Gauss<NGE>::node;
   const double* wt = Gauss<NGE>::wt;
+  double* const x_int = s_buf + ct;          // [2][9][NT]: components 0, 1
+  double* const x_edge = s_buf + NXI + ct;   // [2][2][2 NGE][NT]: directions, components 2, 3
+  // component c's cotangents, pulled back to the stencil values, into this half's space
+  double* const s_d = s_buf + (first ? 0 : 19 * NT);
+  auto pull_back = [&](const double* ui, const double* e0, const double* e1) {
+    double d[19], fb[hw2::NFOLD];
+#pragma unroll
+    for (int k = 0; k < 19; ++k) d[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < hw2::NFOLD; ++k) fb[k] = 0.0;
+    hw2::lin2d_inner_T(ui, fb);
+    if (!hyb) {
+      lin_faces_T<NGE>(0, e0, e0 + NGE, fb);
+      lin_faces_T<NGE>(1, e1, e1 + NGE, fb);
+    }
+    hw2::lin2d_fold_T(fb, d);
+#pragma unroll
+    for (int k = 0; k < 19; ++k) s_d[k * NT + ct] = active ? d[k] : 0.0;
+  };
+  // the sums by position of the two components in LDS: c of the first half, c - 2 of the second
+  auto add_up = [&](int c) {
+    const int cy[5] = {-1, 0, 0, 0, 1}, cx[5] = {0, -1, 0, 1, 0};
+    for (int it = tid; it < 2 * NP1; it += 2 * NT) {
+      const int half = it >= NP1 ? 1 : 0, q = it - half * NP1, py = q / W1 - 1, px = q % W1 - 1;
+      const double* d = s_buf + half * 19 * NT;
+      double w[3] = {0.0, 0.0, 0.0};
+      // slot k of cell j's stencil refers to the position j + offset_k
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        const int oy = py - (k / 3 - 1), ox = px - (k % 3 - 1);
+        const bool in = (unsigned)oy < TY && (unsigned)ox < TX;   // (outside: read at 0, not added)
+        const double v = d[k * NT + (in ? oy * TX + ox : 0)];
+        w[0] += in ? v : 0.0;
+      }
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        const int oy = py - cy[k], ox = px - cx[k];
+        const bool in = (unsigned)oy < TY && (unsigned)ox < TX;
+        const int j = in ? oy * TX + ox : 0;
+        const double v = d[(9 + k) * NT + j], z = d[(14 + k) * NT + j];
+        w[1] += in ? v : 0.0;
+        w[2] += in ? z : 0.0;
+      }
+      const int cc = half ? c - 2 : c, t = by * ((nx + TX - 1) / TX) + bx;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) P.A[sum_at(t, m * NC + cc, q / W1, q % W1)] = w[m];
+    }
+  };
 
-  // volume terms of eq. ode2: the x moment gains (1/dx) sum w f(u(G)), the y moment
-  // (1/dy) sum w g(u(G)); cotangents of the interior values
-  double ubi[NC][9];
-  {
+  if (first) {
+    // volume terms of eq. ode2: the x moment gains (1/dx) sum w f(u(G)), the y moment
+    // (1/dy) sum w g(u(G)); cotangents of the interior values
+    double ubi[NC][9];
     double inner[NC][9];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -642,6 +711,27 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) ubi[c][p] = ub[c];
     }
+    __syncthreads();   // the staged values are done with
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int p = 0; p < 9; ++p) x_int[(c * 9 + p) * NT] = ubi[c][p];
+    __syncthreads();
+    double e[2][2][2 * NGE];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int dir = 0; dir < 2; ++dir)
+#pragma unroll
+        for (int k = 0; k < 2 * NGE; ++k) e[c][dir][k] = x_edge[((dir * 2 + c) * 2 * NGE + k) * NT];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      __syncthreads();   // what was in the space is read
+      pull_back(ubi[2 + c], e[c][0], e[c][1]);
+      __syncthreads();
+      add_up(2 + c);
+    }
+    return;
   }
 
   // edge values of both directions and the cotangents of the four faces' fluxes
@@ -748,23 +838,6 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
     }
   }
 
-  // pull back to the stencil values, component by component
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    double d[19], fb[hw2::NFOLD];
-#pragma unroll
-    for (int k = 0; k < 19; ++k) d[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < hw2::NFOLD; ++k) fb[k] = 0.0;
-    hw2::lin2d_inner_T(ubi[c], fb);
-    if (!hyb) {
-      lin_faces_T<NGE>(0, ube[0][c], ube[0][c] + NGE, fb);
-      lin_faces_T<NGE>(1, ube[1][c], ube[1][c] + NGE, fb);
-    }
-    hw2::lin2d_fold_T(fb, d);
-#pragma unroll
-    for (int k = 0; k < 19; ++k) P.D[(size_t)(c * 19 + k) * plane + gi] = d[k];
-  }
   if (hyb) {
 #pragma unroll
     for (int dir = 0; dir < 2; ++dir)
@@ -773,6 +846,26 @@ __global__ __launch_bounds__(NT) void adjEL2d_kernel(Adj2D P) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
           P.E[((size_t)(dir * 2 * NGE + k) * NC + c) * plane + gi] = ube[dir][c][k];
+  }
+  __syncthreads();   // the staged values are done with
+#pragma unroll
+  for (int dir = 0; dir < 2; ++dir)
+#pragma unroll
+    for (int c = 2; c < NC; ++c)
+#pragma unroll
+      for (int k = 0; k < 2 * NGE; ++k) x_edge[((dir * 2 + c - 2) * 2 * NGE + k) * NT] = ube[dir][c][k];
+  __syncthreads();
+  double ui[2][9];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int p = 0; p < 9; ++p) ui[c][p] = x_int[(c * 9 + p) * NT];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    __syncthreads();
+    pull_back(ui[c], ube[0][c], ube[1][c]);
+    __syncthreads();
+    add_up(2 + c);
   }
 }
 
@@ -934,8 +1027,8 @@ __device__ __forceinline__ void adjEhw2d_cell(const Adj2D& P, int gi, int f, dou
 
 // The hybrid list's reversed HWENO reconstruction: the waves of a workgroup form pairs, the
 // two waves of a pair take the same 16 cells, one the x direction, the other the y
-// direction, and the y wave hands its shares to the x wave through LDS, which adds both to
-// the stencil cotangents.  The two directions thus run side by side.
+// direction, and the y wave hands its shares to the x wave through LDS, which stores their
+// sum.  The two directions thus run side by side.
 // At most 256 VGPRs (two waves per SIMD), so that no value is kept in accumulation registers:
 // forms of this kernel that used them (up to 506 registers) returned stencil cotangents off by
 // 1e-9 on some inputs, and exact ones with the registers limited and nothing else changed.
@@ -968,188 +1061,166 @@ __global__ __launch_bounds__(NT, 2) void adjEhw2d_kernel(Adj2D P) {
     __syncthreads();
     if (on && dir == 0) {
 #pragma unroll
-      for (int k = 0; k < 19; ++k) P.D[(size_t)(f * 19 + k) * plane + gi] += ib[k] + s_x[wv + 1][k * 64 + lane];
+      for (int k = 0; k < 19; ++k) P.D[(size_t)(f * 19 + k) * plane + gi] = ib[k] + s_x[wv + 1][k * 64 + lane];
     }
     __syncthreads();
   }
 }
 
-// Gather of the stencil cotangents and the stage coefficients.
+// The tiles whose sums hold position q in [-1, n] of an axis of n cells, and its place in them
+// (b < 0: none): the tile it lies in or beside, the one it is the ring above of, the one it is
+// the ring below of (around a periodic axis too)
+struct AxisTiles {
+  int b[3], l[3];
+};
+__device__ __forceinline__ AxisTiles axis_tiles(int q, int n, bool periodic) {
+  const int nb = (n + TX - 1) / TX, b0 = q < 0 ? 0 : min(q / TX, nb - 1), r = q - b0 * TX;
+  AxisTiles a{{b0, -1, -1}, {r + 1, TX + 1, 0}};
+  if (r == 0 && b0 > 0) a.b[1] = b0 - 1;
+  if (r == TX - 1 && b0 + 1 < nb) a.b[2] = b0 + 1;
+  if (periodic && q == 0) {
+    a.b[1] = nb - 1;
+    a.l[1] = n - (nb - 1) * TX + 1;
+  }
+  if (periodic && q == n - 1) a.b[2] = 0;
+  return a;
+}
+
+// Gather of the stencil cotangents and the stage coefficients, one tile of cells per workgroup:
+// the tile kernel's sums of every tile that holds the cell's position, the hybrid
+// cells' stencil cotangents, and both at the ghosts and solid positions that take the
+// cell's values.  Four threads per cell, one per component: bound by the latency of
+// dependent loads (masks, then slots; more than one boundary position in a row beside the
+// step), which one thread per cell did not hide (19.0 us against 12.4 at 256^2, 42 against 26 on
+// the forward step at 480 x 160).
 template <int BND>
 __global__ __launch_bounds__(NT) void adjEG2d_kernel(Adj2D P) {
-  constexpr int NC = 4, NF = 12;
+  constexpr int NC = 4;
   constexpr bool WALLS = BND == ADJ_WALLS;
-  const int nx = P.nx, ny = P.ny;
+  const int nx = P.nx, ny = P.ny, ntx = (nx + TX - 1) / TX;
   const size_t plane = (size_t)nx * ny;
-  const size_t i = (size_t)blockIdx.x * NT + threadIdx.x;
-  if (i >= plane) return;
-  const int gy = (int)(i / nx), gx = (int)(i - (size_t)gy * nx);
-  // slot k of cell j's stencil refers to the position j + offset_k; the positions that hold
-  // this cell's values are the cell itself and, beside a transmissive or reflective side,
-  // the ghosts that mirror it (at most one per side, and the corner between two)
-  double Wb[NF];
+  // wave c of a workgroup: component c of 64 cells, four rows of a tile
+  const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int N = gridDim.x, xcd = blockIdx.x % NXCD, rem = N % NXCD;   // as tile_of_block
+  const int q4 = xcd * (N / NXCD) + min(xcd, rem) + blockIdx.x / NXCD, tile = q4 >> 2;
+  const int by = tile / ntx, bx = tile - by * ntx;
+  const int tx = lane % TX, ty = (q4 & 3) * 4 + lane / TX;
+  const int gx = bx * TX + tx, gy = by * TY + ty;
+  if (gx >= nx || gy >= ny) return;
+  const size_t i = (size_t)gy * nx + gx;
+  // a direction that wraps around (the resolver family's do not)
+  const bool px = BND < ADJ_STEP && !(WALLS && P.bcx != BC_PERIODIC);
+  const bool py = BND < ADJ_STEP && !(WALLS && P.bcy != BC_PERIODIC);
+  double Wb[3], l[3], ac[3];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) Wb[f] = 0.0;
-  const int cy[5] = {-1, 0, 0, 0, 1}, cx[5] = {0, -1, 0, 1, 0};
-  if constexpr (BND == ADJ_PERIODIC) {
+  for (int m = 0; m < 3; ++m) {
+    const size_t g = (size_t)(m * NC + c) * plane + i;
+    Wb[m] = P.A[sum_at(tile, m * NC + c, ty + 1, tx + 1)];
+    l[m] = P.lam[g];
+    ac[m] = P.ca != 0.0 || P.acc_mode == 2 ? P.acc_in[g] : 0.0;
+  }
+  // position q's sums in the tiles (all, or all but the cell's own) that hold it
+  auto add_sums = [&](int qx, int qy, bool own, auto factor) {
+    const AxisTiles ax = axis_tiles(qx, nx, px), ay = axis_tiles(qy, ny, py);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        if (ay.b[a] < 0 || ax.b[b] < 0 || (!own && a == 0 && b == 0)) continue;
+        const int t = ay.b[a] * ntx + ax.b[b];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) Wb[m] += factor(m) * P.A[sum_at(t, m * NC + c, ay.l[a], ax.l[b])];
+      }
+  };
+  const int cross[5] = {1, 3, 4, 5, 7};
+  // position q's slots of the hybrid cells around it
+  auto add_hybrid = [&](int qx, int qy, auto factor) {
+    if (!P.H) return;
+    size_t j[9];
+    bool h[9], any = false;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      const size_t j = (size_t)wrap(gy - (k / 3 - 1), ny) * nx + wrap(gx - (k % 3 - 1), nx);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) Wb[c] += P.D[(size_t)(c * 19 + k) * plane + j];
+      int oy = qy - (k / 3 - 1), ox = qx - (k % 3 - 1);
+      if (px) ox = wrap(ox, nx);
+      if (py) oy = wrap(oy, ny);
+      const bool in = ox >= 0 && ox < nx && oy >= 0 && oy < ny;
+      j[k] = in ? (size_t)oy * nx + ox : i;
+      h[k] = in && P.H[j[k]] != 0;
+      if constexpr (BND == ADJ_STEP) h[k] = h[k] && !step::solid(ox, oy, P.si, P.sj);
+      any = any || h[k];
     }
+    if (!any) return;
+    // every load issued (a slot that is no hybrid cell's is read and not added)
+    const double* D = P.D + (size_t)c * 19 * plane;
+    double u[9], v[5], w[5];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) u[k] = D[k * plane + j[k]];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const size_t j = (size_t)wrap(gy - cy[k], ny) * nx + wrap(gx - cx[k], nx);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        Wb[NC + c] += P.D[(size_t)(c * 19 + 9 + k) * plane + j];
-        Wb[2 * NC + c] += P.D[(size_t)(c * 19 + 14 + k) * plane + j];
-      }
+      v[k] = D[(9 + k) * plane + j[cross[k]]];
+      w[k] = D[(14 + k) * plane + j[cross[k]]];
     }
-  }
-  // the forward step: the positions that take this fluid cell's values are the cell itself
-  // and the non-fluid positions whose source it is (at most two cells away in x, one in y);
-  // slot k of a fluid cell j refers to the position j + offset_k
-  if constexpr (BND >= ADJ_STEP) {
-    if (fluid_of<BND>(P, gx, gy)) {
-      // the cell's own position: the slots of its fluid neighbours, with every load issued
-      // (a non-fluid owner's slot is read at this cell and not added)
 #pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        const int ox = gx - (k % 3 - 1), oy = gy - (k / 3 - 1);
-        const bool ok = fluid_of<BND>(P, ox, oy);
-        const size_t j = ok ? (size_t)oy * nx + ox : i;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const double v = P.D[(size_t)(c * 19 + k) * plane + j];
-          Wb[c] += ok ? v : 0.0;
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        const int ox = gx - cx[k], oy = gy - cy[k];
-        const bool ok = fluid_of<BND>(P, ox, oy);
-        const size_t j = ok ? (size_t)oy * nx + ox : i;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const double v = P.D[(size_t)(c * 19 + 9 + k) * plane + j];
-          const double w = P.D[(size_t)(c * 19 + 14 + k) * plane + j];
-          Wb[NC + c] += ok ? v : 0.0;
-          Wb[2 * NC + c] += ok ? w : 0.0;
-        }
-      }
-      // near a boundary: the non-fluid positions whose source the cell is
-      if (!interior_of<BND>(P, gx, gy))
-      for (int ey = -2; ey <= 2; ++ey)
-        for (int ex = -2; ex <= 2; ++ex) {
-          const int qx = gx + ex, qy = gy + ey;
-          if ((ex == 0 && ey == 0) || fluid_of<BND>(P, qx, qy)) continue;
-          const step::Src r = src_of<BND>(P, qx, qy);
-          if (r.pres || r.x != gx || r.y != gy) continue;
-#pragma unroll
-          for (int k = 0; k < 9; ++k) {
-            const int ox = qx - (k % 3 - 1), oy = qy - (k / 3 - 1);
-            if (!fluid_of<BND>(P, ox, oy)) continue;
-            const size_t j = (size_t)oy * nx + ox;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) Wb[c] += step_factor(r, 0, c) * P.D[(size_t)(c * 19 + k) * plane + j];
-          }
-#pragma unroll
-          for (int k = 0; k < 5; ++k) {
-            const int ox = qx - cx[k], oy = qy - cy[k];
-            if (!fluid_of<BND>(P, ox, oy)) continue;
-            const size_t j = (size_t)oy * nx + ox;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-              Wb[NC + c] += step_factor(r, 1, c) * P.D[(size_t)(c * 19 + 9 + k) * plane + j];
-              Wb[2 * NC + c] += step_factor(r, 2, c) * P.D[(size_t)(c * 19 + 14 + k) * plane + j];
-            }
-          }
-        }
-    }
-  }
-  const bool wx = WALLS && P.bcx != BC_PERIODIC, wy = WALLS && P.bcy != BC_PERIODIC;
-  if constexpr (WALLS) {
-    // the cell's own position, every load issued: owners wrap across a periodic side; a
-    // position beyond another side is no cell, its slot is read at this cell and not added
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      int oy = gy - (k / 3 - 1), ox = gx - (k % 3 - 1);
-      bool ok = true;
-      if (wy) ok = ok && oy >= 0 && oy < ny; else oy = wrap(oy, ny);
-      if (wx) ok = ok && ox >= 0 && ox < nx; else ox = wrap(ox, nx);
-      const size_t j = ok ? (size_t)oy * nx + ox : i;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double v = P.D[(size_t)(c * 19 + k) * plane + j];
-        Wb[c] += ok ? v : 0.0;
-      }
-    }
+    for (int k = 0; k < 9; ++k) Wb[0] += h[k] ? factor(0) * u[k] : 0.0;
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      int oy = gy - cy[k], ox = gx - cx[k];
-      bool ok = true;
-      if (wy) ok = ok && oy >= 0 && oy < ny; else oy = wrap(oy, ny);
-      if (wx) ok = ok && ox >= 0 && ox < nx; else ox = wrap(ox, nx);
-      const size_t j = ok ? (size_t)oy * nx + ox : i;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double v = P.D[(size_t)(c * 19 + 9 + k) * plane + j];
-        const double w = P.D[(size_t)(c * 19 + 14 + k) * plane + j];
-        Wb[NC + c] += ok ? v : 0.0;
-        Wb[2 * NC + c] += ok ? w : 0.0;
-      }
+      Wb[1] += h[cross[k]] ? factor(1) * v[k] : 0.0;
+      Wb[2] += h[cross[k]] ? factor(2) * w[k] : 0.0;
     }
-  }
-  // the ghosts that mirror the cell, beside a transmissive or reflective side
-  const int xs[3] = {gx, wx && gx == 0 ? -1 : INT_MIN, wx && gx == nx - 1 ? nx : INT_MIN};
-  const int ys[3] = {gy, wy && gy == 0 ? -1 : INT_MIN, wy && gy == ny - 1 ? ny : INT_MIN};
-  const bool edge = xs[1] != INT_MIN || xs[2] != INT_MIN || ys[1] != INT_MIN || ys[2] != INT_MIN;
-  for (int a = 0; a < 3 && WALLS && edge; ++a) {
-    if (ys[a] == INT_MIN) continue;
-    for (int b = 0; b < 3; ++b) {
-      if (xs[b] == INT_MIN || (a == 0 && b == 0)) continue;
-      const int qy = ys[a], qx = xs[b];
-      const bool mx = b > 0, my = a > 0;
-      // the owner of slot (dy, dx) that refers to (qy, qx): a mesh cell, or none
-      auto owner = [&](int dy, int dx, size_t& j) {
-        int oy = qy - dy, ox = qx - dx;
-        if (wy) { if (oy < 0 || oy >= ny) return false; } else oy = wrap(oy, ny);
-        if (wx) { if (ox < 0 || ox >= nx) return false; } else ox = wrap(ox, nx);
-        j = (size_t)oy * nx + ox;
-        return true;
-      };
+  };
+  bool fluid = true;
+  if constexpr (BND >= ADJ_STEP) fluid = fluid_of<BND>(P, gx, gy);
+  if (!fluid) {   // solid: what refers to its position belongs to its source
 #pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        size_t j;
-        if (!owner(k / 3 - 1, k % 3 - 1, j)) continue;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-          Wb[c] += mirror_factor(P, 0, c, mx, my) * P.D[(size_t)(c * 19 + k) * plane + j];
-      }
-#pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        size_t j;
-        if (!owner(cy[k], cx[k], j)) continue;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          Wb[NC + c] += mirror_factor(P, 1, c, mx, my) * P.D[(size_t)(c * 19 + 9 + k) * plane + j];
-          Wb[2 * NC + c] += mirror_factor(P, 2, c, mx, my) * P.D[(size_t)(c * 19 + 14 + k) * plane + j];
+    for (int m = 0; m < 3; ++m) Wb[m] = 0.0;
+  } else {
+    const bool rim = tx == 0 || tx == TX - 1 || ty == 0 || ty == TY - 1 || gx == nx - 1 || gy == ny - 1;
+    if (rim) add_sums(gx, gy, false, [](int) { return 1.0; });
+    add_hybrid(gx, gy, [](int) { return 1.0; });
+    if constexpr (BND >= ADJ_STEP) {
+      // beside a boundary: the non-fluid positions whose source the cell is and that a fluid
+      // cell's stencil holds, one layer deep: their source is the cell beside the boundary,
+      // and the next one where a step one cell wide meets the outflow
+      bool beside = gx == 0 || gx >= nx - 2 || gy == 0 || gy == ny - 1;
+      if constexpr (BND == ADJ_STEP) beside = beside || (gx >= P.si - 1 && gy <= P.sj);
+      if (beside)
+        for (int ey = -1; ey <= 1; ++ey)
+          for (int ex = -2; ex <= 2; ++ex) {
+            const int qx = gx + ex, qy = gy + ey;
+            if ((ex == 0 && ey == 0) || qx < -1 || qx > nx || qy < -1 || qy > ny || fluid_of<BND>(P, qx, qy)) continue;
+            const step::Src r = src_of<BND>(P, qx, qy);
+            if (r.pres || r.x != gx || r.y != gy) continue;
+            auto factor = [&](int m) { return step_factor(r, m, c); };
+            add_sums(qx, qy, true, factor);
+            add_hybrid(qx, qy, factor);
+          }
+    }
+    if constexpr (WALLS) {
+      // the ghosts that mirror the cell, beside a transmissive or reflective side (at most
+      // one per side, and the corner between two)
+      const int xs[3] = {gx, !px && gx == 0 ? -1 : INT_MIN, !px && gx == nx - 1 ? nx : INT_MIN};
+      const int ys[3] = {gy, !py && gy == 0 ? -1 : INT_MIN, !py && gy == ny - 1 ? ny : INT_MIN};
+      const bool edge = xs[1] != INT_MIN || xs[2] != INT_MIN || ys[1] != INT_MIN || ys[2] != INT_MIN;
+      for (int a = 0; a < 3 && edge; ++a) {
+        if (ys[a] == INT_MIN) continue;
+        for (int b = 0; b < 3; ++b) {
+          if (xs[b] == INT_MIN || (a == 0 && b == 0)) continue;
+          const bool mx = b > 0, my = a > 0;
+          auto factor = [&](int m) { return mirror_factor(P, m, c, mx, my); };
+          add_sums(xs[b], ys[a], true, factor);
+          add_hybrid(xs[b], ys[a], factor);
         }
       }
     }
   }
-  double G[NF];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    const double l = P.lam[f * plane + i];
-    double o = P.cg * l + P.cl * Wb[f];
-    if (P.ca != 0.0) o = fma(P.ca, P.acc_in[f * plane + i], o);
-    G[f] = o;
-    P.gw[f * plane + i] = o;
-    if (P.acc_mode == 1) P.acc_out[f * plane + i] = P.kl * l;
-    else if (P.acc_mode == 2) P.acc_out[f * plane + i] = fma(P.kl, l, P.acc_in[f * plane + i]);
+  for (int m = 0; m < 3; ++m) {
+    const size_t g = (size_t)(m * NC + c) * plane + i;
+    double o = P.cg * l[m] + P.cl * Wb[m];
+    if (P.ca != 0.0) o = fma(P.ca, ac[m], o);
+    P.gw[g] = o;
+    if (P.acc_mode == 1) P.acc_out[g] = P.kl * l[m];
+    else if (P.acc_mode == 2) P.acc_out[g] = fma(P.kl, l[m], ac[m]);
   }
 }
 
@@ -1449,9 +1520,9 @@ void launch_adjE(const hw::Adj2D* P, dim3 grid, dim3 cells, hipStream_t s) {
   // the limiter kernels share one instance between periodic sides and mirrors
   constexpr int LB = BND >= hw::ADJ_STEP ? BND : hw::ADJ_WALLS;
   const dim3 block(hw::NT);
-  hipLaunchKernelGGL((hw::adjEL2d_kernel<NGE, BND>), grid, block, 0, s, *P);
+  hipLaunchKernelGGL((hw::adjEL2d_kernel<NGE, BND>), grid, dim3(2 * hw::NT), 0, s, *P);
   if (P->counts) hipLaunchKernelGGL((hw::adjEhw2d_kernel<NGE, BND>), dim3(1024), block, 0, s, *P);
-  hipLaunchKernelGGL(hw::adjEG2d_kernel<BND>, cells, block, 0, s, *P);
+  hipLaunchKernelGGL(hw::adjEG2d_kernel<BND>, dim3(4 * grid.x), block, 0, s, *P);
   if (P->T) hipLaunchKernelGGL(hw::adjEC2d_kernel<LB>, dim3(1024), block, 0, s, *P);
   hipLaunchKernelGGL(hw::adjElim2d_kernel<LB>, cells, block, 0, s, *P);
 }

@@ -256,7 +256,7 @@ namespace hw {
 // U = (rho, m, n, E), with u = m / rho, v = n / rho, p = (gamma - 1)(E - (m u + n v) / 2).
 __device__ __forceinline__ void euler_flux2d_vjp(const double* U, double gam, const double* fb,
                                                  const double* gb, double* ub) {
-  const double r = 1.0 / U[0];
+  const double r = rcp_nr(U[0]);
   const double m = U[1], n = U[2], E = U[3];
   const double u = m * r, v = n * r;
   const double p = (gam - 1.0) * (E - 0.5 * (m * u + n * v));

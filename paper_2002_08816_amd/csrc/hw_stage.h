@@ -133,9 +133,10 @@ struct Adj2D {
                            // (flagged at [0], hybrid at [3]: a stage's entries of stats)
   const int* flist;        // flagged cells
   const int* hlist;        // hybrid cells
-  double* D;               // stencil cotangents of every cell [4][19][ny][nx]
+  double* D;               // stencil cotangents of hybrid cells [4][19][ny][nx]
   double* E;               // edge-value cotangents of hybrid cells [2 dir][2 NG][4][ny][nx]
   double* C;               // limiter cotangents of flagged cells [2 dir][5][4][ny][nx]
+  double* A;               // sums of the stencil cotangents by position [tile][3][4][18][18]
   double* gw;              // cotangent of the limited stage input [3][4][ny][nx]
 };
 

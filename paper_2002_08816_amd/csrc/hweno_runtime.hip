@@ -156,7 +156,7 @@ struct hw_solver {
   double* adt = nullptr;                  // device copy of the fixed step
   double *lam = nullptr, *mu = nullptr, *G = nullptr, *acc = nullptr;
   // 2D Euler reverse: stencil, hybrid edge-value and limiter cotangents
-  double *adjD = nullptr, *adjE = nullptr, *adjC = nullptr;
+  double *adjD = nullptr, *adjA = nullptr, *adjE = nullptr, *adjC = nullptr;
   // 2D Euler reverse with troubled-cell detection: every stage of the recorded segment
   // keeps what the forward's list passes computed on its input (flags, hybrid masks,
   // limited moments, HWENO edge values, work lists; [3 adj_k] stages) and its steps' list
@@ -482,7 +482,7 @@ extern "C" hw_status hw_destroy(hw_solver* h) {
                   h->t, h->steps, h->status, h->off, h->dxs, h->items,
                   h->flagsT[0], h->flagsT[1], h->flagsT[2], h->flagsH[0], h->flagsH[1], h->flagsH[2],
                   h->ckpt, h->hist, h->ahist, h->adt, h->lam, h->mu, h->G, h->acc,
-                  h->adjD, h->adjE, h->adjC, h->nu, h->dtab,
+                  h->adjD, h->adjA, h->adjE, h->adjC, h->nu, h->dtab,
                   h->recT, h->recH, h->recLim, h->recHwv, h->recWl, h->recStats, h->recDtab,
                   h->adj_times};
   for (void* p : ptrs)
@@ -1045,6 +1045,8 @@ static hw_status ensure_adj_work(hw_solver* h) {
   if (h->cfg.eq == HW_EULER) {
     const size_t cell = (size_t)h->ncell * sizeof(double);
     if (!h->adjD) HWCHK(hipMalloc(&h->adjD, 4 * 19 * cell));
+    const size_t tiles = (size_t)((h->cfg.nx + 15) / 16) * ((h->cfg.ny + 15) / 16);
+    if (!h->adjA) HWCHK(hipMalloc(&h->adjA, tiles * 12 * 18 * 18 * sizeof(double)));
     if (!h->adjC) HWCHK(hipMalloc(&h->adjC, 2 * 5 * 4 * cell));
     if (!h->adjE) HWCHK(hipMalloc(&h->adjE, 2 * 2 * (size_t)h->cfg.ng_edge * 4 * cell));
   }
@@ -1098,7 +1100,7 @@ static hw_status launch_adj(hw_solver* h, const double* in, const double* lam, c
       P.counts = h->wl; P.flist = h->wl + 2; P.hlist = h->wl + 2 + h->ncell;
     }
     P.gam = h->cfg.gamma_gas;
-    P.D = h->adjD; P.E = h->adjE; P.C = h->adjC;
+    P.D = h->adjD; P.A = h->adjA; P.E = h->adjE; P.C = h->adjC;
     P.gw = h->G;
     P.out = out;
     HWCHK(hw_launch_adj2d_euler(h->cfg.ng_edge, &P, h->stream));
