@@ -110,6 +110,28 @@ __device__ __forceinline__ void block_append2(bool ma, bool mb, int value, int* 
   }
 }
 
+// the flag of one fluid cell of the forward step's mesh, from memory
+template <int EQ>
+__device__ __forceinline__ uint8_t step_flag(const Stage2D& P, int gx, int gy) {
+  constexpr int NC = 4;
+  if (P.tc_mode == TC_ALL) return 1;
+  const size_t plane = (size_t)P.nx * P.ny, g0 = (size_t)gy * P.nx + gx;
+  const double velx = P.in[plane + g0] / P.in[g0], vely = P.in[2 * plane + g0] / P.in[g0];
+  uint8_t t = 0;
+  for (int c = 0; c < NC; c += NC - 1) {   // density, then energy
+    double v[5][3];
+    for (int k = 0; k < 5; ++k) {   // the cell, its left, right, lower and upper neighbours
+      const step::Src r = step::resolve(gx + (k == 2) - (k == 1), gy + (k == 4) - (k == 3), P.nx, P.ny, P.si, P.sj);
+      const size_t g = (size_t)r.y * P.nx + r.x;
+      v[k][0] = r.pres ? P.uin[c] : P.in[c * plane + g];
+      v[k][1] = r.pres ? 0.0 : r.sx * P.in[(NC + c) * plane + g];
+      v[k][2] = r.pres ? 0.0 : r.sy * P.in[(2 * NC + c) * plane + g];
+    }
+    if (kxrcf2d(v[0], v[1], v[2], v[3], v[4], velx, vely, P.dx, P.dy, P.h)) t = 1;
+  }
+  return t;
+}
+
 // KXRCF flags of every cell (Step 4, Remark 3; Euler: density or energy fires).  Each
 // tile stages only what the indicator reads, with two ghost layers, and evaluates the
 // flags of tile+1 so that it also knows its hybrid cells (a flag in the 3 x 3 block,
@@ -249,11 +271,14 @@ __global__ __launch_bounds__(NT) void stage2d_flags_kernel(Stage2D P) {
       if (q >= W1 * W1) break;
       const int ly = 1 + q / W1, lx = 1 + q % W1;
       if constexpr (BK == BK_STEP) {
-        // the flag of the source cell; a source outside the staged block only belongs to
-        // a position that no tile cell's 3 x 3 block holds
+        // the flag of the source cell; a source outside tile+1 only belongs to a position
+        // that no tile cell's 3 x 3 block holds, but for the step's corner cell, whose
+        // source lies across the corner
         const step::Src sr = step::resolve(gx0 + lx, gy0 + ly, nx, ny, P.si, P.sj);
         const int mx = sr.x - gx0, my = sr.y - gy0;
-        tg[r] = (!sr.pres && mx >= 0 && mx < L2 && my >= 0 && my < L2) ? s_T[my * L2 + mx] : 0;
+        tg[r] = 0;
+        if (!sr.pres && mx >= 1 && mx <= W1 && my >= 1 && my <= W1) tg[r] = s_T[my * L2 + mx];
+        else if (gx0 + lx == P.si && gy0 + ly == P.sj - 1) tg[r] = step_flag<EQ>(P, sr.x, sr.y);
       } else {
         const int mx = mirror1(gx0 + lx, nx, P.bcx) - gx0, my = mirror1(gy0 + ly, ny, P.bcy) - gy0;
         tg[r] = dmr_prescribed<BK>(P, gx0 + lx, gy0 + ly) ? 0 : s_T[my * L2 + mx];
