@@ -51,6 +51,14 @@ struct Stage2D {
   double* wout;           // optional export of the limited stage input
   int* status;            // bit 0: non-finite output, bit 1: rho <= 0 or p <= 0
   int keep_lists;         // one-launch stage: store the work lists too (a recorded stage)
+  // one-launch stages that run a whole step by themselves (sdt not null): stage 1 takes the
+  // time step from the speeds of u^n and stores it at sdt, stage 2 advances the time and the
+  // step count, and each stage clears the speeds its successor accumulates (azero) and
+  // publishes its predecessor's list lengths (pub; stats then only accumulates)
+  double *sdt, *st;
+  long long *ssteps, *pub;
+  unsigned long long* azero;
+  double fixed_dt, T_end, cfl;
   int nx, ny, bcx, bcy, tc_mode, mode;
   double dx, dy, h, gam, adv0, adv1;
   double idx, idy;        // 1/dx, 1/dy
@@ -146,6 +154,8 @@ extern "C" {
 // ev (may be null): three events recorded after the flags, limiter and HWENO launches
 // (for timing each launch; immediately one after another without troubled-cell detection)
 hipError_t hw_launch_stage2d(int eq, int ng, const hw::Stage2D* P, hipStream_t s, hipEvent_t* ev);
+// whether its stages are one launch each on such a mesh
+int hw_one_launch2d(int eq, int tc_mode, int bcx, int nx, int ny);
 // cells gx >= si, gy < sj are skipped (solid cells of the forward step; si = nx: none)
 hipError_t hw_launch_alpha2d(int eq, const double* U, int nx, int ny, double gam, double a0,
                              double a1, int si, int sj, unsigned long long* alpha_out,

@@ -90,6 +90,25 @@ __global__ void dt_kernel(int ninst, int ndir, int spread, const unsigned long l
   }
 }
 
+// The end of a recorded run on a mesh of one-launch stages: the last step's speeds and list
+// lengths become the handle's (the third stage's lengths where a step leaves them).
+__global__ void end_record_kernel(unsigned long long* alpha3, const unsigned long long* from, int n,
+                                  long long* stats, const long long* rec, int one) {
+  const int i = threadIdx.x;
+  for (int k = i; k < n; k += blockDim.x) alpha3[k] = from[k];
+  if (rec && i < 6) {
+    stats[i] = rec[i];
+    if (one && i % 3 == 2) stats[6 + i] = rec[i];
+  }
+}
+
+__global__ void begin_segment_kernel(unsigned long long* a, int na, const unsigned long long* a0, int w,
+                                     long long* stats, int ns) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < na) a[i] = a0 && i < w ? a0[i] : 0ull;
+  if (i < ns) stats[i] = 0;
+}
+
 // zeroes p[0..n) and, when q is not null, q[0], q[stride] .. q[(m - 1) stride]
 __global__ void zero_u64(unsigned long long* p, int n, unsigned long long* q, int m, int stride) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -114,7 +133,8 @@ struct hw_solver {
   double* hwv = nullptr;                 // 2D: HWENO edge values of hybrid cells
   double* dtab = nullptr;                // double Mach reflection: prescribed ghosts of a stage
   int* wl = nullptr;                     // 2D: work lists [2 counts][flagged][hybrid]
-  long long* stats = nullptr;            // 2D: list lengths of each stage of the last step [2][3]
+  long long* stats = nullptr;            // 2D: list lengths of each stage of the last step [2][3],
+                                         // then those that one-launch stages accumulate
   unsigned long long* alpha = nullptr;   // [4][aw] speed slots
   unsigned long long* alpha_op = nullptr;  // [aw]
   int aw = 1;                            // entries per slot: 1D ninst*ndir, 2D 2*ASPREAD
@@ -332,8 +352,8 @@ static hw_status alloc_common(hw_solver* h) {
     HWCHK(hipMalloc(&h->hwv, (size_t)4 * h->cfg.ng_edge * h->nc * h->ncell * sizeof(double)));
     HWCHK(hipMalloc(&h->wl, (2 + 2 * (size_t)h->ncell) * sizeof(int)));
     HWCHK(hipMemsetAsync(h->wl, 0, 2 * sizeof(int), h->stream));
-    HWCHK(hipMalloc(&h->stats, 6 * sizeof(long long)));
-    HWCHK(hipMemsetAsync(h->stats, 0, 6 * sizeof(long long), h->stream));
+    HWCHK(hipMalloc(&h->stats, 12 * sizeof(long long)));
+    HWCHK(hipMemsetAsync(h->stats, 0, 12 * sizeof(long long), h->stream));
   }
   if (h->cfg.bc_x == HW_BC_DMR)
     HWCHK(hipMalloc(&h->dtab, (size_t)12 * (4 * (h->cfg.nx + 4) + 4 * h->cfg.ny) * sizeof(double)));
@@ -556,6 +576,17 @@ static StageRec stage_rec(hw_solver* h, int r) {
   return q;
 }
 
+// A one-launch stage of a whole step (Stage2D's sdt and what follows it).  slots: the four speed
+// slots, of which each stage clears its successor's (null: cleared before)
+struct StepCtl {
+  double fixed_dt, T_end;
+  unsigned long long* slots;
+};
+// whether the handle's stages are one launch each and take care of their steps themselves
+static bool one_launch(const hw_solver* h) {
+  return h->dim == 2 && hw_one_launch2d(h->cfg.eq, h->cfg.tc_mode, h->cfg.bc_x, h->cfg.nx, h->cfg.ny);
+}
+
 static void stage1d_params(hw_solver* h, hw::Stage1D& P) {
   P.items = h->items; P.off = h->off; P.dxs = h->dxs;
   P.status = h->status;
@@ -570,7 +601,8 @@ static hw_status launch_stage(hw_solver* h, int mode, const double* in, const do
                               double* out, const unsigned long long* ain, unsigned long long* aout,
                               int fslot, double* wout, int persistent,
                               const double* dtp = nullptr, hipEvent_t* ev = nullptr,
-                              const StageRec* rec = nullptr) {
+                              const StageRec* rec = nullptr,
+                              const StepCtl* ctl = nullptr) {
   uint8_t* fT = (h->export_flags && fslot >= 0) ? h->flagsT[fslot] : nullptr;
   uint8_t* fH = (h->export_flags && fslot >= 0) ? h->flagsH[fslot] : nullptr;
   if (h->dim == 2) {
@@ -594,6 +626,15 @@ static hw_status launch_stage(hw_solver* h, int mode, const double* in, const do
       P.hlist = rec->wl + 2 + h->ncell;
       P.stats = rec->stats;
       P.keep_lists = 1;
+    }
+    if (ctl) {
+      P.sdt = h->dt; P.st = h->t; P.ssteps = h->steps;
+      P.fixed_dt = ctl->fixed_dt; P.T_end = ctl->T_end; P.cfl = h->cfg.cfl;
+      if (!rec) {
+        P.pub = h->stats;
+        P.stats = h->stats + 6;
+      }
+      if (ctl->slots) P.azero = ctl->slots + (mode == hw::MODE_RK1 ? 2 : (mode == hw::MODE_RK2 ? 3 : 1)) * h->aw;
     }
     P.alpha_in = ain; P.alpha_out = aout; P.dt = dtp ? dtp : h->dt;
     P.flagsT = fT; P.flagsH = fH; P.wout = wout; P.status = h->status;
@@ -624,7 +665,8 @@ static hw_status launch_stage(hw_solver* h, int mode, const double* in, const do
   return HW_OK;
 }
 
-// enqueue one step (dt kernel + three stages); fixed_dt > 0 fixes dt, T_end > 0 clips
+// enqueue one step (dt kernel, but for one-launch stages, + three stages); fixed_dt > 0 fixes
+// dt, T_end > 0 clips
 static void launch_dt(hw_solver* h, double fixed_dt, double T_end, const unsigned long long* from,
                       unsigned long long* alpha, long long* stats) {
   const double dy = h->dim == 2 ? (h->cfg.y1 - h->cfg.y0) / h->cfg.ny : 1.0;
@@ -663,15 +705,28 @@ static hw_status enqueue_steps_1d(hw_solver* h, long n, double fixed_dt, double 
   return HW_OK;
 }
 
+// stage st of a step; ev: as for launch_stage
+static hw_status enqueue_stage(hw_solver* h, int st, double fixed_dt, double T_end, int persistent, hipEvent_t* ev = nullptr) {
+  const int W = h->aw;
+  const double* ins[3] = {h->S0, h->S1, h->S2};
+  double* outs[3] = {h->S1, h->S2, h->S0};
+  const StepCtl ctl{fixed_dt, T_end, h->alpha};
+  const bool one = one_launch(h);
+  // (a one-launch stage 1 reads the speeds of u^n where the last stage left them)
+  return launch_stage(h, hw::MODE_RK1 + st, ins[st], h->S0, outs[st], h->alpha + (one && st == 0 ? 3 : st) * W,
+                      h->alpha + (st + 1) * W, st, nullptr, persistent, nullptr, ev, nullptr, one ? &ctl : nullptr);
+}
+
 static hw_status enqueue_step(hw_solver* h, double fixed_dt, double T_end, int persistent) {
   if (step1d_threads(h)) return enqueue_steps_1d(h, 1, fixed_dt, T_end);
-  const int W = h->aw;
-  launch_dt(h, fixed_dt, T_end);
-  HWCHK(hipGetLastError());
-  hw_status s;
-  if ((s = launch_stage(h, hw::MODE_RK1, h->S0, h->S0, h->S1, h->alpha, h->alpha + W, 0, nullptr, persistent)) != HW_OK) return s;
-  if ((s = launch_stage(h, hw::MODE_RK2, h->S1, h->S0, h->S2, h->alpha + W, h->alpha + 2 * W, 1, nullptr, persistent)) != HW_OK) return s;
-  if ((s = launch_stage(h, hw::MODE_RK3, h->S2, h->S0, h->S0, h->alpha + 2 * W, h->alpha + 3 * W, 2, nullptr, persistent)) != HW_OK) return s;
+  if (!one_launch(h)) {
+    launch_dt(h, fixed_dt, T_end);
+    HWCHK(hipGetLastError());
+  }
+  for (int st = 0; st < 3; ++st) {
+    hw_status s = enqueue_stage(h, st, fixed_dt, T_end, persistent);
+    if (s != HW_OK) return s;
+  }
   return HW_OK;
 }
 
@@ -795,9 +850,14 @@ extern "C" hw_status hw_get_stats(hw_solver* h, double* alpha, long* flagged, lo
     long f[3] = {-1, -1, -1}, hy[3] = {-1, -1, -1};
     if (h->dim == 2 && h->stats) {
       long long c[6];
+      long long c3[6];
+      const bool one = one_launch(h);   // the third stage's lengths are published by the next step
       HWCHK(hipMemcpyAsync(c, h->stats, sizeof c, hipMemcpyDeviceToHost, h->stream));
+      if (one) HWCHK(hipMemcpyAsync(c3, h->stats + 6, sizeof c3, hipMemcpyDeviceToHost, h->stream));
       hw_status s = sync(h);
       if (s != HW_OK) return s;
+      if (one)
+        for (int e = 2; e < 6; e += 3) c[e] = c3[e];
       for (int k = 0; k < 3; ++k) { f[k] = (long)c[k]; hy[k] = (long)c[3 + k]; }
     } else if (h->dim == 2 || h->cfg.tc_mode == HW_TC_NONE) {
       for (int k = 0; k < 3; ++k) f[k] = hy[k] = 0;
@@ -961,7 +1021,6 @@ extern "C" hw_status hw_profile_steps(hw_solver* h, int nsteps, double dt, doubl
                                      double* ms_step, double* ms_kernels) {
   if (!h) return fail(nullptr, HW_EINVAL, "null handle");
   if (nsteps <= 0) return fail(h, HW_EINVAL, "nsteps must be positive");
-  const int W = h->aw;
   // per stage five events: start, after flags, after limiter, after HWENO, end (2D); the
   // middle three coincide with the start in 1D
   const int ns = 3 * nsteps;
@@ -969,18 +1028,17 @@ extern "C" hw_status hw_profile_steps(hw_solver* h, int nsteps, double dt, doubl
   for (auto& e : ev) HWCHK(hipEventCreate(&e));
   HWCHK(hipEventRecord(ev[5 * ns], h->stream));
   for (int k = 0; k < nsteps; ++k) {
-    launch_dt(h, dt > 0.0 ? dt : 0.0, 0.0);
-    HWCHK(hipGetLastError());
-    const double* ins[3] = {h->S0, h->S1, h->S2};
-    double* outs[3] = {h->S1, h->S2, h->S0};
+    const double fixed_dt = dt > 0.0 ? dt : 0.0;
+    if (!one_launch(h)) {
+      launch_dt(h, fixed_dt, 0.0);
+      HWCHK(hipGetLastError());
+    }
     for (int st = 0; st < 3; ++st) {
       hipEvent_t* e = &ev[5 * (3 * k + st)];
       HWCHK(hipEventRecord(e[0], h->stream));
       if (h->dim == 1)
         for (int m = 1; m <= 3; ++m) HWCHK(hipEventRecord(e[m], h->stream));
-      hw_status s = launch_stage(h, hw::MODE_RK1 + st, ins[st], h->S0, outs[st], h->alpha + st * W,
-                                 h->alpha + (st + 1) * W, st, nullptr, 0, nullptr,
-                                 h->dim == 2 ? e + 1 : nullptr);
+      hw_status s = enqueue_stage(h, st, fixed_dt, 0.0, 0, h->dim == 2 ? e + 1 : nullptr);
       if (s != HW_OK) return s;
       HWCHK(hipEventRecord(e[4], h->stream));
     }
@@ -1133,7 +1191,7 @@ static double* seg_state(hw_solver* h, int seg, int i, int stage) {
 // the three stages of step i of segment seg into its workspace (out: the last one's output, null
 // to leave that stage out); slot0: flag export slot of the first stage, or -1
 static hw_status segment_stages(hw_solver* h, int seg, int i, const double* dtp, double* out, int slot0,
-                                const double* t) {
+                                const double* t, const StepCtl* ctl = nullptr) {
   static const int modes[3] = {hw::MODE_RK1, hw::MODE_RK2, hw::MODE_RK3};
   double* const S = seg_state(h, seg, i, 0);
   for (int q = 0; q < (out ? 3 : 2); ++q) {
@@ -1145,19 +1203,34 @@ static hw_status segment_stages(hw_solver* h, int seg, int i, const double* dtp,
     }
     hw_status s = launch_stage(h, modes[q], seg_state(h, seg, i, q), S, q < 2 ? seg_state(h, seg, i, q + 1) : out, a,
                                a + h->aw, slot0 < 0 ? -1 : slot0 + q, nullptr, 0, dtp, nullptr,
-                               h->recT ? &r : nullptr);
+                               h->recT ? &r : nullptr, ctl);
     if (s != HW_OK) return s;
   }
+  return HW_OK;
+}
+
+// speeds and list lengths of a segment of m steps start at zero, but for the speeds of its first
+// state, a copy of alpha0's (null: left to the caller)
+static hw_status begin_segment(hw_solver* h, int m, const unsigned long long* alpha0) {
+  const int na = (3 * m + 1) * h->aw;
+  hipLaunchKernelGGL(begin_segment_kernel, dim3((na + 255) / 256), dim3(256), 0, h->stream, h->ahist, na, alpha0, h->aw,
+                     h->recStats, h->recT ? 6 * m : 0);
+  HWCHK(hipGetLastError());
   return HW_OK;
 }
 
 // step i of segment seg, advancing the handle like enqueue_step and keeping the segment's
 // history; last: the run's last step, whose result is the handle's state
 static hw_status record_step(hw_solver* h, int seg, int i, double dt, bool last) {
+  double* out = last ? h->S0 : seg_state(h, seg, i + 1, 0);
+  if (one_launch(h)) {   // (its speeds and list lengths were cleared for the whole segment)
+    const StepCtl ctl{dt, 0.0, nullptr};
+    return segment_stages(h, seg, i, h->dt, out, 0, nullptr, &ctl);
+  }
   unsigned long long* a = h->ahist + 3 * (size_t)i * h->aw;
-  launch_dt(h, dt, 0.0, i == 0 ? h->alpha + 3 * h->aw : a, a, h->recStats ? h->recStats + 6 * (size_t)i : h->stats);
+  launch_dt(h, dt, 0.0, a, a, h->recStats ? h->recStats + 6 * (size_t)i : h->stats);
   HWCHK(hipGetLastError());
-  return segment_stages(h, seg, i, h->dt, last ? h->S0 : seg_state(h, seg, i + 1, 0), 0, nullptr);
+  return segment_stages(h, seg, i, h->dt, out, 0, nullptr);
 }
 
 extern "C" hw_status hw_forward_ckpt(hw_solver* h, int nsteps, double dt, int k) {
@@ -1231,6 +1304,7 @@ extern "C" hw_status hw_forward_ckpt(hw_solver* h, int nsteps, double dt, int k)
     if (n % k == 0)
       HWCHK(hipMemcpyAsync(h->ckpt + (size_t)(n / k) * st, h->S0, st * sizeof(double),
                            hipMemcpyDeviceToDevice, h->stream));
+    if (n == n0 && (s = begin_segment(h, nsteps - n0, h->alpha + 3 * h->aw)) != HW_OK) return s;
     if ((s = n < n0 ? enqueue_step(h, dt, 0.0, 0) : record_step(h, seg, n - n0, dt, n == nsteps - 1)) != HW_OK)
       return s;
     // the step's time after its dt update: the prescribed data of its stages in the replay
@@ -1239,11 +1313,10 @@ extern "C" hw_status hw_forward_ckpt(hw_solver* h, int nsteps, double dt, int k)
   }
   // the handle's speeds and list lengths are those of the last step
   const int m = nsteps - n0;
-  HWCHK(hipMemcpyAsync(h->alpha + 3 * h->aw, h->ahist + 3 * (size_t)m * h->aw, h->aw * sizeof(unsigned long long),
-                       hipMemcpyDeviceToDevice, h->stream));
-  if (h->recStats)
-    HWCHK(hipMemcpyAsync(h->stats, h->recStats + (size_t)(m - 1) * 6, 6 * sizeof(long long),
-                         hipMemcpyDeviceToDevice, h->stream));
+  hipLaunchKernelGGL(end_record_kernel, dim3(1), dim3(128), 0, h->stream, h->alpha + 3 * h->aw,
+                     h->ahist + 3 * (size_t)m * h->aw, h->aw, h->stats,
+                     h->recStats ? h->recStats + (size_t)(m - 1) * 6 : (const long long*)nullptr, one_launch(h) ? 1 : 0);
+  HWCHK(hipGetLastError());
   int bad = 0;
   if ((s = read_status(h, &bad)) != HW_OK) return s;
   if (bad) return fail(h, HW_ENONFINITE, "non-finite value in the recorded forward run");
@@ -1269,11 +1342,7 @@ extern "C" hw_status hw_adjoint(hw_solver* h, const double* d_lambda_T, double* 
     if (seg != h->adj_seg) {
       // replay the segment, keeping its stage inputs and speeds
       h->adj_seg = -1;
-      const int na = (3 * m + 1) * h->aw;
-      // the segment's speeds and its recorded stages' list lengths start at zero
-      hipLaunchKernelGGL(zero_u64, dim3((na + 255) / 256), dim3(256), 0, h->stream, h->ahist, na,
-                         (unsigned long long*)h->recStats, rec ? 6 * m : 0, 1);
-      HWCHK(hipGetLastError());
+      if ((s = begin_segment(h, m, nullptr)) != HW_OK) return s;
       if ((s = launch_alpha(h, seg_state(h, seg, 0, 0), h->ahist)) != HW_OK) return s;
       for (int i = 0; i < m; ++i) {
         // the segment's end state is not read: its last stage runs only for what it records

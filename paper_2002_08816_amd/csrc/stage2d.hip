@@ -1345,6 +1345,8 @@ __global__ __launch_bounds__(NT, 3) void stage2d_kernel(Stage2D P) {
 // hybrid cells of the tile and its ring.  The arithmetic is that of the four kernels.  Results
 // that outlast the stage (flags, masks, limited moments and edge values of the tile's own
 // cells, the list lengths, on request the lists) are stored as there.
+// Such stages run a step by themselves (Stage2D's sdt): a launch that only sets the time step,
+// clears the speeds and advances the time costs its latency and a gap, 3 of 45 us a step at 80^2.
 // With at most one tile per compute unit (256 tiles) a tile has two threads per cell: one wave
 // per SIMD cannot hide the latency of its own chains.  The second half of the waves takes its share
 // of the staging, the flags and the lists, and the ring cells and y traces of the tile phase.
@@ -1472,7 +1474,9 @@ __global__ __launch_bounds__(TH, 2) void stage2d_fused_kernel(Stage2D P) {
   __shared__ TileShared<EQ, NGE, BK_RECT> sh;
 
   const int mode = P.mode, tid = threadIdx.x, nx = P.nx, ny = P.ny;
-  const double dtv = *P.dt;   // (valid in every mode; zero: the run has reached its final time)
+  const bool begin = mode == MODE_RK1 && P.sdt;   // this stage sets the time step
+  double dtv = begin ? 1.0 : *P.dt;   // (valid in every mode; zero: the run has reached its final time)
+  const double t0 = begin ? *P.st : 0.0;
   int bx, by;
   tile_of_block(nx, bx, by);
   const int gx0 = bx * TX - HL, gy0 = by * TY - HL;
@@ -1513,6 +1517,29 @@ __global__ __launch_bounds__(TH, 2) void stage2d_fused_kernel(Stage2D P) {
   }
   reduce_speeds(P.alpha_in, sh.alpha);
   __syncthreads();
+  if (P.sdt) {   // (uniform over the grid)
+    if (begin) {
+      dtv = P.fixed_dt > 0.0 ? P.fixed_dt : P.cfl / (sh.alpha[0] / P.dx + sh.alpha[1] / P.dy);
+      if (P.T_end > 0.0) {
+        if (t0 >= P.T_end) dtv = 0.0;
+        else if (t0 + dtv > P.T_end) dtv = P.T_end - t0;
+      }
+      if (blockIdx.x == 0 && tid == 0) *P.sdt = dtv;   // (read by the later stages)
+      if (dtv == 0.0) return;   // uniform over the grid
+    }
+    if (blockIdx.x == 0) {
+      if (mode == MODE_RK2 && tid == 0 && dtv > 0.0) {   // (no other stage reads these)
+        *P.st += dtv;
+        *P.ssteps += 1;
+      }
+      if (P.azero && tid < 2 * ASPREAD) P.azero[tid] = 0ull;
+      if (P.pub && tid < 2) {
+        const int e = 3 * tid + (mode + 2 - MODE_RK1) % 3;   // the stage before
+        if (mode != MODE_RK1) P.pub[e] = P.stats[e];
+        P.stats[e] = 0;
+      }
+    }
+  }
 
   // ---------------------------------------------------------------- flags, masks, lists
   // flags of tile+2; a mirror image takes the flag of the cell it mirrors
@@ -1703,14 +1730,19 @@ __global__ __launch_bounds__(NT) void dmr_table_kernel(Stage2D P) {
 constexpr int FUSED_TILES_EULER = 400, FUSED_TILES_SCALAR = 1600;
 // two threads per cell up to one tile per compute unit (measured there)
 constexpr int HELP_TILES = 256;
-static bool one_launch(int eq, const Stage2D* P) {
-  const long long tiles = (long long)((P->nx + TX - 1) / TX) * ((P->ny + TY - 1) / TY);
-  return P->bcx != BC_DMR && P->bcx != BC_STEP && tiles <= (eq == EQ_EULER ? FUSED_TILES_EULER : FUSED_TILES_SCALAR);
+static bool one_launch(int eq, int tc_mode, int bcx, int nx, int ny) {
+  const long long tiles = (long long)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
+  return tc_mode != TC_NONE && bcx != BC_DMR && bcx != BC_STEP &&
+         tiles <= (eq == EQ_EULER ? FUSED_TILES_EULER : FUSED_TILES_SCALAR);
 }
 
 }  // namespace hw
 
 // ------------------------------------------------------------------ launch wrappers
+extern "C" int hw_one_launch2d(int eq, int tc_mode, int bcx, int nx, int ny) {
+  return hw::one_launch(eq, tc_mode, bcx, nx, ny) ? 1 : 0;
+}
+
 extern "C" hipError_t hw_launch_stage2d(int eq, int ng, const hw::Stage2D* P, hipStream_t s,
                                         hipEvent_t* ev) {
   dim3 grid(((P->nx + hw::TX - 1) / hw::TX) * ((P->ny + hw::TY - 1) / hw::TY));
@@ -1720,7 +1752,7 @@ extern "C" hipError_t hw_launch_stage2d(int eq, int ng, const hw::Stage2D* P, hi
   const int wgrid = 2048;
 #define HW_MARK(i) \
   if (ev && hipEventRecord(ev[i], s) != hipSuccess) return hipErrorLaunchFailure
-  if (pre && hw::one_launch(eq, P)) {
+  if (hw::one_launch(eq, P->tc_mode, P->bcx, P->nx, P->ny)) {
     HW_MARK(0);
     HW_MARK(1);
     HW_MARK(2);

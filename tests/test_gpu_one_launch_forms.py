@@ -69,3 +69,42 @@ def test_both_forms_against_the_oracle(hw, eq, bc, ng, nx, ny):
     assert array_err(L, Lo) < TOL
     assert array_err(W, info["limited"]) < TOL
     s.close()
+
+
+@pytest.mark.parametrize("eq,n", [("euler", 40), ("burgers", 300)])
+def test_one_launch_steps_by_every_call(hw, eq, n):
+    """The stages set the time step, the time, the step count, the speeds and the list lengths by
+    themselves: one state advanced by steps(), step(), profile() and run() is the same, bit for
+    bit, and the oracle's."""
+    U = state(eq, n, n)
+    kw = dict(bc="periodic", ng_edge=2, tc_mode="kxrcf")
+    s = hw.Solver(2, n, n, eq=eq, **kw)
+    s.set_state(U)
+    s.steps(11)
+    ref, t = s.get_state()
+    stats = s.stats()
+    assert s.time() == (t, 11)
+    s.set_state(U)
+    s.steps(3)
+    s.step()
+    s.profile(2)
+    s.apply_operator(U)          # leaves the state and its speeds alone
+    s.steps(4)
+    s.step()
+    got, t2 = s.get_state()
+    assert np.array_equal(got, ref) and t2 == t and s.time() == (t, 11)
+    for a, b in zip(s.stats(), stats):
+        assert np.array_equal(np.asarray(a), np.asarray(b))
+    s.set_state(U)
+    steps, T = s.run(t)
+    assert T == t and abs(steps - 11) <= 1 and np.abs(s.get_state()[0] - ref).max() < 1e-12 * np.abs(ref).max()
+    s.steps(2)                   # past the final time of the run before
+    assert s.time()[1] == steps + 2 and s.time()[0] > t
+    s.set_state(U)
+    s.steps(2, dt=1e-4)
+    o = Scheme2D(Equation(eq, 2), n, n, 0.0, 1.0, 0.0, 1.0, **kw)
+    V = U
+    for _ in range(2):
+        V, _ = o.rk3_step(V, 1e-4)
+    assert array_err(s.get_state()[0], V) < TOL and abs(s.time()[0] - 2e-4) < 1e-18
+    s.close()
