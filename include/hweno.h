@@ -210,8 +210,8 @@ hw_status hw_profile_steps(hw_solver* h, int nsteps, double dt, double* ms_stage
 hw_status hw_batch_steps(hw_solver* h, int nsteps, int persistent);
 
 /* Autotuner of the batched stage: times one captured step (3 replays after a warm-up)
- * on the handle's own workload for every tile width (64, 128, 256, 512 cells = 1, 2, 4, 8
- * waves per workgroup) and launch form (one workgroup per tile; persistent grids of
+ * on the handle's own workload for every tile width (64, 128, 256, 512 positions = 1, 2, 4,
+ * 8 waves per workgroup; six of them ghosts) and launch form (one workgroup per tile; persistent grids of
  * 1, 2, 4, 8 workgroups per compute unit), keeps the fastest for later calls, and leaves
  * the state, times and step counts as they were.  choice (may be NULL) receives three
  * ints: tile width, persistent (0/1), persistent grid size (0 when not persistent).  The

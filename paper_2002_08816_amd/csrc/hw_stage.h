@@ -72,6 +72,9 @@ struct Stage2D {
   Weights w;
 };
 
+// positions of a 1D tile that are ghosts: a tile of T threads yields T - 6 cells
+constexpr int TILE1D_GHOSTS = 6;
+
 // One-dimensional stage, single or batched (see stage1d.hip).
 struct Stage1D {
   const double* in;        // [2][nc][total]  (averages, first moments; instances concatenated)

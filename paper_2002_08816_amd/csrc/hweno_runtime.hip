@@ -152,7 +152,7 @@ struct hw_solver {
   double* dxs = nullptr;
   int2* items = nullptr;                 // (instance, first cell) of every tile
   int nitems = 0;
-  int tile1d = 256;                      // cells per 1D tile (= threads per workgroup)
+  int tile1d = 256;                      // positions per 1D tile (= threads per workgroup)
   int pgrid = 0;                         // persistent grid (0: default)
   int auto_persist = 1;                  // launch form chosen by hw_batch_tune
   std::vector<int> h_off;
@@ -377,7 +377,7 @@ static hw_status alloc_common(hw_solver* h) {
 static hw_status build_items(hw_solver* h, int tile) {
   std::vector<int2> items;
   for (int b = 0; b < h->ninst; ++b)
-    for (int i0 = 0; i0 < h->h_off[b + 1] - h->h_off[b]; i0 += tile) items.push_back(make_int2(b, i0));
+    for (int i0 = 0; i0 < h->h_off[b + 1] - h->h_off[b]; i0 += tile - hw::TILE1D_GHOSTS) items.push_back(make_int2(b, i0));
   if (h->items) HWCHK(hipFree(h->items));
   h->items = nullptr;
   h->nitems = 0;

@@ -1,12 +1,14 @@
 // Fused one-dimensional stage kernel of the hybrid Hermite WENO scheme
 // (Zhao & Qiu, arXiv 2002.08816, Section 2.1, Steps 1-3 and eq. odeH).
 //
-// A workgroup (T threads, one per cell; T = 64, 128, 256 or 512) processes one tile of T
-// cells of one instance: the tile plus three ghost layers is staged in LDS, then KXRCF flags
+// A workgroup (T threads; T = 64, 128, 256 or 512) processes one tile of one instance, one
+// position per thread: T - 6 cells and three ghost layers on either side are staged in LDS,
+// then KXRCF flags
 // (tile+2), the Step-1 limiter on flagged cells (Jacobi, characteristic-wise for Euler),
 // the hybrid mask (tile+1), interface values (Step 2.2 linear or Step 2.1 HWENO) and
-// interior Gauss-Lobatto values (Step 2.3), Lax-Friedrichs fluxes exchanged through
-// LDS, the four-point Gauss-Lobatto volume term, and the TVD-RK3 stage combination.
+// interior Gauss-Lobatto values (Step 2.3), each side's share of the Lax-Friedrichs fluxes
+// exchanged through LDS, the four-point Gauss-Lobatto volume term, and the TVD-RK3 stage
+// combination.
 //
 // The same tile routine serves a single solver (one instance) and the batched form: many
 // independent instances of different sizes, concatenated field by field, advanced by a
@@ -102,15 +104,29 @@ __device__ __forceinline__ void flux1d(const double* U, double gam, double a, do
   else f[0] = scalar_flux<EQ>(U[0], a);
 }
 
+// A number of the sign of the velocity m / rho as the rounded quotient has it (zero where the
+// quotient underflows): the quotient itself only where the operands do not tell.
+__device__ __forceinline__ double velocity_sign(double m, double rho) {
+  if (rho > 0.0 && rho < 1e100 && (m == 0.0 || fabs(m) > 1e-200)) return m;
+  return m / rho;
+}
+
+// One tile: the cells i0 .. i0 + T1 - 7 of an instance, thread l on position i0 + l - 3.
+// Bound by VALU issue (FP64), so every phase is one pass of the workgroup.  A tile of T1 cells took a
+// second pass of its first or last wave for the two to six positions beyond them in the flags, the
+// limiter, the traces and the faces, half as much again with two waves a tile, and evaluated
+// each face's fluxes in both of its cells: 52.9 -> 42.5 us a launch for 512 Euler instances of 256 to
+// 8192 cells with 128 threads, of which the bytes alone take 32 at the rate of a large copy.
 // NU: a single instance on cells of different sizes (per-cell tables, hw_mesh1d.h)
 template <int EQ, int T1, bool NU>
 __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, double* s_face,
-                             uint8_t* s_T, uint8_t* s_H, double* s_red) {
-  constexpr int L1 = T1 + 2 * H1;
+                             uint8_t* s_T, double* s_red) {
+  constexpr int L1 = T1;
   constexpr int NC = (EQ == EQ_EULER) ? 3 : 1;
   constexpr int NF = 2 * NC;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, l = tid;
   const int mode = P.mode;
+  const double alpha = __longlong_as_double((long long)P.alpha_in[inst]);
   double dt = 0.0;
   if (mode != MODE_L) {
     dt = P.dt[inst];
@@ -123,35 +139,20 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
     double sg;
     return mesh1d::Tab{P.nu, tot, off + map_index(i0 + l - H1, n, P.bc, sg)};
   };
-  const double dx = NU ? tab(tid + H1)[mesh1d::K_DX] : P.dxs[inst];
+  const double dx = NU ? tab(l)[mesh1d::K_DX] : P.dxs[inst];
   const double h = 0.5 * dx, idx = 1.0 / dx;
 
-  // stage input -> LDS: positions tid and tid + T1 of the tile plus ghosts, every load
-  // issued before the stores
+  // stage input -> LDS; a reflective wall's ghost also negates the momentum (average, moment)
   {
-    double v0[NF], v1[NF], s0, s1;
-    const int g0 = map_index(i0 + tid - H1, n, P.bc, s0);
-    const bool two = tid + T1 < L1;
-    const int g1 = two ? map_index(i0 + tid + T1 - H1, n, P.bc, s1) : 0;
+    double v[NF], sg;
+    const int g = map_index(i0 + l - H1, n, P.bc, sg);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) v0[f] = P.in[f * tot + off + g0];
-    if (two) {
-#pragma unroll
-      for (int f = 0; f < NF; ++f) v1[f] = P.in[f * tot + off + g1];
-    }
-    // a reflective wall's ghost also negates the momentum (average and moment)
+    for (int f = 0; f < NF; ++f) v[f] = P.in[f * tot + off + g];
     const bool refl = EQ == EQ_EULER && P.bc == BC_REFLECTIVE;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-      const double m = (refl && s0 < 0.0 && f % NC == 1) ? -1.0 : 1.0;
-      s_in[f * L1 + tid] = m * (f >= NC ? s0 * v0[f] : v0[f]);
-    }
-    if (two) {
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const double m = (refl && s1 < 0.0 && f % NC == 1) ? -1.0 : 1.0;
-        s_in[f * L1 + tid + T1] = m * (f >= NC ? s1 * v1[f] : v1[f]);
-      }
+      const double m = (refl && sg < 0.0 && f % NC == 1) ? -1.0 : 1.0;
+      s_in[f * L1 + l] = m * (f >= NC ? sg * v[f] : v[f]);
     }
   }
   __syncthreads();
@@ -173,14 +174,15 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
   };
 
   // ---------------------------------------------------------------- flags on tile+2
-  for (int l = 1 + tid; l < L1 - 1; l += T1) {
-    uint8_t t = 0;
+  const bool in2 = l >= 1 && l < L1 - 1, in1 = l >= 2 && l < L1 - 2;   // tile+2, tile+1
+  uint8_t myT = 0;
+  if (in2) {
     if (P.tc_mode == TC_ALL) {
-      t = 1;
+      myT = 1;
     } else if (P.tc_mode == TC_KXRCF) {
       const int lc = mirror_src(l);
       double vel;
-      if constexpr (EQ == EQ_EULER) vel = A(1, lc) / A(0, lc);
+      if constexpr (EQ == EQ_EULER) vel = velocity_sign(A(1, lc), A(0, lc));
       else if constexpr (EQ == EQ_BURGERS) vel = A(0, lc);
       else vel = P.adv;
       constexpr int ncheck = (EQ == EQ_EULER) ? 2 : 1;
@@ -189,39 +191,33 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
         const int c = (k == 0) ? 0 : NC - 1;   // density, then energy
         if (kxrcf1d(A(c, lc), A(NC + c, lc), A(c, lc - 1), A(NC + c, lc - 1), A(c, lc + 1),
                     A(NC + c, lc + 1), vel, hl))
-          t = 1;
+          myT = 1;
       }
     }
-    s_T[l] = t;
   }
+  s_T[l] = myT;
   __syncthreads();
 
   // ---------------------------------------------------------------- limiter (Jacobi)
-  double limv[2][NC];
-  bool limdo[2] = {false, false};
-  if (P.tc_mode != TC_NONE) {
-#pragma unroll
-    for (int rep = 0; rep < 2; ++rep) {
-      const int lt = 1 + tid + rep * T1;
-      if (lt >= L1 - 1) break;
-      if (!s_T[lt]) continue;
-      limdo[rep] = true;
+  double limv[NC];
+  {
+    if (myT) {
       // the ghost next to a wall takes the mirror of its neighbour's limited moments
-      const int l = mirror_src(lt);
-      const bool mir = l != lt;
+      const int l = mirror_src(tid);
+      const bool mir = l != tid;
       if constexpr (EQ != EQ_EULER) {
         if constexpr (NU)
-          limv[rep][0] = mesh1d::limit_moment_nu(tab(l), A(0, l - 1), A(0, l), A(0, l + 1),
+          limv[0] = mesh1d::limit_moment_nu(tab(l), A(0, l - 1), A(0, l), A(0, l + 1),
                                                  A(1, l - 1), A(1, l + 1), P.w.lim, P.w.eps);
         else
-          limv[rep][0] = limit_moment(A(0, l - 1), A(0, l), A(0, l + 1), A(1, l - 1), A(1, l + 1),
+          limv[0] = limit_moment(A(0, l - 1), A(0, l), A(0, l + 1), A(1, l - 1), A(1, l + 1),
                                       P.w.lim, P.w.eps);
-        if (mir) limv[rep][0] = -limv[rep][0];
+        if (mir) limv[0] = -limv[0];
       } else {
         // field by field: project, limit, and add R's column times the limited moment
         const Char1 k = char1d(A(0, l), A(1, l), A(2, l), P.gam);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) limv[rep][c] = 0.0;
+        for (int c = 0; c < 3; ++c) limv[c] = 0.0;
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
           double Lr[3], Rc[3];
@@ -240,33 +236,32 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
           else vc = limit_moment(um, u0, up, vm, vp, P.w.lim, P.w.eps);
           char1d_right(k, f, Rc);
 #pragma unroll
-          for (int c = 0; c < 3; ++c) limv[rep][c] = fma(Rc[c], vc, limv[rep][c]);
+          for (int c = 0; c < 3; ++c) limv[c] = fma(Rc[c], vc, limv[c]);
           __builtin_amdgcn_sched_barrier(0);
         }
         if (mir) {
           // first moments are odd under the mirror; a wall also reverses the momentum
-          limv[rep][0] = -limv[rep][0];
-          if (P.bc != BC_REFLECTIVE) limv[rep][1] = -limv[rep][1];
-          limv[rep][2] = -limv[rep][2];
+          limv[0] = -limv[0];
+          if (P.bc != BC_REFLECTIVE) limv[1] = -limv[1];
+          limv[2] = -limv[2];
         }
       }
     }
   }
   __syncthreads();
+  if (myT) {
 #pragma unroll
-  for (int rep = 0; rep < 2; ++rep) {
-    if (!limdo[rep]) continue;
-    const int l = 1 + tid + rep * T1;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) s_in[(NC + c) * L1 + l] = limv[rep][c];
+    for (int c = 0; c < NC; ++c) s_in[(NC + c) * L1 + l] = limv[c];
   }
-  for (int l = 2 + tid; l < L1 - 2; l += T1) s_H[l] = s_T[l - 1] | s_T[l] | s_T[l + 1];
+  const uint8_t myH = in1 ? s_T[l - 1] | s_T[l] | s_T[l + 1] : 0;
   __syncthreads();
 
   // ---------------------------------------------------------------- reconstruction
-  // interface values of cell l: left (u^+_{l-1/2}) and right (u^-_{l+1/2})
-  auto traces = [&](int l, double* left, double* right, double* im, double* ip) {
-    const bool hyb = s_H[l] != 0;
+  // interface values of cell l: left (u^+_{l-1/2}) and right (u^-_{l+1/2}), and the sum of the
+  // Gauss-Lobatto rule over the cell's fluxes
+  double left[NC], right[NC], fL[NC], fR[NC], Fi[NC];
+  if (in1) {
+    const bool hyb = myH != 0;
     // the HWENO branch first, so that no linear value is live across it
     if (hyb) {
       if constexpr (EQ != EQ_EULER) {
@@ -310,94 +305,67 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
       }
     }
     // linear values: the interface values of non-hybrid cells, the interior points of all
+    double um[NC], up[NC], fm[NC], fp[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      double a, b, m, p;
+      double a, b;
       if constexpr (NU) {
         const double d6[6] = {A(c, l - 1), A(c, l), A(c, l + 1), A(NC + c, l - 1), A(NC + c, l),
                               A(NC + c, l + 1)};
-        mesh1d::linear1d_nu(tab(l), d6, a, b, m, p);
+        mesh1d::linear1d_nu(tab(l), d6, a, b, um[c], up[c]);
       } else {
         linear1d(A(c, l - 1), A(c, l), A(c, l + 1), A(NC + c, l - 1), A(NC + c, l),
-                 A(NC + c, l + 1), a, b, m, p);
+                 A(NC + c, l + 1), a, b, um[c], up[c]);
       }
       if (!hyb) {
         left[c] = a;
         right[c] = b;
       }
-      if (im) { im[c] = m; ip[c] = p; }
     }
-  };
-
-  const int l = tid + H1;
-  const int gi = i0 + tid;
-  const bool active = gi < n;
-  // ---------------------------------------------------------------- face exchange
-  // face q of the tile lies between cells q - 1 and q (q = 0..T1): u^- and u^+ there
-  double* s_fm = s_face;             // u^- then the flux
-  double* s_fp = s_face + NC * (T1 + 1);
-  // ring cells first, in one pass of the last wave (the first wave takes the other extra
-  // positions of the phases before and after): the left neighbour of the tile gives u^- at
-  // face 0, the right neighbour u^+ at face T1
-  if (tid >= T1 - 2) {
-    const bool left_ring = tid == T1 - 2;
-    double rL[NC], rR[NC];
-    traces(left_ring ? H1 - 1 : H1 + T1, rL, rR, nullptr, nullptr);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if (left_ring) s_fm[c * (T1 + 1)] = rR[c];
-      else s_fp[c * (T1 + 1) + T1] = rL[c];
-    }
-  }
-  double uL[NC], uR[NC], um[NC], up[NC];
-  traces(l, uL, uR, um, up);
-  const uint8_t myT = s_T[l];
-  const uint8_t myH = s_H[l];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    s_fp[c * (T1 + 1) + tid] = uL[c];
-    s_fm[c * (T1 + 1) + tid + 1] = uR[c];
-  }
-  __syncthreads();
-  const double alpha = __longlong_as_double((long long)P.alpha_in[inst]);
-  for (int q = tid; q < T1 + 1; q += T1) {
-    double a[NC], b[NC], fa[NC], fb[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      a[c] = s_fm[c * (T1 + 1) + q];
-      b[c] = s_fp[c * (T1 + 1) + q];
-    }
-    if (walls) {
-      // boundary face: the ghost's trace is the inner cell's (momentum reversed at a wall)
-      const int gf = i0 + q;
-      if (gf == 0 || gf == n) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const double m = (EQ == EQ_EULER && P.bc == BC_REFLECTIVE && c == 1) ? -1.0 : 1.0;
-          if (gf == 0) a[c] = m * b[c];
-          else b[c] = m * a[c];
-        }
-      }
-    }
-    flux1d<EQ>(a, P.gam, P.adv, fa);
-    flux1d<EQ>(b, P.gam, P.adv, fb);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) s_fm[c * (T1 + 1) + q] = 0.5 * (fa[c] + fb[c]) - 0.5 * alpha * (b[c] - a[c]);
-  }
-  __syncthreads();
-  double LU[NC], LV[NC];
-  {
-    double fL[NC], fR[NC], fm[NC], fp[NC];
-    flux1d<EQ>(uL, P.gam, P.adv, fL);
-    flux1d<EQ>(uR, P.gam, P.adv, fR);
+    flux1d<EQ>(left, P.gam, P.adv, fL);
+    flux1d<EQ>(right, P.gam, P.adv, fR);
     flux1d<EQ>(um, P.gam, P.adv, fm);
     flux1d<EQ>(up, P.gam, P.adv, fp);
+    // the cell's shares of twice the fluxes f(u-) + f(u+) - alpha (u+ - u-) of its two faces
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const double FL = s_fm[c * (T1 + 1) + tid], FR = s_fm[c * (T1 + 1) + tid + 1];
-      const double Fi = (fL[c] + fR[c]) * (1.0 / 12.0) + (fm[c] + fp[c]) * (5.0 / 12.0);
+      Fi[c] = (fL[c] + fR[c]) * (1.0 / 12.0) + (fm[c] + fp[c]) * (5.0 / 12.0);
+      fL[c] = fma(-alpha, left[c], fL[c]);
+      fR[c] = fma(alpha, right[c], fR[c]);
+      s_face[c * T1 + l] = fL[c];
+      s_face[(NC + c) * T1 + l] = fR[c];
+    }
+  }
+  const int gi = i0 + l - H1;
+  const bool active = l >= H1 && l < T1 - H1 && gi < n;
+  __syncthreads();
+  double LU[NC], LV[NC];
+  if (active) {
+    double lo[NC], hi[NC];   // the neighbours' shares
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      lo[c] = s_face[(NC + c) * T1 + l - 1];
+      hi[c] = s_face[c * T1 + l + 1];
+    }
+    if (walls && (gi == 0 || gi == n - 1)) {
+      // boundary face: the ghost's trace is the inner cell's (momentum reversed at a wall)
+      double g[NC], fg[NC];
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        if (gi != (side == 0 ? 0 : n - 1)) continue;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          g[c] = ((EQ == EQ_EULER && P.bc == BC_REFLECTIVE && c == 1) ? -1.0 : 1.0) * (side == 0 ? left[c] : right[c]);
+        flux1d<EQ>(g, P.gam, P.adv, fg);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) (side == 0 ? lo : hi)[c] = fma(side == 0 ? alpha : -alpha, g[c], fg[c]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const double FL = 0.5 * (lo[c] + fL[c]), FR = 0.5 * (fR[c] + hi[c]);
       LU[c] = -(FR - FL) * idx;
-      LV[c] = (Fi - 0.5 * (FL + FR)) * idx;
+      LV[c] = (Fi[c] - 0.5 * (FL + FR)) * idx;
     }
   }
   double own[NF];   // the (limited) stage input
@@ -477,34 +445,27 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
 
 template <int EQ, int T1, bool NU>
 __global__ __launch_bounds__(T1) void stage1d_kernel(Stage1D P) {
-  constexpr int NF = (EQ == EQ_EULER) ? 6 : 2, L1 = T1 + 2 * H1;
-  __shared__ double s_in[NF * L1];
-  __shared__ double s_face[2 * NF / 2 * (T1 + 1)];
-  __shared__ uint8_t s_T[L1], s_H[L1];
+  constexpr int NF = (EQ == EQ_EULER) ? 6 : 2;
+  __shared__ double s_in[NF * T1];
+  __shared__ double s_face[NF * T1];
+  __shared__ uint8_t s_T[T1];
   __shared__ double s_red[T1 / 64];
   const int2 it = P.items[blockIdx.x];
-  stage1d_tile<EQ, T1, NU>(P, it.x, it.y, s_in, s_face, s_T, s_H, s_red);
+  stage1d_tile<EQ, T1, NU>(P, it.x, it.y, s_in, s_face, s_T, s_red);
 }
 
 // persistent form: a grid sized to the machine walks the work list
 template <int EQ, int T1>
 __global__ __launch_bounds__(T1, 4) void stage1d_persistent(Stage1D P) {
-  constexpr int NF = (EQ == EQ_EULER) ? 6 : 2, L1 = T1 + 2 * H1;
-  __shared__ double s_in[NF * L1];
-  __shared__ double s_face[2 * NF / 2 * (T1 + 1)];
-  __shared__ uint8_t s_T[L1], s_H[L1];
+  constexpr int NF = (EQ == EQ_EULER) ? 6 : 2;
+  __shared__ double s_in[NF * T1];
+  __shared__ double s_face[NF * T1];
+  __shared__ uint8_t s_T[T1];
   __shared__ double s_red[T1 / 64];
   for (int item = blockIdx.x; item < P.nitems; item += gridDim.x) {
     const int2 it = P.items[item];
-    stage1d_tile<EQ, T1, false>(P, it.x, it.y, s_in, s_face, s_T, s_H, s_red);
+    stage1d_tile<EQ, T1, false>(P, it.x, it.y, s_in, s_face, s_T, s_red);
   }
-}
-
-// A number of the sign of the velocity m / rho as the rounded quotient has it (zero where the
-// quotient underflows): the quotient itself only where the operands do not tell.
-__device__ __forceinline__ double velocity_sign(double m, double rho) {
-  if (rho > 0.0 && rho < 1e100 && (m == 0.0 || fabs(m) > 1e-200)) return m;
-  return m / rho;
 }
 
 // maximum over a wave of non-negative values (NaN ignored), in lane 63: register moves within
