@@ -491,14 +491,14 @@ __device__ __forceinline__ double pres_value(const Adj2D& P, int m, int c, int g
   if constexpr (BND == ADJ_STEP) return m == 0 ? sel4(P.uin, c) : 0.0;
   else return P.dtab[(size_t)(m * 4 + c) * dmr::ring2_size(P.nx, P.ny) + dmr::ring2_index(gx, gy, P.nx, P.ny)];
 }
-// whether every position within two cells of the fluid cell (gx, gy) is a fluid cell: then
-// the cell is the source of no other position, and every slot that refers to it belongs to
-// a fluid neighbour
+// whether the fluid cell (gx, gy) may be the source of a position outside the fluid that a fluid
+// cell's stencil holds: those positions are one layer deep, and their source is the cell
+// beside the boundary, or the next one where a step one cell wide meets the outflow
 template <int BND>
-__device__ __forceinline__ bool interior_of(const Adj2D& P, int gx, int gy) {
-  const bool in = gx >= 2 && gx <= P.nx - 3 && gy >= 2 && gy <= P.ny - 3;
-  if constexpr (BND == ADJ_STEP) return in && !(gx >= P.si - 2 && gy <= P.sj + 1);
-  else return in;
+__device__ __forceinline__ bool beside_boundary(const Adj2D& P, int gx, int gy) {
+  bool b = gx == 0 || gx >= P.nx - 2 || gy == 0 || gy == P.ny - 1;
+  if constexpr (BND == ADJ_STEP) b = b || (gx >= P.si - 1 && gy <= P.sj);
+  return b;
 }
 template <int BND>
 __device__ __forceinline__ int face_of(const Adj2D& P, int gx, int gy, int dir, int side) {
@@ -1178,12 +1178,8 @@ __global__ __launch_bounds__(NT) void adjEG2d_kernel(Adj2D P) {
     if (rim) add_sums(gx, gy, false, [](int) { return 1.0; });
     add_hybrid(gx, gy, [](int) { return 1.0; });
     if constexpr (BND >= ADJ_STEP) {
-      // beside a boundary: the non-fluid positions whose source the cell is and that a fluid
-      // cell's stencil holds, one layer deep: their source is the cell beside the boundary,
-      // and the next one where a step one cell wide meets the outflow
-      bool beside = gx == 0 || gx >= nx - 2 || gy == 0 || gy == ny - 1;
-      if constexpr (BND == ADJ_STEP) beside = beside || (gx >= P.si - 1 && gy <= P.sj);
-      if (beside)
+      // the non-fluid positions whose source the cell is
+      if (beside_boundary<BND>(P, gx, gy))
         for (int ey = -1; ey <= 1; ++ey)
           for (int ex = -2; ex <= 2; ++ex) {
             const int qx = gx + ex, qy = gy + ey;
@@ -1342,63 +1338,55 @@ __global__ __launch_bounds__(NT) void adjEC2d_kernel(Adj2D P) {
 // The transposed limiter Jacobian: a flagged cell's limited moments replace its stored
 // ones (their cotangent moves to the limiter's inputs); the limiter of a flagged cell
 // reads the averages of the cell and its two neighbours along the direction and the
-// neighbours' moments (slots um, u0, up, vm, vp).  BND as for adjEC2d_kernel.
+// neighbours' moments (slots um, u0, up, vm, vp).  BND as for adjEC2d_kernel.  Bound by the
+// latency of flags, then slots: four threads per cell, one per component (8.2 -> 7.4 us
+// at 256^2 with shocks, 14.5 -> 11.1 on the forward step at 480 x 160).
 template <int BND>
 __global__ __launch_bounds__(NT) void adjElim2d_kernel(Adj2D P) {
   constexpr int NC = 4;
   const int nx = P.nx, ny = P.ny;
   const size_t plane = (size_t)nx * ny;
-  const size_t i = (size_t)blockIdx.x * NT + threadIdx.x;
-  if (i == 0 && P.counts) {   // the list passes are done: empty the lists for the next stage
+  // wave c of a workgroup: component c of 64 cells
+  const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t i = (size_t)blockIdx.x * 64 + (threadIdx.x & 63);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && P.counts) {   // the list passes are done: empty the lists for the next stage
     P.counts[0] = 0;
     P.counts[1] = 0;
   }
   if (i >= plane) return;
   const int gy = (int)(i / nx), gx = (int)(i - (size_t)gy * nx);
-  double ou[NC], ov[NC], ow[NC];
   const bool ti = P.T && P.T[i];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    ou[c] = P.gw[c * plane + i];
-    ov[c] = ti ? 0.0 : P.gw[(NC + c) * plane + i];
-    ow[c] = ti ? 0.0 : P.gw[(2 * NC + c) * plane + i];
-  }
-  auto C = [&](int dir, int s, int c, size_t j) {
-    return P.C[((size_t)(dir * 5 + s) * NC + c) * plane + j];
-  };
+  double ou = P.gw[c * plane + i];
+  double ov = ti ? 0.0 : P.gw[(NC + c) * plane + i];
+  double ow = ti ? 0.0 : P.gw[(2 * NC + c) * plane + i];
+  auto C = [&](int dir, int s, size_t j) { return P.C[((size_t)(dir * 5 + s) * NC + c) * plane + j]; };
   // the forward step: the limiter of a flagged fluid cell j reads the positions j -+ e_dir;
   // this fluid cell gathers what refers to itself and to the non-fluid positions whose
   // source it is (solid cells are never flagged and are nobody's source)
-  if (BND >= ADJ_STEP && P.T && interior_of<BND>(P, gx, gy)) {
+  if (BND >= ADJ_STEP && P.T && !beside_boundary<BND>(P, gx, gy)) {
     // the plain gather: the cell's own slots and its four neighbours' (right / top see it
     // as (um, vm), left / bottom as (up, vp))
-    if (ti) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) ou[c] += C(0, 1, c, i) + C(1, 1, c, i);
-    }
+    if (ti) ou += C(0, 1, i) + C(1, 1, i);
     const size_t xr = i + 1, xl = i - 1, yt = i + nx, yb = i - nx;
     if (P.T[xr]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(0, 0, c, xr); ov[c] += C(0, 3, c, xr); }
+      ou += C(0, 0, xr);
+      ov += C(0, 3, xr);
     }
     if (P.T[xl]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(0, 2, c, xl); ov[c] += C(0, 4, c, xl); }
+      ou += C(0, 2, xl);
+      ov += C(0, 4, xl);
     }
     if (P.T[yt]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(1, 0, c, yt); ow[c] += C(1, 3, c, yt); }
+      ou += C(1, 0, yt);
+      ow += C(1, 3, yt);
     }
     if (P.T[yb]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(1, 2, c, yb); ow[c] += C(1, 4, c, yb); }
+      ou += C(1, 2, yb);
+      ow += C(1, 4, yb);
     }
   } else if (BND >= ADJ_STEP && P.T && fluid_of<BND>(P, gx, gy)) {
-    if (ti) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) ou[c] += C(0, 1, c, i) + C(1, 1, c, i);
-    }
-    for (int ey = -2; ey <= 2; ++ey)
+    if (ti) ou += C(0, 1, i) + C(1, 1, i);
+    for (int ey = -1; ey <= 1; ++ey)
       for (int ex = -2; ex <= 2; ++ex) {
         const int qx = gx + ex, qy = gy + ey;
         step::Src r{gx, gy, 1.0, 1.0, 1.0, 1.0, false};
@@ -1418,72 +1406,60 @@ __global__ __launch_bounds__(NT) void adjElim2d_kernel(Adj2D P) {
             const size_t j = (size_t)oy * nx + ox;
             if (!P.T[j]) continue;
             const int su = s == 0 ? 2 : 0, sv = s == 0 ? 4 : 3;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-              ou[c] += step_factor(r, 0, c) * C(dir, su, c, j);
-              const double v = step_factor(r, 1 + dir, c) * C(dir, sv, c, j);
-              if (dir == 0) ov[c] += v;
-              else ow[c] += v;
-            }
+            ou += step_factor(r, 0, c) * C(dir, su, j);
+            const double v = step_factor(r, 1 + dir, c) * C(dir, sv, j);
+            if (dir == 0) ov += v;
+            else ow += v;
           }
         }
       }
   }
   if (BND < ADJ_STEP && P.T) {
-    if (ti) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) ou[c] += C(0, 1, c, i) + C(1, 1, c, i);
-    }
+    if (ti) ou += C(0, 1, i) + C(1, 1, i);
     const bool wx = P.bcx != BC_PERIODIC, wy = P.bcy != BC_PERIODIC;
     const size_t xr = (size_t)gy * nx + wrap(gx + 1, nx), xl = (size_t)gy * nx + wrap(gx - 1, nx);
     const size_t yt = (size_t)wrap(gy + 1, ny) * nx + gx, yb = (size_t)wrap(gy - 1, ny) * nx + gx;
     // the right / top neighbour sees this cell as (um, vm), the left / bottom one as (up, vp)
     if (!(wx && gx == nx - 1) && P.T[xr]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(0, 0, c, xr); ov[c] += C(0, 3, c, xr); }
+      ou += C(0, 0, xr);
+      ov += C(0, 3, xr);
     }
     if (!(wx && gx == 0) && P.T[xl]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(0, 2, c, xl); ov[c] += C(0, 4, c, xl); }
+      ou += C(0, 2, xl);
+      ov += C(0, 4, xl);
     }
     if (!(wy && gy == ny - 1) && P.T[yt]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(1, 0, c, yt); ow[c] += C(1, 3, c, yt); }
+      ou += C(1, 0, yt);
+      ow += C(1, 3, yt);
     }
     if (!(wy && gy == 0) && P.T[yb]) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { ou[c] += C(1, 2, c, yb); ow[c] += C(1, 4, c, yb); }
+      ou += C(1, 2, yb);
+      ow += C(1, 4, yb);
     }
     // beside a transmissive or reflective side, this cell's own limiter reads the ghost
     // that mirrors it as its neighbour across that side
     if (ti) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (wx && gx == 0) {
-          ou[c] += mirror_factor(P, 0, c, true, false) * C(0, 0, c, i);
-          ov[c] += mirror_factor(P, 1, c, true, false) * C(0, 3, c, i);
-        }
-        if (wx && gx == nx - 1) {
-          ou[c] += mirror_factor(P, 0, c, true, false) * C(0, 2, c, i);
-          ov[c] += mirror_factor(P, 1, c, true, false) * C(0, 4, c, i);
-        }
-        if (wy && gy == 0) {
-          ou[c] += mirror_factor(P, 0, c, false, true) * C(1, 0, c, i);
-          ow[c] += mirror_factor(P, 2, c, false, true) * C(1, 3, c, i);
-        }
-        if (wy && gy == ny - 1) {
-          ou[c] += mirror_factor(P, 0, c, false, true) * C(1, 2, c, i);
-          ow[c] += mirror_factor(P, 2, c, false, true) * C(1, 4, c, i);
-        }
+      if (wx && gx == 0) {
+        ou += mirror_factor(P, 0, c, true, false) * C(0, 0, i);
+        ov += mirror_factor(P, 1, c, true, false) * C(0, 3, i);
+      }
+      if (wx && gx == nx - 1) {
+        ou += mirror_factor(P, 0, c, true, false) * C(0, 2, i);
+        ov += mirror_factor(P, 1, c, true, false) * C(0, 4, i);
+      }
+      if (wy && gy == 0) {
+        ou += mirror_factor(P, 0, c, false, true) * C(1, 0, i);
+        ow += mirror_factor(P, 2, c, false, true) * C(1, 3, i);
+      }
+      if (wy && gy == ny - 1) {
+        ou += mirror_factor(P, 0, c, false, true) * C(1, 2, i);
+        ow += mirror_factor(P, 2, c, false, true) * C(1, 4, i);
       }
     }
   }
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    P.out[c * plane + i] = ou[c];
-    P.out[(NC + c) * plane + i] = ov[c];
-    P.out[(2 * NC + c) * plane + i] = ow[c];
-  }
+  P.out[c * plane + i] = ou;
+  P.out[(NC + c) * plane + i] = ov;
+  P.out[(2 * NC + c) * plane + i] = ow;
 }
 
 }  // namespace hw
@@ -1524,14 +1500,14 @@ void launch_adjE(const hw::Adj2D* P, dim3 grid, dim3 cells, hipStream_t s) {
   if (P->counts) hipLaunchKernelGGL((hw::adjEhw2d_kernel<NGE, BND>), dim3(1024), block, 0, s, *P);
   hipLaunchKernelGGL(hw::adjEG2d_kernel<BND>, dim3(4 * grid.x), block, 0, s, *P);
   if (P->T) hipLaunchKernelGGL(hw::adjEC2d_kernel<LB>, dim3(1024), block, 0, s, *P);
-  hipLaunchKernelGGL(hw::adjElim2d_kernel<LB>, cells, block, 0, s, *P);
+  hipLaunchKernelGGL(hw::adjElim2d_kernel<LB>, cells, block, 0, s, *P);   // 64 cells a workgroup
 }
 }  // namespace
 
 extern "C" hipError_t hw_launch_adj2d_euler(int ng, const hw::Adj2D* P, hipStream_t s) {
   const size_t plane = (size_t)P->nx * P->ny;
   dim3 grid(((P->nx + hw::TX - 1) / hw::TX) * ((P->ny + hw::TY - 1) / hw::TY));
-  dim3 cells((unsigned)((plane + hw::NT - 1) / hw::NT));
+  dim3 cells((unsigned)((plane + 63) / 64));
   const int bnd = P->bcx == hw::BC_STEP  ? hw::ADJ_STEP
                   : P->bcx == hw::BC_DMR ? hw::ADJ_DMR
                   : (P->bcx != hw::BC_PERIODIC || P->bcy != hw::BC_PERIODIC) ? hw::ADJ_WALLS
