@@ -401,165 +401,158 @@ __global__ __launch_bounds__(NT) void stage2d_limit_kernel(Stage2D P) {
   }
 }
 
-// HWENO edge values (Step 5.1) of every hybrid cell, one work item per (cell,
-// characteristic field), grouped as in the limiter: lane f reads component f of the
-// 19-value stencil (through the cache, with the limited moments of flagged cells), and
-// for each direction in turn the group projects onto that direction's characteristic
-// fields, reconstructs field f, and returns to component f, which the lane stores.  Each
-// wave takes 64 / NC cells; the stencil is loaded once for both directions (the loads,
-// scattered over the hybrid cells, are what this pass waits on).
+// component f of one half of a hybrid cell's 19-value stencil (through the cache, with the
+// limited moments of flagged cells), value k to s[64 k]: HALF 0 the nine averages, HALF 1 the ten
+// first moments of the cross.  The stored values and the flags are loaded together, the limited
+// moments of the (few) flagged cells afterwards.
+template <int EQ, int BK, int HALF>
+__device__ __forceinline__ void hweno_load(const Stage2D& P, int gi, int f, double dtv, double* s) {
+  constexpr int NC = (EQ == EQ_EULER) ? 4 : 1, N = HALF == 0 ? 9 : 5;
+  const size_t plane = (size_t)P.nx * P.ny;
+  const int gy = gi / P.nx, gx = gi - gy * P.nx;
+  const int cross[5] = {1, 3, 4, 5, 7};
+  // the positions: stored index, moment signs (mirrored ghosts), prescribed or not
+  int gb[N];
+  unsigned neg_x = 0, neg_y = 0, neg_w = 0, pres = 0;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const int k = HALF == 0 ? j : cross[j];
+    if constexpr (BK == BK_STEP) {
+      // forward step: the position's source cell (prescribed: the inflow state, below)
+      const step::Src sr = step::resolve(gx + k % 3 - 1, gy + k / 3 - 1, P.nx, P.ny, P.si, P.sj);
+      gb[j] = sr.y * P.nx + sr.x;
+      if (sr.pres) pres |= 1u << j;
+      if (sr.sx < 0.0) neg_x |= 1u << j;
+      if (sr.sy < 0.0) neg_y |= 1u << j;
+      if (step::comp_factor(sr, f) < 0.0) neg_w |= 1u << j;
+    } else {
+      double sx, sy;
+      const int x = map_index(gx + k % 3 - 1, P.nx, P.bcx, sx);
+      const int y = map_index(gy + k / 3 - 1, P.ny, P.bcy, sy);
+      gb[j] = y * P.nx + x;
+      if (sx < 0.0) neg_x |= 1u << j;
+      if (sy < 0.0) neg_y |= 1u << j;
+      // a reflective wall also reverses the normal momentum of its ghost cells
+      if (wall_factor<EQ>(f, sx < 0.0, sy < 0.0, P.bcx, P.bcy) < 0.0) neg_w |= 1u << j;
+      // double Mach reflection: prescribed ghosts hold the exact solution (the signs apply to
+      // mirrored ghosts only) and are never troubled
+      if (dmr_prescribed<BK>(P, gx + k % 3 - 1, gy + k / 3 - 1)) pres |= 1u << j;
+    }
+  }
+  auto value = [&](int m, int j, double v) {   // moment m at position j, prescribed or as stored
+    if (!((pres >> j) & 1u)) return ((m == 0 ? neg_w : (m == 1 ? neg_x ^ neg_w : neg_y ^ neg_w)) >> j) & 1u ? -v : v;
+    if constexpr (BK == BK_STEP) return m == 0 ? P.uin[f] : 0.0;   // inflow state, zero moments
+    if constexpr (BK == BK_DMR) {
+      const int k = HALF == 0 ? j : cross[j];
+      return dmr_value(P, m * NC + f, gx + k % 3 - 1, gy + k / 3 - 1, stage_time_of<BK>(P, dtv));
+    }
+    return v;
+  };
+  if constexpr (HALF == 0) {
+    double u[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) u[j] = P.in[f * plane + gb[j]];
+#pragma unroll
+    for (int j = 0; j < N; ++j) s[j * 64] = value(0, j, u[j]);
+  } else {
+    double v[N], w[N];
+    uint8_t t[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      t[j] = P.Tcur[gb[j]];
+      v[j] = P.in[(NC + f) * plane + gb[j]];
+      w[j] = P.in[(2 * NC + f) * plane + gb[j]];
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (t[j]) {
+        v[j] = P.limcur[f * plane + gb[j]];
+        w[j] = P.limcur[(NC + f) * plane + gb[j]];
+      }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      s[(9 + j) * 64] = value(1, j, v[j]);
+      s[(14 + j) * 64] = value(2, j, w[j]);
+    }
+  }
+}
+
+// the edge values of direction DIR of one hybrid cell (lane: field and component f of it, as in
+// the limiter) from the stencils in s_x ([19][64])
+template <int EQ, int NGE, int DIR>
+__device__ __forceinline__ void hweno_list_values(const Stage2D& P, const double* s_x, int lane, int f, double* v) {
+  if constexpr (EQ == EQ_EULER) {
+    const double* s = s_x + (lane & ~3);   // the cell's four components
+    double U[4], Lr[4], Rr[4], x[4], w19[19], wv[2 * NGE];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) U[c] = s[4 * 64 + c];
+    euler_rows2d(U, P.gam, DIR, f, Lr, Rr);
+#pragma unroll
+    for (int k = 0; k < 19; ++k) {
+      double a = 0.0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) a = fma(Lr[c], s[k * 64 + c], a);
+      w19[k] = a;
+    }
+    hweno2d_field<NGE>(w19, P.w, DIR, wv);
+#pragma unroll
+    for (int k = 0; k < 2 * NGE; ++k) {
+      quad_gather(wv[k], x);
+      double a = 0.0;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) a = fma(Rr[g], x[g], a);
+      v[k] = a;
+    }
+  } else {
+    double in[19];
+#pragma unroll
+    for (int k = 0; k < 19; ++k) in[k] = s_x[k * 64 + lane];
+    hweno2d_field<NGE>(in, P.w, DIR, v);
+  }
+}
+
+// HWENO edge values (Step 5.1) of every hybrid cell, one work item per (cell, direction,
+// characteristic field), grouped as in the limiter.  The pass waits on its scattered loads and on the
+// length of a wave's chain, so the waves of a workgroup form pairs: both waves of a pair take
+// the same 64 / NC cells, each loads half of their stencils into LDS, and each reconstructs one
+// direction.  Measured against one wave that loaded a cell's whole stencil, passed its components
+// round by lane moves and took the directions in turn (236 to 248 VGPRs), us a launch: 15.4 -> 13.6 on
+// the forward step at 960 x 320, 14.4 -> 10.9 at 480 x 160, 19.7 -> 15.6 at 1501 x 997, the mean of a
+// run 19.7 -> 18.9 at 1024^2 and 25.4 -> 23.4 on the double Mach reflection at 1920 x 480.
 template <int EQ, int NGE, int BK>
-__global__ __launch_bounds__(NT, BK == BK_DMR ? 2 : 1) void stage2d_hweno_kernel(Stage2D P) {
+__global__ __launch_bounds__(NT, 2) void stage2d_hweno_kernel(Stage2D P) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
-  constexpr int CPW = 64 / NC;   // cells per wave
+  constexpr int CPW = 64 / NC, NPAIR = NT / 128;   // cells per wave, pairs
+  __shared__ double s_x[NPAIR][19 * 64];
   // the list length and the time step are loaded together (the time step pointer is valid
   // in every mode); a finished run or an empty list has nothing to do
   const int ncell = P.counts[1];
   const double dtv = *P.dt;
   if ((P.mode != MODE_L && dtv == 0.0) || ncell == 0) return;
-  const long long nwave = (ncell + CPW - 1) / CPW;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, pr = wv >> 1, dir = wv & 1, f = lane % NC;
   const size_t plane = (size_t)P.nx * P.ny;
-  // the cross of the first-moment stencil inside the 3 x 3 block
-  const int cross[5] = {1, 3, 4, 5, 7};
-  for (long long wq = ((long long)blockIdx.x * NT + threadIdx.x) >> 6; wq < nwave;
-       wq += ((long long)gridDim.x * NT) >> 6) {
-    const long long cell = wq * CPW + lane / NC;
-    if (cell >= ncell) continue;   // whole groups of NC lanes
-    const int f = lane % NC;
-    const int gi = P.hlist[cell];
-    const int gy = gi / P.nx, gx = gi - gy * P.nx;
-    // the 3 x 3 block: stored index, moment signs (transmissive ghosts)
-    int gb[9];
-    unsigned neg_x = 0, neg_y = 0, neg_w = 0, pres = 0;
+  // the loop's bounds are the workgroup's, so every wave meets both barriers
+  for (long long base = (long long)blockIdx.x * NPAIR * CPW; base < ncell;
+       base += (long long)gridDim.x * NPAIR * CPW) {
+    const long long cell = base + pr * CPW + lane / NC;
+    const bool on = cell < ncell;   // whole groups of NC lanes
+    const int gi = on ? P.hlist[cell] : 0;
+    if (on) {
+      if (dir == 0) hweno_load<EQ, BK, 0>(P, gi, f, dtv, s_x[pr] + lane);
+      else hweno_load<EQ, BK, 1>(P, gi, f, dtv, s_x[pr] + lane);
+    }
+    __syncthreads();
+    if (on) {
+      double v[2 * NGE];
+      if (dir == 0) hweno_list_values<EQ, NGE, 0>(P, s_x[pr], lane, f, v);
+      else hweno_list_values<EQ, NGE, 1>(P, s_x[pr], lane, f, v);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      if constexpr (BK == BK_STEP) {
-        // forward step: the position's source cell (prescribed: the inflow state, below)
-        const step::Src sr = step::resolve(gx + k % 3 - 1, gy + k / 3 - 1, P.nx, P.ny, P.si, P.sj);
-        gb[k] = sr.y * P.nx + sr.x;
-        if (sr.pres) pres |= 1u << k;
-        if (sr.sx < 0.0) neg_x |= 1u << k;
-        if (sr.sy < 0.0) neg_y |= 1u << k;
-        if (step::comp_factor(sr, f) < 0.0) neg_w |= 1u << k;
-      } else {
-        double sx, sy;
-        const int x = map_index(gx + k % 3 - 1, P.nx, P.bcx, sx);
-        const int y = map_index(gy + k / 3 - 1, P.ny, P.bcy, sy);
-        gb[k] = y * P.nx + x;
-        if (sx < 0.0) neg_x |= 1u << k;
-        if (sy < 0.0) neg_y |= 1u << k;
-        if (wall_factor<EQ>(f, sx < 0.0, sy < 0.0, P.bcx, P.bcy) < 0.0) neg_w |= 1u << k;
+      for (int k = 0; k < NGE; ++k) {
+        P.G[((((size_t)(dir * 2 + 0) * NGE + k) * NC + f)) * plane + gi] = v[k];
+        P.G[((((size_t)(dir * 2 + 1) * NGE + k) * NC + f)) * plane + gi] = v[NGE + k];
       }
     }
-    // component f of the stencil: 9 averages, then x and y moments of the cross; the
-    // stored values and the cross cells' flags are loaded together, the limited moments
-    // of the (few) flagged cells afterwards
-    double in[19];
-    uint8_t tf[5];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) in[k] = P.in[f * plane + gb[k]];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      const int k = cross[j];
-      tf[j] = P.Tcur[gb[k]];
-      in[9 + j] = P.in[(NC + f) * plane + gb[k]];
-      in[14 + j] = P.in[(2 * NC + f) * plane + gb[k]];
-    }
-    // forward step: prescribed inflow positions hold the inflow state, zero moments, and
-    // are never troubled
-    if constexpr (BK == BK_STEP) {
-      if (pres) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k)
-          if ((pres >> k) & 1u) in[k] = P.uin[f];
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-          if (!((pres >> cross[j]) & 1u)) continue;
-          tf[j] = 0;
-          in[9 + j] = in[14 + j] = 0.0;
-        }
-      }
-    }
-    // double Mach reflection: prescribed ghosts of the block hold the exact solution (signs
-    // below apply to mirrored ghosts only) and are never troubled
-    if constexpr (BK == BK_DMR) {
-      const double ts = stage_time_of<BK>(P, dtv);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        const int bx = gx + k % 3 - 1, by = gy + k / 3 - 1;
-        if (!dmr_prescribed<BK>(P, bx, by)) continue;
-        pres |= 1u << k;
-        in[k] = dmr_value(P, f, bx, by, ts);
-      }
-#pragma unroll
-      for (int j = 0; j < 5; ++j) {
-        const int k = cross[j];
-        if (!((pres >> k) & 1u)) continue;
-        tf[j] = 0;
-        in[9 + j] = dmr_value(P, NC + f, gx + k % 3 - 1, gy + k / 3 - 1, ts);
-        in[14 + j] = dmr_value(P, 2 * NC + f, gx + k % 3 - 1, gy + k / 3 - 1, ts);
-      }
-      neg_x &= ~pres;
-      neg_y &= ~pres;
-      neg_w &= ~pres;
-    }
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      const int k = cross[j];
-      if (tf[j]) {
-        in[9 + j] = P.limcur[f * plane + gb[k]];
-        in[14 + j] = P.limcur[(NC + f) * plane + gb[k]];
-      }
-      if ((neg_x ^ neg_w) >> k & 1u) in[9 + j] = -in[9 + j];
-      if ((neg_y ^ neg_w) >> k & 1u) in[14 + j] = -in[14 + j];
-    }
-    // a reflective wall also reverses the normal momentum of its ghost cells
-    if (neg_w) {
-#pragma unroll
-      for (int k = 0; k < 9; ++k)
-        if ((neg_w >> k) & 1u) in[k] = -in[k];
-    }
-    // both directions from the one stencil (the loop is unrolled: the direction is a
-    // constant in each copy)
-#pragma unroll
-    for (int dir = 0; dir < 2; ++dir) {
-    double v[2 * NGE];
-    if constexpr (EQ == EQ_EULER) {
-      double U[4], Lr[4], Rr[4], x[4];
-      quad_gather(in[4], U);   // the cell's own averages
-      euler_rows2d(U, P.gam, dir, f, Lr, Rr);
-      double w19[19];
-#pragma unroll
-      for (int k = 0; k < 19; ++k) {
-        quad_gather(in[k], x);
-        double a = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) a = fma(Lr[c], x[c], a);
-        w19[k] = a;
-      }
-      double wv[2 * NGE];
-      if (dir == 0) hweno2d_field<NGE>(w19, P.w, 0, wv);   // the direction as a constant
-      else hweno2d_field<NGE>(w19, P.w, 1, wv);
-#pragma unroll
-      for (int k = 0; k < 2 * NGE; ++k) {
-        quad_gather(wv[k], x);
-        double a = 0.0;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) a = fma(Rr[g], x[g], a);
-        v[k] = a;
-      }
-    } else {
-      if (dir == 0) hweno2d_field<NGE>(in, P.w, 0, v);
-      else hweno2d_field<NGE>(in, P.w, 1, v);
-    }
-#pragma unroll
-    for (int k = 0; k < NGE; ++k) {
-      P.G[((((size_t)(dir * 2 + 0) * NGE + k) * NC + f)) * plane + gi] = v[k];
-      P.G[((((size_t)(dir * 2 + 1) * NGE + k) * NC + f)) * plane + gi] = v[NGE + k];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    }
+    __syncthreads();
   }
 }
 
