@@ -109,11 +109,17 @@ __global__ void begin_segment_kernel(unsigned long long* a, int na, const unsign
   if (i < ns) stats[i] = 0;
 }
 
-// zeroes p[0..n) and, when q is not null, q[0], q[stride] .. q[(m - 1) stride]
-__global__ void zero_u64(unsigned long long* p, int n, unsigned long long* q, int m, int stride) {
+// zeroes p[0..n); when q is not null, q[0] and q[3]; and when t is not null, the times and step
+// counts of ni instances and the status word (a new state: one launch in place of four)
+__global__ void zero_u64(unsigned long long* p, int n, long long* q, double* t, long long* steps, int ni, int* status) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0ull;
-  if (q && i < m) q[i * stride] = 0ull;
+  if (q && i < 2) q[3 * i] = 0;
+  if (t && i < ni) {
+    t[i] = 0.0;
+    steps[i] = 0;
+  }
+  if (t && i == 0) *status = 0;
 }
 
 }  // namespace
@@ -524,11 +530,12 @@ extern "C" hw_status hw_get_sizes(const hw_solver* h, long* cells, int* ncomp, i
 
 // the speeds of U into out; stats (may be null): the list lengths a following operator adds to
 // (its entries of the first stage, [0] and [3])
+// reset: the times, step counts and status start at zero too (W >= the instances)
 static hw_status launch_alpha(hw_solver* h, const double* U, unsigned long long* out,
-                              long long* stats = nullptr) {
+                              long long* stats = nullptr, bool reset = false) {
   const int W = h->aw;
-  hipLaunchKernelGGL(zero_u64, dim3((W + 255) / 256), dim3(256), 0, h->stream, out, W,
-                     (unsigned long long*)stats, 2, 3);
+  hipLaunchKernelGGL(zero_u64, dim3((W + 255) / 256), dim3(256), 0, h->stream, out, W, stats,
+                     reset ? h->t : (double*)nullptr, h->steps, h->ninst, h->status);
   HWCHK(hipGetLastError());
   if (h->dim == 2) {
     int si, sj;
@@ -744,11 +751,8 @@ static hw_status read_status(hw_solver* h, int* st) {
 static hw_status after_state_change(hw_solver* h) {
   // speed of the new state into slot 3 (read by the next step's dt kernel), time 0
   const int W = h->aw;
-  hw_status s = launch_alpha(h, h->S0, h->alpha + 3 * W);
+  hw_status s = launch_alpha(h, h->S0, h->alpha + 3 * W, nullptr, true);
   if (s != HW_OK) return s;
-  HWCHK(hipMemsetAsync(h->t, 0, h->ninst * sizeof(double), h->stream));
-  HWCHK(hipMemsetAsync(h->steps, 0, h->ninst * sizeof(long long), h->stream));
-  HWCHK(hipMemsetAsync(h->status, 0, sizeof(int), h->stream));
   return sync(h);
 }
 
