@@ -10,7 +10,10 @@
 //   stage 1, stage 2, stage 3 (1D: one stage kernel each; 2D: flags and work lists,
 //   limiter, HWENO, stage kernel; each stage also accumulates the speed of its output for
 //   the next stage).
-// Speeds live in four slots: slot 0 = u^n, 1 = u^(1), 2 = u^(2), 3 = u^(n+1).
+// On small 2D rectangles a stage is one launch and there is no dt kernel; short 1D instances
+// on uniform meshes run up to 64 whole steps in one launch, without a graph.
+// Speeds live in four slots: slot 0 = u^n, 1 = u^(1), 2 = u^(2), 3 = u^(n+1) (one-launch
+// stages read those of u^n in slot 3 and leave slot 0 alone).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

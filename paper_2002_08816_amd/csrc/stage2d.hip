@@ -9,8 +9,9 @@
 //  stage2d_limit  the Jacobi limiter of the first moments (Step 4, Remark 4) over the
 //                 flagged-cell list, one (cell, direction, characteristic field) per thread.
 //  stage2d_hweno  the HWENO edge values (Step 5.1) over the hybrid-cell list, one
-//                 (cell, characteristic field) per thread, both directions.  Work lists rather than tiles: the few tiles a shock crosses
-//                 would otherwise each run their whole share on one compute unit.
+//                 (cell, direction, characteristic field) per thread.  Work lists rather
+//                 than tiles: the few tiles a shock crosses would otherwise each run their
+//                 whole share on one compute unit.
 //  stage2d_kernel per 16 x 16 tile with two ghost layers (flags, hybrid masks and
 //                 limited moments read back): interior Gauss values of the least-squares quartic -> volume
 //                 integrals (Step 5.3); the edge values of the cell (Step 5.2 linear, or the
