@@ -687,10 +687,15 @@ __global__ __launch_bounds__(2 * NT, 2) void adjEL2d_kernel(Adj2D P) {
     }
   };
 
+  // A half's cotangents of the two components it pulls back (interior values, edge values of both
+  // directions), and those of the other two, which it hands over.  Both halves meet at every
+  // barrier from here on, each a single statement outside the branches.
+  double ui[2][9], e[2][2][2 * NGE];
+  constexpr int NHAND = 18 > 8 * NGE ? 18 : 8 * NGE;
+  double hand[NHAND];
   if (first) {
     // volume terms of eq. ode2: the x moment gains (1/dx) sum w f(u(G)), the y moment
     // (1/dy) sum w g(u(G)); cotangents of the interior values
-    double ubi[NC][9];
     double inner[NC][9];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -718,161 +723,156 @@ __global__ __launch_bounds__(2 * NT, 2) void adjEL2d_kernel(Adj2D P) {
       }
       euler_flux2d_vjp(U, P.gam, fb, gb, ub);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) ubi[c][p] = ub[c];
+      for (int c = 0; c < 2; ++c) {
+        hand[c * 9 + p] = ub[c];
+        ui[c][p] = ub[2 + c];
+      }
     }
-    __syncthreads();   // the staged values are done with
+  } else {
+    // edge values of both directions and the cotangents of the four faces' fluxes
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+      double v[NC][2 * NGE];
+      if (!hyb) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          double in[19], fold[hw2::NFOLD];
+          gather19<NC, W>(s_w, c, ly, lx, in);
+          hw2::lin2d_fold(in, fold);
+          lin_faces<NGE>(fold, dir, v[c], v[c] + NGE);
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int k = 0; k < NGE; ++k) {
+            v[c][k] = P.hwv[((((size_t)(dir * 2 + 0) * NGE + k) * NC + c)) * plane + gi];
+            v[c][NGE + k] = P.hwv[((((size_t)(dir * 2 + 1) * NGE + k) * NC + c)) * plane + gi];
+          }
+      }
+      const int oy = dir, ox = 1 - dir;
+      const double inv = dir == 0 ? idx : idy;
+      const double a = s_alpha[dir];
+      // the moment fed by (F_L + F_R)/2 and the one fed by the node-weighted difference
+      const int fP = dir == 0 ? 1 : 2, fQ = 3 - fP;
+#pragma unroll
+      for (int k = 0; k < NGE; ++k) {
+        const double wk = wt[k] * inv, nk = node[k];
+        double flo[NC], fhi[NC], zero[NC], ul[NC], uh[NC], Ul[NC], Uh[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const double lU = S<W>(s_l, c, ly, lx), cP = S<W>(s_l, fP * NC + c, ly, lx),
+                       cQ = S<W>(s_l, fQ * NC + c, ly, lx);
+          const double mU = S<W>(s_l, c, ly - oy, lx - ox), mP = S<W>(s_l, fP * NC + c, ly - oy, lx - ox),
+                       mQ = S<W>(s_l, fQ * NC + c, ly - oy, lx - ox);
+          const double pU = S<W>(s_l, c, ly + oy, lx + ox), pP = S<W>(s_l, fP * NC + c, ly + oy, lx + ox),
+                       pQ = S<W>(s_l, fQ * NC + c, ly + oy, lx + ox);
+          // low face: this cell's left/bottom face and the neighbour's right/top face
+          const double Flo = wk * ((lU - 0.5 * cP + nk * cQ) - (mU + 0.5 * mP + nk * mQ));
+          // high face: this cell's right/top face and the neighbour's left/bottom face
+          const double Fhi = wk * ((pU - 0.5 * pP + nk * pQ) - (lU + 0.5 * cP + nk * cQ));
+          // F = (f(u-) + f(u+))/2 - a (u+ - u-)/2: this cell is u+ on the low face, u- on
+          // the high face
+          flo[c] = 0.5 * Flo;
+          fhi[c] = 0.5 * Fhi;
+          ul[c] = -0.5 * a * Flo;
+          uh[c] = 0.5 * a * Fhi;
+          zero[c] = 0.0;
+          Ul[c] = v[c][k];
+          Uh[c] = v[c][NGE + k];
+        }
+        if (dir == 0) {
+          euler_flux2d_vjp(Ul, P.gam, flo, zero, ul);
+          euler_flux2d_vjp(Uh, P.gam, fhi, zero, uh);
+        } else {
+          euler_flux2d_vjp(Ul, P.gam, zero, flo, ul);
+          euler_flux2d_vjp(Uh, P.gam, zero, fhi, uh);
+        }
+        // a face on a transmissive or reflective side: the ghost's trace there is this
+        // cell's own trace (the normal momentum reversed at a reflective side), so the
+        // ghost's side of the flux, d/du- on the low face and d/du+ on the high face, also
+        // belongs to this cell
+        const int bc = dir == 0 ? P.bcx : P.bcy;
+        if (WALLS && bc != BC_PERIODIC) {
+          const int gd = dir == 0 ? gx : gy, nd = dir == 0 ? nx : ny;
+          const int cn = bc == BC_REFLECTIVE ? 1 + dir : -1;
+#pragma unroll
+          for (int side = 0; side < 2; ++side) {
+            if (side == 0 ? gd != 0 : gd != nd - 1) continue;
+            double Ug[NC], fg[NC], gg[NC], ug[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+              const double r = c == cn ? -1.0 : 1.0;
+              const double Fw = side == 0 ? flo[c] : fhi[c];   // half the face's weight
+              Ug[c] = r * (side == 0 ? Ul[c] : Uh[c]);
+              fg[c] = dir == 0 ? Fw : 0.0;
+              gg[c] = dir == 0 ? 0.0 : Fw;
+              ug[c] = (side == 0 ? a : -a) * Fw;   // d/du- = (f' + a)/2, d/du+ = (f' - a)/2
+            }
+            euler_flux2d_vjp(Ug, P.gam, fg, gg, ug);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+              const double r = c == cn ? -1.0 : 1.0;
+              if (side == 0) ul[c] += r * ug[c];
+              else uh[c] += r * ug[c];
+            }
+          }
+        }
+        // the resolver family: the face rule on faces towards a non-fluid position
+        if constexpr (BND >= ADJ_STEP) {
+          const int kl = face_of<BND>(P, gx, gy, dir, 0), kh = face_of<BND>(P, gx, gy, dir, 1);
+          if (kl != -2) own_trace_face(dir, 0, kl, a, P.gam, flo, Ul, ul);
+          if (kh != -2) own_trace_face(dir, 1, kh, a, P.gam, fhi, Uh, uh);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          e[c][dir][k] = ul[c];
+          e[c][dir][NGE + k] = uh[c];
+          hand[(dir * 2 + c) * 2 * NGE + k] = ul[2 + c];
+          hand[(dir * 2 + c) * 2 * NGE + NGE + k] = uh[2 + c];
+        }
+      }
+    }
+
+    if (hyb) {
+#pragma unroll
+      for (int dir = 0; dir < 2; ++dir)
+#pragma unroll
+        for (int k = 0; k < 2 * NGE; ++k)
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+            P.E[((size_t)(dir * 2 * NGE + k) * NC + c) * plane + gi] =
+                c < 2 ? e[c & 1][dir][k] : hand[(dir * 2 + (c & 1)) * 2 * NGE + k];
+    }
+  }
+  __syncthreads();   // the staged values are done with
+  if (first) {
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int p = 0; p < 9; ++p) x_int[(c * 9 + p) * NT] = ubi[c][p];
-    __syncthreads();
-    double e[2][2][2 * NGE];
+      for (int p = 0; p < 9; ++p) x_int[(c * 9 + p) * NT] = hand[c * 9 + p];
+  } else {
+#pragma unroll
+    for (int k = 0; k < 8 * NGE; ++k) x_edge[k * NT] = hand[k];
+  }
+  __syncthreads();
+  if (first) {
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int dir = 0; dir < 2; ++dir)
 #pragma unroll
         for (int k = 0; k < 2 * NGE; ++k) e[c][dir][k] = x_edge[((dir * 2 + c) * 2 * NGE + k) * NT];
+  } else {
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      __syncthreads();   // what was in the space is read
-      pull_back(ubi[2 + c], e[c][0], e[c][1]);
-      __syncthreads();
-      add_up(2 + c);
-    }
-    return;
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int p = 0; p < 9; ++p) ui[c][p] = x_int[(c * 9 + p) * NT];
   }
-
-  // edge values of both directions and the cotangents of the four faces' fluxes
-  double ube[2][NC][2 * NGE];
-#pragma unroll
-  for (int dir = 0; dir < 2; ++dir) {
-    double v[NC][2 * NGE];
-    if (!hyb) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        double in[19], fold[hw2::NFOLD];
-        gather19<NC, W>(s_w, c, ly, lx, in);
-        hw2::lin2d_fold(in, fold);
-        lin_faces<NGE>(fold, dir, v[c], v[c] + NGE);
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int k = 0; k < NGE; ++k) {
-          v[c][k] = P.hwv[((((size_t)(dir * 2 + 0) * NGE + k) * NC + c)) * plane + gi];
-          v[c][NGE + k] = P.hwv[((((size_t)(dir * 2 + 1) * NGE + k) * NC + c)) * plane + gi];
-        }
-    }
-    const int oy = dir, ox = 1 - dir;
-    const double inv = dir == 0 ? idx : idy;
-    const double a = s_alpha[dir];
-    // the moment fed by (F_L + F_R)/2 and the one fed by the node-weighted difference
-    const int fP = dir == 0 ? 1 : 2, fQ = 3 - fP;
-#pragma unroll
-    for (int k = 0; k < NGE; ++k) {
-      const double wk = wt[k] * inv, nk = node[k];
-      double flo[NC], fhi[NC], zero[NC], ul[NC], uh[NC], Ul[NC], Uh[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double lU = S<W>(s_l, c, ly, lx), cP = S<W>(s_l, fP * NC + c, ly, lx),
-                     cQ = S<W>(s_l, fQ * NC + c, ly, lx);
-        const double mU = S<W>(s_l, c, ly - oy, lx - ox), mP = S<W>(s_l, fP * NC + c, ly - oy, lx - ox),
-                     mQ = S<W>(s_l, fQ * NC + c, ly - oy, lx - ox);
-        const double pU = S<W>(s_l, c, ly + oy, lx + ox), pP = S<W>(s_l, fP * NC + c, ly + oy, lx + ox),
-                     pQ = S<W>(s_l, fQ * NC + c, ly + oy, lx + ox);
-        // low face: this cell's left/bottom face and the neighbour's right/top face
-        const double Flo = wk * ((lU - 0.5 * cP + nk * cQ) - (mU + 0.5 * mP + nk * mQ));
-        // high face: this cell's right/top face and the neighbour's left/bottom face
-        const double Fhi = wk * ((pU - 0.5 * pP + nk * pQ) - (lU + 0.5 * cP + nk * cQ));
-        // F = (f(u-) + f(u+))/2 - a (u+ - u-)/2: this cell is u+ on the low face, u- on
-        // the high face
-        flo[c] = 0.5 * Flo;
-        fhi[c] = 0.5 * Fhi;
-        ul[c] = -0.5 * a * Flo;
-        uh[c] = 0.5 * a * Fhi;
-        zero[c] = 0.0;
-        Ul[c] = v[c][k];
-        Uh[c] = v[c][NGE + k];
-      }
-      if (dir == 0) {
-        euler_flux2d_vjp(Ul, P.gam, flo, zero, ul);
-        euler_flux2d_vjp(Uh, P.gam, fhi, zero, uh);
-      } else {
-        euler_flux2d_vjp(Ul, P.gam, zero, flo, ul);
-        euler_flux2d_vjp(Uh, P.gam, zero, fhi, uh);
-      }
-      // a face on a transmissive or reflective side: the ghost's trace there is this
-      // cell's own trace (the normal momentum reversed at a reflective side), so the
-      // ghost's side of the flux, d/du- on the low face and d/du+ on the high face, also
-      // belongs to this cell
-      const int bc = dir == 0 ? P.bcx : P.bcy;
-      if (WALLS && bc != BC_PERIODIC) {
-        const int gd = dir == 0 ? gx : gy, nd = dir == 0 ? nx : ny;
-        const int cn = bc == BC_REFLECTIVE ? 1 + dir : -1;
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-          if (side == 0 ? gd != 0 : gd != nd - 1) continue;
-          double Ug[NC], fg[NC], gg[NC], ug[NC];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const double r = c == cn ? -1.0 : 1.0;
-            const double Fw = side == 0 ? flo[c] : fhi[c];   // half the face's weight
-            Ug[c] = r * (side == 0 ? Ul[c] : Uh[c]);
-            fg[c] = dir == 0 ? Fw : 0.0;
-            gg[c] = dir == 0 ? 0.0 : Fw;
-            ug[c] = (side == 0 ? a : -a) * Fw;   // d/du- = (f' + a)/2, d/du+ = (f' - a)/2
-          }
-          euler_flux2d_vjp(Ug, P.gam, fg, gg, ug);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const double r = c == cn ? -1.0 : 1.0;
-            if (side == 0) ul[c] += r * ug[c];
-            else uh[c] += r * ug[c];
-          }
-        }
-      }
-      // the resolver family: the face rule on faces towards a non-fluid position
-      if constexpr (BND >= ADJ_STEP) {
-        const int kl = face_of<BND>(P, gx, gy, dir, 0), kh = face_of<BND>(P, gx, gy, dir, 1);
-        if (kl != -2) own_trace_face(dir, 0, kl, a, P.gam, flo, Ul, ul);
-        if (kh != -2) own_trace_face(dir, 1, kh, a, P.gam, fhi, Uh, uh);
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        ube[dir][c][k] = ul[c];
-        ube[dir][c][NGE + k] = uh[c];
-      }
-    }
-  }
-
-  if (hyb) {
-#pragma unroll
-    for (int dir = 0; dir < 2; ++dir)
-#pragma unroll
-      for (int k = 0; k < 2 * NGE; ++k)
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-          P.E[((size_t)(dir * 2 * NGE + k) * NC + c) * plane + gi] = ube[dir][c][k];
-  }
-  __syncthreads();   // the staged values are done with
-#pragma unroll
-  for (int dir = 0; dir < 2; ++dir)
-#pragma unroll
-    for (int c = 2; c < NC; ++c)
-#pragma unroll
-      for (int k = 0; k < 2 * NGE; ++k) x_edge[((dir * 2 + c - 2) * 2 * NGE + k) * NT] = ube[dir][c][k];
-  __syncthreads();
-  double ui[2][9];
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int p = 0; p < 9; ++p) ui[c][p] = x_int[(c * 9 + p) * NT];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    __syncthreads();
-    pull_back(ui[c], ube[0][c], ube[1][c]);
+    __syncthreads();   // what was in the space is read
+    pull_back(ui[c], e[c][0], e[c][1]);
     __syncthreads();
     add_up(2 + c);
   }
