@@ -143,7 +143,8 @@ struct hw_solver {
   double* dtab = nullptr;                // double Mach reflection: prescribed ghosts of a stage
   int* wl = nullptr;                     // 2D: work lists [2 counts][flagged][hybrid]
   long long* stats = nullptr;            // 2D: list lengths of each stage of the last step [2][3],
-                                         // then those that one-launch stages accumulate
+                                         // those that one-launch stages accumulate, and those of
+                                         // stages that are replayed
   unsigned long long* alpha = nullptr;   // [4][aw] speed slots
   unsigned long long* alpha_op = nullptr;  // [aw]
   int aw = 1;                            // entries per slot: 1D ninst*ndir, 2D 2*ASPREAD
@@ -361,8 +362,8 @@ static hw_status alloc_common(hw_solver* h) {
     HWCHK(hipMalloc(&h->hwv, (size_t)4 * h->cfg.ng_edge * h->nc * h->ncell * sizeof(double)));
     HWCHK(hipMalloc(&h->wl, (2 + 2 * (size_t)h->ncell) * sizeof(int)));
     HWCHK(hipMemsetAsync(h->wl, 0, 2 * sizeof(int), h->stream));
-    HWCHK(hipMalloc(&h->stats, 12 * sizeof(long long)));
-    HWCHK(hipMemsetAsync(h->stats, 0, 12 * sizeof(long long), h->stream));
+    HWCHK(hipMalloc(&h->stats, 18 * sizeof(long long)));
+    HWCHK(hipMemsetAsync(h->stats, 0, 18 * sizeof(long long), h->stream));
   }
   if (h->cfg.bc_x == HW_BC_DMR)
     HWCHK(hipMalloc(&h->dtab, (size_t)12 * (4 * (h->cfg.nx + 4) + 4 * h->cfg.ny) * sizeof(double)));
@@ -607,6 +608,8 @@ static void stage1d_params(hw_solver* h, hw::Stage1D& P) {
   P.nu = h->nu;
 }
 
+// fslot: the stage's slot of the exported flags (-1: a replayed stage, which leaves the flags and
+// the handle's list lengths alone)
 static hw_status launch_stage(hw_solver* h, int mode, const double* in, const double* base,
                               double* out, const unsigned long long* ain, unsigned long long* aout,
                               int fslot, double* wout, int persistent,
@@ -626,7 +629,7 @@ static hw_status launch_stage(hw_solver* h, int mode, const double* in, const do
       P.counts = h->wl;
       P.flist = h->wl + 2;
       P.hlist = h->wl + 2 + h->ncell;
-      P.stats = h->stats;
+      P.stats = fslot < 0 ? h->stats + 12 : h->stats;
     }
     if (rec) {   // a stage of a recorded segment: its list passes' results kept in rec
       P.Tn = rec->Tn; P.limn = rec->limn;

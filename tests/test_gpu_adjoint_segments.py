@@ -65,3 +65,23 @@ def test_gradient_does_not_depend_on_the_segments(eq, tc, bc, nx, ny):
     s.steps(2, dt)
     assert np.array_equal(a, s.get_state()[0])
     s.close()
+
+
+@pytest.mark.parametrize("eq,nx,ny", [("burgers", 33, 20), ("burgers", 650, 641), ("advection", 33, 20),
+                                      ("euler", 40, 32), ("euler", 330, 322)])
+def test_a_gradient_leaves_the_list_lengths_alone(eq, nx, ny):
+    """The list lengths are those of the last step before and after a gradient, whose replayed
+    stages have lists of their own (one-launch stages and list passes)."""
+    import paper_2002_08816_amd as hw
+    nc = 4 if eq == "euler" else 1
+    U = hi.euler_wall_state(nx, ny, 4)[:, :nc].copy()
+    U[1:] *= 0.02
+    s = hw.Solver(2, nx, ny, eq=eq, ng_edge=2, tc_mode="kxrcf", bc="periodic", domain=(0.0, nx / ny, 0.0, 1.0))
+    s.set_state(U)
+    s.forward_ckpt(5, 2e-4, 2)
+    before = s.stats()
+    assert sum(before[1]) > 0
+    s.adjoint(np.ones_like(U))
+    for a, b in zip(s.stats(), before):
+        assert np.array_equal(np.asarray(a), np.asarray(b))
+    s.close()
