@@ -298,13 +298,15 @@ __device__ __forceinline__ double scalar_flux(double u, double a) {
   return 0.5 * u * u;
 }
 
-// Euler 1D flux (rho u, rho u^2 + p, u (E + p))
+// Euler 1D flux (rho u, rho u^2 + p, u (E + p)); contracted as written, so that every kernel
+// evaluates the same
 __device__ __forceinline__ void euler_flux1d(const double* U, double gam, double* f) {
-  const double u = U[1] * rcp_nr(U[0]);
-  const double p = (gam - 1.0) * (U[2] - 0.5 * U[1] * u);
+#pragma clang fp contract(off)
+  const double g1 = gam - 1.0, u = U[1] * rcp_nr(U[0]);
+  const double e = __builtin_fma(-0.5 * U[1], u, U[2]);   // p / (gamma - 1)
   f[0] = U[1];
-  f[1] = U[1] * u + p;
-  f[2] = u * (U[2] + p);
+  f[1] = __builtin_fma(U[1], u, g1 * e);
+  f[2] = u * __builtin_fma(g1, e, U[2]);
 }
 
 // Euler 2D fluxes f (x) and g (y) at one point

@@ -95,3 +95,40 @@ def test_batch_of_short_instances_equals_the_tile_kernels(hw):
     for b in range(len(sizes)):
         assert p1_field_err(out[0][0][b], out[1][0][b]) < TOL
         assert abs(out[0][1][b] - out[1][1][b]) <= 1e-14
+
+
+@pytest.mark.parametrize("eq,bc,tc", [("euler", "transmissive", "kxrcf"), ("euler", "reflective", "kxrcf"),
+                                      ("euler", "periodic", "all"), ("euler", "periodic", "none"),
+                                      ("burgers", "transmissive", "kxrcf"), ("advection", "periodic", "all")])
+def test_whole_steps_equal_the_stage_launches_to_the_bit(hw, eq, bc, tc):
+    """An instance's values do not depend on the launch form, nor, with it, on the other instances
+    of its batch: with an instance of 1025 cells beside them the same instances run through the
+    tile kernels."""
+    sizes = [100, 1000, 64, 512, 700, 300, 1024, 257, 7]
+    if eq != "euler":
+        Us = [scalar_state(n, n) for n in sizes + [1025]]
+    elif bc == "transmissive":
+        Us = [hi.euler_riemann_1d(b + 3, n)[0] if n >= 64 else hi.example_3_2(n, x1=2.0) for b, n in enumerate(sizes + [1025])]
+    elif bc == "reflective":
+        Us = []
+        for n in sizes + [1025]:   # (a slow density wave with a jump of the pressure)
+            U = hi.example_3_2(n, x1=2.0)
+            U[:, 1] *= 0.1
+            U[0, 2] += 1.0 * (np.arange(n) > 0.4 * n)
+            Us.append(U)
+    else:
+        Us = [hi.example_3_2(n, x1=2.0) for n in sizes + [1025]]
+    out = []
+    for m in (len(sizes), len(sizes) + 1):
+        bs = hw.BatchSolver((sizes + [1025])[:m], eq=eq, bc=bc, tc_mode=tc, adv=(0.8,))
+        bs.set_states(Us[:m])
+        bs.flag_export(True)
+        bs.steps(9)
+        out.append((bs.get_states(), bs.times()[0], [bs.flags(st) for st in range(3)]))
+        bs.close()
+    for b, n in enumerate(sizes):
+        assert np.all(np.isfinite(out[0][0][b]))
+        assert np.array_equal(out[0][0][b], out[1][0][b]) and out[0][1][b] == out[1][1][b], n
+        for st in range(3):
+            assert np.array_equal(out[0][2][st][0][b], out[1][2][st][0][b])
+            assert np.array_equal(out[0][2][st][1][b], out[1][2][st][1][b])
