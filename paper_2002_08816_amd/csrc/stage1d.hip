@@ -449,7 +449,9 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
   __syncthreads();   // the LDS is reused by the next work item
 
   // ---------------------------------------------------------------- epilogue
-  double sp = 0.0;
+  // (the ghosts' speeds are left out of the maximum as NaN is: a full tile without a speed that is a
+  // number counts as infinitely fast, and the steps after it stand still)
+  double sp = l >= H1 && l < T1 - H1 ? 0.0 : __builtin_nan("");
   if (active) {
     const size_t gidx = (size_t)off + gi;
     if (P.flagsT) P.flagsT[gidx] = myT;
@@ -529,12 +531,12 @@ __global__ __launch_bounds__(T1, 4) void stage1d_persistent(Stage1D P) {
   }
 }
 
-// maximum over a wave of non-negative values (NaN ignored), in lane 63: register moves within
-// rows of 16 lanes, then across them
+// maximum over a wave of non-negative values (NaN ignored; NaN where all are), in lane 63: register
+// moves within rows of 16 lanes, then across them (a lane without a source keeps its own value)
 __device__ __forceinline__ double wave_max63(double v) {
 #define HW_MAX_DPP(ctrl)                                                                         \
-  v = fmax(v, __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xF, 0xF, true), \
-                               __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xF, 0xF, true)))
+  v = fmax(v, __hiloint2double(__builtin_amdgcn_update_dpp(__double2hiint(v), __double2hiint(v), ctrl, 0xF, 0xF, false), \
+                               __builtin_amdgcn_update_dpp(__double2loint(v), __double2loint(v), ctrl, 0xF, 0xF, false)))
   HW_MAX_DPP(0x111);   // row_shr:1
   HW_MAX_DPP(0x112);
   HW_MAX_DPP(0x114);
@@ -543,6 +545,22 @@ __device__ __forceinline__ double wave_max63(double v) {
   HW_MAX_DPP(0x143);   // row_bcast:31
 #undef HW_MAX_DPP
   return v;
+}
+
+// The instance's speed from its waves' maxima: 256 cells without a speed that is a number count as
+// infinitely fast, as a full tile of the stage launches does.
+template <int NW>
+__device__ __forceinline__ double whole_speed(const double* red) {
+  double a = 0.0;
+#pragma unroll
+  for (int g = 0; g < NW; g += 4) {
+    double m = red[g];
+#pragma unroll
+    for (int i = g + 1; i < g + 4 && i < NW; ++i) m = fmax(m, red[i]);
+    if (NW >= 4 && !(m >= 0.0)) m = __longlong_as_double(0x7ff0000000000000ll);
+    a = fmax(a, m);
+  }
+  return a;
 }
 
 // LDS of one whole instance of at most T1 cells
@@ -804,10 +822,7 @@ __global__ __launch_bounds__(T1) void step1d_kernel(Stage1D P, Step1D Q, int nst
     if (k > 0) {
       // speed of the last stage's output (written before barriers of that stage's end)
       __syncthreads();
-      alpha = s_red[0];
-#pragma unroll
-      for (int i = 1; i < NW; ++i) alpha = fmax(alpha, s_red[i]);
-      if (!(alpha >= 0.0)) alpha = __longlong_as_double(0x7ff0000000000000ll);
+      alpha = whole_speed<NW>(s_red);
     }
     dt = Q.fixed_dt > 0.0 ? Q.fixed_dt : Q.cfl * dxs / alpha;
     if (Q.T_end > 0.0) {
@@ -834,12 +849,7 @@ __global__ __launch_bounds__(T1) void step1d_kernel(Stage1D P, Step1D Q, int nst
       }
       if (tid < 2) sh.cnt[tid] = 0;
       __syncthreads();
-      if (stage > 0) {
-        alpha = s_red[0];
-#pragma unroll
-        for (int i = 1; i < NW; ++i) alpha = fmax(alpha, s_red[i]);
-        if (!(alpha >= 0.0)) alpha = __longlong_as_double(0x7ff0000000000000ll);
-      }
+      if (stage > 0) alpha = whole_speed<NW>(s_red);
       double LU[NC], LV[NC], own[NF];
       uint8_t myT = 0, myH = 0;
       whole_operator<EQ, T1>(P, sh, n, 0.5 * dxs, idx, alpha, LU, LV, own, myT, myH);
@@ -877,10 +887,7 @@ __global__ __launch_bounds__(T1) void step1d_kernel(Stage1D P, Step1D Q, int nst
   if (tid == 0) {
     if (steps != Q.steps[inst] || !(dt == 0.0)) {
       // (at least one step was taken: the speed of its result)
-      double m = s_red[0];
-      for (int i = 1; i < NW; ++i) m = fmax(m, s_red[i]);
-      if (!(m >= 0.0)) m = __longlong_as_double(0x7ff0000000000000ll);
-      Q.alpha[3 * W + inst] = (unsigned long long)__double_as_longlong(m);
+      Q.alpha[3 * W + inst] = (unsigned long long)__double_as_longlong(whole_speed<NW>(s_red));
     }
     Q.dt[inst] = dt;
     Q.t[inst] = t;

@@ -132,3 +132,17 @@ def test_whole_steps_equal_the_stage_launches_to_the_bit(hw, eq, bc, tc):
         for st in range(3):
             assert np.array_equal(out[0][2][st][0][b], out[1][2][st][0][b])
             assert np.array_equal(out[0][2][st][1][b], out[1][2][st][1][b])
+
+
+@pytest.mark.parametrize("n", [300, 512, 1000, 1024, 1100])
+def test_a_state_of_nan_stands_still(hw, n):
+    """Cells whose speeds are no numbers make the Lax-Friedrichs speed infinite and the CFL step
+    zero, in the whole-step form (up to 1024 cells) as in the tile kernels: the time of a run that
+    has gone bad stays finite."""
+    s = hw.Solver(1, n, eq="euler", bc="transmissive", tc_mode="kxrcf")
+    s.set_state(np.full((2, 3, n), np.nan))
+    s.steps(1, dt=1e-3)
+    assert s.stats()[0][0] == np.inf
+    s.steps(3)
+    assert s.time() == (1e-3, 1)
+    s.close()
