@@ -148,10 +148,14 @@ __device__ __forceinline__ void wall_share1d(const double* u, int bc, double gam
   for (int c = 0; c < NC; ++c) share[c] = flux_share1d(g[c], fg[c], al, ref[c]);
 }
 
-// the four-point Gauss-Lobatto sum of a cell's fluxes
-__device__ __forceinline__ double lobatto_sum(double fL, double fR, double fm, double fp) {
+// the four-point Gauss-Lobatto sum of a cell's fluxes: the interior points' part, then all
+__device__ __forceinline__ double lobatto_inner(double fm, double fp) {
 #pragma clang fp contract(off)
-  return mad(fL + fR, 1.0 / 12.0, (fm + fp) * (5.0 / 12.0));
+  return (fm + fp) * (5.0 / 12.0);
+}
+__device__ __forceinline__ double lobatto_sum(double fL, double fR, double inner) {
+#pragma clang fp contract(off)
+  return mad(fL + fR, 1.0 / 12.0, inner);
 }
 
 // right-hand sides of eq. odeH: the shares of the low face and of the high face (own and other side)
@@ -412,7 +416,7 @@ __device__ void stage1d_tile(const Stage1D& P, int inst, int i0, double* s_in, d
     // the cell's shares of its two faces' fluxes
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      Fi[c] = lobatto_sum(fL[c], fR[c], fm[c], fp[c]);
+      Fi[c] = lobatto_sum(fL[c], fR[c], lobatto_inner(fm[c], fp[c]));
       fL[c] = flux_share1d(left[c], fL[c], -alpha, A(c, l - 1));
       fR[c] = flux_share1d(right[c], fR[c], alpha, A(c, l));
       s_face[c * T1 + l] = fL[c];
@@ -700,21 +704,28 @@ __device__ __forceinline__ void whole_operator(const Stage1D& P, WholeShared<EQ,
       if (f < 3) put(i, f, ol, orr);
     }
   }
-  double um[NC], up[NC];
+  // (what needs no other lane's traces comes before the barrier: it covers the lists' latency)
+  double Fi[NC], refL[NC], refR[NC];
   if (active) {
+    double um[NC], up[NC], fm[NC], fp[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       double a, b;
-      linear1d(A(c, l - 1), A(c, l), A(c, l + 1), A(NC + c, l - 1), A(NC + c, l), A(NC + c, l + 1), a, b, um[c], up[c]);
+      refL[c] = A(c, l - 1);
+      refR[c] = A(c, l);
+      linear1d(refL[c], refR[c], A(c, l + 1), A(NC + c, l - 1), A(NC + c, l), A(NC + c, l + 1), a, b, um[c], up[c]);
       if (!myH) put(tid, c, a, b);
     }
+    flux1d<EQ>(um, P.gam, P.adv, fm);
+    flux1d<EQ>(up, P.gam, P.adv, fp);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) Fi[c] = lobatto_inner(fm[c], fp[c]);
   }
   __syncthreads();
   // ---------------------------------------------------------------- fluxes
   // the cell's shares of its two faces take the place of its traces
-  double left[NC], right[NC], Fi[NC], fL[NC], fR[NC];
+  double left[NC], right[NC], fL[NC], fR[NC];
   if (active) {
-    double fm[NC], fp[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       left[c] = sh.fp[c * F1 + tid];
@@ -722,13 +733,11 @@ __device__ __forceinline__ void whole_operator(const Stage1D& P, WholeShared<EQ,
     }
     flux1d<EQ>(left, P.gam, P.adv, fL);
     flux1d<EQ>(right, P.gam, P.adv, fR);
-    flux1d<EQ>(um, P.gam, P.adv, fm);
-    flux1d<EQ>(up, P.gam, P.adv, fp);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      Fi[c] = lobatto_sum(fL[c], fR[c], fm[c], fp[c]);
-      fL[c] = flux_share1d(left[c], fL[c], -alpha, A(c, l - 1));
-      fR[c] = flux_share1d(right[c], fR[c], alpha, A(c, l));
+      Fi[c] = lobatto_sum(fL[c], fR[c], Fi[c]);
+      fL[c] = flux_share1d(left[c], fL[c], -alpha, refL[c]);
+      fR[c] = flux_share1d(right[c], fR[c], alpha, refR[c]);
       sh.fp[c * F1 + tid] = fL[c];
       sh.fm[c * F1 + tid + 1] = fR[c];
       // around the ends of a periodic instance (walls: replaced below)
@@ -748,10 +757,8 @@ __device__ __forceinline__ void whole_operator(const Stage1D& P, WholeShared<EQ,
 #pragma unroll
       for (int side = 0; side < 2; ++side) {
         if (tid != (side == 0 ? 0 : n - 1)) continue;
-        double ref[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) ref[c] = A(c, l - 1 + side);
-        wall_share1d<EQ>(side == 0 ? left : right, P.bc, P.gam, P.adv, side == 0 ? alpha : -alpha, ref, side == 0 ? lo : hi);
+        wall_share1d<EQ>(side == 0 ? left : right, P.bc, P.gam, P.adv, side == 0 ? alpha : -alpha,
+                         side == 0 ? refL : refR, side == 0 ? lo : hi);
       }
     }
 #pragma unroll
