@@ -204,24 +204,29 @@ hw_status hw_profile_steps(hw_solver* h, int nsteps, double dt, double* ms_stage
 /* Batched form: runs nsteps CFL steps of every instance through a captured HIP graph of
  * the step's launches; persistent = 1 runs each stage as one persistent grid over the
  * (instance, tile) work list, 0 as one workgroup per work item, -1 the form picked by
- * hw_batch_tune (one workgroup per work item until it has run).  Batches on uniform meshes
- * whose instances all have at most 1024 cells run whole steps in one workgroup per
- * instance, whatever the form. */
+ * hw_batch_tune or hw_batch_set_form.  Until one of them has run, -1 is one workgroup per work
+ * item; or, on uniform meshes whose instances all have at most 1024 cells and where the batch's
+ * size and mixture make it the faster form, whole steps in one launch, one workgroup per
+ * instance (hw_step, hw_steps and hw_run of a 1D handle choose likewise). */
 hw_status hw_batch_steps(hw_solver* h, int nsteps, int persistent);
 
 /* Autotuner of the batched stage: times one captured step (3 replays after a warm-up)
  * on the handle's own workload for every tile width (64, 128, 256, 512 positions = 1, 2, 4,
  * 8 waves per workgroup; six of them ghosts) and launch form (one workgroup per tile; persistent grids of
- * 1, 2, 4, 8 workgroups per compute unit), keeps the fastest for later calls, and leaves
- * the state, times and step counts as they were.  choice (may be NULL) receives three
- * ints: tile width, persistent (0/1), persistent grid size (0 when not persistent).  The
- * halo is fixed at three cells by the stencil. */
+ * 1, 2, 4, 8 workgroups per compute unit), and whole steps where the batch allows them, keeps the
+ * fastest for later calls, and leaves the state, times and step counts as they were.  choice
+ * (may be NULL) receives three ints for hw_batch_set_form: tile width, persistent (0/1),
+ * persistent grid size.  Not persistent, the last is 0, or 1 for tiles that were faster than the
+ * whole steps the library would choose.  Where whole steps are fastest, the tile is the best of one
+ * workgroup per tile.  The halo is fixed at three cells by the stencil. */
 hw_status hw_batch_tune(hw_solver* h, int* choice);
 
 /* Sets the batched launch form directly (e.g. a choice hw_batch_tune made earlier for the
- * same workload and kept by the caller): tile width 64, 128, 256 or 512 cells, persistent
- * 0 or 1, and for a persistent form the grid size (>= 1 workgroups).  Every form computes
- * the same values; only the launch changes.  HW_EINVAL for other values or a 2D handle. */
+ * same workload and kept by the caller): tile width 64, 128, 256 or 512 positions (six of them
+ * ghosts), persistent 0 or 1, and for a persistent form the grid size (>= 1 workgroups).  Not
+ * persistent with a grid of 0 or less, whole steps may still take the place of the tiles, as
+ * without a call; with a grid above 0 they do not.  Every form computes the same values to the
+ * bit; only the launch changes.  HW_EINVAL for other values or a 2D handle. */
 hw_status hw_batch_set_form(hw_solver* h, int tile, int persistent, int grid);
 
 /* ---- Reverse mode (Section 2.2 operator and eq. RK, differentiated).  Two-dimensional

@@ -169,6 +169,8 @@ hipError_t hw_launch_stage1d(int eq, int persistent, int grid, int tile, const h
                              hipStream_t s);
 // whole steps of short 1D instances: threads per instance (0: not for this batch), nsteps steps
 int hw_step1d_threads(int maxn, int nonuniform);
+// whether they beat the stage launches for ninst instances of so many cells in all
+int hw_step1d_pays(int eq, int threads, int ninst, long cells);
 hipError_t hw_launch_step1d(int eq, int threads, int ninst, const hw::Stage1D* P, const hw::Step1D* Q,
                             int nsteps, hipStream_t s);
 hipError_t hw_launch_alpha1d(int eq, const double* U, const int* off, int ninst, int total,

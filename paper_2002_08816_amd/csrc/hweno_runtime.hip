@@ -165,6 +165,8 @@ struct hw_solver {
   int tile1d = 256;                      // positions per 1D tile (= threads per workgroup)
   int pgrid = 0;                         // persistent grid (0: default)
   int auto_persist = 1;                  // launch form chosen by hw_batch_tune
+  int whole1d = -1;                      // whole steps in one workgroup per instance: by the rule
+                                         // of hw_step1d_pays (-1), never (0), always (1)
   std::vector<int> h_off;
   std::vector<double> h_dxs;             // per instance: the uniform cell size
   // graphs of one step and of STEPS_PER_GRAPH steps (fewer graph boundaries, each of which
@@ -696,9 +698,27 @@ static void launch_dt(hw_solver* h, double fixed_dt, double T_end) {
   launch_dt(h, fixed_dt, T_end, h->alpha + 3 * h->aw, h->alpha, h->stats);
 }
 
+// launch forms of a step
+enum { FORM_STAGES = 0, FORM_PERSISTENT = 1, FORM_WHOLE = 2 };
+
 // Threads per instance of the one-workgroup form of whole 1D steps (0: not for this handle)
 static int step1d_threads(const hw_solver* h) {
   return h->dim == 1 ? hw_step1d_threads(h->maxn, h->nu != nullptr) : 0;
+}
+
+static bool whole_pays(const hw_solver* h) {
+  const int threads = step1d_threads(h);
+  if (!threads) return false;
+  return hw_step1d_pays(h->cfg.eq, threads, h->ninst, h->ncell) != 0;
+}
+
+// The form of a handle's steps.  asked: 0 or 1 (hw_batch_steps: one workgroup per tile, a
+// persistent grid), -1 the handle's own (where that is stage launches, hw_batch_steps takes the
+// persistent grid that was set or tuned).  Not part of the ABI; the tests read it too.
+extern "C" int hw_step_form(const hw_solver* h, int asked) {
+  if (asked >= 0) return asked ? FORM_PERSISTENT : FORM_STAGES;
+  if (h->whole1d != 0 && step1d_threads(h) && (h->whole1d == 1 || whole_pays(h))) return FORM_WHOLE;
+  return FORM_STAGES;
 }
 
 // n whole steps of every instance in one workgroup each (step1d_threads(h) != 0); a launch
@@ -730,14 +750,14 @@ static hw_status enqueue_stage(hw_solver* h, int st, double fixed_dt, double T_e
                       h->alpha + (st + 1) * W, st, nullptr, persistent, nullptr, ev, nullptr, one ? &ctl : nullptr);
 }
 
-static hw_status enqueue_step(hw_solver* h, double fixed_dt, double T_end, int persistent) {
-  if (step1d_threads(h)) return enqueue_steps_1d(h, 1, fixed_dt, T_end);
+static hw_status enqueue_step(hw_solver* h, double fixed_dt, double T_end, int form) {
+  if (form == FORM_WHOLE) return enqueue_steps_1d(h, 1, fixed_dt, T_end);
   if (!one_launch(h)) {
     launch_dt(h, fixed_dt, T_end);
     HWCHK(hipGetLastError());
   }
   for (int st = 0; st < 3; ++st) {
-    hw_status s = enqueue_stage(h, st, fixed_dt, T_end, persistent);
+    hw_status s = enqueue_stage(h, st, fixed_dt, T_end, form);
     if (s != HW_OK) return s;
   }
   return HW_OK;
@@ -923,7 +943,7 @@ extern "C" hw_status hw_step(hw_solver* h, double dt) {
   HWCHK(hipMemcpyAsync(tsave.data(), h->t, h->ninst * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HWCHK(hipMemcpyAsync(ssave.data(), h->steps, h->ninst * sizeof(long long), hipMemcpyDeviceToHost, h->stream));
   HWCHK(hipMemsetAsync(h->status, 0, sizeof(int), h->stream));
-  hw_status s = enqueue_step(h, dt > 0.0 ? dt : 0.0, 0.0, 0);
+  hw_status s = enqueue_step(h, dt > 0.0 ? dt : 0.0, 0.0, hw_step_form(h, -1));
   if (s != HW_OK) return s;
   int st = 0;
   if ((s = read_status(h, &st)) != HW_OK) return s;
@@ -949,11 +969,11 @@ static hw_status launch_steps(hw_solver* h, long n) {
   return HW_OK;
 }
 
-// n steps: whole steps in one workgroup per instance where every 1D instance is short enough,
-// else from the captured graphs
-static hw_status run_steps(hw_solver* h, double fixed_dt, double T_end, int persistent, long n) {
-  if (step1d_threads(h)) return enqueue_steps_1d(h, n, fixed_dt, T_end);
-  hw_status s = capture_step(h, fixed_dt, T_end, persistent, n);
+// n steps in a launch form: whole steps in one workgroup per instance, else from the captured
+// graphs
+static hw_status run_steps(hw_solver* h, double fixed_dt, double T_end, int form, long n) {
+  if (form == FORM_WHOLE) return enqueue_steps_1d(h, n, fixed_dt, T_end);
+  hw_status s = capture_step(h, fixed_dt, T_end, form, n);
   if (s != HW_OK) return s;
   return launch_steps(h, n);
 }
@@ -964,7 +984,7 @@ extern "C" hw_status hw_steps(hw_solver* h, int nsteps, double dt) {
   if (!h) return fail(nullptr, HW_EINVAL, "null handle");
   if (nsteps < 0 || !std::isfinite(dt)) return fail(h, HW_EINVAL, "invalid step count or dt");
   if (nsteps == 0) return HW_OK;
-  return run_steps(h, dt > 0.0 ? dt : 0.0, 0.0, 0, nsteps);
+  return run_steps(h, dt > 0.0 ? dt : 0.0, 0.0, hw_step_form(h, -1), nsteps);
 }
 
 extern "C" hw_status hw_run(hw_solver* h, double T, long max_steps, long* steps_out, double* t_out) {
@@ -977,12 +997,13 @@ extern "C" hw_status hw_run(hw_solver* h, double T, long max_steps, long* steps_
   HWCHK(hipMemcpyAsync(&start, h->steps, sizeof(long long), hipMemcpyDeviceToHost, h->stream));
   HWCHK(hipStreamSynchronize(h->stream));
   long done_steps = 0;
+  const int form = hw_step_form(h, -1);
   while (true) {
     // (the one-workgroup form of a single instance stops by itself at T, and on a bad state
     // after the same multiples of 16 steps)
-    const long chunk = std::min<long>(h->ninst == 1 && step1d_threads(h) ? 64 : 16, max_steps - done_steps);
+    const long chunk = std::min<long>(h->ninst == 1 && form == FORM_WHOLE ? 64 : 16, max_steps - done_steps);
     if (chunk <= 0) break;
-    hw_status s = run_steps(h, 0.0, T, 0, chunk);
+    hw_status s = run_steps(h, 0.0, T, form, chunk);
     if (s != HW_OK) return s;
     HWCHK(hipMemcpyAsync(tt.data(), h->t, h->ninst * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HWCHK(hipMemcpyAsync(ss.data(), h->steps, h->ninst * sizeof(long long), hipMemcpyDeviceToHost, h->stream));
@@ -1434,7 +1455,8 @@ static hw_status capture_step(hw_solver* h, double fixed_dt, double T_end, int p
 extern "C" hw_status hw_batch_steps(hw_solver* h, int nsteps, int persistent) {
   if (!h) return fail(nullptr, HW_EINVAL, "null handle");
   if (h->dim != 1 || nsteps < 0) return fail(h, HW_EINVAL, "batched steps need a 1D handle and nsteps >= 0");
-  const int form = persistent < 0 ? h->auto_persist : (persistent ? 1 : 0);
+  int form = hw_step_form(h, persistent);
+  if (persistent < 0 && form == FORM_STAGES && h->auto_persist) form = FORM_PERSISTENT;
   return run_steps(h, 0.0, 0.0, form, nsteps);
 }
 
@@ -1477,6 +1499,7 @@ extern "C" hw_status hw_set_mesh_1d(hw_solver* h, const double* faces) {
       h->pgrid = 0;
     }
     h->auto_persist = 0;
+    h->whole1d = -1;
   }
   // captured steps hold the old kernel arguments
   HWCHK(hipMemcpyAsync(h->dxs, dmin.data(), ni * sizeof(double), hipMemcpyHostToDevice, h->stream));
@@ -1497,6 +1520,7 @@ extern "C" hw_status hw_batch_set_form(hw_solver* h, int tile, int persistent, i
   if (s != HW_OK) return s;
   h->pgrid = persistent ? grid : 0;
   h->auto_persist = persistent;
+  h->whole1d = persistent || grid > 0 ? 0 : -1;
   drop_graph(h);
   return HW_OK;
 }
@@ -1522,15 +1546,26 @@ extern "C" hw_status hw_batch_tune(hw_solver* h, int* grid_chosen) {
   HWCHK(hipMemcpyAsync(ssave.data(), h->steps, h->ninst * sizeof(long long), hipMemcpyDeviceToHost, h->stream));
   HWCHK(hipStreamSynchronize(h->stream));
   // candidates: tile width (= waves per workgroup x 64) x launch form (one workgroup per
-  // tile, or a persistent grid of cu x m workgroups walking the work list)
+  // tile, or a persistent grid of cu x m workgroups walking the work list), and whole steps
   const int tiles[] = {64, 128, 256, 512};
   const int mults[] = {0, 1, 2, 4, 8};   // 0: one workgroup per tile
-  double best = 1e300;
-  int best_tile = 256, best_persist = 0, best_grid = 0;
+  double best = 1e300, best_plain = 1e300;
+  int best_tile = 256, best_persist = 0, best_grid = 0, plain_tile = 256;
   hipEvent_t e0, e1;
   HWCHK(hipEventCreate(&e0));
   HWCHK(hipEventCreate(&e1));
   hw_status s = HW_OK;
+  // us of three steps in one form, after one that captures and warms up
+  auto timed = [&](int form, float& ms) -> hw_status {
+    hw_status r = run_steps(h, 0.0, 0.0, form, 1);
+    if (r != HW_OK) return r;
+    HWCHK(hipEventRecord(e0, h->stream));
+    if ((r = run_steps(h, 0.0, 0.0, form, 3)) != HW_OK) return r;
+    HWCHK(hipEventRecord(e1, h->stream));
+    HWCHK(hipEventSynchronize(e1));
+    HWCHK(hipEventElapsedTime(&ms, e0, e1));
+    return HW_OK;
+  };
   for (int tile : tiles) {
     if ((s = build_items(h, tile)) != HW_OK) break;
     for (int m : mults) {
@@ -1538,13 +1573,12 @@ extern "C" hw_status hw_batch_tune(hw_solver* h, int* grid_chosen) {
       const int grid = persist ? std::min(cu * m, std::max(1, h->nitems)) : 0;
       if (persist && grid >= h->nitems) continue;   // no better than one workgroup per tile
       h->pgrid = grid;
-      if ((s = hw_batch_steps(h, 1, persist)) != HW_OK) break;   // capture + warm-up
-      HWCHK(hipEventRecord(e0, h->stream));
-      if ((s = hw_batch_steps(h, 3, persist)) != HW_OK) break;
-      HWCHK(hipEventRecord(e1, h->stream));
-      HWCHK(hipEventSynchronize(e1));
       float ms = 0.f;
-      HWCHK(hipEventElapsedTime(&ms, e0, e1));
+      if ((s = timed(persist, ms)) != HW_OK) break;
+      if (!persist && ms < best_plain) {
+        best_plain = ms;
+        plain_tile = tile;
+      }
       if (ms < best) {
         best = ms;
         best_tile = tile;
@@ -1554,12 +1588,26 @@ extern "C" hw_status hw_batch_tune(hw_solver* h, int* grid_chosen) {
     }
     if (s != HW_OK) break;
   }
+  // whole steps in one workgroup per instance, where the handle has them
+  int whole = 0;
+  if (s == HW_OK && step1d_threads(h)) {
+    float ms = 0.f;
+    s = timed(FORM_WHOLE, ms);
+    whole = s == HW_OK && ms < best;
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (s != HW_OK) return s;
+  if (whole) {   // (with the best of the forms that leave the choice to the library's rule)
+    best_tile = plain_tile;
+    best_persist = best_grid = 0;
+  } else if (!best_persist && whole_pays(h)) {
+    best_grid = 1;   // the tile form in spite of the rule
+  }
   if ((s = build_items(h, best_tile)) != HW_OK) return s;
-  h->pgrid = best_grid;
+  h->pgrid = best_persist ? best_grid : 0;
   h->auto_persist = best_persist;
+  h->whole1d = whole;
   drop_graph(h);
   HWCHK(hipMemcpyAsync(h->S0, h->backup, n * sizeof(double), hipMemcpyDeviceToDevice, h->stream));
   HWCHK(hipMemcpyAsync(h->alpha + 3 * W, asave.data(), W * sizeof(unsigned long long), hipMemcpyHostToDevice, h->stream));

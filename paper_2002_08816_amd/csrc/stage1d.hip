@@ -1182,6 +1182,25 @@ extern "C" int hw_step1d_threads(int maxn, int nonuniform) {
   return maxn <= 128 ? 128 : (maxn <= 256 ? 256 : (maxn <= 512 ? 512 : 1024));
 }
 
+// Whether whole steps take less time than the stage launches, from what both measured (us a step;
+// shock tubes).  A round of workgroups takes as long as one of them, whatever its instance fills of it, and
+// a compute unit holds 4, 2, 1 and 1 Euler workgroups of 128 to 1024 threads, 8, 4, 2 and 1 scalar ones;
+// the stage launches take a time per cell and one per instance (at their default width).
+// Whole steps / stage launches, Euler: 1 of 1000 cells 22 / 26; 512 of 64 to 1024 45 / 50, 1024 of them
+// 86 / 70, 4096 313 / 169; 4096 of 1000 351 / 406; 2048 of 500 135 / 125; 4096 of 64 77 / 93; 4000 of 64 with one
+// of 1000 276 / 93.  Burgers: 512 of 64 to 1024 23 / 26, 4096 of them 158 / 79; 4096 of 256 45 / 65; 4000 of 64
+// with one of 1000 140 / 43.
+extern "C" int hw_step1d_pays(int eq, int threads, int ninst, long cells) {
+  const int w = threads <= 128 ? 0 : (threads <= 256 ? 1 : (threads <= 512 ? 2 : 3));
+  const bool euler = eq == hw::EQ_EULER;
+  const int round_e[4] = {1024, 512, 256, 256}, round_s[4] = {2048, 1024, 512, 256};
+  const double us_e[4] = {19.0, 17.6, 16.7, 23.0}, us_s[4] = {13.0, 11.3, 10.9, 11.5};
+  const int per = euler ? round_e[w] : round_s[w];
+  const double whole = (euler ? us_e[w] : us_s[w]) * ((ninst + per - 1) / per);
+  const double stages = euler ? 30.0 + 8e-5 * cells + 9e-3 * ninst : 18.0 + 3.5e-5 * cells + 4e-3 * ninst;
+  return whole <= stages;
+}
+
 template <int EQ>
 static hipError_t launch_step1d(int threads, int ninst, const hw::Stage1D* P, const hw::Step1D* Q, int nsteps,
                                 hipStream_t s) {

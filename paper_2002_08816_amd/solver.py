@@ -251,7 +251,9 @@ class BatchSolver:
         return t, steps
 
     def steps(self, n, persistent=None):
-        """n graph-replayed CFL steps; persistent None uses the autotuned launch form."""
+        """n CFL steps; persistent None uses the tuned or set launch form, or whole steps in one
+        launch where the instances are short and that is the faster form; True and False the
+        stage launches, as a persistent grid and as one workgroup per tile."""
         capi.hw_batch_steps(self.h, n, -1 if persistent is None else (1 if persistent else 0))
 
     def tune(self, cache=None):
@@ -287,7 +289,8 @@ class BatchSolver:
         return choice
 
     def set_form(self, tile, persistent, grid=0):
-        """Sets the launch form directly (tile width, persistent 0/1, persistent grid)."""
+        """Sets the launch form directly (tile width, persistent 0/1, persistent grid); not
+        persistent, a grid above 0 keeps the library from whole steps."""
         capi.hw_batch_set_form(self.h, tile, persistent, grid)
 
     def set_meshes(self, faces):

@@ -146,3 +146,90 @@ def test_a_state_of_nan_stands_still(hw, n):
     s.steps(3)
     assert s.time() == (1e-3, 1)
     s.close()
+
+
+def test_launch_forms_are_obeyed(hw):
+    """A call that names a launch form gets it, on batches of short instances too; the tuner
+    times whole steps beside the tile forms, and its choice can be set again.  All forms give the
+    same values."""
+    from paper_2002_08816_amd import capi
+    form = lambda bs, asked=-1: capi._lib.hw_step_form(bs.h, asked)
+    stages, persistent, whole = 0, 1, 2
+    short, skewed = [300, 700, 64], [64] * 1000 + [1000]
+    out = []
+    for k, (sizes, own) in enumerate(((short, whole), (skewed, stages), (short + [1100], stages))):
+        bs = hw.BatchSolver(sizes, eq="euler", bc="transmissive", tc_mode="kxrcf")
+        Us = [hi.euler_riemann_1d(b % 7 + 3, n)[0] for b, n in enumerate(sizes)]
+        assert form(bs) == own and form(bs, 0) == stages and form(bs, 1) == persistent
+        states = []
+        for asked in (None, False, True):
+            bs.set_states(Us)
+            bs.steps(9, persistent=asked)
+            states.append(np.concatenate(bs.get_states(), axis=-1))
+        bs.set_form(128, 0)
+        assert form(bs) == own
+        bs.set_form(128, 0, 1)
+        assert form(bs) == stages
+        bs.set_form(128, 1, 4)
+        assert form(bs) == stages
+        bs.set_states(Us)
+        bs.steps(9)
+        states.append(np.concatenate(bs.get_states(), axis=-1))
+        tile, pers, grid = bs.tune()
+        tuned = form(bs)
+        bs.set_states(Us)
+        bs.steps(9)
+        states.append(np.concatenate(bs.get_states(), axis=-1))
+        if pers or grid > 0:
+            bs.set_form(tile, pers, grid)
+            assert form(bs) == tuned == stages
+        assert pers == 0 or grid > 1
+        for s in states[1:]:
+            assert np.array_equal(s, states[0], equal_nan=True)
+        bs.set_meshes([np.linspace(0.0, 1.0, n + 1) for n in sizes])
+        assert form(bs) == stages
+        bs.set_meshes(None)
+        assert form(bs) == own
+        bs.close()
+
+
+def test_blast_batch_in_every_form_with_a_longer_instance(hw):
+    """Reflective walls in the tile kernels, one workgroup per tile and persistent, against the
+    oracle: an instance of 1100 cells keeps the batch from whole steps."""
+    from paper_2002_08816_amd import capi
+    sizes = [1100, 400]
+    Us = [hi.example_3_8(n) for n in sizes]
+    os_ = [Scheme1D("euler", n, 0.0, 1.0, bc="reflective", tc_mode="kxrcf") for n in sizes]
+    for k in range(51):
+        if k == 50:
+            refs = [o.rk3_step(U, o.cfl_dt(U, 0.6))[0] for o, U in zip(os_, Us)]
+            for asked in (False, True):
+                bs = hw.BatchSolver(sizes, eq="euler", bc="reflective", tc_mode="kxrcf")
+                assert capi._lib.hw_step_form(bs.h, -1) == 0
+                bs.set_states(Us)
+                bs.steps(1, persistent=asked)
+                for got, ref in zip(bs.get_states(), refs):
+                    assert p1_field_err(got, ref) < TOL
+                bs.close()
+        Us = [o.rk3_step(U, o.cfl_dt(U, 0.6))[0] for o, U in zip(os_, Us)]
+
+
+def test_eight_step_graph_of_stage_launches(hw):
+    """Eleven steps of the stage launches (a replay of the eight-step graph and three of one step)
+    and eleven single replays, one workgroup per tile and persistent."""
+    from paper_2002_08816_amd import capi
+    sizes = [64, 300, 1100, 2000]
+    Us = [hi.euler_riemann_1d(b + 3, n)[0] for b, n in enumerate(sizes)]
+    res = []
+    for asked in (False, True):
+        for parts in ([11], [1] * 11):
+            bs = hw.BatchSolver(sizes, eq="euler", bc="transmissive", tc_mode="kxrcf")
+            assert capi._lib.hw_step_form(bs.h, -1) == 0
+            bs.set_states(Us)
+            for n in parts:
+                bs.steps(n, persistent=asked)
+            res.append(np.concatenate(bs.get_states(), axis=-1))
+            bs.close()
+    assert np.all(np.isfinite(res[0]))
+    for r in res[1:]:
+        assert np.array_equal(r, res[0])
