@@ -74,6 +74,8 @@ struct Stage2D {
 
 // positions of a 1D tile that are ghosts: a tile of T threads yields T - 6 cells
 constexpr int TILE1D_GHOSTS = 6;
+// threads per tile of a mesh of cells of different sizes
+constexpr int TILE1D_NU = 256;
 
 // One-dimensional stage, single or batched (see stage1d.hip).
 struct Stage1D {
@@ -171,6 +173,8 @@ hipError_t hw_launch_stage1d(int eq, int persistent, int grid, int tile, const h
 int hw_step1d_threads(int maxn, int nonuniform);
 // whether they beat the stage launches for ninst instances of so many cells in all
 int hw_step1d_pays(int eq, int threads, int ninst, long cells);
+// threads per tile of the stage launches of a handle that is not tuned
+int hw_tile1d_default(int eq, int ninst, long cells, int maxn);
 hipError_t hw_launch_step1d(int eq, int threads, int ninst, const hw::Stage1D* P, const hw::Step1D* Q,
                             int nsteps, hipStream_t s);
 hipError_t hw_launch_alpha1d(int eq, const double* U, const int* off, int ninst, int total,

@@ -162,9 +162,9 @@ struct hw_solver {
   double* dxs = nullptr;
   int2* items = nullptr;                 // (instance, first cell) of every tile
   int nitems = 0;
-  int tile1d = 256;                      // positions per 1D tile (= threads per workgroup)
+  int tile1d = 0;                        // positions per 1D tile (= threads per workgroup)
   int pgrid = 0;                         // persistent grid (0: default)
-  int auto_persist = 1;                  // launch form chosen by hw_batch_tune
+  int auto_persist = 0;                  // launch form chosen by hw_batch_tune
   int whole1d = -1;                      // whole steps in one workgroup per instance: by the rule
                                          // of hw_step1d_pays (-1), never (0), always (1)
   std::vector<int> h_off;
@@ -414,7 +414,7 @@ static hw_status setup_1d(hw_solver* h, const std::vector<int>& nxs, const std::
   HWCHK(hipMalloc(&h->dxs, h->ninst * sizeof(double)));
   HWCHK(hipMemcpyAsync(h->off, h->h_off.data(), (h->ninst + 1) * sizeof(int), hipMemcpyHostToDevice, h->stream));
   HWCHK(hipMemcpyAsync(h->dxs, dxs.data(), h->ninst * sizeof(double), hipMemcpyHostToDevice, h->stream));
-  hw_status s = build_items(h, 256);
+  hw_status s = build_items(h, hw_tile1d_default(h->cfg.eq, h->ninst, h->ncell, h->maxn));
   if (s != HW_OK) return s;
   return alloc_common(h);
 }
@@ -1469,8 +1469,12 @@ extern "C" hw_status hw_set_mesh_1d(hw_solver* h, const double* faces) {
   std::vector<double> dmin(ni);
   if (!faces) {
     // back to the configuration's uniform meshes
-    if (h->nu) HWCHK(hipFree(h->nu));
-    h->nu = nullptr;
+    if (h->nu) {
+      HWCHK(hipFree(h->nu));
+      h->nu = nullptr;
+      hw_status s = build_items(h, hw_tile1d_default(h->cfg.eq, h->ninst, h->ncell, h->maxn));
+      if (s != HW_OK) return s;
+    }
     dmin = h->h_dxs;
   } else {
     for (int b = 0; b < ni; ++b) {
@@ -1493,8 +1497,8 @@ extern "C" hw_status hw_set_mesh_1d(hw_solver* h, const double* faces) {
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     (void)hipFree(d_faces);
     HWCHK(e);
-    if (h->tile1d != 256 || h->pgrid != 0) {
-      hw_status s = build_items(h, 256);
+    if (h->tile1d != hw::TILE1D_NU || h->pgrid != 0) {
+      hw_status s = build_items(h, hw::TILE1D_NU);
       if (s != HW_OK) return s;
       h->pgrid = 0;
     }

@@ -1201,6 +1201,18 @@ extern "C" int hw_step1d_pays(int eq, int threads, int ninst, long cells) {
   return whole <= stages;
 }
 
+// Threads per tile where neither the caller nor the tuner has chosen: narrow tiles pack short instances
+// better (a tile yields six cells less than it has threads), but every tile of an instance takes the maximum
+// of its speeds to one address, 12 ns each in turn.  us a step with 64 / 128 / 256 threads, Euler: 4096
+// instances of 256 cells 133 / 174 / 236; 512 of 512 45 / 49 / 68; 2000 of 1100 221 / 236 / 242; 512 of 2048
+// 122 / 110 / 118; 64 of 4096 72 / 50 / 50; one of 262144 178 / 98 / 64.  Burgers: 4096 of 256 65 / 77 / 95; 1024 of
+// 1000 62 / 58 / 57; 300 of 4096 107 / 71 / 60.
+extern "C" int hw_tile1d_default(int eq, int ninst, long cells, int maxn) {
+  const bool euler = eq == hw::EQ_EULER;
+  if (maxn <= 4096 && cells <= (euler ? 1100L : 600L) * ninst) return 64;
+  return euler && maxn <= 16384 ? 128 : 256;
+}
+
 template <int EQ>
 static hipError_t launch_step1d(int threads, int ninst, const hw::Stage1D* P, const hw::Step1D* Q, int nsteps,
                                 hipStream_t s) {
