@@ -354,7 +354,8 @@ class Scheme2D:
         the neighbours)."""
         A = A.copy()
         nx, ny = self.nx, self.ny
-        rows = slice(NG, NG + ny)
+        # with y periodic, the rows beyond the mesh are mesh rows: their x ghosts mirror too
+        rows = slice(NG, NG + ny) if self.bc[1] != "periodic" else slice(None)
         if self.bc[0] != "periodic":
             for g in range(1, NG + 1):
                 A[..., rows, NG - g] = sx * A[..., rows, NG + g - 1]

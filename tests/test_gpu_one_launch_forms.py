@@ -108,3 +108,23 @@ def test_one_launch_steps_by_every_call(hw, eq, n):
         V, _ = o.rk3_step(V, 1e-4)
     assert array_err(s.get_state()[0], V) < TOL and abs(s.time()[0] - 2e-4) < 1e-18
     s.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(9, 40), (12, 40), (16, 40), (17, 40), (40, 9), (321, 330)])
+@pytest.mark.parametrize("eq,ng", [("euler", 2), ("euler", 3), ("burgers", 3)])
+def test_walls_in_x_with_y_periodic(hw, eq, ng, nx, ny):
+    """The cells where the periodic rows meet the transmissive columns (one-launch stage; list
+    passes on the last mesh for Euler)."""
+    h = 1.0 / ny
+    U = state(eq, nx, ny)
+    kw = dict(bc=("transmissive", "periodic"), ng_edge=ng, tc_mode="kxrcf")
+    s = hw.Solver(2, nx, ny, domain=(0.0, nx * h, 0.0, 1.0), eq=eq, **kw)
+    s.flag_export(True)
+    L, W = s.apply_operator(U)
+    T, H = s.flags(0)
+    o = Scheme2D(Equation(eq, 2), nx, ny, 0.0, nx * h, 0.0, 1.0, **kw)
+    Lo, info = o.operator(U)
+    assert np.array_equal(T, info["T"]) and np.array_equal(H, info["H"])
+    assert array_err(L, Lo) < TOL
+    assert array_err(W, info["limited"]) < TOL
+    s.close()
