@@ -9,7 +9,7 @@ import pytest
 import hweno_inputs as hi
 from oracle.physics import Equation
 from oracle.scheme2d import Scheme2D
-from parity import TOL, array_err
+from parity import TOL, array_err, p1_field_err
 
 pytestmark = pytest.mark.gpu
 
@@ -100,4 +100,37 @@ def test_list_passes_on_a_mesh_with_walls(hw, eq, bc, nx, ny):
     assert np.array_equal(T, info["T"]) and np.array_equal(H, info["H"])
     assert array_err(L, Lo) < TOL
     assert array_err(W, info["limited"]) < TOL
+    s.close()
+
+
+@pytest.mark.parametrize("eq,bc,ng,tc,nx,ny", [
+    ("euler", ("periodic", "reflective"), 2, "kxrcf", 35, 2145), ("euler", ("reflective", "transmissive"), 2, "all", 17, 3217),
+    ("euler", ("transmissive", "reflective"), 3, "all", 17, 3217), ("euler", ("reflective", "periodic"), 3, "kxrcf", 35, 2145),
+    ("advection", ("transmissive", "periodic"), 2, "kxrcf", 17, 12817),
+    ("burgers", ("periodic", "transmissive"), 2, "all", 17, 12817)])
+def test_list_passes_with_walls_and_a_step(hw, eq, bc, ng, tc, nx, ny):
+    """Strips of more tiles than the one-launch stage takes, so that the flags, limiter, HWENO and
+    stage launches run: the operator, and one Runge-Kutta step (the limited values of u^n in its
+    second and third stage), against the oracle."""
+    h = 1.0 / 64
+    U = hi.euler_wall_state(nx, ny, 5)
+    U[1:] *= 0.02
+    if eq != "euler":
+        U = np.ascontiguousarray(U[:, :1])
+    kw = dict(bc=bc, ng_edge=ng, tc_mode=tc)
+    s = hw.Solver(2, nx, ny, domain=(0.0, nx * h, 0.0, ny * h), eq=eq, adv=(0.7, -0.45), **kw)
+    s.flag_export(True)
+    L, W = s.apply_operator(U)
+    T, H = s.flags(0)
+    o = Scheme2D(Equation(eq, 2, adv=(0.7, -0.45)), nx, ny, 0.0, nx * h, 0.0, ny * h, **kw)
+    Lo, info = o.operator(U)
+    assert np.array_equal(T, info["T"]) and np.array_equal(H, info["H"]) and T.any()
+    assert array_err(L, Lo) < TOL
+    assert array_err(W, info["limited"]) < TOL
+    s.set_state(U)
+    s.steps(1, dt=1e-3)
+    V, infos = o.rk3_step(U, 1e-3)
+    for st in range(3):
+        assert np.array_equal(s.flags(st)[0], infos[st]["T"])
+    assert p1_field_err(s.get_state()[0], V) < TOL
     s.close()
