@@ -16,8 +16,8 @@ K steps), inputs resident in HBM before the timed region.
 Beside the headline, on the same GPU:
 * batched: 512 independent 1D Euler instances, sizes log-uniform in [256, 8192]
   (hweno_inputs.batch_euler_1d), 200 CFL steps each through the captured step graph with
-  the autotuned tile width and launch form; compared with the untuned default (256-cell
-  tiles, one workgroup per tile), and with the plain single-instance solver run instance
+  the autotuned tile width and launch form; compared with tiles of 256 positions, one
+  workgroup per tile, and with the plain single-instance solver run instance
   after instance (on a sample of instances); batched.roofline prices the algorithmic
   128 B per cell-stage over the whole step;
 * adjoint: 2D Burgers 256^2 on [0, 4]^2, NG = 3, 200 steps of dt = 1/(200 pi), checkpoints
@@ -87,7 +87,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "stage2d_euler_1024_hbm_traffic.md
 FP64_FILE = os.path.join(ROOT, "profiles", "stage2d_euler_1024_instruction_mix.md")
 FP64_PEAK_TFLOPS = 78.6
 # launch form of the 512-instance batch for counter runs: the autotuner's choice for it on
-# MI355X (128-cell tiles, one workgroup per tile)
+# MI355X (tiles of 128 positions, one workgroup per tile)
 BATCH_FORM = (128, 0, 0)
 
 
@@ -276,7 +276,8 @@ def bench_batched(seed):
     nsteps = 200
     cells = int(np.sum(sizes))
     bs = BatchSolver(sizes, eq="euler", bc="transmissive", tc_mode="kxrcf")
-    # before tuning: 256-cell tiles, one workgroup per tile
+    # before tuning: tiles of 256 positions, one workgroup per tile
+    bs.set_form(256, 0)
     bs.set_states(Us)
     bs.steps(9, persistent=False)         # captures the 8-step and 1-step graphs; warm-up
     bs.set_states(Us)
@@ -310,8 +311,8 @@ def bench_batched(seed):
                     f"(sum {cells} cells), transmissive, KXRCF, per-instance CFL dt, "
                     f"{nsteps} steps, captured step graph",
         "value": r_p, "unit": "cell-stage updates/s", "ms_per_step": ms_p / nsteps,
-        "tuned": {"tile_cells": tile, "persistent": bool(persist), "grid": grid},
-        "untuned_256_cell_tiles": {"value": r_np, "ms_per_step": ms_np / nsteps},
+        "tuned": {"tile_positions": tile, "persistent": bool(persist), "grid": grid},
+        "tiles_of_256_positions": {"value": r_np, "ms_per_step": ms_np / nsteps},
         "plain_one_instance_at_a_time": {"value": r_plain, "instances_sampled": len(sample)},
         "vs_plain": r_p / r_plain,
         "roofline": {"bound": "hbm", "achieved": gbps, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -552,7 +553,7 @@ def profile_run(seed, leg):
         bs.tstream.synchronize()
         bs.close()
         print(f"profile run done: 1 copy of 256 MiB, 12 batched stages ({int(np.sum(sizes))} "
-              f"cells, {BATCH_FORM[0]}-cell tiles)", flush=True)
+              f"cells, tiles of {BATCH_FORM[0]} positions)", flush=True)
     elif leg == "adjoint_euler":
         n, k = 256, 20
         U0, _ = hi.euler_shock_vortex_2d(seed, n=n)

@@ -176,7 +176,7 @@ hw_status hw_set_time(hw_solver* h, double t);
  * neighbour sizes; a mirrored ghost at a transmissive or reflective boundary has the size
  * of the cell it mirrors.  faces = NULL returns to the configuration's uniform meshes.  2D
  * handles get HW_EINVAL, and so do faces that are not strictly increasing.  Fixes the
- * launch form (256-cell tiles, one workgroup per tile: hw_batch_tune and hw_batch_set_form
+ * launch form (tiles of 256 positions, one workgroup per tile: hw_batch_tune and hw_batch_set_form
  * then return HW_EINVAL); captured step graphs are rebuilt.  Tables of 112 doubles per
  * cell are kept on the device. */
 hw_status hw_set_mesh_1d(hw_solver* h, const double* faces);

@@ -73,7 +73,7 @@ __device__ __forceinline__ void mirror_ghost_bytes(const Adj2D& P, int gx0, int 
 // reconstruction leave a compute unit one or two waves per SIMD).  Burgers NG 3 at 256^2 without hybrid
 // cells: 16.0 us with 256 threads, two rounds and both kinds of cells in one loop (more than
 // 256 VGPRs, accumulation registers among them); 9.8 us now.  With the stencil of the hybrid loop kept
-// across the directions it spilled 820 B a thread.
+// across the directions it spilled 820 B a thread; now 96 (20 values, Burgers NG 3; 16 to 32 in the others).
 template <int EQ, int NGE>
 __global__ __launch_bounds__(AT, 2) void adjL2d_kernel(Adj2D P) {
   static_assert(EQ != EQ_EULER, "scalar equations only");
@@ -543,7 +543,7 @@ __device__ __forceinline__ size_t sum_at(int t, int f, int ly, int lx) {
 // Measured with the two kernels that read the sums, us a launch, before -> now: 256^2 NG 2 with
 // shocks 21.3 -> 19.3, the hybrid cells' 24.4 -> 18.3 (its results are stored, not added), the
 // gather 14.3 -> 12.4; forward step 480 x 160 NG 3 43.5 -> 39.3, 35.0 -> 27.8, 23.0 -> 26.0.  Of the 19.3 the
-// staging and start take 6, the arithmetic 9, the sums 4; 200 VGPRs: one workgroup per CU, so the
+// staging and start take 6, the arithmetic 9, the sums 4; 180 to 230 VGPRs: one workgroup per CU, so the
 // 300 tiles of the latter mesh take two rounds.
 // With the limited moments loaded after the stored ones, not in their place once the flags were
 // there: 19.3 -> 18.8 and 39.4 -> 36.4.
@@ -1038,7 +1038,8 @@ __device__ __forceinline__ void adjEhw2d_cell(const Adj2D& P, int gi, int f, dou
 // two waves of a pair take the same 16 cells, one the x direction, the other the y
 // direction, and the y wave hands its shares to the x wave through LDS, which stores their
 // sum.  The two directions thus run side by side.
-// At most 256 VGPRs (two waves per SIMD), so that no value is kept in accumulation registers:
+// At most 256 VGPRs (two waves per SIMD; 8 to 14 values at NG 2 and 32 to 39 at NG 3 are kept in
+// scratch for it, 36 to 160 B a lane), so that no value is kept in accumulation registers:
 // forms of this kernel that used them (up to 506 registers) returned stencil cotangents off by
 // 1e-9 on some inputs, and exact ones with the registers limited and nothing else changed.
 template <int NGE, int BND>

@@ -309,40 +309,6 @@ __device__ __forceinline__ void euler_flux1d(const double* U, double gam, double
   f[2] = u * __builtin_fma(g1, e, U[2]);
 }
 
-// Euler 2D fluxes f (x) and g (y) at one point
-__device__ __forceinline__ void euler_flux2d_x(const double* U, double gam, double* f) {
-  const double r = rcp_nr(U[0]);
-  const double u = U[1] * r, v = U[2] * r;
-  const double p = (gam - 1.0) * (U[3] - 0.5 * (U[1] * u + U[2] * v));
-  f[0] = U[1];
-  f[1] = U[1] * u + p;
-  f[2] = U[2] * u;
-  f[3] = u * (U[3] + p);
-}
-__device__ __forceinline__ void euler_flux2d_y(const double* U, double gam, double* g) {
-  const double r = rcp_nr(U[0]);
-  const double u = U[1] * r, v = U[2] * r;
-  const double p = (gam - 1.0) * (U[3] - 0.5 * (U[1] * u + U[2] * v));
-  g[0] = U[2];
-  g[1] = U[1] * v;
-  g[2] = U[2] * v + p;
-  g[3] = v * (U[3] + p);
-}
-__device__ __forceinline__ void euler_flux2d_xy(const double* U, double gam, double* f, double* g) {
-  const double r = rcp_nr(U[0]);
-  const double u = U[1] * r, v = U[2] * r;
-  const double p = (gam - 1.0) * (U[3] - 0.5 * (U[1] * u + U[2] * v));
-  const double Ep = U[3] + p;
-  f[0] = U[1];
-  f[1] = U[1] * u + p;
-  f[2] = U[2] * u;
-  f[3] = u * Ep;
-  g[0] = U[2];
-  g[1] = U[1] * v;
-  g[2] = U[2] * v + p;
-  g[3] = v * Ep;
-}
-
 // The 2D characteristic decomposition in direction d (the matrices of euler_eig2d_field) as
 // the lane of a four-lane group that works on characteristic field f and on physical
 // component f needs it: row f of L (projection onto field f) and row f of R (component f

@@ -778,11 +778,9 @@ __device__ __forceinline__ void whole_operator(const Stage1D& P, WholeShared<EQ,
 // the tile routine's, to the bit: an instance's values depend neither on the form nor on the other
 // instances of its batch.
 //
-// Measured, us a step, Euler shock tube, separate launches -> this: 80 cells 34.9 -> 19.3; 200
-// 38.7 -> 20.3; 400 39.5 -> 21.7; 512 36.3 -> 22.1; 700 38.2 -> 26.2; 1000 38.4 -> 27.7.
-// Batches, against their best form so far: 16 instances of up to 128 cells 50.9 -> 20.5; 64 of
-// 500 to 1000 57 -> 27; 300 of them 73.6 -> 49.8; 512 of them 82.5 -> 49.2; 2000 of 50 to 120
-// 86.7 -> 43.4.
+// Measured, us a step, Euler shock tubes, stage launches in their best width / this: 64 cells 26 /
+// 14; 256 25 / 15; 500 26 / 16; 1000 26 / 21.  Batches: hw_step1d_pays.  (1024 threads: 128 VGPRs, 17
+// values in scratch.)
 template <int EQ, int T1>
 __global__ __launch_bounds__(T1) void step1d_kernel(Stage1D P, Step1D Q, int nsteps) {
   constexpr int NC = (EQ == EQ_EULER) ? 3 : 1, NF = 2 * NC, L1 = T1 + 2 * H1, NW = T1 / 64;
@@ -1160,7 +1158,8 @@ static hipError_t launch1d_tile(int persistent, int grid, int tile, const hw::St
 extern "C" hipError_t hw_launch_stage1d(int eq, int persistent, int grid, int tile,
                                         const hw::Stage1D* P, hipStream_t s) {
   if (P->nu) {
-    // cells of different sizes: one instance, 256-cell tiles, one workgroup per tile
+    // cells of different sizes: tiles of TILE1D_NU positions, one workgroup per tile.  (The Euler
+    // instance keeps 146 values in accumulation registers beside 256 VGPRs: one wave per SIMD.)
     dim3 g(P->nitems), b(256);
     if (eq == hw::EQ_EULER) hipLaunchKernelGGL((hw::stage1d_kernel<hw::EQ_EULER, 256, true>), g, b, 0, s, *P);
     else if (eq == hw::EQ_BURGERS) hipLaunchKernelGGL((hw::stage1d_kernel<hw::EQ_BURGERS, 256, true>), g, b, 0, s, *P);

@@ -1174,7 +1174,8 @@ __device__ __forceinline__ void stage_tile(const Stage2D& P, TileShared<EQ, NGE,
 // shuffles: 121 -> 96 us at 1024^2 NG = 2; 248 -> 155 us at 1501 x 997 NG = 3, where the smaller
 // exchange also lets three workgroups run per CU instead of two; 162 -> 101 us on the double
 // Mach reflection at 1920 x 480; 63 -> 40 us on the forward step at 960 x 320.  168 VGPRs and
-// 43-52 KB of LDS: three workgroups per CU.
+// 43-52 KB of LDS: three workgroups per CU (the forward step's instance keeps 7 values in scratch at
+// NG = 2, the double Mach reflection's one at NG = 3).
 template <int EQ, int NGE, int BK>
 __global__ __launch_bounds__(NT, 3) void stage2d_kernel(Stage2D P) {
   constexpr int NC = (EQ == EQ_EULER) ? 4 : 1;
