@@ -202,7 +202,7 @@ __device__ __forceinline__ double speed1d(const double* U, double gam, double ad
 // Bound by VALU issue (FP64), so every phase is one pass of the workgroup.  A tile of T1 cells took a
 // second pass of its first or last wave for the two to six positions beyond them in the flags, the
 // limiter, the traces and the faces, half as much again with two waves a tile, and evaluated
-// each face's fluxes in both of its cells: 52.9 -> 42.5 us a launch for 512 Euler instances of 256 to
+// each face's fluxes in both of its cells: 52.9 -> 42.9 us a launch for 512 Euler instances of 256 to
 // 8192 cells with 128 threads, of which the bytes alone take 32 at the rate of a large copy.
 // NU: a single instance on cells of different sizes (per-cell tables, hw_mesh1d.h)
 template <int EQ, int T1, bool NU>
