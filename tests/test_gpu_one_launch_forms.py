@@ -128,3 +128,29 @@ def test_walls_in_x_with_y_periodic(hw, eq, ng, nx, ny):
     assert array_err(L, Lo) < TOL
     assert array_err(W, info["limited"]) < TOL
     s.close()
+
+
+@pytest.mark.parametrize("ng", [2, 3])
+@pytest.mark.parametrize("n,copies", [(11, 10), (16, 7), (41, 3), (99, 2)])
+def test_small_meshes_of_troubled_cells_equal_their_copies(hw, n, copies, ng):
+    """Euler with every cell troubled: meshes that take four launches, and their data repeated on
+    one that takes one launch."""
+    U = state("euler", n, n)
+    out = []
+    for m in (1, copies):
+        s = hw.Solver(2, m * n, m * n, domain=(0.0, float(m), 0.0, float(m)), eq="euler", bc="periodic", ng_edge=ng,
+                      tc_mode="all")
+        s.flag_export(True)
+        V = np.ascontiguousarray(np.tile(U, (1, 1, m, m)))
+        L, W = s.apply_operator(V)
+        F = s.flags(0)
+        s.set_state(V)
+        s.steps(2, dt=2e-4)
+        out.append((L, W, F, s.get_state()[0], s.stats()))
+        s.close()
+    (L, W, F, S, st), (Lk, Wk, Fk, Sk, stk) = out
+    sl = np.s_[..., (copies - 1) * n:, n:2 * n]
+    assert np.array_equal(F[0], Fk[0][sl]) and np.array_equal(F[1], Fk[1][sl])
+    assert array_err(Lk[sl], L) < TOL and array_err(Wk[sl], W) < TOL and array_err(Sk[sl], S) < TOL
+    assert [m * copies * copies for m in st[1] + st[2]] == list(stk[1] + stk[2])
+    assert np.allclose(st[0], stk[0], rtol=1e-12, atol=0.0)
