@@ -1359,11 +1359,13 @@ __global__ __launch_bounds__(NT, 3) void stage2d_kernel(Stage2D P) {
 // 256^2, 88 / 121 at 512^2, 103 / 126 at 640^2 (1600 tiles), 127 / 150 at 768^2; advection NG 2 71 / 81 at 512^2,
 // 93 / 98 at 640^2, 107 / 114 at 768^2.
 // Euler with every cell troubled: a full tile's own HWENO cells are then the stage's time, whatever
-// the number of tiles, while four launches spread them over the chip.  One launch / four, NG 2: 99 / 83
-// at 16^2, 99 / 88 at 32^2, 101 / 88 at 64^2, 103 / 92 at 90^2, but 103 / 105 at 100^2 and 103 / 109 at 120^2, and
-// where tiles are not full 76 / 77 at 9^2, 80 / 79 at 10^2, 85 / 78 at 11^2, 79 / 79 at 13 x 8, 87 / 88 at 8 x 512
-// (NG 3 alike: 106 / 87, 107 / 91, 108 / 94, 111 / 102, 111 / 117, 110 / 119; 81 / 83, 84 / 84, 89 / 83): four from 11
-// cells a side to 10 000 in all.  A scalar law's cells are cheap enough: 37 / 65 at 32^2 and 64^2 Burgers NG 3.
+// the number of tiles, while four launches spread them over the chip.  One launch / four, us a step,
+// NG 2 and NG 3: 87 / 79 and 94 / 86 at 13^2, 99 / 82 and 106 / 87 at 16^2, 101 / 88 and 108 / 94 at 64^2, 103 / 92
+// and 111 / 102 at 90^2, 102 / 100 and 110 / 107 at 96^2 (36 tiles), but 103 / 102 and 112 / 114 at 99^2, 103 / 105 and
+// 111 / 117 at 100^2; where the tiles are not full 76 / 77 and 81 / 83 at 9^2, 87 / 88 and 93 / 95 at 8 x 512.  Between,
+// at 11^2 and 12^2, steps gain (84 / 78, 84 / 82) and a recorded run with its adjoint loses (12 steps 3730 / 3780 and
+// 3740 / 3820 us; 3990 / 3790 at 16^2).  So four launches from 13 cells a side to 36 tiles.  A scalar law's
+// cells are cheap enough: 37 / 65 at 32^2 and 64^2 Burgers NG 3.
 
 // Appends the threads marked in m (of the workgroup's first four waves) to a work list (no list:
 // counts only), the length kept in a 64-bit statistics entry: one atomic per workgroup that has
@@ -1731,11 +1733,11 @@ __global__ __launch_bounds__(NT) void dmr_table_kernel(Stage2D P) {
 constexpr int FUSED_TILES_EULER = 400, FUSED_TILES_SCALAR = 1600;
 // two threads per cell up to one tile per compute unit (measured there)
 constexpr int HELP_TILES = 256;
-// Euler with every cell troubled takes four launches from this many cells a side to that many in all
-constexpr int FULL_SIDE = 11, FULL_CELLS = 10000;
+// Euler with every cell troubled takes four launches from this many cells a side to that many tiles
+constexpr int FULL_SIDE = 13, FULL_TILES = 36;
 static bool one_launch(int eq, int tc_mode, int bcx, int nx, int ny) {
   const long long tiles = (long long)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
-  const bool full = eq == EQ_EULER && tc_mode == TC_ALL && min(nx, ny) >= FULL_SIDE && (long long)nx * ny < FULL_CELLS;
+  const bool full = eq == EQ_EULER && tc_mode == TC_ALL && min(nx, ny) >= FULL_SIDE && tiles <= FULL_TILES;
   return tc_mode != TC_NONE && bcx != BC_DMR && bcx != BC_STEP && !full &&
          tiles <= (eq == EQ_EULER ? FUSED_TILES_EULER : FUSED_TILES_SCALAR);
 }

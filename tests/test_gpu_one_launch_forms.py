@@ -131,7 +131,7 @@ def test_walls_in_x_with_y_periodic(hw, eq, ng, nx, ny):
 
 
 @pytest.mark.parametrize("ng", [2, 3])
-@pytest.mark.parametrize("n,copies", [(11, 10), (16, 7), (41, 3), (99, 2)])
+@pytest.mark.parametrize("n,copies", [(13, 8), (16, 7), (41, 3), (96, 2)])
 def test_small_meshes_of_troubled_cells_equal_their_copies(hw, n, copies, ng):
     """Euler with every cell troubled: meshes that take four launches, and their data repeated on
     one that takes one launch."""

@@ -1,5 +1,6 @@
 """The rule that chooses between one launch and four for a 2D stage (CPU): at the sizes where both
-were measured, expected is the faster side where they differ by more than one part in fifty."""
+were measured, expected is the faster side where they differ by more than one part in fifty (of
+steps, and of recorded runs with their adjoint)."""
 import ctypes
 
 import pytest
@@ -14,8 +15,8 @@ def one(eq, tc, nx, ny, bc=capi.HW_BC_PERIODIC):
 
 
 @pytest.mark.parametrize("nx,ny,expected", [
-    (8, 8, True), (9, 9, True), (11, 11, False), (12, 12, False), (16, 16, False), (32, 32, False), (64, 64, False),
-    (90, 90, False), (96, 96, False), (100, 100, True), (120, 120, True), (128, 128, True), (8, 512, True), (512, 8, True)])
+    (8, 8, True), (9, 9, True), (12, 12, True), (13, 13, False), (16, 16, False), (32, 32, False), (64, 64, False),
+    (90, 90, False), (96, 96, False), (97, 97, True), (100, 100, True), (120, 120, True), (128, 128, True), (8, 512, True), (512, 8, True)])
 def test_euler_with_every_cell_troubled(nx, ny, expected):
     assert one(capi.HW_EULER, capi.HW_TC_ALL, nx, ny) == expected
 
